@@ -12,7 +12,8 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libvidkv.so")
 
 SOURCES = ["vidkv_api.hip", "quant_keys.hip", "quant_keys_mfma.hip", "quant_values.hip",
-           "quant_values_enc.hip", "decode_attn.hip", "decode_attn_mfma.hip", "saliency.hip"]
+           "quant_values_enc.hip", "decode_attn.hip", "decode_attn_mfma.hip", "decode_attn_mfma_b.hip",
+           "decode_attn_mfma_c.hip", "saliency.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed-fp32 VALU forms are kept off for all device code
@@ -44,7 +45,7 @@ def _compile(src: str) -> str:
 
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=4) as ex:
+    with cf.ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(_compile, SOURCES))
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
     r = subprocess.run(cmd, capture_output=True, text=True)

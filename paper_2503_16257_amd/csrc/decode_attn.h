@@ -21,7 +21,6 @@ struct AttnArgs {
   int ngc;                   // groups of capacity: stride of the per-head record arrays
   int use_fft;               // normal key channels coded by Eq. 5 (1) or by Eq. 4 at 1 bit (0)
   int sal_bits, npg;         // protected rows kept as fp16 (16) or Eq. 4 codes (2); groups of 32 rows
-  int split0;                // added to blockIdx.x (tail-only launches start at nsplit)
   int tail_per;              // 32-token steps of the residual buffer per tail split
   float scale2;              // softmax scale * log2(e): scores live in the exp2 domain
 };
@@ -30,18 +29,7 @@ struct AttnArgs {
 // p = 2^(score2 - m), l = sum p, o = sum p v.
 constexpr int PART_STRIDE = D + 2;
 
-// Channel c of protected row r of head hd when the rows are kept at 2 bits (Eq. 4):
-// code * s + z with the record's fp16 s, z.
-__device__ __forceinline__ float protected2_value(const AttnArgs& a, long long hd, uint32_t r, int c) {
-  const uint8_t* rec = reinterpret_cast<const uint8_t*>(a.vrows) + (hd * a.npg + (r >> 5)) * (long long)PREC;
-  const uint32_t code = (rec[(r & 31) * 32 + (c >> 2)] >> (2 * (c & 3))) & 3u;
-  const float s = (float)reinterpret_cast<const _Float16*>(rec + 1024)[c];
-  const float z = (float)reinterpret_cast<const _Float16*>(rec + 1280)[c];
-  return fmaf((float)code, s, z);
-}
-
-// true if the MFMA kernel has an instantiation for this anomalous-channel count
-bool attn_mfma_supported(int n_a);
+// the packed tokens; one instantiation per anomalous-channel count (any multiple of 8 up to 128)
 void launch_attn_mfma(const AttnArgs& a, dim3 grid, hipStream_t st);
 
 }  // namespace vidkv

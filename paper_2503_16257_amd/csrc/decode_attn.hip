@@ -7,237 +7,12 @@
 // so per 32-token group the +-s coefficients are contracted over channels first
 // (Y[h][slot]) and a single 32-point inverse real DFT per query head follows.
 //
-// This file holds the plain-VALU kernel (any anomalous-channel count, and the
-// fp16 residual tokens), the merge kernel and the launcher; the MFMA kernel
-// that handles the common channel counts is in decode_attn_mfma.hip.
+// This file holds the kernel for the fp16 residual tokens, the merge kernels and
+// the launcher; the MFMA kernel that reads the packed tokens is in decode_attn_mfma.h.
 #include "decode_attn.h"
 #include <atomic>
 
 namespace vidkv {
-
-// One workgroup = one (split, KV head, sequence); 256 threads.  Split index
-// nsplit is the block that handles the fp16 residual tokens.
-__global__ __launch_bounds__(256) void attn_partial_kernel(AttnArgs a) {
-  const int split = blockIdx.x + a.split0, kvh = blockIdx.y, b = blockIdx.z;
-  const int tid = threadIdx.x;
-  const int R = a.rep;
-  const long long hd = ((long long)a.layer * a.B + b) * a.H + kvh;
-
-  __shared__ float qp[MAX_REP][D];          // q in PERM order (anomalous first)
-  __shared__ float qu[MAX_REP][D];          // q in channel order
-  __shared__ u32x4 krec4[1536 / 16];
-  __shared__ u32x4 vrec4[VREC / 16];
-  __shared__ float Y[MAX_REP][32];
-  __shared__ float P[MAX_REP][32];
-  __shared__ float Alpha[MAX_REP];
-  __shared__ float cs[32], sn[32];
-
-  if (tid < 32) { cs[tid] = kCosT[tid]; sn[tid] = kCosT[(tid + 24) & 31]; }   // sin x = cos(x - pi/2)
-  for (int i = tid; i < R * D; i += 256) {
-    const int h = i >> 7, c = i & 127;
-    const _Float16* qrow = a.q + ((long long)b * a.Hq + kvh * R + h) * D;
-    qu[h][c] = (float)qrow[c];
-    qp[h][c] = a.ng > 0 ? (float)qrow[a.kperm[hd * D + c]] : 0.0f;
-  }
-  __syncthreads();
-
-  // roles
-  const int t_s = tid & 31, h_s = tid >> 5;          // score / softmax role: (token, head)
-  const int c_o = tid & 127, half_o = tid >> 7;      // output role: channel, heads half_o + 2 i
-  float m_run = -INFINITY, l_run = 0.0f;             // valid in threads with h_s < R
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-
-  // splits nsplit .. nsplit + ntail - 1 share the residual tokens, 32 * tail_per at a time
-  const bool is_tail = (split >= a.nsplit);
-  int n_iter, g_begin = 0, tl = 0, it0 = 0;
-  if (!is_tail) {
-    g_begin = split * a.gps;
-    const int g_end = min(a.ng, g_begin + a.gps);
-    n_iter = max(0, g_end - g_begin);
-  } else {
-    tl = a.tail_len ? a.tail_len[b] : 0;
-    tl = min(max(tl, 0), a.cap);
-    it0 = (split - a.nsplit) * a.tail_per;
-    n_iter = max(0, min((tl + 31) / 32, it0 + a.tail_per) - it0);
-  }
-
-  const uint16_t* kbits = reinterpret_cast<const uint16_t*>(krec4) + 6 * a.n_a;
-  const _Float16* krec16 = reinterpret_cast<const _Float16*>(krec4);
-  const uint8_t* kcodes = reinterpret_cast<const uint8_t*>(krec4);
-  const uint32_t* vwords = reinterpret_cast<const uint32_t*>(vrec4);
-  const _Float16* vscale = reinterpret_cast<const _Float16*>(vrec4) + 512;
-
-  for (int it = 0; it < n_iter; ++it) {
-    float score = -INFINITY;
-    uint32_t smask = 0, srank = 0;
-    const int g = g_begin + it;
-    if (!is_tail) {
-      // ---- stage the two records
-      const u32x4* ks = reinterpret_cast<const u32x4*>(a.krec + (hd * a.ngc + g) * (long long)a.krec_bytes);
-      const u32x4* vs = reinterpret_cast<const u32x4*>(a.vrec + (hd * a.ngc + g) * (long long)VREC);
-      if (tid < a.krec_bytes / 16) krec4[tid] = ks[tid];
-      if (tid >= 128 && tid - 128 < VREC / 16) vrec4[tid - 128] = vs[tid - 128];
-      if (a.n_s > 0) {
-        smask = a.vmask[(size_t)b * a.ngc + g];
-        srank = a.vrank[(size_t)b * a.ngc + g];
-      }
-      __syncthreads();
-      // ---- Y[h][slot] = sum over normal channels of q * (+-s)
-      if (h_s < R) {
-        const int slot = t_s, k = slot & 15, hi = slot >> 4;
-        const int use_im = (hi && k) ? 1 : 0;
-        float y = 0.0f;
-        for (int i = 0; i < a.n_n; ++i) {
-          const int blk = i >> 3, e = i & 7;
-          const uint32_t w = kbits[blk * 16 + k];
-          const uint32_t bit = (w >> (8 * hi + e)) & 1u;
-          const _Float16* meta = krec16 + 6 * a.n_a + 2 * a.n_n + blk * 16;
-          float val;
-          if (a.use_fft) {
-            val = bit ? (float)meta[use_im * 8 + e] : -(float)meta[use_im * 8 + e];
-          } else {
-            val = fmaf((float)bit, (float)meta[e], (float)meta[8 + e]);
-          }
-          y += qp[h_s][a.n_a + i] * val;
-        }
-        Y[h_s][slot] = y;
-      }
-      __syncthreads();
-      // ---- score[h][t]: inverse real DFT of Y plus the 2-bit channels
-      if (h_s < R) {
-        const int t = t_s;
-        float v;
-        if (a.use_fft) {
-          v = Y[h_s][0] + ((t & 1) ? -Y[h_s][16] : Y[h_s][16]);
-          float w2 = 0.0f;
-#pragma unroll
-          for (int k = 1; k < 16; ++k) {
-            const int ph = (k * t) & 31;
-            w2 += Y[h_s][k] * cs[ph] - Y[h_s][16 + k] * sn[ph];
-          }
-          v = (v + 2.0f * w2) * (1.0f / 32.0f);
-        } else {
-          v = Y[h_s][t];                     // Eq. 4 at 1 bit: slot = token, value = code * s + z
-        }
-        const int nq = a.n_a >> 2;
-        for (int j = 0; j < a.n_a; ++j) {
-          const uint32_t code = (kcodes[t * nq + (j >> 2)] >> (2 * (j & 3))) & 3u;
-          const float s = (float)krec16[4 * a.n_a + j], z = (float)krec16[5 * a.n_a + j];
-          v += qp[h_s][j] * ((float)code * s + z);
-        }
-        score = v * a.scale2;
-      }
-    } else {
-      // ---- residual tokens: plain fp16 rows
-      const int tok = (it0 + it) * 32 + t_s;
-      if (h_s < R && tok < tl) {
-        const u32x4* row = reinterpret_cast<const u32x4*>(
-            a.ktail + (((long long)b * a.H + kvh) * a.cap + tok) * D);
-        float v = 0.0f;
-        for (int i = 0; i < 16; ++i) {
-          U4H u;
-          u.u = row[i];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) v += qu[h_s][i * 8 + e] * (float)u.e[e];
-        }
-        score = v * a.scale2;
-      }
-    }
-    // ---- online softmax over the 32 tokens of this step, per head (exp2 domain)
-    if (h_s < R) {
-      float mx = score;
-#pragma unroll
-      for (int d = 16; d >= 1; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 32));
-      const float m_new = fmaxf(m_run, mx);
-      const float p = (score == -INFINITY) ? 0.0f : exp2f(score - m_new);
-      const float al = (m_run == -INFINITY) ? 0.0f : exp2f(m_run - m_new);
-      float ps = p;
-#pragma unroll
-      for (int d = 16; d >= 1; d >>= 1) ps += __shfl_xor(ps, d, 32);
-      l_run = l_run * al + ps;
-      m_run = m_new;
-      P[h_s][t_s] = p;
-      if (t_s == 0) Alpha[h_s] = al;
-    }
-    __syncthreads();
-    // ---- output accumulation
-    if (!is_tail) {
-      uint32_t w[4];
-#pragma unroll
-      for (int kb = 0; kb < 4; ++kb) w[kb] = vwords[(kb * 16 + (c_o & 15)) * 4 + (c_o >> 5)];
-      const float s = (float)vscale[(c_o & 15) * 8 + (c_o >> 4)];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int h = half_o + 2 * i;
-        if (h < R) {
-          float dot = 0.0f;
-#pragma unroll
-          for (int t = 0; t < 32; ++t) {
-            const int kb = (t & 15) >> 2, j = (t & 3) + ((t >= 16) ? 4 : 0);
-            const uint32_t f = (w[kb] >> (8 * ((c_o >> 4) & 1) + 16 * (j & 1) + 2 * (j >> 1))) & 3u;
-            const float val = (f & 1u) ? ((f & 2u) ? -1.0f : 1.0f) : 0.0f;
-            dot += P[h][t] * val;
-          }
-          acc[i] = acc[i] * Alpha[h] + s * dot;
-        }
-      }
-      uint32_t sm = smask;
-      uint32_t r = srank;
-      while (sm) {
-        const int t = __ffs(sm) - 1;
-        sm &= sm - 1;
-        const float v = a.sal_bits == 2 ? protected2_value(a, hd, r, c_o)
-                                        : (float)a.vrows[(hd * a.n_s + r) * D + c_o];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int h = half_o + 2 * i;
-          if (h < R) acc[i] += P[h][t] * v;
-        }
-        ++r;
-      }
-    } else {
-      const int nt = min(32, tl - (it0 + it) * 32);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int h = half_o + 2 * i;
-        if (h < R) acc[i] *= Alpha[h];
-      }
-      // 8 rows in flight per thread (a row past the end repeats the last one and is not used)
-      const _Float16* vcol = a.vtail + (((long long)b * a.H + kvh) * a.cap + (it0 + it) * 32) * D + c_o;
-      for (int t0 = 0; t0 < nt; t0 += 8) {
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = (float)vcol[(long long)min(t0 + u, nt - 1) * D];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          if (t0 + u < nt) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const int h = half_o + 2 * i;
-              if (h < R) acc[i] += P[h][t0 + u] * v[u];
-            }
-          }
-        }
-      }
-    }
-    __syncthreads();
-  }
-
-  // ---- write the partial (o, m, l) of every head of this KV head
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int h = half_o + 2 * i;
-    if (h < R) {
-      float* o = a.part + (((long long)split * a.B + b) * a.Hq + kvh * R + h) * PART_STRIDE;
-      o[c_o] = acc[i];
-    }
-  }
-  if (h_s < R && t_s == 0) {
-    float* o = a.part + (((long long)split * a.B + b) * a.Hq + kvh * R + h_s) * PART_STRIDE;
-    o[D] = m_run;
-    o[D + 1] = l_run;
-  }
-}
 
 // The fp16 residual tokens (Alg. 1's X_Kr, X_Vr): one workgroup = one (tail split, KV head,
 // sequence); split ts takes the 32-token steps ts * tail_per .. of the buffer and writes its
@@ -482,14 +257,11 @@ static int device_cu_count() {
 int attn_num_splits(const Geom& g) {
   if (g.ng == 0) return 0;
   const long long bh = (long long)g.B * g.H;
-  const bool mfma = attn_mfma_supported(g.n_a);
-  // MFMA kernel: 4 waves per workgroup, each wave walks pairs of groups; two workgroups
-  // are resident per compute unit, so aim at one full round of them, and at no less than
-  // 8 pairs per workgroup. The scalar kernel runs four workgroups per compute unit.
-  const long long cus = device_cu_count();
-  const long long target = mfma ? 2 * cus : 4 * cus;
+  // 4 waves per workgroup, each wave walks pairs of groups; two workgroups are resident per
+  // compute unit, so aim at one full round of them, and at no less than 8 pairs per workgroup
+  const long long target = 2LL * device_cu_count();
   long long n = (target + bh - 1) / bh;
-  const long long units = mfma ? ((g.ng + 1) / 2 + 7) / 8 : g.ng;
+  const long long units = ((g.ng + 1) / 2 + 7) / 8;
   if (n > units) n = units;
   if (n < 1) n = 1;
   return (int)n;
@@ -498,7 +270,7 @@ int attn_num_splits(const Geom& g) {
 // A large block of residual tokens is worth a stream of its own: its kernel is short of
 // memory parallelism, not of arithmetic, and runs well beside the MFMA kernel.
 bool attn_tail_beside(const Geom& g, int cap) {
-  if (cap <= 0 || g.ng == 0 || !attn_mfma_supported(g.n_a)) return false;
+  if (cap <= 0 || g.ng == 0) return false;
   const int iters = (cap + 31) / 32;
   const long long wgs = (long long)(iters < ATTN_TAIL_SPLITS ? iters : ATTN_TAIL_SPLITS) * g.B * g.H;
   return wgs >= 4LL * device_cu_count();
@@ -529,37 +301,29 @@ hipError_t launch_decode_attention(const Geom& g, int layer, float scale, const 
   a.sal_bits = g.sal_bits; a.npg = g.npg; a.use_fft = g.use_fft ? 1 : 0;
   a.nsplit = attn_num_splits(g);
   a.scale2 = scale * 1.4426950408889634f;
-  a.split0 = 0;
   // stages: bit 0 split-T partial kernel(s), bit 1 merge
-  const bool mfma = a.nsplit > 0 && attn_mfma_supported(g.n_a);
-  // with the MFMA kernel the residual-token block is a launch of its own and is
-  // skipped when there is no residual buffer
-  // residual tokens: up to ATTN_TAIL_SPLITS workgroups per (sequence, KV head)
+  // the residual-token block is a launch of its own, up to ATTN_TAIL_SPLITS workgroups per
+  // (sequence, KV head); with no token at all one empty part per head is still written
   const int tail_iters = has_tail ? (cap + 31) / 32 : 0;
-  const int ntail = has_tail ? (tail_iters < ATTN_TAIL_SPLITS ? tail_iters : ATTN_TAIL_SPLITS) : (mfma ? 0 : 1);
+  const int ntail = has_tail ? (tail_iters < ATTN_TAIL_SPLITS ? tail_iters : ATTN_TAIL_SPLITS) : (a.nsplit > 0 ? 0 : 1);
   a.tail_per = ntail > 0 && tail_iters > 0 ? (tail_iters + ntail - 1) / ntail : 0;
   const int nparts = a.nsplit + ntail;
   if (stages & 1u) {
-    if (mfma) {
-      const int npairs = (g.ng + 1) / 2;
-      a.gps = (npairs + a.nsplit - 1) / a.nsplit;          // pairs per split
-      if (has_tail && side) {
-        if (hipEventRecord(fork, st) != hipSuccess) return hipErrorUnknown;
-        if (hipStreamWaitEvent(side, fork, 0) != hipSuccess) return hipErrorUnknown;
-        // the side stream now depends on `st`: it is joined back whatever fails below
-        hipLaunchKernelGGL(attn_tail_kernel, dim3(ntail, g.H, g.B), dim3(256), 0, side, a);
-        const bool rec = hipEventRecord(join, side) == hipSuccess;
-        launch_attn_mfma(a, dim3(a.nsplit, g.H, g.B), st);
-        const bool joined = hipStreamWaitEvent(st, join, 0) == hipSuccess;
-        if (!rec || !joined) return hipErrorUnknown;
-      } else {
-        launch_attn_mfma(a, dim3(a.nsplit, g.H, g.B), st);
-        if (has_tail)
-          hipLaunchKernelGGL(attn_tail_kernel, dim3(ntail, g.H, g.B), dim3(256), 0, st, a);
-      }
+    const int npairs = (g.ng + 1) / 2;
+    a.gps = a.nsplit > 0 ? (npairs + a.nsplit - 1) / a.nsplit : 0;   // pairs per split
+    const dim3 gtail(ntail, g.H, g.B), gmain(a.nsplit, g.H, g.B);
+    if (has_tail && side && a.nsplit > 0) {
+      if (hipEventRecord(fork, st) != hipSuccess) return hipErrorUnknown;
+      if (hipStreamWaitEvent(side, fork, 0) != hipSuccess) return hipErrorUnknown;
+      // the side stream now depends on `st`: it is joined back whatever fails below
+      hipLaunchKernelGGL(attn_tail_kernel, gtail, dim3(256), 0, side, a);
+      const bool rec = hipEventRecord(join, side) == hipSuccess;
+      launch_attn_mfma(a, gmain, st);
+      const bool joined = hipStreamWaitEvent(st, join, 0) == hipSuccess;
+      if (!rec || !joined) return hipErrorUnknown;
     } else {
-      a.gps = a.nsplit ? (g.ng + a.nsplit - 1) / a.nsplit : 0;
-      hipLaunchKernelGGL(attn_partial_kernel, dim3(a.nsplit + ntail, g.H, g.B), dim3(256), 0, st, a);
+      if (a.nsplit > 0) launch_attn_mfma(a, gmain, st);
+      if (ntail > 0) hipLaunchKernelGGL(attn_tail_kernel, gtail, dim3(256), 0, st, a);
     }
   }
   if (stages & 2u) {
