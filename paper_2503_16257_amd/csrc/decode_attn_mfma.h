@@ -32,7 +32,7 @@
 // in memory and in the ring, so one run of 1 KB transfers covers both).
 //
 // Two-stage software pipeline per wave: while the keys of pair p are scored,
-// the values of pair p - 4 (the wave's previous pair) are multiplied by the
+// the values of the wave's previous pair are multiplied by the
 // probabilities that the previous step left in registers, as one interleaved
 // instruction stream; the ring holds two key stages and two value stages.
 //
@@ -56,14 +56,31 @@
 // the kernel has no other user of M0.
 //
 // Softmax is online in the exp2 domain with a lazily raised running maximum
-// shared by the two parities of a head.  Protected (fp16) value rows are added
-// on the VALU from the probabilities staged in LDS.
+// shared by the two parities of a head.
+//
+// Protected value rows are a product of their own, [heads] x [protected tokens] x
+// [channels], in batches of 16 fp16 rows (or one record of 32 rows at 2 bits): a wave
+// walks consecutive pairs, gathers its protected tokens' probabilities into a list
+// and multiplies a batch when it is full, since a pair has only a few such tokens (3
+// of 64 at 5 %, 13 at 20 %) and one multiplication costs the same for 1 row as for 16.
+// fp16 rows are transposed by the LDS read itself (ds_read_b64_tr_b16); a 2-bit code
+// becomes an fp16 number where it stands (masked, then times 2^15: as the denormal number
+// that its bits are, the products came out with fewer bits).  The probabilities enter as
+// hi + lo halves, at no cost: 8 of the 16 operand rows would be empty.  (Rows one or two
+// at a time on the vector ALU, 2-bit rows beyond the eighth of a pair straight from
+// memory, and masks loaded with vector loads whose waits drained the transfers: 67.4 us
+// against 13.9 for 28 query heads x 6272 tokens, n_a = 64, 20 % at 2 bits; 180 against 152
+// for 64 sequences x 25088 tokens, n_a = 16, 5 % in fp16; 29.8 against 27.7 for one of 196000.)
 #pragma once
 #include <type_traits>
 
 #include "decode_attn.h"
 
 namespace vidkv {
+
+typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(4))) uint32_t cu32;   // read with scalar loads
 
 __device__ __forceinline__ float swap_sum32(float v) {       // v(lane) + v(lane ^ 32)
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -125,8 +142,9 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   constexpr int KCH = KREC / 16;             // 16-byte chunks of a key record (64 < KCH <= 96, or 64)
   constexpr int OFF_AS = 8 * NA, OFF_AZ = 10 * NA, OFF_BITS = 12 * NA, OFF_META = 12 * NA + 4 * NN;
   constexpr int RING = 4 * KREC + 4 * VREC;  // a wave's ring: two stages of a pair's key records, two of its value records
-  constexpr int NROW = 8;                    // protected rows fetched ahead per pair (2-bit records: to registers)
-  constexpr int NROWL = 12;                  // ... fp16 rows: to LDS, four rows per transfer instruction
+  constexpr int BS = (SAL == 2) ? 32 : 16;   // protected rows multiplied at a time: a 2-bit record, or 16 fp16 rows
+  constexpr int LCAP = 96;                   // a wave's list of protected probabilities: 32 waiting + a pair's 64
+  constexpr int ROWB = (SAL == 2) ? PREC : BS * 2 * D;
 
   const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -141,15 +159,15 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   __shared__ uint2 t_trit[256];              // byte -> 4 halves, half i = +1 / -1 / 0 from bits 2i (nonzero), 2i+1 (negative)
   __shared__ u32x4 w_tab[4][64];             // per lane: inverse-DFT operands Wh[0], Wh[1], Wl[0], Wl[1]
   // q and the channel permutation are needed only until the constant operands are built;
-  // the staged probabilities of the protected rows take their place afterwards
-  constexpr int PL_BYTES = (SAL != 0) ? 4 * 64 * 8 * 2 : 0;
+  // the lists of the protected tokens' probabilities take their place afterwards
+  constexpr int PL_BYTES = (SAL != 0) ? 4 * LCAP * 8 * 4 : 0;
   constexpr int PRE_BYTES = 8 * D * 2 + D;
   __shared__ __align__(16) uint8_t pre_s[PRE_BYTES > PL_BYTES ? PRE_BYTES : PL_BYTES];
   _Float16 (*qs)[D] = reinterpret_cast<_Float16 (*)[D]>(pre_s);
   uint8_t* perm_s = pre_s + 8 * D * 2;
-  _Float16 (*pl)[64][8] = reinterpret_cast<_Float16 (*)[64][8]>(pre_s);   // per wave: probabilities [token of the pair][head]
-  __shared__ __align__(16) uint8_t rowring[(SAL == 1) ? 4 : 1][2][(SAL == 1) ? NROWL * 2 * D : 16];   // per wave, two stages of fp16 rows
-  __shared__ float al16[4][16];              // per wave: rescale factors per column
+  float (*plist)[LCAP][8] = reinterpret_cast<float (*)[LCAP][8]>(pre_s);   // per wave, a ring: probabilities [protected token][head]
+  __shared__ __align__(256) uint8_t rowbuf[(SAL != 0) ? 4 : 1][(SAL != 0) ? ROWB : 16];   // per wave: the rows of the next batch
+  __shared__ __align__(16) float al16[4][16];   // per wave: rescale factors per column
   __shared__ float mw[4][8], lw[4][8];
   static_assert(sizeof(float) * 8 * D <= RING, "a wave's partial output must fit its ring");
 
@@ -195,8 +213,13 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
 
   // ---------------- transfers
   const int npairs = (a.ng + 1) >> 1;
-  const int p_begin = split * a.gps;
-  const int p_end = min(npairs, p_begin + a.gps);
+  // the waves take turns at the split's pairs - or, when there are protected rows, each walks a
+  // contiguous run of them, so that its rows are consecutive in ROWS
+  constexpr int PSTEP = (SAL != 0) ? 1 : 4;
+  const int s_begin = split * a.gps;
+  const int s_end = min(npairs, s_begin + a.gps), s_n = max(0, s_end - s_begin);
+  const int p_begin = (SAL != 0) ? s_begin + (s_n * wave) / 4 : s_begin + wave;
+  const int p_end = (SAL != 0) ? s_begin + (s_n * (wave + 1)) / 4 : s_end;
 
   const uint8_t* krec_base = a.krec + hd * a.ngc * (long long)KREC;
   const uint8_t* vrec_base = a.vrec + hd * a.ngc * (long long)VREC;
@@ -242,49 +265,53 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       fetch_run(vs, dst + VREC, std::integral_constant<int, VREC>{});
     }
   };
-  // Protected rows of a pair are consecutive in ROWS (rank grows with the token).  Masks:
-  // of the pair whose values are being added (v), whose keys are being scored (c), the next (n).
-  uint32_t rows0[NROW], rows1[NROW];         // 2-bit records only
-  uint32_t sm0v = 0, sm1v = 0, rkv = 0, sm0c = 0, sm1c = 0, rkc = 0, sm0n = 0, sm1n = 0, rkn = 0;
-  auto load_masks = [&](int pp, uint32_t& s0, uint32_t& s1, uint32_t& rk) {
-    s0 = s1 = rk = 0;
-    if ((SAL != 0) && pp < p_end) {
-      const size_t gi = (size_t)b * a.ngc + 2 * pp;
-      s0 = a.vmask[gi];
-      rk = a.vrank[gi];
-      if (2 * pp + 1 < a.ng) s1 = a.vmask[gi + 1];
+  // Protected tokens.  The probabilities of a wave's protected tokens are gathered, in token
+  // order, into a list in LDS; whenever it holds a batch (BS of them) their rows - consecutive in
+  // ROWS, requested when the batch before was done - are multiplied on the matrix cores.  Masks:
+  // of the pair whose probabilities are collected next (v), the pair being scored (c), the next (n).
+  uint32_t sm0v = 0, sm1v = 0, sm0c = 0, sm1c = 0, sm0n = 0, sm1n = 0;
+  auto load_masks = [&](int pp, uint32_t& s0, uint32_t& s1) {
+    s0 = s1 = 0;
+    if (SAL != 0) {
+      // scalar loads (constant address space, no branch): as vector loads the compiler waited
+      // for each of them, and with it for every transfer in flight, at the end of every step
+      const cu32* mk = (const cu32*)a.vmask + (size_t)b * a.ngc;
+      const uint32_t m0 = mk[min(2 * pp, a.ng - 1)], m1 = mk[min(2 * pp + 1, a.ng - 1)];
+      s0 = pp < p_end ? m0 : 0u;
+      s1 = pp < p_end && 2 * pp + 1 < a.ng ? m1 : 0u;
     }
   };
-  // what a lane keeps of protected row r: its two channels 2 lane, 2 lane + 1 as an fp16
-  // pair, or (2-bit records) the byte that holds their codes
-  auto row_word = [&](uint32_t r) -> uint32_t {
-    if (SAL == 2) {
-      const uint8_t* rec = reinterpret_cast<const uint8_t*>(a.vrows) + (hd * a.npg + (r >> 5)) * (long long)PREC;
-      return rec[(r & 31) * 32 + (lane >> 1)];
+  int rb = 0, rk_end = 0;                    // rank of the first row of the batch being filled; end of the wave's rows
+  int lpos = 0, lcnt = 0, lfirst = 0;        // where that batch starts in the ring, entries in it and behind it, first valid entry
+  if ((SAL != 0) && p_begin < p_end) {
+    const size_t g0 = (size_t)b * a.ngc + 2 * p_begin, g1 = (size_t)b * a.ngc + min(2 * p_end, a.ng) - 1;
+    rb = (int)((const cu32*)a.vrank)[g0];
+    rk_end = (int)((const cu32*)a.vrank)[g1] + __popc(((const cu32*)a.vmask)[g1]);
+    if (SAL == 2) {                          // batches are whole records
+      lfirst = lcnt = rb & 31;
+      rb &= ~31;
     }
-    return __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(a.vrows + (hd * a.n_s + r) * D) + lane);
-  };
-  auto issue_rows = [&](uint32_t s0, uint32_t s1, uint32_t rk, uint32_t* rows, int st) {
-    const int cnt = __popc(s0) + __popc(s1);
-    if (SAL == 2) {
+  }
+  const uint32_t rowbuf_lds = (uint32_t)reinterpret_cast<uintptr_t>(&rowbuf[(SAL != 0) ? wave : 0][0]);
+  auto fetch_rows = [&]() {
+    if (SAL == 1) {
+      // four rows (1 KB) per instruction; row r keeps its 16-byte pieces in the order
+      // piece ^ 2 (r & 7), so that the transposing reads of a batch spread over the banks.
+      const uint8_t* base = reinterpret_cast<const uint8_t*>(a.vrows + (hd * a.n_s + rb) * D);
+      const int n = min(BS, rk_end - rb);
+      uint32_t ln = lane;
+      asm volatile("" : "+v"(ln));
 #pragma unroll
-      for (int j = 0; j < NROW; ++j)
-        if (j < cnt) rows[j] = row_word(rk + j);
-    } else {
-      // consecutive fp16 rows straight into LDS, four rows (1 KB) per instruction: lane l
-      // brings bytes 16 (l & 15) .. of row 4 j + (l >> 4)
-      const uint8_t* base = reinterpret_cast<const uint8_t*>(a.vrows + (hd * a.n_s + rk) * D) + lane * 16;
-      const uint32_t dst = (uint32_t)reinterpret_cast<uintptr_t>(&rowring[wave][st][0]);
-      const int n = min(cnt, NROWL);
-#pragma unroll
-      for (int j = 0; j < NROWL / 4; ++j)
-        if (4 * j < n && 4 * j + (lane >> 4) < n) dma16(base + j * 1024, dst + j * 1024u);
+      for (int j = 0; j < BS / 4; ++j) {
+        const int r = 4 * j + (ln >> 4), x16 = ln & 15;
+        if (4 * j < n && r < n) dma16(base + r * 2 * D + (x16 ^ (2 * (r & 7))) * 16, rowbuf_lds + j * 1024u);
+      }
+    } else if (rb < rk_end) {
+      fetch_run(reinterpret_cast<const uint8_t*>(a.vrows) + (hd * a.npg + (rb >> 5)) * (long long)PREC, rowbuf_lds,
+                std::integral_constant<int, PREC>{});
     }
   };
-  // scale and zero point (Eq. 4) of my two channels in the current group of protected rows
-  int sal_pg = -1;
-  float sal_s0 = 0.f, sal_s1 = 0.f, sal_z0 = 0.f, sal_z1 = 0.f;
-  int p = p_begin + wave;
+  int p = p_begin;
 
   // ---------------- set-up: q and the channel permutation go straight to LDS (wave 0 asks for
   // them), the first pair's key records are requested right behind them, and only the
@@ -304,14 +331,15 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   }
   if (p < p_end) fetch_keys(p, 0);
   if ((SAL != 0)) {
-    load_masks(p, sm0c, sm1c, rkc);
-    load_masks(p + 4, sm0n, sm1n, rkn);
+    load_masks(p, sm0c, sm1c);
+    load_masks(p + 1, sm0n, sm1n);
   }
   if (wave == 0) {
     if (p < p_end) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NDMA_K) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
   __syncthreads();
+  if (SAL != 0) fetch_rows();
   const bool hv = hcol < R;
   const _Float16* qrow = &qs[hv ? hcol : 0][0];
   // The permutation bytes of my channel blocks and quads come in one LDS read each, then
@@ -366,13 +394,11 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
 
   // ---------------- running state
   // o[m][i]: row 4kb+i = (parity, head) column of the score tile, channel 16 m + x16;
-  // holds sum p * code * s of the quantized tokens.
+  // holds sum p * code * s of the quantized tokens.  Protected tokens add to the same sums: the
+  // high parts of their probabilities in the rows of parity 0, the low parts in those of parity 1.
   f4 o[8];
 #pragma unroll
   for (int m = 0; m < 8; ++m) o[m] = zero;
-  float osal[8][2];                          // protected rows: head h, channels 2 lane, 2 lane + 1
-#pragma unroll
-  for (int h = 0; h < 8; ++h) { osal[h][0] = 0.f; osal[h][1] = 0.f; }
   float m_run = -INFINITY, l_run = 0.0f;     // of my column (shared by both parities of a head)
   uint32_t pp[4] = {0u, 0u, 0u, 0u};         // probabilities of the pair whose values come next
   uint32_t pq[4] = {0u, 0u, 0u, 0u};         // ... their low parts (PLO)
@@ -626,89 +652,94 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     }
   };
 
-  // protected rows of the pair with masks (s0, s1), first rank rk0: fp16 rows (fetched ahead
-  // into `rows`) weighted by the probabilities staged in pl
-  auto add_protected = [&](uint32_t s0, uint32_t s1, uint32_t rk0, const uint32_t* rows, int st) {
-    unsigned long long sm = (unsigned long long)s0 | ((unsigned long long)s1 << 32);
-    auto add_row = [&](uint32_t bits, uint32_t r) {
-      const int t64 = __ffsll((long long)sm) - 1;      // token of the pair
-      sm &= sm - 1;
-      float v0, v1;
-      if (SAL == 2) {
-        if ((int)(r >> 5) != sal_pg) {
-          sal_pg = (int)(r >> 5);
-          const uint8_t* rec = reinterpret_cast<const uint8_t*>(a.vrows) + (hd * a.npg + sal_pg) * (long long)PREC;
-          const h2 s2 = bits_h2(reinterpret_cast<const uint32_t*>(rec + 1024)[lane]);
-          const h2 z2 = bits_h2(reinterpret_cast<const uint32_t*>(rec + 1280)[lane]);
-          sal_s0 = (float)s2[0]; sal_s1 = (float)s2[1];
-          sal_z0 = (float)z2[0]; sal_z1 = (float)z2[1];
-        }
-        const uint32_t nib = bits >> (4 * (lane & 1));
-        v0 = fmaf((float)(nib & 3u), sal_s0, sal_z0);
-        v1 = fmaf((float)((nib >> 2) & 3u), sal_s1, sal_z1);
-      } else {
-        const h2 v = bits_h2(bits);
-        v0 = (float)v[0]; v1 = (float)v[1];
-      }
-      Op ph;
-      ph.q = *reinterpret_cast<const u32x4*>(&pl[wave][t64][0]);
-#pragma unroll
-      for (int h = 0; h < 8; ++h) {
-        const float f = (float)ph.v[h];
-        osal[h][0] += f * v0;
-        osal[h][1] += f * v1;
-      }
-    };
-    // fp16 rows go two at a time: (row A, row B) of one channel as a packed pair against
-    // the pair of their probabilities, one v_dot2_f32_f16 per (head, channel)
-    auto add_rows2 = [&](uint32_t bitsA, uint32_t bitsB) {
-      const int tA = __ffsll((long long)sm) - 1;
-      sm &= sm - 1;
-      const bool hasB = sm != 0;
-      const int tB = hasB ? __ffsll((long long)sm) - 1 : tA;
-      if (hasB) sm &= sm - 1; else bitsB = 0u;
-      const h2 c0 = bits_h2(__builtin_amdgcn_perm(bitsB, bitsA, 0x05040100u));   // channel 2 lane
-      const h2 c1 = bits_h2(__builtin_amdgcn_perm(bitsB, bitsA, 0x07060302u));   // channel 2 lane + 1
-      Op pa, pb;
-      pa.q = *reinterpret_cast<const u32x4*>(&pl[wave][tA][0]);
-      pb.q = *reinterpret_cast<const u32x4*>(&pl[wave][tB][0]);
-#pragma unroll
-      for (int h = 0; h < 8; ++h) {
-        const h2 w = bits_h2(__builtin_amdgcn_perm(pb.u[h >> 1], pa.u[h >> 1],
-                                                   (h & 1) ? 0x07060302u : 0x05040100u));
-        osal[h][0] = __builtin_amdgcn_fdot2(c0, w, osal[h][0], false);
-        osal[h][1] = __builtin_amdgcn_fdot2(c1, w, osal[h][1], false);
-      }
+  // the probabilities of the pair with masks (s0, s1), staged as [token][head] at stg: those of
+  // its protected tokens go to the end of the list (lane = token; there is room for a pair)
+  auto collect = [&](uint32_t s0, uint32_t s1, const uint8_t* stg) {
+    uint32_t lane = tid & 63;
+    asm volatile("" : "+v"(lane));
+    const f4 va = *reinterpret_cast<const f4*>(stg + lane * 32), vb = *reinterpret_cast<const f4*>(stg + lane * 32 + 16);
+    int pos = lpos + lcnt + (int)__builtin_amdgcn_mbcnt_hi(s1, __builtin_amdgcn_mbcnt_lo(s0, 0u));
+    pos = pos >= LCAP ? pos - LCAP : pos;
+    if (((lane < 32 ? s0 : s1) >> (lane & 31)) & 1u) {
+      *reinterpret_cast<f4*>(&plist[wave][pos][0]) = va;
+      *reinterpret_cast<f4*>(&plist[wave][pos][4]) = vb;
+    }
+    lcnt += __popc(s0) + __popc(s1);
+  };
+  // one batch: entries lfirst .. min(lcnt, BS) - 1 of the list against the rows in rowbuf (which
+  // have landed), then the next batch's rows are requested.  Operand rows 0-7 are the heads'
+  // probabilities rounded to fp16, rows 8-15 what the rounding left.
+  auto batch = [&]() {
+    const int n = min(lcnt, BS);
+    // lane numbers of its own, so that no address of a batch occupies a register between batches
+    uint32_t ln = lane;
+    asm volatile("" : "+v"(ln));
+    const int x16 = ln & 15, kb = ln >> 4, hcol = x16 & 7, par = x16 >> 3;
+    auto entry = [&](int idx) -> _Float16 {
+      float v = plist[wave][lpos + idx][hcol];
+      v = (unsigned)(idx - lfirst) < (unsigned)(n - lfirst) ? v : 0.0f;
+      const _Float16 hi = (_Float16)v;
+      return par ? (_Float16)(v - (float)hi) : hi;
     };
     if (SAL == 1) {
-      // my two channels of row j: one dword of the staged row
-      const uint32_t* rl = reinterpret_cast<const uint32_t*>(&rowring[wave][st][0]) + lane;
+      if (n < BS) {
+        // rows without an entry count 0 times, and must not hold a NaN (a last batch only)
 #pragma unroll
-      for (int j = 0; j < NROWL; j += 2)
-        if (sm) add_rows2(rl[j * (D / 2)], rl[(j + 1) * (D / 2)]);
-      uint32_t rk = rk0 + NROWL;                        // more than NROWL rows: fetch on demand
-      while (sm) {
-        const uint32_t ra = row_word(rk);
-        const uint32_t rb = (sm & (sm - 1)) ? row_word(rk + 1) : 0u;
-        add_rows2(ra, rb);
-        rk += 2;
+        for (int j = 0; j < BS / 4; ++j)
+          if (4 * j + kb >= n) *reinterpret_cast<u32x4*>(&rowbuf[wave][j * 1024 + ln * 16]) = u32x4{0u, 0u, 0u, 0u};
+        asm volatile("" ::: "memory");
+      }
+      h4 A;                                  // k-slots: rows 4 kb + i
+#pragma unroll
+      for (int i = 0; i < 4; ++i) A[i] = entry(4 * kb + i);
+      // a transposing read hands lane x16 of kb the rows 4 kb .. 4 kb + 3 of channel 16 m + x16
+      const int r = 4 * kb + (x16 >> 2);
+      const uint32_t at = rowbuf_lds + r * 2 * D + (r & 7) * 32 + (x16 & 3) * 8;
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        const h4 B = __builtin_bit_cast(h4, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            reinterpret_cast<__attribute__((address_space(3))) s16x4*>(at ^ (m * 32))));
+        o[m] = __builtin_amdgcn_mfma_f32_16x16x16f16(A, B, o[m], 0, 0, 0);
       }
     } else {
+      const uint8_t* rec = &rowbuf[wave][0];
+      Op A, one;                             // k-slots: rows kb + 4 i
 #pragma unroll
-      for (int j = 0; j < NROW; ++j)
-        if (sm) add_row(rows[j], rk0 + j);
-      uint32_t rk = rk0 + NROW;                         // more than NROW rows: fetch on demand
-      while (sm) {
-        add_row(row_word(rk), rk);
-        ++rk;
+      for (int i = 0; i < 8; ++i) A.v[i] = entry(kb + 4 * i);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) one.u[i] = 0x3C003C00u;
+      const f4 P = mma(A, one, zero);
+      // channel 16 m + x16 is field x16 % 4 of byte 4 m + x16 / 4 of a row; the code stays where
+      // it is: as an fp16 number code 2^(2 (x16 % 4) - 24), here times 2^15
+      const uint8_t* codes = rec + kb * 32 + (x16 >> 2);
+      const uint32_t field = 0x00030003u << (2 * (x16 & 3));
+      const float unit = (float)(1 << 9) / (float)(1 << (2 * (x16 & 3)));
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        Op B;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          B.p[i] = bits_h2(((uint32_t)codes[256 * i + 4 * m] | ((uint32_t)codes[256 * i + 128 + 4 * m] << 16)) & field) *
+                   h2{(_Float16)32768.0f, (_Float16)32768.0f};
+        const f4 C = mma(A, B, zero);
+        const float sc = (float)reinterpret_cast<const _Float16*>(rec + 1024)[16 * m + x16] * unit;
+        const float zc = (float)reinterpret_cast<const _Float16*>(rec + 1280)[16 * m + x16];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[m][i] = fmaf(zc, P[i], fmaf(sc, C[i], o[m][i]));
       }
     }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the rows have been read: their place may be refilled
+    lpos = lpos + BS == LCAP ? 0 : lpos + BS;
+    lcnt = max(0, lcnt - BS);
+    lfirst = 0;
+    rb += BS;
+    fetch_rows();
   };
 
   // online softmax of the pair's scores: updates m_run, l_run (and rescales the running
-  // sums when the maximum is raised), leaves the packed probabilities in pp and, when the
-  // pair has protected tokens, stages them in pl as [token][head]
-  auto softmax = [&](const f4 (&S)[2], float cst, bool v1ok, bool stage_pl) {
+  // sums and the listed probabilities when the maximum is raised), leaves the packed
+  // probabilities in pp and, when the pair has protected tokens, stages them at stg as [token][head]
+  auto softmax = [&](const f4 (&S)[2], float cst, bool v1ok, bool stage_pl, uint8_t* stg) {
     // t = score - running maximum, in the exp2 domain, for my column at token slot i
     // (i < 4: token 4kb+i, else 16+4kb+i-4); a column without a group gets -inf
     const bool dead = par && !v1ok;
@@ -758,11 +789,12 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) o[m][i] *= ar[i];
       if ((SAL != 0)) {
-#pragma unroll
-        for (int h = 0; h < 8; ++h) {
-          const float ah = al16[wave][h];
-          osal[h][0] *= ah;
-          osal[h][1] *= ah;
+        const f4 aa = *reinterpret_cast<const f4*>(&al16[wave][0]), ab = *reinterpret_cast<const f4*>(&al16[wave][4]);
+        for (int e = lane; e < lcnt; e += 64) {
+          const int pos = lpos + e >= LCAP ? lpos + e - LCAP : lpos + e;
+          f4* l4 = reinterpret_cast<f4*>(&plist[wave][pos][0]);
+          l4[0] *= aa;
+          l4[1] *= ab;
         }
       }
     }
@@ -788,16 +820,12 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       }
     }
     if ((SAL != 0) && stage_pl) {
-      _Float16* pw = &pl[wave][32 * par][hcol];
-      const h2 a0 = bits_h2(pp[0]), a1 = bits_h2(pp[1]), a2 = bits_h2(pp[2]), a3 = bits_h2(pp[3]);
-      pw[8 * slot_token(kb, 0)] = a0[0];
-      pw[8 * slot_token(kb, 2)] = a0[1];
-      pw[8 * slot_token(kb, 4)] = a1[0];
-      pw[8 * slot_token(kb, 6)] = a1[1];
-      pw[8 * slot_token(kb, 1)] = a2[0];
-      pw[8 * slot_token(kb, 3)] = a2[1];
-      pw[8 * slot_token(kb, 5)] = a3[0];
-      pw[8 * slot_token(kb, 7)] = a3[1];
+      uint32_t ln = lane;
+      asm volatile("" : "+v"(ln));
+      const int kb = ln >> 4;
+      float* pw = reinterpret_cast<float*>(stg) + (ln & 8) * 32 + (ln & 7);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) pw[8 * slot_token(kb, i)] = pr[i];
     }
   };
 
@@ -806,61 +834,74 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   // independent chains of LDS reads, MFMAs and ALU work in one instruction stream.  A
   // pair's value records are therefore requested one step after its key records.
   // Step with key stage KS: keys of pair p in key stage KS; its values are requested into
-  // value stage KS and its protected rows into rows<KS>; the previous pair's are in KS ^ 1.
+  // value stage KS; the previous pair's are in KS ^ 1.  The probabilities of a pair with protected
+  // tokens are staged where its keys were (nothing is requested into that stage before the next
+  // step has collected them).
+  static_assert(2 * KREC >= 64 * 8 * 4, "a pair's probabilities must fit its key stage");
   auto step = [&](auto ks_c, auto first_c) {
     constexpr int KS = decltype(ks_c)::value;
     constexpr bool FIRST = decltype(first_c)::value;
     const bool v1ok = (2 * p + 1) < a.ng;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // keys of p, values and rows of the pair before
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // keys of p, values of the pair before, rows of the batch
+    if ((SAL != 0) && !FIRST && (sm0v | sm1v)) collect(sm0v, sm1v, ring_w + (KS ^ 1) * 2 * KREC);
+    if ((SAL != 0) && !FIRST) {
+      // one batch a step as a rule; more, each with a wait for its rows, when a pair brings many.
+      // (Here, where few registers are in use.)
+      bool landed = true;
+      while (lcnt >= BS && (landed || lcnt > LCAP - 64)) {
+        if (!landed) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        batch();
+        landed = false;
+      }
+    }
     FirstHop hop;
     first_hop(ks_c, std::true_type{}, std::integral_constant<bool, !FIRST>{}, hop);
     __builtin_amdgcn_sched_barrier(0);
-    if (p + 4 < p_end) fetch_keys(p + 4, KS ^ 1);
+    if (p + PSTEP < p_end) fetch_keys(p + PSTEP, KS ^ 1);
     fetch_values(p, KS);
-    if ((SAL != 0)) {
-      if (sm0c | sm1c) issue_rows(sm0c, sm1c, rkc, KS ? rows1 : rows0, KS);
-      if (!FIRST && (sm0v | sm1v)) add_protected(sm0v, sm1v, rkv, KS ? rows0 : rows1, KS ^ 1);
-    }
     f4 S[2];
     float cst;
     scores_and_values(ks_c, std::true_type{}, std::integral_constant<bool, !FIRST>{}, hop, S, cst);
-    softmax(S, cst, v1ok, (sm0c | sm1c) != 0);
+    softmax(S, cst, v1ok, (sm0c | sm1c) != 0, &ring[wave][0] + KS * 2 * KREC);
     if ((SAL != 0)) {
-      sm0v = sm0c; sm1v = sm1c; rkv = rkc;
-      sm0c = sm0n; sm1c = sm1n; rkc = rkn;
-      load_masks(p + 8, sm0n, sm1n, rkn);
+      sm0v = sm0c; sm1v = sm1c;
+      sm0c = sm0n; sm1c = sm1n;
+      load_masks(p + 2, sm0n, sm1n);
     }
   };
   int last_ks = -1;
   if (p < p_end) {
     step(std::integral_constant<int, 0>{}, std::true_type{});
     last_ks = 0;
-    p += 4;
+    p += PSTEP;
     while (p < p_end) {
       step(std::integral_constant<int, 1>{}, std::false_type{});
       last_ks = 1;
-      p += 4;
+      p += PSTEP;
       if (p >= p_end) break;
       step(std::integral_constant<int, 0>{}, std::false_type{});
       last_ks = 0;
-      p += 4;
+      p += PSTEP;
     }
   }
   // the last pair's values
   if (last_ks >= 0) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if ((SAL != 0) && (sm0v | sm1v)) collect(sm0v, sm1v, ring_w + last_ks * 2 * KREC);
+    f4 S[2]; float cst;
+    FirstHop hop;
     if (last_ks == 0) {
-      if ((SAL != 0) && (sm0v | sm1v)) add_protected(sm0v, sm1v, rkv, rows0, 0);
-      f4 S[2]; float cst;
-      FirstHop hop;
       first_hop(std::integral_constant<int, 1>{}, std::false_type{}, std::true_type{}, hop);
       scores_and_values(std::integral_constant<int, 1>{}, std::false_type{}, std::true_type{}, hop, S, cst);
     } else {
-      if ((SAL != 0) && (sm0v | sm1v)) add_protected(sm0v, sm1v, rkv, rows1, 1);
-      f4 S[2]; float cst;
-      FirstHop hop;
       first_hop(std::integral_constant<int, 0>{}, std::false_type{}, std::true_type{}, hop);
       scores_and_values(std::integral_constant<int, 0>{}, std::false_type{}, std::true_type{}, hop, S, cst);
+    }
+    if (SAL != 0) {
+      while (lcnt > lfirst) {                  // what is left of the list
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        batch();
+      }
     }
   }
 
@@ -883,14 +924,6 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       ow[(4 * (kb & 1) + i) * D + 16 * (m + 4 * (kb >> 1)) + x16] = s;
     }
   if (kb == 0 && par == 0) { mw[wave][hcol] = m_run; lw[wave][hcol] = l_run; }
-  if ((SAL != 0)) {
-    // same wave, LDS operations complete in order: add the fp16-row part
-#pragma unroll
-    for (int h = 0; h < 8; ++h) {
-      ow[h * D + 2 * lane] += osal[h][0];
-      ow[h * D + 2 * lane + 1] += osal[h][1];
-    }
-  }
   __syncthreads();
   // ---------------- workgroup merge of the 4 waves, then the split partial
   {

@@ -1,0 +1,55 @@
+"""GPU parity of decode attention where protected value tokens come in runs around the batch
+sizes of the kernel (16 fp16 rows, records of 32 rows at 2 bits, 64 tokens of a pair), and where
+an index list names fewer tokens than it has entries."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+import parity as P
+from paper_2503_16257_amd import synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _run(idx, bits, t_capacity=0, n_a=16):
+    w = dataclasses.replace(synth.reduced(synth.WORKLOADS["c4_long"], 8), Hkv=2, Hq=14, n_anom=n_a,
+                            n_salient=len(idx))
+    d = torch.from_numpy(np.asarray(idx, np.int32)[None]).to(DEV)
+    return P.GpuRun(w, DEV, salient_idx=d, salient_bits=bits, t_capacity=t_capacity), w
+
+
+@pytest.mark.parametrize("bits", [16, 2])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 31, 32, 33, 95, 129, 700])
+def test_runs_of_protected_tokens(n, bits):
+    run, w = _run(list(range(45, 45 + n)) + [w for w in (1200, 1567) if w >= 45 + n], bits)
+    q = synth.query(w, 0)
+    out = run.attention(0, torch.from_numpy(q).to(DEV)).cpu().numpy()
+    P.assert_out_close(out[0], P.oracle_attention(run, 0, 0, q[0]), f"{n} protected in a row, {bits} bits")
+
+
+@pytest.mark.parametrize("bits", [16, 2])
+def test_dropped_entries_and_a_flush_behind_them(bits):
+    """Entries outside the cache are dropped: the rows behind the last protected token are never
+    written (here: stale bytes that are NaN as fp16), and a flushed group's rank counts all entries."""
+    idx = list(range(3, 903, 100)) + [5000, 6000, 7000] * 9
+    run, w = _run(idx, bits, t_capacity=1568 + 32)
+    sec = P.LY.value_sections(w.L, w.B, w.Hkv, run.Tcap, w.n_salient, run.sal_bits)
+    if bits == 16:
+        rows = run.pv[sec["rows"]:sec["rows"] + w.n_heads * w.n_salient * 256].view(w.n_heads, w.n_salient, 256)
+        rows[:, 9:] = 0xFF
+    q = torch.from_numpy(synth.query(w, 0)).to(DEV)
+    a = run.attention(0, q)
+    assert torch.isfinite(a).all()
+    Kt = np.stack([synth.tail_heads(w, 0, b, 32)[0] for b in range(w.B)])
+    Vt = np.stack([synth.tail_heads(w, 0, b, 32)[1] for b in range(w.B)])
+    run.flush(0, torch.from_numpy(Kt).to(DEV), torch.from_numpy(Vt).to(DEV), 32, 32)
+    run.advance(32)
+    b = run.attention(0, q)
+    assert torch.isfinite(b).all()
+    # the same cache with exactly the nine tokens protected gives the same attention
+    ref, _ = _run(idx[:9], bits)
+    if bits == 16:
+        assert torch.equal(a, ref.attention(0, q))
