@@ -16,7 +16,10 @@ struct AttnArgs {
   const _Float16* ktail;     // [B, H, cap, 128]
   const _Float16* vtail;
   const int32_t* tail_len;   // [B] or NULL
-  float* part;               // [nsplit + tail splits, B, Hq, 130]
+  // one partial per (split, sequence, query head): o[128], and m, l with
+  // p = 2^(score2 - m), l = sum p, o = sum p v
+  float* part_o;             // [nsplit + tail splits, B, Hq, 128]
+  float* part_ml;            // [nsplit + tail splits, B, Hq, 2]
   int layer, B, H, Hq, rep, ng, n_a, n_n, n_s, krec_bytes, cap, nsplit, gps;
   int ngc;                   // groups of capacity: stride of the per-head record arrays
   int use_fft;               // normal key channels coded by Eq. 5 (1) or by Eq. 4 at 1 bit (0)
@@ -24,10 +27,6 @@ struct AttnArgs {
   int tail_per;              // 32-token steps of the residual buffer per tail split
   float scale2;              // softmax scale * log2(e): scores live in the exp2 domain
 };
-
-// One split partial per (split, sequence, query head): o[128], m, l with
-// p = 2^(score2 - m), l = sum p, o = sum p v.
-constexpr int PART_STRIDE = D + 2;
 
 // the packed tokens; one instantiation per anomalous-channel count (any multiple of 8 up to 128)
 void launch_attn_mfma(const AttnArgs& a, dim3 grid, hipStream_t st);

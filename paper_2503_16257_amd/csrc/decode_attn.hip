@@ -94,143 +94,77 @@ __global__ __launch_bounds__(256) void attn_tail_kernel(AttnArgs a) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int h = half_o + 2 * i;
-    if (h < R) a.part[(((long long)split * a.B + b) * a.Hq + kvh * R + h) * PART_STRIDE + c_o] = acc[i];
+    if (h < R) a.part_o[(((long long)split * a.B + b) * a.Hq + kvh * R + h) * D + c_o] = acc[i];
   }
   if (h_s < R && t_s == 0) {
-    float* o = a.part + (((long long)split * a.B + b) * a.Hq + kvh * R + h_s) * PART_STRIDE;
-    o[D] = m_run;
-    o[D + 1] = l_run;
+    float* ml = a.part_ml + (((long long)split * a.B + b) * a.Hq + kvh * R + h_s) * 2;
+    ml[0] = m_run;
+    ml[1] = l_run;
   }
 }
 
 // Merge of the split partials: out = sum_i o_i 2^{m_i - M} / sum_i l_i 2^{m_i - M}.
-// grid (Hq, B), block 1024 = 128 channels x 8 slices of the split list.
-__global__ __launch_bounds__(1024) void attn_merge_kernel(const float* __restrict__ part,
-                                                          int nparts, int B, int Hq,
-                                                          _Float16* __restrict__ out) {
-  const int h = blockIdx.x, b = blockIdx.y;
-  const int c = threadIdx.x & 127, sl = threadIdx.x >> 7;
-  __shared__ float so[8][D];
-  __shared__ float sl_[8];
-  // running maximum over all parts: one part per thread, then wave and block maxima
-  __shared__ float sW[16];
-  float M = -INFINITY;
-  for (int i = threadIdx.x; i < nparts; i += 1024)
-    M = fmaxf(M, part[(((long long)i * B + b) * Hq + h) * PART_STRIDE + D]);
+// grid (Hq, B), block 256 = 32 channel quads x 8 slices of the list of parts.  What takes time is
+// latency - the launch, one round trip to memory, the reduction - so up to 8 MAXU parts are
+// requested before the first is used, 16 bytes of a part per thread (a block of 128 threads that
+// held 16 or 32 parts as single floats: 3.6 and 5.4 us, 6.4 at 1792 (sequence, head) rows; of 1024
+// threads up to 136 parts: 5.8; this: 3.2, 3.3, 4.6 and 4.6).
+template <int MAXU>
+__global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ part_o,
+                                                         const float2* __restrict__ part_ml,
+                                                         int nparts, int BHq,
+                                                         _Float16* __restrict__ out) {
+  const int row = blockIdx.y * gridDim.x + blockIdx.x;             // (sequence, query head)
+  const int c4 = threadIdx.x & 31, sl = threadIdx.x >> 5;
+  __shared__ f4 so[8][32];
+  __shared__ float sl_[8], sM[8];
+  const f4* po = reinterpret_cast<const f4*>(part_o) + (size_t)row * (D / 4) + c4;
+  f4 o = f4{0.f, 0.f, 0.f, 0.f};
+  float l = 0.0f, M = -INFINITY;
+  // slice sl takes parts sl, sl + 8, ...; its sums are relative to its own running maximum
+  for (int i0 = sl; i0 < nparts; i0 += 8 * MAXU) {
+    f4 oi[MAXU];
+    float2 ml[MAXU];
 #pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) M = fmaxf(M, __shfl_xor(M, d, 64));
-  if ((threadIdx.x & 63) == 0) sW[threadIdx.x >> 6] = M;
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 16; ++i) M = fmaxf(M, sW[i]);
-  // weighted sums, 4 parts in flight per thread
-  float o = 0.0f, l = 0.0f;
-  for (int i0 = sl; i0 < nparts; i0 += 32) {
-    float mi[4], oi[4], li[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = i0 + 8 * u;
-      const bool ok = i < nparts;
-      const float* p = part + (((long long)(ok ? i : 0) * B + b) * Hq + h) * PART_STRIDE;
-      mi[u] = ok ? p[D] : -INFINITY;
-      oi[u] = ok ? p[c] : 0.0f;
-      li[u] = ok ? p[D + 1] : 0.0f;
+    for (int u = 0; u < MAXU; ++u) {
+      const int i = i0 + 8 * u, ii = i < nparts ? i : i0;
+      oi[u] = po[(size_t)ii * BHq * (D / 4)];
+      ml[u] = part_ml[(size_t)ii * BHq + row];
+      if (i >= nparts) ml[u].x = -INFINITY;
     }
+    float Mn = M;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const float w = mi[u] == -INFINITY ? 0.0f : exp2f(mi[u] - M);
-      if (w != 0.0f) {                     // an empty part's sums are never looked at
+    for (int u = 0; u < MAXU; ++u) Mn = fmaxf(Mn, ml[u].x);
+    const float w0 = M == -INFINITY ? 0.0f : exp2f(M - Mn);
+    o *= w0;
+    l *= w0;
+    M = Mn;
+#pragma unroll
+    for (int u = 0; u < MAXU; ++u) {
+      const float w = ml[u].x == -INFINITY ? 0.0f : exp2f(ml[u].x - M);
+      if (w != 0.0f) {                       // an empty part's sums are never looked at
         o += w * oi[u];
-        l += w * li[u];
+        l += w * ml[u].y;
       }
     }
   }
-  so[sl][c] = o;
-  if (c == 0) sl_[sl] = l;
+  so[sl][c4] = o;
+  if (c4 == 0) { sl_[sl] = l; sM[sl] = M; }
   __syncthreads();
-  if (sl == 0) {
+  if (threadIdx.x < D) {
+    const int c = threadIdx.x;
+    float Mx = sM[0];
 #pragma unroll
-    for (int i = 1; i < 8; ++i) { o += so[i][c]; l += sl_[i]; }
-    out[((long long)b * Hq + h) * D + c] = (_Float16)(l > 0.0f ? o / l : 0.0f);
-  }
-}
-
-// The same merge for at most 8 * MAXU parts: every load of a thread is issued before the
-// first use (one round trip to memory instead of one per 32 parts and one for the maximum).
-// Thread (slice sl, channel c) owns parts sl, sl + 8, ...
-template <int MAXU>
-__global__ __launch_bounds__(1024) void attn_merge_small_kernel(const float* __restrict__ part,
-                                                                int nparts, int B, int Hq,
-                                                                _Float16* __restrict__ out) {
-  const int h = blockIdx.x, b = blockIdx.y;
-  const int c = threadIdx.x & 127, sl = threadIdx.x >> 7;
-  __shared__ float so[8][D];
-  __shared__ float sl_[8];
-  __shared__ float sM[8];
-  float mi[MAXU], oi[MAXU], li[MAXU];
+    for (int i = 1; i < 8; ++i) Mx = fmaxf(Mx, sM[i]);
+    float acc = 0.0f, L = 0.0f;
 #pragma unroll
-  for (int u = 0; u < MAXU; ++u) {
-    const int i = sl + 8 * u;
-    const bool ok = i < nparts;
-    const float* p = part + (((long long)(ok ? i : 0) * B + b) * Hq + h) * PART_STRIDE;
-    mi[u] = ok ? p[D] : -INFINITY;
-    oi[u] = ok ? p[c] : 0.0f;
-    li[u] = ok ? p[D + 1] : 0.0f;
-  }
-  float M = mi[0];
-#pragma unroll
-  for (int u = 1; u < MAXU; ++u) M = fmaxf(M, mi[u]);
-  if (c == 0) sM[sl] = M;
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 8; ++i) M = fmaxf(M, sM[i]);
-  float o = 0.0f, l = 0.0f;
-#pragma unroll
-  for (int u = 0; u < MAXU; ++u) {
-    const float w = mi[u] == -INFINITY ? 0.0f : exp2f(mi[u] - M);
-    if (w != 0.0f) {                       // an empty part's sums are never looked at
-      o += w * oi[u];
-      l += w * li[u];
+    for (int i = 0; i < 8; ++i) {
+      const float w = sM[i] == -INFINITY ? 0.0f : exp2f(sM[i] - Mx);
+      acc += w * so[i][c >> 2][c & 3];
+      L += w * sl_[i];
     }
+    out[(size_t)row * D + c] = (_Float16)(L > 0.0f ? acc / L : 0.0f);
   }
-  so[sl][c] = o;
-  if (c == 0) sl_[sl] = l;
-  __syncthreads();
-  if (sl == 0) {
-#pragma unroll
-    for (int i = 1; i < 8; ++i) { o += so[i][c]; l += sl_[i]; }
-    out[((long long)b * Hq + h) * D + c] = (_Float16)(l > 0.0f ? o / l : 0.0f);
-  }
-}
-
-// At most MAXP parts (large batches): one thread per channel holds every part, no LDS.
-template <int MAXP>
-__global__ __launch_bounds__(128) void attn_merge_tiny_kernel(const float* __restrict__ part,
-                                                              int nparts, int B, int Hq,
-                                                              _Float16* __restrict__ out) {
-  const int h = blockIdx.x, b = blockIdx.y, c = threadIdx.x;
-  float mi[MAXP], oi[MAXP], li[MAXP];
-#pragma unroll
-  for (int u = 0; u < MAXP; ++u) {
-    const bool ok = u < nparts;
-    const float* p = part + (((long long)(ok ? u : 0) * B + b) * Hq + h) * PART_STRIDE;
-    mi[u] = ok ? p[D] : -INFINITY;
-    oi[u] = ok ? p[c] : 0.0f;
-    li[u] = ok ? p[D + 1] : 0.0f;
-  }
-  float M = mi[0];
-#pragma unroll
-  for (int u = 1; u < MAXP; ++u) M = fmaxf(M, mi[u]);
-  float o = 0.0f, l = 0.0f;
-#pragma unroll
-  for (int u = 0; u < MAXP; ++u) {
-    const float w = mi[u] == -INFINITY ? 0.0f : exp2f(mi[u] - M);
-    if (w != 0.0f) {                       // an empty part's sums are never looked at
-      o += w * oi[u];
-      l += w * li[u];
-    }
-  }
-  out[((long long)b * Hq + h) * D + c] = (_Float16)(l > 0.0f ? o / l : 0.0f);
 }
 
 // Compute units of the current device, asked once per device. A process with no usable
@@ -295,7 +229,6 @@ hipError_t launch_decode_attention(const Geom& g, int layer, float scale, const 
   a.vtail = reinterpret_cast<const _Float16*>(vtail);
   const bool has_tail = cap > 0 && ktail && vtail && tail_len;
   a.tail_len = has_tail ? tail_len : nullptr;
-  a.part = reinterpret_cast<float*>(ws);
   a.layer = layer; a.B = g.B; a.H = g.H; a.Hq = g.Hq; a.rep = g.rep; a.ng = g.ng; a.ngc = g.ngc;
   a.n_a = g.n_a; a.n_n = g.n_n; a.n_s = g.n_s; a.krec_bytes = g.krec; a.cap = cap;
   a.sal_bits = g.sal_bits; a.npg = g.npg; a.use_fft = g.use_fft ? 1 : 0;
@@ -308,6 +241,8 @@ hipError_t launch_decode_attention(const Geom& g, int layer, float scale, const 
   const int ntail = has_tail ? (tail_iters < ATTN_TAIL_SPLITS ? tail_iters : ATTN_TAIL_SPLITS) : (a.nsplit > 0 ? 0 : 1);
   a.tail_per = ntail > 0 && tail_iters > 0 ? (tail_iters + ntail - 1) / ntail : 0;
   const int nparts = a.nsplit + ntail;
+  a.part_o = reinterpret_cast<float*>(ws);                        // 16-byte aligned rows
+  a.part_ml = a.part_o + (size_t)nparts * g.B * g.Hq * D;
   if (stages & 1u) {
     const int npairs = (g.ng + 1) / 2;
     a.gps = a.nsplit > 0 ? (npairs + a.nsplit - 1) / a.nsplit : 0;   // pairs per split
@@ -328,18 +263,17 @@ hipError_t launch_decode_attention(const Geom& g, int layer, float scale, const 
   }
   if (stages & 2u) {
     _Float16* o16 = reinterpret_cast<_Float16*>(out);
+    const dim3 gm(g.Hq, g.B);
+    const int BHq = g.B * g.Hq;
+    const float2* ml = reinterpret_cast<const float2*>(a.part_ml);
     if (nparts <= 16)
-      hipLaunchKernelGGL(attn_merge_tiny_kernel<16>, dim3(g.Hq, g.B), dim3(128), 0, st, a.part,
-                         nparts, g.B, g.Hq, o16);
+      hipLaunchKernelGGL(attn_merge_kernel<2>, gm, dim3(256), 0, st, a.part_o, ml, nparts, BHq, o16);
     else if (nparts <= 32)
-      hipLaunchKernelGGL(attn_merge_tiny_kernel<32>, dim3(g.Hq, g.B), dim3(128), 0, st, a.part,
-                         nparts, g.B, g.Hq, o16);
-    else if (nparts <= 136)
-      hipLaunchKernelGGL(attn_merge_small_kernel<17>, dim3(g.Hq, g.B), dim3(1024), 0, st, a.part,
-                         nparts, g.B, g.Hq, o16);
+      hipLaunchKernelGGL(attn_merge_kernel<4>, gm, dim3(256), 0, st, a.part_o, ml, nparts, BHq, o16);
+    else if (nparts <= 72)
+      hipLaunchKernelGGL(attn_merge_kernel<9>, gm, dim3(256), 0, st, a.part_o, ml, nparts, BHq, o16);
     else
-      hipLaunchKernelGGL(attn_merge_kernel, dim3(g.Hq, g.B), dim3(1024), 0, st, a.part, nparts,
-                         g.B, g.Hq, o16);
+      hipLaunchKernelGGL(attn_merge_kernel<17>, gm, dim3(256), 0, st, a.part_o, ml, nparts, BHq, o16);
   }
   return hipGetLastError();
 }

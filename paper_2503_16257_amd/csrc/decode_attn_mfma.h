@@ -941,9 +941,9 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
           L += f * lw[w][h];
         }
       }
-      float* dst = a.part + (((long long)split * a.B + b) * a.Hq + kvh * R + h) * PART_STRIDE;
-      dst[c] = acc;
-      if (c == 0) { dst[D] = M; dst[D + 1] = L; }
+      const long long row = ((long long)split * a.B + b) * a.Hq + kvh * R + h;
+      a.part_o[row * D + c] = acc;
+      if (c == 0) { a.part_ml[row * 2] = M; a.part_ml[row * 2 + 1] = L; }
     }
   }
 }
