@@ -13,7 +13,7 @@ LIB = os.path.join(HERE, "libvidkv.so")
 
 SOURCES = ["vidkv_api.hip", "quant_keys.hip", "quant_keys_mfma.hip", "quant_values.hip",
            "quant_values_enc.hip", "decode_attn.hip", "decode_attn_mfma.hip", "decode_attn_mfma_b.hip",
-           "decode_attn_mfma_c.hip", "saliency.hip"]
+           "decode_attn_mfma_c.hip", "decode_attn_mfma_t.hip", "saliency.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed-fp32 VALU forms are kept off for all device code

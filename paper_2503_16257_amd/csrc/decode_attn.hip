@@ -10,97 +10,17 @@
 // This file holds the kernel for the fp16 residual tokens, the merge kernels and
 // the launcher; the MFMA kernel that reads the packed tokens is in decode_attn_mfma.h.
 #include "decode_attn.h"
+
+#include <algorithm>
 #include <atomic>
 
 namespace vidkv {
 
-// The fp16 residual tokens (Alg. 1's X_Kr, X_Vr): one workgroup = one (tail split, KV head,
-// sequence); split ts takes the 32-token steps ts * tail_per .. of the buffer and writes its
-// partial (o, m, l) as split index nsplit + ts.  Thread roles: scores (token = tid % 32,
-// head = tid / 32), output (channel = tid % 128, heads tid / 128 + 2 i).
+// The residual tokens as a launch of their own (the MFMA kernel takes them along when its grid
+// has room for them).
 __global__ __launch_bounds__(256) void attn_tail_kernel(AttnArgs a) {
-  const int ts = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
-  const int split = a.nsplit + ts;
-  const int tid = threadIdx.x;
-  const int R = a.rep;
-  __shared__ float t_q[MAX_REP][D];
-  __shared__ float t_P[MAX_REP][32];
-  __shared__ float t_alpha[MAX_REP];
-  for (int i = tid; i < R * D; i += 256)
-    t_q[i >> 7][i & 127] = (float)a.q[((long long)b * a.Hq + kvh * R + (i >> 7)) * D + (i & 127)];
-  const int t_s = tid & 31, h_s = tid >> 5;
-  const int c_o = tid & 127, half_o = tid >> 7;
-  float m_run = -INFINITY, l_run = 0.0f;
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  int tl = a.tail_len ? a.tail_len[b] : 0;
-  tl = min(max(tl, 0), a.cap);
-  const int it0 = ts * a.tail_per;
-  const int n_iter = max(0, min((tl + 31) / 32, it0 + a.tail_per) - it0);
-  const long long head_row0 = ((long long)b * a.H + kvh) * a.cap;
-  for (int it = 0; it < n_iter; ++it) {
-    const int tok0 = (it0 + it) * 32;
-    const int nt = min(32, tl - tok0);
-    // everything this step reads is requested up front: my key row (16 pieces) and my
-    // channel of the 32 value rows (a row past the end repeats the last one and is not used)
-    const bool scorer = h_s < R && t_s < nt;
-    U4H kr[16];
-    if (scorer) {
-      const u32x4* row = reinterpret_cast<const u32x4*>(a.ktail + (head_row0 + tok0 + t_s) * D);
-#pragma unroll
-      for (int i = 0; i < 16; ++i) kr[i].u = row[i];
-    }
-    const _Float16* vcol = a.vtail + (head_row0 + tok0) * D + c_o;
-    _Float16 vv[32];
-#pragma unroll
-    for (int u = 0; u < 32; ++u) vv[u] = vcol[(long long)min(u, nt - 1) * D];
-    if (it == 0) __syncthreads();                    // q is in LDS (its loads overlapped the above)
-    float score = -INFINITY;
-    if (scorer) {
-      float v = 0.0f;
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v += t_q[h_s][i * 8 + e] * (float)kr[i].e[e];
-      score = v * a.scale2;
-    }
-    if (h_s < R) {                                   // online softmax of this step (exp2 domain)
-      float mx = score;
-#pragma unroll
-      for (int d = 16; d >= 1; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 32));
-      const float m_new = fmaxf(m_run, mx);
-      const float p = (score == -INFINITY) ? 0.0f : exp2f(score - m_new);
-      const float al = (m_run == -INFINITY) ? 0.0f : exp2f(m_run - m_new);
-      float ps = p;
-#pragma unroll
-      for (int d = 16; d >= 1; d >>= 1) ps += __shfl_xor(ps, d, 32);
-      l_run = l_run * al + ps;
-      m_run = m_new;
-      t_P[h_s][t_s] = p;
-      if (t_s == 0) t_alpha[h_s] = al;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int h = half_o + 2 * i;
-      if (h < R) {
-        float s_acc = acc[i] * t_alpha[h];
-#pragma unroll
-        for (int u = 0; u < 32; ++u) s_acc += t_P[h][u] * (float)vv[u];   // t_P is 0 past the end
-        acc[i] = s_acc;
-      }
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int h = half_o + 2 * i;
-    if (h < R) a.part_o[(((long long)split * a.B + b) * a.Hq + kvh * R + h) * D + c_o] = acc[i];
-  }
-  if (h_s < R && t_s == 0) {
-    float* ml = a.part_ml + (((long long)split * a.B + b) * a.Hq + kvh * R + h_s) * 2;
-    ml[0] = m_run;
-    ml[1] = l_run;
-  }
+  __shared__ TailLds t;
+  attn_tail_part(a, blockIdx.x, blockIdx.y, blockIdx.z, t);
 }
 
 // Merge of the split partials: out = sum_i o_i 2^{m_i - M} / sum_i l_i 2^{m_i - M}.
@@ -187,18 +107,42 @@ static int device_cu_count() {
   return n;
 }
 
-// Number of split-T workgroups per (sequence, KV head).
-int attn_num_splits(const Geom& g) {
+// The most split-T workgroups per (sequence, KV head) that attn_splits() can choose: what the
+// workspace is sized for.  Grows with the number of groups.
+int attn_max_splits(const Geom& g) {
   if (g.ng == 0) return 0;
-  const long long bh = (long long)g.B * g.H;
-  // 4 waves per workgroup, each wave walks pairs of groups; two workgroups are resident per
-  // compute unit, so aim at one full round of them, and at no less than 8 pairs per workgroup
-  const long long target = 2LL * device_cu_count();
-  long long n = (target + bh - 1) / bh;
-  const long long units = ((g.ng + 1) / 2 + 7) / 8;
-  if (n > units) n = units;
-  if (n < 1) n = 1;
-  return (int)n;
+  const long long bh = (long long)g.B * g.H, npairs = (g.ng + 1) / 2;
+  const long long by_pairs = (npairs + 3) / 4, by_grid = 4LL * device_cu_count() / bh;
+  return (int)std::max(1LL, std::min(by_pairs, by_grid));
+}
+
+// Split-T workgroups per (sequence, KV head), with `others` workgroups of another kind in the same
+// launch.  4 waves per workgroup, each takes s pairs of groups one after another; two workgroups
+// are resident per compute unit.  Tried are all s up to 64, then the even split over one round.
+// Time of a round, measured for n_a = 64: 6 us to get going and finish, 2.2 us per pair where a
+// compute unit has one workgroup, 3.5 where it has two.  (A fixed aim of two workgroups per unit
+// and at least 2 pairs per wave took 2.2 us more where there are few pairs, a second, nearly empty
+// round where 512 / (B H) is no whole number, and more workgroups than needed for the same s.  This and the
+// residual tokens in the same launch: 28 layers of 6272 tokens, n_a = 64, 606 -> 402 us a step; of
+// 2 x 3136, n_a = 96, 555 -> 407.)
+static int attn_splits(const Geom& g, long long others) {
+  const long long bh = (long long)g.B * g.H, cus = device_cu_count(), npairs = (g.ng + 1) / 2;
+  const long long nmax = attn_max_splits(g);
+  long long best_n = 1, best = -1;
+  auto consider = [&](long long n) {
+    if (n < 1 || n > nmax) return;
+    const long long s = ((npairs + n - 1) / n + 3) / 4, w = n * bh + others;
+    const long long t = (w + 2 * cus - 1) / (2 * cus) * (60 + s * (w <= cus ? 22 : 35));
+    if (best < 0 || t < best) { best = t; best_n = n; }
+  };
+  const long long one_round = std::max(1LL, (2 * cus - others) / bh);
+  consider(std::min(one_round, nmax));
+  for (long long s = std::min(64LL, (npairs + 3) / 4); s >= 1; --s) {
+    const long long n = (npairs + 4 * s - 1) / (4 * s);
+    if (n > nmax) break;
+    consider(n);
+  }
+  return (int)best_n;
 }
 
 // A large block of residual tokens is worth a stream of its own: its kernel is short of
@@ -232,13 +176,30 @@ hipError_t launch_decode_attention(const Geom& g, int layer, float scale, const 
   a.layer = layer; a.B = g.B; a.H = g.H; a.Hq = g.Hq; a.rep = g.rep; a.ng = g.ng; a.ngc = g.ngc;
   a.n_a = g.n_a; a.n_n = g.n_n; a.n_s = g.n_s; a.krec_bytes = g.krec; a.cap = cap;
   a.sal_bits = g.sal_bits; a.npg = g.npg; a.use_fft = g.use_fft ? 1 : 0;
-  a.nsplit = attn_num_splits(g);
   a.scale2 = scale * 1.4426950408889634f;
   // stages: bit 0 split-T partial kernel(s), bit 1 merge
-  // the residual-token block is a launch of its own, up to ATTN_TAIL_SPLITS workgroups per
-  // (sequence, KV head); with no token at all one empty part per head is still written
+  // Residual tokens.  Where all workgroups fit one round, the MFMA kernel's launch takes them
+  // along (their time disappears behind the packed tokens': 5-6 us each as a launch of its own):
+  // 32 tokens per workgroup while there are few, else 128, which still end first.  Otherwise a
+  // launch of its own, on the side stream or behind, with up to ATTN_TAIL_SPLITS workgroups per
+  // (sequence, KV head).  With no token at all one empty part per head is still written.
+  const long long bh = (long long)g.B * g.H, slots = 2LL * device_cu_count();
   const int tail_iters = has_tail ? (cap + 31) / 32 : 0;
-  const int ntail = has_tail ? (tail_iters < ATTN_TAIL_SPLITS ? tail_iters : ATTN_TAIL_SPLITS) : (a.nsplit > 0 ? 0 : 1);
+  int ntail = std::min(tail_iters, ATTN_TAIL_SPLITS);
+  bool along = false;
+  a.nsplit = 0;
+  if (g.ng > 0) {
+    if (has_tail && !attn_tail_beside(g, cap)) {   // (not by whether a side stream is there: the result is the same with and without)
+      const int nt = std::min((tail_iters + (bh * tail_iters <= 64 ? 0 : 3)) / (bh * tail_iters <= 64 ? 1 : 4), ATTN_TAIL_SPLITS);
+      a.nsplit = attn_splits(g, bh * nt);
+      along = bh * (a.nsplit + nt) <= slots;
+      if (along) ntail = nt;
+    }
+    if (!along) a.nsplit = attn_splits(g, 0);
+  } else if (ntail == 0) {
+    ntail = 1;
+  }
+  a.early = bh * (a.nsplit + (along ? ntail : 0)) <= slots / 2;
   a.tail_per = ntail > 0 && tail_iters > 0 ? (tail_iters + ntail - 1) / ntail : 0;
   const int nparts = a.nsplit + ntail;
   a.part_o = reinterpret_cast<float*>(ws);                        // 16-byte aligned rows
@@ -246,7 +207,7 @@ hipError_t launch_decode_attention(const Geom& g, int layer, float scale, const 
   if (stages & 1u) {
     const int npairs = (g.ng + 1) / 2;
     a.gps = a.nsplit > 0 ? (npairs + a.nsplit - 1) / a.nsplit : 0;   // pairs per split
-    const dim3 gtail(ntail, g.H, g.B), gmain(a.nsplit, g.H, g.B);
+    const dim3 gtail(ntail, g.H, g.B), gmain(a.nsplit + (along ? ntail : 0), g.H, g.B);
     if (has_tail && side && a.nsplit > 0) {
       if (hipEventRecord(fork, st) != hipSuccess) return hipErrorUnknown;
       if (hipStreamWaitEvent(side, fork, 0) != hipSuccess) return hipErrorUnknown;
@@ -258,7 +219,7 @@ hipError_t launch_decode_attention(const Geom& g, int layer, float scale, const 
       if (!rec || !joined) return hipErrorUnknown;
     } else {
       if (a.nsplit > 0) launch_attn_mfma(a, gmain, st);
-      if (ntail > 0) hipLaunchKernelGGL(attn_tail_kernel, gtail, dim3(256), 0, st, a);
+      if (ntail > 0 && !along) hipLaunchKernelGGL(attn_tail_kernel, gtail, dim3(256), 0, st, a);
     }
   }
   if (stages & 2u) {

@@ -130,7 +130,9 @@ __device__ __forceinline__ uint32_t byte_x8(uint32_t w) {
 // The counts of the workloads carry a probability into P V as one fp16 number; every other
 // count as fp16 hi + lo parts (two more products per value tile and group), because those
 // counts have always had their probabilities in 32 bits.
-template <int NA8, int SAL, bool FFT>
+// TAIL: workgroups with split >= nsplit of the grid take residual tokens.  A variant of its own,
+// since the branch costs the others 3 % (28 x 8 x 12544 tokens, n_a = 64: 597 us a step against 577).
+template <int NA8, int SAL, bool FFT, bool TAIL>
 __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   constexpr int NA = 8 * NA8, NN = D - NA;
   constexpr int NB = NN / 8;                 // normal 8-channel blocks
@@ -209,6 +211,15 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       W.v[i] = wlo ? (_Float16)(w - (float)hi) : hi;
     }
     w_tab[2 * wlo + wmt][wl] = W.q;
+  }
+
+  if (TAIL && split >= a.nsplit) {
+    // (arguments read anew here, so that the main path's registers do not hold them)
+    const __attribute__((address_space(4))) AttnArgs* ap =
+        (const __attribute__((address_space(4))) AttnArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(ap));
+    attn_tail_part(*(const AttnArgs*)ap, split - ap->nsplit, kvh, b, *reinterpret_cast<TailLds*>(&ring[0][0]));
+    return;
   }
 
   // ---------------- transfers
@@ -329,13 +340,17 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
                    :: "s"(q_lds + 8u * D * 2u), "v"(a.kperm + hd * D + lane * 16) : "memory", "m0");
   }
-  if (p < p_end) fetch_keys(p, 0);
+  if (p < p_end) {
+    fetch_keys(p, 0);
+    if (a.early) fetch_values(p, 0);
+  }
   if ((SAL != 0)) {
     load_masks(p, sm0c, sm1c);
     load_masks(p + 1, sm0n, sm1n);
   }
   if (wave == 0) {
-    if (p < p_end) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NDMA_K) : "memory");
+    if (p < p_end && a.early) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NDMA_K + NDMA_V) : "memory");
+    else if (p < p_end) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NDMA_K) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
   __syncthreads();
@@ -858,7 +873,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     first_hop(ks_c, std::true_type{}, std::integral_constant<bool, !FIRST>{}, hop);
     __builtin_amdgcn_sched_barrier(0);
     if (p + PSTEP < p_end) fetch_keys(p + PSTEP, KS ^ 1);
-    fetch_values(p, KS);
+    if (!FIRST || !a.early) fetch_values(p, KS);         // (early: requested at the start)
     f4 S[2];
     float cst;
     scores_and_values(ks_c, std::true_type{}, std::integral_constant<bool, !FIRST>{}, hop, S, cst);
@@ -888,6 +903,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   if (last_ks >= 0) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if ((SAL != 0) && (sm0v | sm1v)) collect(sm0v, sm1v, ring_w + last_ks * 2 * KREC);
+    if ((SAL != 0) && lcnt > lfirst) batch();   // the rows of another batch arrive beside the values' products
     f4 S[2]; float cst;
     FirstHop hop;
     if (last_ks == 0) {
@@ -948,10 +964,10 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   }
 }
 
-template <int NA8>
+template <int NA8, bool TAIL>
 static void launch_one(const AttnArgs& a, dim3 grid, hipStream_t st) {
   const int sal = a.n_s > 0 ? (a.sal_bits == 2 ? 2 : 1) : 0;
-#define VIDKV_ATTN(S, F) hipLaunchKernelGGL((attn_mfma_kernel<NA8, S, F>), grid, dim3(256), 0, st, a)
+#define VIDKV_ATTN(S, F) hipLaunchKernelGGL((attn_mfma_kernel<NA8, S, F, TAIL>), grid, dim3(256), 0, st, a)
   if (a.use_fft) {
     if (sal == 2) VIDKV_ATTN(2, true); else if (sal == 1) VIDKV_ATTN(1, true); else VIDKV_ATTN(0, true);
   } else {

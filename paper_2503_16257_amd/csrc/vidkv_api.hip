@@ -18,7 +18,7 @@ hipError_t launch_decode_attention(const Geom& g, int layer, float scale, const 
                                    void* ws, unsigned stages, hipStream_t st, hipStream_t side,
                                    hipEvent_t fork, hipEvent_t join);
 bool attn_tail_beside(const Geom& g, int cap);
-int attn_num_splits(const Geom& g);
+int attn_max_splits(const Geom& g);
 void launch_k_encode(const Geom& g, const EncodeSpan& sp, const void* K, uint8_t* packed,
                      bool use_fft, hipStream_t st);
 void launch_v_encode(const Geom& g, const EncodeSpan& sp, int n_s, float gamma, const void* V,
@@ -39,7 +39,7 @@ static size_t ws_attn(const Geom& g) {
   Geom c = g;
   c.T = g.Tcap;
   c.ng = g.ngc;
-  const int ns = attn_num_splits(c) > attn_num_splits(g) ? attn_num_splits(c) : attn_num_splits(g);
+  const int ns = attn_max_splits(c);
   return align256((size_t)(ns + ATTN_TAIL_SPLITS) * g.B * g.Hq * (D + 2) * sizeof(float)) + 256;
 }
 static bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }

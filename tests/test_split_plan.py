@@ -1,0 +1,45 @@
+"""How a decode call is split: the workspace of a cache with room to grow stays the same while it
+grows (CPU), and grids just below and above one round, with and without residual tokens in the
+same launch, against the oracle (GPU)."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+import parity as P
+from paper_2503_16257_amd import binding as vk
+from paper_2503_16257_amd import synth
+
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("batch,heads", [(1, 1), (1, 4), (3, 5), (43, 4), (300, 1), (1100, 1)])
+def test_workspace_does_not_depend_on_the_fill(batch, heads):
+    cap = 32 * 700
+    sizes = {vk.workspace_bytes(vk.make_params(1, batch, heads, heads, 32 * g, 16, 0, t_capacity=cap), 2)
+             for g in list(range(1, 60)) + [100, 257, 699, 700]}
+    assert len(sizes) == 1
+    full = [vk.workspace_bytes(vk.make_params(1, batch, heads, heads, 32 * g, 16, 0), 2) for g in range(1, 700)]
+    assert full == sorted(full) and full[-1] <= max(sizes)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("batch,heads", [(1, 1), (9, 4), (31, 4), (43, 3), (129, 1), (130, 4)])
+@pytest.mark.parametrize("cap", [1, 40, 256])
+def test_grids_around_one_round(batch, heads, cap):
+    w = dataclasses.replace(synth.reduced(synth.WORKLOADS["c3_stack"], 8, L=1, B=batch), Hkv=heads, Hq=2 * heads)
+    print(f"[case] {batch} x {heads} heads, residual capacity {cap}", flush=True)
+    K, V = synth.device_kv(w, DEV)
+    run = P.GpuRun(w, DEV, K=K, V=V)
+    g = torch.Generator(device=DEV); g.manual_seed(cap)
+    shape = (batch, heads, cap, 128)
+    Kt, Vt = (torch.randn(shape, generator=g, device=DEV).to(torch.float16) for _ in range(2))
+    tl = torch.randint(0, cap + 1, (batch,), generator=g, device=DEV, dtype=torch.int32)
+    tl[0], tl[-1] = cap, 0 if batch > 1 else cap
+    q = synth.query(w, 0)
+    out = run.attention(0, torch.from_numpy(q).to(DEV), Kt, Vt, cap, tl).cpu().numpy()
+    for b in {0, batch // 2, batch - 1}:
+        n = int(tl[b])
+        ref = P.oracle_attention(run, 0, b, q[b], Kt[b, :, :n].cpu().numpy(), Vt[b, :, :n].cpu().numpy())
+        P.assert_out_close(out[b], ref, f"seq {b}")
