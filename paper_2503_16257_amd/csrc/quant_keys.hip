@@ -2,172 +2,42 @@
 // top-n_a channel selection, and per 32-token group the 2-bit uniform code
 // (Eq. 4) of the selected channels and the sign bits of a 32-point real DFT
 // (Eq. 5) of the others.
-#include "vidkv_common.h"
+#include "select_keys.h"
+#include "select_values.h"
 
 namespace vidkv {
 
-// ---------------------------------------------------------------------------
-// Pass 1: partial per-channel min / max over RANGE_CHUNK tokens of one head.
-// grid (range_chunks, nheads), block 256.  Thread (row = tid/16, col = tid%16)
-// streams 16-byte pieces (8 channels) of rows row, row+16, ...; fp16 min/max
-// are exact, so no precision is involved.
-// ws layout: fp16 [nheads][chunks][2][128]  (min then max).
-// ---------------------------------------------------------------------------
+// Pass 1 as a launch of its own.  grid (range_chunks, nheads), block 256.
 __global__ __launch_bounds__(256) void k_range_kernel(const u32x4* __restrict__ K, int T,
                                                       int chunks, _Float16* __restrict__ ws) {
-  const int chunk = blockIdx.x;
-  const long long hd = blockIdx.y;
-  const int tid = threadIdx.x;
-  const int col = tid & 15, row = tid >> 4;
-  const int t0 = chunk * RANGE_CHUNK;
-  const int t1 = min(T, t0 + RANGE_CHUNK);
-  const u32x4* base = K + (hd * T) * 16 + col;   // 16 u32x4 per token row
-
-  const _Float16 big = (_Float16)65504.0f;
-  h2 mn[4], mx[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) { mn[i] = h2{big, big}; mx[i] = h2{-big, -big}; }
-
-  int t = t0 + row;
-  // 4 independent 16-byte loads in flight per thread
-  for (; t + 48 < t1; t += 64) {
-    U4H a, b, c, d;
-    a.u = __builtin_nontemporal_load(base + (long long)t * 16);
-    b.u = __builtin_nontemporal_load(base + (long long)(t + 16) * 16);
-    c.u = __builtin_nontemporal_load(base + (long long)(t + 32) * 16);
-    d.u = __builtin_nontemporal_load(base + (long long)(t + 48) * 16);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      mn[i] = __builtin_elementwise_min(__builtin_elementwise_min(mn[i], a.h[i]),
-                                        __builtin_elementwise_min(b.h[i], c.h[i]));
-      mn[i] = __builtin_elementwise_min(mn[i], d.h[i]);
-      mx[i] = __builtin_elementwise_max(__builtin_elementwise_max(mx[i], a.h[i]),
-                                        __builtin_elementwise_max(b.h[i], c.h[i]));
-      mx[i] = __builtin_elementwise_max(mx[i], d.h[i]);
-    }
-  }
-  for (; t < t1; t += 16) {
-    U4H a;
-    a.u = __builtin_nontemporal_load(base + (long long)t * 16);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      mn[i] = __builtin_elementwise_min(mn[i], a.h[i]);
-      mx[i] = __builtin_elementwise_max(mx[i], a.h[i]);
-    }
-  }
-
-  __shared__ h2 smn[16][16][4];
-  __shared__ h2 smx[16][16][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) { smn[row][col][i] = mn[i]; smx[row][col][i] = mx[i]; }
-  __syncthreads();
-  if (tid < 128) {
-    const int c8 = tid >> 3, e = tid & 7;
-    _Float16 lo = big, hi = -big;
-    for (int r = 0; r < 16; ++r) {
-      const _Float16 a = smn[r][c8][e >> 1][e & 1];
-      const _Float16 b = smx[r][c8][e >> 1][e & 1];
-      lo = a < lo ? a : lo;
-      hi = b > hi ? b : hi;
-    }
-    _Float16* o = ws + ((hd * chunks + chunk) * 2) * D;
-    o[tid] = lo;
-    o[D + tid] = hi;
-  }
+  __shared__ RangeLds lds;
+  range_part(K, T, chunks, ws, blockIdx.x, blockIdx.y, threadIdx.x, true, lds);
 }
 
-// ---------------------------------------------------------------------------
-// Channel selection: R_c = float(max) - float(min); the n_a largest (ties to
-// the lower channel) are anomalous.  perm = anomalous ascending, then normal
-// ascending.  grid nheads, block 1024: 64 slices of the chunk list, 8 channels per thread.
-// ---------------------------------------------------------------------------
+// Pass 1 with the protected-token selection of the same call in the first B workgroups: a chain of
+// dependent work that needs no bandwidth, beside a pass that needs nothing else.  Workgroups of
+// 1024 threads, four chunks each.
+// (28 x 6272 tokens: range pass 29 us, then six selection launches of 4.7 us; both in one 31.4.)
+__global__ __launch_bounds__(1024, 8) void k_range_select_kernel(const u32x4* __restrict__ K, int T,
+                                                                 int chunks, int total, int B,
+                                                                 _Float16* __restrict__ ws, OneSelArgs sel) {
+  __shared__ union { RangeLds range[4]; OneSelLds one; } lds;
+  if ((int)blockIdx.x < B) {
+    select_one(sel, blockIdx.x, lds.one);
+    return;
+  }
+  const int sub = threadIdx.x >> 8;
+  const int id = (blockIdx.x - B) * 4 + sub;
+  const bool on = id < total;
+  range_part(K, T, chunks, ws, on ? id % chunks : 0, on ? id / chunks : 0, threadIdx.x & 255, on, lds.range[sub]);
+}
+
+// Channel selection as a launch of its own.  grid nheads, block 1024.
 __global__ __launch_bounds__(1024) void k_select_kernel(const _Float16* __restrict__ ws,
                                                         int chunks, int n_a,
                                                         uint8_t* __restrict__ perm) {
-  const long long hd = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // gather: thread (slice = tid / 16, col = tid % 16) folds 8 channels of the
-  // chunks slice, slice + 64, ... with 16-byte loads, 8 chunks in flight
-  const int col = tid & 15, slice = tid >> 4;
-  const u32x4* p4 = reinterpret_cast<const u32x4*>(ws + hd * chunks * 2 * D) + col;
-  const _Float16 big = (_Float16)65504.0f;
-  h2 mn[4], mx[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) { mn[i] = h2{big, big}; mx[i] = h2{-big, -big}; }
-  for (int k0 = slice; k0 < chunks; k0 += 512) {
-    U4H a[8], b[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int k = k0 + 64 * u;
-      const int kk = k < chunks ? k : k0;             // a repeated chunk changes nothing
-      a[u].u = p4[(kk * 2) * 16];
-      b[u].u = p4[(kk * 2 + 1) * 16];
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        mn[i] = __builtin_elementwise_min(mn[i], a[u].h[i]);
-        mx[i] = __builtin_elementwise_max(mx[i], b[u].h[i]);
-      }
-  }
-  // the 4 slices of a wave (lanes 16 apart), then the 16 waves through LDS
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-#pragma unroll
-    for (int d = 16; d <= 32; d <<= 1) {
-      mn[i] = __builtin_elementwise_min(mn[i], __builtin_bit_cast(h2, __shfl_xor(__builtin_bit_cast(int, mn[i]), d, 64)));
-      mx[i] = __builtin_elementwise_max(mx[i], __builtin_bit_cast(h2, __shfl_xor(__builtin_bit_cast(int, mx[i]), d, 64)));
-    }
-  }
-  __shared__ h2 smn[16][16][4];
-  __shared__ h2 smx[16][16][4];
-  __shared__ float R[D];
-  __shared__ int cnt0;
-  if (lane < 16) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) { smn[wave][col][i] = mn[i]; smx[wave][col][i] = mx[i]; }
-  }
-  __syncthreads();
-  // from here on threads 0..127 (waves 0 and 1) own one channel each; the other
-  // waves only keep the barriers company
-  const int c = tid & (D - 1);
-  const bool own = tid < D;
-  float r = 0.0f;
-  if (own) {
-    const int c8 = c >> 3, e = c & 7;
-    _Float16 lo = big, hi = -big;
-#pragma unroll
-    for (int s = 0; s < 16; ++s) {
-      const _Float16 a = smn[s][c8][e >> 1][e & 1];
-      const _Float16 b = smx[s][c8][e >> 1][e & 1];
-      lo = a < lo ? a : lo;
-      hi = b > hi ? b : hi;
-    }
-    r = (float)hi - (float)lo;
-    R[c] = r;
-  }
-  __syncthreads();
-  int an = 0, below = 0;
-  if (own) {
-    int rank = 0;
-#pragma unroll 16
-    for (int j = 0; j < D; ++j) {
-      const float rj = R[j];
-      rank += (rj > r || (rj == r && j < c)) ? 1 : 0;
-    }
-    an = rank < n_a ? 1 : 0;
-  }
-  // anomalous channels below mine: inside my wave by ballot, wave 0's total through LDS
-  const unsigned long long bal = __ballot(an);
-  below = __popcll(bal & ((1ull << lane) - 1ull));
-  if (tid == 0) cnt0 = __popcll(bal);
-  __syncthreads();
-  if (own) {
-    if (wave == 1) below += cnt0;
-    const int pos = an ? below : n_a + (c - below);
-    perm[hd * D + pos] = (uint8_t)c;
-  }
+  __shared__ ChanSelLds<1024> lds;
+  select_channels<1024>(ws, chunks, n_a, perm, blockIdx.x, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -261,6 +131,15 @@ __global__ __launch_bounds__(128) void k_metric_select_kernel(const double* __re
 // The per-group coding pass (Eq. 4 and Eq. 5) lives in quant_keys_mfma.hip.
 void launch_k_encode(const Geom& g, const EncodeSpan& sp, const void* K, uint8_t* packed,
                      bool use_fft, hipStream_t st);
+
+// The range pass (Range metric) and the protected-token selection of short sequences in one launch.
+void launch_k_range_select(const Geom& g, const void* K, void* ws, const float* scores, const int32_t* idx,
+                           uint8_t* packed_V, hipStream_t st) {
+  const int total = (int)(g.nheads * g.range_chunks);            // T <= ONE_MAX_T: at most 65535 * 64
+  hipLaunchKernelGGL(k_range_select_kernel, dim3(g.B + (total + 3) / 4), dim3(1024), 0, st,
+                     reinterpret_cast<const u32x4*>(K), g.T, g.range_chunks, total, g.B,
+                     reinterpret_cast<_Float16*>(ws), one_sel_args(g, scores, idx, packed_V));
+}
 
 // ---------------------------------------------------------------------------
 // stages: bit 0 range pass, bit 1 channel selection, bit 2 coding pass

@@ -20,12 +20,13 @@
 //  4. Anomalous channels: min / max over the 32 tokens, codes, 4 channels per
 //     byte assembled inside lane quads.
 // The record is assembled in LDS and written with 16-byte stores.
-#include "mfma_util.h"
+#include "protect2.h"
+#include "quant_values_enc.h"
 
 namespace vidkv {
 
 constexpr int ENC_MAXT = 9;          // channel tiles of 16: at most 1 + 8
-constexpr int ENC_ROW = 272;         // LDS bytes per token row (256 + 16 of padding)
+constexpr int ENC_ROW = VENC_ROW;    // LDS bytes per token row (256 + 16 of padding)
 
 // DFT operand table.  Slot x of tile tt (tt = 0: Re X[0..15]; tt = 1: Re X[16],
 // Im X[1..15]) against token t: 64 * (w/2) * {cos, -sin}(2 pi k t / 32), with
@@ -69,14 +70,29 @@ static __device__ const DftTab kDftTab = make_dft_tab();
 // the record keeps its shape, bit (blk, k) e / 8 + e holds the code of channel
 // 8 blk + e at token k / 16 + k, and the two scale slots hold s = max - min and
 // z = min.
-template <int NA8T, bool FFT>
+// EXTRA: the first x_rows rows of the grid do something else of the same call, 1: code the protected
+// value rows (2 bits), 2: the value coding pass (a flush: both blocks are small, one launch).
+template <int NA8T, bool FFT, int EXTRA>
 __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restrict__ K,
                                                             const uint8_t* __restrict__ perm_g,
                                                             int T, int ng, int n_a_rt, int krec, int gpb,
                                                             int ngc, int g_out0,
-                                                            uint8_t* __restrict__ rec_out) {
+                                                            uint8_t* __restrict__ rec_out, int x_rows,
+                                                            Protect2Args p2, VEncArgs ve) {
   const int n_a = NA8T >= 0 ? 8 * NA8T : n_a_rt;
-  const long long hd = blockIdx.y;
+  __shared__ EncTile tile4[4];                    // per wave: the group's tile
+  if (EXTRA == 1 && (int)blockIdx.y < x_rows) {
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long long id = 4 * ((long long)blockIdx.y * gridDim.x + blockIdx.x) + w;
+    if (id < p2.total) protect2_part(p2, id, reinterpret_cast<Protect2Lds*>(&tile4[0][0])[w]);
+    return;
+  }
+  if (EXTRA == 2 && (int)blockIdx.y < x_rows) {
+    v_encode_part<true>(ve.V, ve.T, ve.ng, ve.B, ve.H, ve.n_s, ve.gamma, ve.gpb, ve.ngc, ve.g_out0, ve.mask, ve.rank,
+                        ve.rec_out, ve.rows_out, ve.mask, ve.rank, ve.mark_rank, blockIdx.x, blockIdx.y, tile4);
+    return;
+  }
+  const long long hd = blockIdx.y - (EXTRA ? x_rows : 0);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int x16 = lane & 15, kb = lane >> 4;
@@ -84,7 +100,6 @@ __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restr
   const int NTa = (n_a + 15) >> 4, NTn = (n_n + 15) >> 4, NT = NTa + NTn;
   const int nq = n_a >> 2;
 
-  __shared__ u32x4 tile4[4][32 * ENC_ROW / 16];   // per wave: the group's tile
   // per wave: the record being assembled (12 n_a + 8 n_n bytes; 1536 at most).  With n_a known
   // the workgroup stays below a quarter of the LDS and four of them share a compute unit.
   constexpr int RECB = NA8T >= 0 ? 12 * 8 * NA8T + 8 * (D - 8 * NA8T) : 1536;
@@ -300,32 +315,66 @@ __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restr
   }
 }
 
-void launch_k_encode(const Geom& g, const EncodeSpan& sp, const void* K, uint8_t* packed,
-                     bool use_fft, hipStream_t st) {
-  // two groups per wave: short-lived workgroups keep the memory system evenly loaded,
-  // and the second group's load overlaps the first group's arithmetic
-  const int gpb = 8;
-  dim3 grid((sp.ng + gpb - 1) / gpb, (unsigned)sp.heads);
+template <int NA8T, int EXTRA>
+static void launch_one(bool use_fft, dim3 grid, hipStream_t st, const u32x4* k4, const uint8_t* perm, const Geom& g,
+                       const EncodeSpan& sp, int gpb, uint8_t* rec, int rows, const Protect2Args& p2, const VEncArgs& ve) {
+  if (use_fft)
+    hipLaunchKernelGGL((k_encode_mfma_kernel<NA8T, true, EXTRA>), grid, dim3(256), 0, st, k4, perm, sp.in_tokens, sp.ng,
+                       g.n_a, g.krec, gpb, g.ngc, sp.g_out0, rec, rows, p2, ve);
+  else
+    hipLaunchKernelGGL((k_encode_mfma_kernel<NA8T, false, EXTRA>), grid, dim3(256), 0, st, k4, perm, sp.in_tokens, sp.ng,
+                       g.n_a, g.krec, gpb, g.ngc, sp.g_out0, rec, rows, p2, ve);
+}
+
+template <int EXTRA>
+static void launch_any(const Geom& g, const EncodeSpan& sp, int gpb, int gx, const void* K, uint8_t* packed, bool use_fft,
+                       hipStream_t st, int rows, const Protect2Args& p2, const VEncArgs& ve) {
+  const dim3 grid(gx, (unsigned)(sp.heads + rows));
   const u32x4* k4 = reinterpret_cast<const u32x4*>(K);
   const uint8_t* perm = packed + g.k_perm + sp.head0 * D;
   uint8_t* rec = packed + g.k_rec + (size_t)sp.head0 * g.ngc * g.krec;
-#define VIDKV_ENC(N)                                                                          \
-  do {                                                                                        \
-    if (use_fft)                                                                              \
-      hipLaunchKernelGGL((k_encode_mfma_kernel<N, true>), grid, dim3(256), 0, st, k4, perm,   \
-                         sp.in_tokens, sp.ng, g.n_a, g.krec, gpb, g.ngc, sp.g_out0, rec);     \
-    else                                                                                      \
-      hipLaunchKernelGGL((k_encode_mfma_kernel<N, false>), grid, dim3(256), 0, st, k4, perm,  \
-                         sp.in_tokens, sp.ng, g.n_a, g.krec, gpb, g.ngc, sp.g_out0, rec);     \
-  } while (0)
   switch (g.n_a) {
-    case 8:  VIDKV_ENC(1); break;
-    case 16: VIDKV_ENC(2); break;
-    case 32: VIDKV_ENC(4); break;
-    case 64: VIDKV_ENC(8); break;
-    default: VIDKV_ENC(-1); break;
+    case 8:  launch_one<1, EXTRA>(use_fft, grid, st, k4, perm, g, sp, gpb, rec, rows, p2, ve); break;
+    case 16: launch_one<2, EXTRA>(use_fft, grid, st, k4, perm, g, sp, gpb, rec, rows, p2, ve); break;
+    case 32: launch_one<4, EXTRA>(use_fft, grid, st, k4, perm, g, sp, gpb, rec, rows, p2, ve); break;
+    case 64: launch_one<8, EXTRA>(use_fft, grid, st, k4, perm, g, sp, gpb, rec, rows, p2, ve); break;
+    case 0: launch_one<0, EXTRA>(use_fft, grid, st, k4, perm, g, sp, gpb, rec, rows, p2, ve); break;
+    case 96: launch_one<12, EXTRA>(use_fft, grid, st, k4, perm, g, sp, gpb, rec, rows, p2, ve); break;
+    case 128: launch_one<16, EXTRA>(use_fft, grid, st, k4, perm, g, sp, gpb, rec, rows, p2, ve); break;
+    default: launch_one<-1, EXTRA>(use_fft, grid, st, k4, perm, g, sp, gpb, rec, rows, p2, ve); break;
   }
-#undef VIDKV_ENC
+}
+
+// two groups per wave: short-lived workgroups keep the memory system evenly loaded,
+// and the second group's load overlaps the first group's arithmetic
+constexpr int K_GPB = 8;
+
+void launch_k_encode(const Geom& g, const EncodeSpan& sp, const void* K, uint8_t* packed,
+                     bool use_fft, hipStream_t st) {
+  launch_any<0>(g, sp, K_GPB, (sp.ng + K_GPB - 1) / K_GPB, K, packed, use_fft, st, 0, Protect2Args{}, VEncArgs{});
+}
+
+// false: too many heads for one grid, nothing done
+bool launch_k_encode_protect2(const Geom& g, const void* K, uint8_t* packed_K, const void* V, uint8_t* packed_V,
+                              hipStream_t st) {
+  const Protect2Args p2 = protect2_args(g, V, packed_V);
+  const EncodeSpan sp{g.T, g.ng, 0, g.nheads, 0};
+  const long long gx = (g.ng + K_GPB - 1) / K_GPB, rows = ((p2.total + 3) / 4 + gx - 1) / gx;
+  if (g.nheads + rows > 65535) return false;
+  launch_any<1>(g, sp, K_GPB, (int)gx, K, packed_K, g.use_fft, st, (int)rows, p2, VEncArgs{});
+  return true;
+}
+
+// Key and value coding passes of a residual block, MASK and RANK of its groups: one launch, one group
+// per wave.  As three (5.6 + 4.0 + 1.3 us and their gaps at 4 heads x 128 tokens) 28 layers took 446 us,
+// as one (5.8 us) 269, most of it the caller's.
+bool launch_flush_encode(const Geom& g, const EncodeSpan& sp, float gamma, const void* K, const void* V,
+                         uint8_t* packed_K, uint8_t* packed_V, hipStream_t st) {
+  if (2 * sp.heads > 65535) return false;
+  VEncArgs ve = v_encode_args(g, sp, 0, gamma, V, packed_V);
+  if (g.n_s > 0) ve.mark_rank = g.n_s;
+  launch_any<2>(g, sp, ve.gpb, (sp.ng + ve.gpb - 1) / ve.gpb, K, packed_K, g.use_fft, st, (int)sp.heads, Protect2Args{}, ve);
+  return true;
 }
 
 }  // namespace vidkv

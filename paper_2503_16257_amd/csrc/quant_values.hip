@@ -1,15 +1,10 @@
 // Value quantizer kernels (Alg. 2): protected-token selection (top-n saliency
 // scores, Sec. 3.3 (2)) and the per-channel ternary code of Eq. 6 over
 // 32-token groups, with protected rows copied verbatim in fp16.
-#include "vidkv_common.h"
+#include "protect2.h"
+#include "select_values.h"
 
 namespace vidkv {
-
-// Order-preserving map float -> uint32 (ascending).
-__device__ __forceinline__ uint32_t fkey(float f) {
-  const uint32_t b = __float_as_uint(f + 0.0f);   // -0 and +0 are the same score
-  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-}
 
 // Exclusive scan of one int per thread over a 256-thread block; `sw` is LDS
 // scratch of 4 ints.  Returns the exclusive prefix, *total the block sum.
@@ -36,7 +31,8 @@ __device__ __forceinline__ int block_exscan_256(int v, int* sw, int* total) {
 }
 
 // ---------------------------------------------------------------------------
-// Protected-token selection, several workgroups per sequence.
+// Protected-token selection, several workgroups per sequence (sequences of more than ONE_MAX_T
+// tokens; shorter ones: select_values.h).
 //
 // From scores: the n_s largest by (score desc, index asc) via a 3-level radix
 // select on the ordered 32-bit keys (11 + 11 + 10 bits).  Each level is one
@@ -77,6 +73,12 @@ __device__ __host__ inline SelWs sel_ws(void* ws, int B, int nslice) {
   w.cnt = p;
   w.nslice = nslice;
   return w;
+}
+
+// The selection of a short sequence: one workgroup each, one launch.
+__global__ __launch_bounds__(ONE_THREADS) void v_select_one_kernel(OneSelArgs a) {
+  __shared__ OneSelLds s;
+  select_one(a, blockIdx.x, s);
 }
 
 // zeroes the histograms (and, for the index-list path, MASK)
@@ -289,62 +291,21 @@ __global__ __launch_bounds__(256) void v_sel_scatter_kernel(const int32_t* __res
 void launch_v_encode(const Geom& g, const EncodeSpan& sp, int n_s, float gamma, const void* V,
                      uint8_t* packed, hipStream_t st);
 
-// Alg. 2, STPQuant, protected branch: the protected rows of one head, gathered
-// in token order, coded with Eq. 4 at 2 bits per channel over groups of 32
-// protected tokens (the last group may hold fewer).  grid (npg, nheads), block
-// 128: thread = channel.  Record: codes [32 rows][32 bytes] (channel 4 j + r of
-// a row in bits 2r.. of byte j), fp16 s[128], fp16 z[128].
-__global__ __launch_bounds__(128) void v_protect2_kernel(const _Float16* __restrict__ V, int T,
-                                                         int B, int H, int n_s, int npg,
-                                                         const int32_t* __restrict__ idx,
-                                                         uint8_t* __restrict__ out) {
-  const int pg = blockIdx.x, c = threadIdx.x;
-  const long long hd = blockIdx.y;
-  const int b = (int)((hd / H) % B);
-  const int cnt = min(G, n_s - pg * G);
-  __shared__ int tok[G];
-  __shared__ uint8_t code_s[G][D];
-  // rows beyond the last one repeat it: every load is valid and changes neither min nor max
-  // (an index list with repeated or out-of-range entries leaves the end of IDX unwritten:
-  // whatever is there is clamped into the tensor, such rows are never read back)
-  if (c < G) tok[c] = min(max(idx[(size_t)b * n_s + pg * G + min(c, cnt - 1)], 0), T - 1);
-  __syncthreads();
-  const _Float16* head = V + hd * (long long)T * D;
-  _Float16 xh[G];
-#pragma unroll
-  for (int r = 0; r < G; ++r) xh[r] = head[(size_t)tok[r] * D + c];
-  float x[G];
-  float lo = 65504.0f, hi = -65504.0f;
-#pragma unroll
-  for (int r = 0; r < G; ++r) {
-    x[r] = (float)xh[r];
-    lo = fminf(lo, x[r]);
-    hi = fmaxf(hi, x[r]);
-  }
-  const float rng = hi - lo;
-  const float inv = rng > 0.0f ? 3.0f / rng : 0.0f;
-#pragma unroll
-  for (int r = 0; r < G; ++r) {
-    float u = (x[r] - lo) * inv;
-    u = fminf(fmaxf(rintf(u), 0.0f), 3.0f);
-    code_s[r][c] = r < cnt ? (uint8_t)u : (uint8_t)0;
-  }
-  uint8_t* rec = out + (hd * npg + pg) * (long long)PREC;
-  reinterpret_cast<_Float16*>(rec + 1024)[c] = (_Float16)(rng / 3.0f);
-  reinterpret_cast<_Float16*>(rec + 1280)[c] = (_Float16)lo;
-  __syncthreads();
-  // 256 dwords of codes: dword w = row w / 8, channels 16 (w % 8) ..
-  for (int w = c; w < 256; w += 128) {
-    const int r = w >> 3, c0 = 16 * (w & 7);
-    uint32_t v = 0;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) v |= (uint32_t)code_s[r][c0 + k] << (2 * k);
-    reinterpret_cast<uint32_t*>(rec)[w] = v;
-  }
+__global__ __launch_bounds__(256) void v_protect2_kernel(Protect2Args a) {
+  __shared__ Protect2Lds lds[4];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const long long id = 4LL * blockIdx.x + wave;
+  if (id < a.total) protect2_part(a, id, lds[wave]);
+}
+
+Protect2Args protect2_args(const Geom& g, const void* V, uint8_t* packed) {
+  return Protect2Args{reinterpret_cast<const _Float16*>(V), g.T, g.B, g.H, g.n_s, g.npg,
+                      reinterpret_cast<const int32_t*>(packed + g.v_idx), packed + g.v_rows, g.nheads * g.npg};
 }
 
 // MASK and RANK of groups appended behind the prefill tokens: none of their
-// tokens is protected, all n_s protected tokens lie before them.
+// tokens is protected, all n_s protected tokens lie before them.  (Only where a flush has too many
+// heads for the one launch that does it all.)
 __global__ __launch_bounds__(256) void v_flush_marks_kernel(uint32_t* __restrict__ mask,
                                                             uint32_t* __restrict__ rank, int B,
                                                             int ngc, int g0, int n, uint32_t n_s) {
@@ -370,6 +331,18 @@ size_t values_ws_bytes(const Geom& g) {
   return align256(sel_ws_ints(g.B, nslice > 0 ? nslice : 1) * sizeof(int)) + 256;
 }
 
+void launch_v_protect2(const Geom& g, const void* V, uint8_t* packed, hipStream_t st) {
+  hipLaunchKernelGGL(v_protect2_kernel, dim3((unsigned)((g.nheads * g.npg + 3) / 4)), dim3(256), 0, st,
+                     protect2_args(g, V, packed));
+}
+
+bool one_workgroup_selection(const Geom& g) { return g.T <= ONE_MAX_T; }
+
+OneSelArgs one_sel_args(const Geom& g, const float* scores, const int32_t* idx, uint8_t* packed) {
+  return OneSelArgs{scores, idx, g.T, g.ng, g.ngc, g.n_s, reinterpret_cast<int32_t*>(packed + g.v_idx),
+                    reinterpret_cast<uint32_t*>(packed + g.v_mask), reinterpret_cast<uint32_t*>(packed + g.v_rank)};
+}
+
 hipError_t launch_quantize_values(const Geom& g, float gamma, const void* V, const float* scores,
                                   const int32_t* idx, uint8_t* packed, void* ws,
                                   unsigned stages, hipStream_t st) {
@@ -377,7 +350,11 @@ hipError_t launch_quantize_values(const Geom& g, float gamma, const void* V, con
   uint32_t* mask = reinterpret_cast<uint32_t*>(packed + g.v_mask);
   uint32_t* rank = reinterpret_cast<uint32_t*>(packed + g.v_rank);
   // stages: bit 0 protected-token selection, bit 1 coding pass
-  if (g.n_s > 0 && (stages & 1u)) {
+  if (g.n_s > 0 && (stages & 1u) && one_workgroup_selection(g)) {
+    // One workgroup reads a sequence once and keeps its scores in registers: one launch of 5 to 10 us
+    // instead of six of 2 to 5 us, each waiting for the one before
+    hipLaunchKernelGGL(v_select_one_kernel, dim3(g.B), dim3(ONE_THREADS), 0, st, one_sel_args(g, scores, idx, packed));
+  } else if (g.n_s > 0 && (stages & 1u)) {
     const int nslice = (g.T + SEL_SLICE - 1) / SEL_SLICE;
     SelWs w = sel_ws(ws, g.B, nslice);
     const size_t n_hist = (size_t)g.B * 3 * SEL_BINS;
@@ -406,9 +383,7 @@ hipError_t launch_quantize_values(const Geom& g, float gamma, const void* V, con
   if (stages & 2u) {
     launch_v_encode(g, EncodeSpan{g.T, g.ng, 0, g.nheads, 0}, g.n_s, gamma, V, packed, st);
     if (g.n_s > 0 && g.sal_bits == 2)
-      hipLaunchKernelGGL(v_protect2_kernel, dim3(g.npg, (unsigned)g.nheads), dim3(128), 0, st,
-                         reinterpret_cast<const _Float16*>(V), g.T, g.B, g.H, g.n_s, g.npg,
-                         reinterpret_cast<const int32_t*>(packed + g.v_idx), packed + g.v_rows);
+      launch_v_protect2(g, V, packed, st);
   }
   return hipGetLastError();
 }

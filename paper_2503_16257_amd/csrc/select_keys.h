@@ -1,0 +1,182 @@
+// Per-channel range over all tokens and top-n_a channel selection of the key quantizer (Alg. 3), as
+// pieces that a launch of their own or a part of another one runs.
+#pragma once
+#include "vidkv_common.h"
+
+namespace vidkv {
+
+// ---------------------------------------------------------------------------
+// Pass 1: partial per-channel min / max over RANGE_CHUNK tokens of one head.
+// 256 threads: thread (row = tid/16, col = tid%16)
+// streams 16-byte pieces (8 channels) of rows row, row+16, ...; fp16 min/max
+// are exact, so no precision is involved.
+// ws layout: fp16 [nheads][chunks][2][128]  (min then max).
+// ---------------------------------------------------------------------------
+struct RangeLds {
+  h2 mn[16][16][4], mx[16][16][4];
+};
+
+// on = false: nothing is read or written, only the barrier is kept
+__device__ __forceinline__ void range_part(const u32x4* __restrict__ K, int T, int chunks,
+                                           _Float16* __restrict__ ws, int chunk, long long hd, int tid,
+                                           bool on, RangeLds& lds) {
+  const int col = tid & 15, row = tid >> 4;
+  const int t0 = chunk * RANGE_CHUNK;
+  const int t1 = on ? min(T, t0 + RANGE_CHUNK) : 0;
+  const u32x4* base = K + (hd * T) * 16 + col;   // 16 u32x4 per token row
+
+  const _Float16 big = (_Float16)65504.0f;
+  h2 mn[4], mx[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { mn[i] = h2{big, big}; mx[i] = h2{-big, -big}; }
+
+  int t = t0 + row;
+  // 4 independent 16-byte loads in flight per thread
+  for (; t + 48 < t1; t += 64) {
+    U4H a, b, c, d;
+    a.u = __builtin_nontemporal_load(base + (long long)t * 16);
+    b.u = __builtin_nontemporal_load(base + (long long)(t + 16) * 16);
+    c.u = __builtin_nontemporal_load(base + (long long)(t + 32) * 16);
+    d.u = __builtin_nontemporal_load(base + (long long)(t + 48) * 16);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      mn[i] = __builtin_elementwise_min(__builtin_elementwise_min(mn[i], a.h[i]),
+                                        __builtin_elementwise_min(b.h[i], c.h[i]));
+      mn[i] = __builtin_elementwise_min(mn[i], d.h[i]);
+      mx[i] = __builtin_elementwise_max(__builtin_elementwise_max(mx[i], a.h[i]),
+                                        __builtin_elementwise_max(b.h[i], c.h[i]));
+      mx[i] = __builtin_elementwise_max(mx[i], d.h[i]);
+    }
+  }
+  for (; t < t1; t += 16) {
+    U4H a;
+    a.u = __builtin_nontemporal_load(base + (long long)t * 16);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      mn[i] = __builtin_elementwise_min(mn[i], a.h[i]);
+      mx[i] = __builtin_elementwise_max(mx[i], a.h[i]);
+    }
+  }
+
+  h2 (&smn)[16][16][4] = lds.mn;
+  h2 (&smx)[16][16][4] = lds.mx;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { smn[row][col][i] = mn[i]; smx[row][col][i] = mx[i]; }
+  __syncthreads();
+  if (on && tid < 128) {
+    const int c8 = tid >> 3, e = tid & 7;
+    _Float16 lo = big, hi = -big;
+    for (int r = 0; r < 16; ++r) {
+      const _Float16 a = smn[r][c8][e >> 1][e & 1];
+      const _Float16 b = smx[r][c8][e >> 1][e & 1];
+      lo = a < lo ? a : lo;
+      hi = b > hi ? b : hi;
+    }
+    _Float16* o = ws + ((hd * chunks + chunk) * 2) * D;
+    o[tid] = lo;
+    o[D + tid] = hi;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Channel selection: R_c = float(max) - float(min); the n_a largest (ties to
+// the lower channel) are anomalous.  perm = anomalous ascending, then normal
+// ascending.  NT threads: NT / 16 slices of the chunk list, 8 channels per thread.
+// ---------------------------------------------------------------------------
+template <int NT>
+struct ChanSelLds {
+  h2 mn[NT / 64][16][4], mx[NT / 64][16][4];
+  float R[D];
+  int cnt0;
+};
+
+template <int NT>
+__device__ __forceinline__ void select_channels(const _Float16* __restrict__ ws, int chunks, int n_a,
+                                                uint8_t* __restrict__ perm, long long hd, ChanSelLds<NT>& lds) {
+  constexpr int SL = NT / 16;                        // slices
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // gather: thread (slice = tid / 16, col = tid % 16) folds 8 channels of the
+  // chunks slice, slice + SL, ... with 16-byte loads, 8 chunks in flight
+  const int col = tid & 15, slice = tid >> 4;
+  const u32x4* p4 = reinterpret_cast<const u32x4*>(ws + hd * chunks * 2 * D) + col;
+  const _Float16 big = (_Float16)65504.0f;
+  h2 mn[4], mx[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { mn[i] = h2{big, big}; mx[i] = h2{-big, -big}; }
+  for (int k0 = slice; k0 < chunks; k0 += 8 * SL) {
+    U4H a[8], b[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int k = k0 + SL * u;
+      const int kk = k < chunks ? k : k0;             // a repeated chunk changes nothing
+      a[u].u = p4[(kk * 2) * 16];
+      b[u].u = p4[(kk * 2 + 1) * 16];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        mn[i] = __builtin_elementwise_min(mn[i], a[u].h[i]);
+        mx[i] = __builtin_elementwise_max(mx[i], b[u].h[i]);
+      }
+  }
+  // the 4 slices of a wave (lanes 16 apart), then the waves through LDS
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+#pragma unroll
+    for (int d = 16; d <= 32; d <<= 1) {
+      mn[i] = __builtin_elementwise_min(mn[i], __builtin_bit_cast(h2, __shfl_xor(__builtin_bit_cast(int, mn[i]), d, 64)));
+      mx[i] = __builtin_elementwise_max(mx[i], __builtin_bit_cast(h2, __shfl_xor(__builtin_bit_cast(int, mx[i]), d, 64)));
+    }
+  }
+  auto& smn = lds.mn;
+  auto& smx = lds.mx;
+  float (&R)[D] = lds.R;
+  int& cnt0 = lds.cnt0;
+  if (lane < 16) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { smn[wave][col][i] = mn[i]; smx[wave][col][i] = mx[i]; }
+  }
+  __syncthreads();
+  // from here on threads 0..127 (waves 0 and 1) own one channel each; the other
+  // waves only keep the barriers company
+  const int c = tid & (D - 1);
+  const bool own = tid < D;
+  float r = 0.0f;
+  if (own) {
+    const int c8 = c >> 3, e = c & 7;
+    _Float16 lo = big, hi = -big;
+#pragma unroll
+    for (int s = 0; s < NT / 64; ++s) {
+      const _Float16 a = smn[s][c8][e >> 1][e & 1];
+      const _Float16 b = smx[s][c8][e >> 1][e & 1];
+      lo = a < lo ? a : lo;
+      hi = b > hi ? b : hi;
+    }
+    r = (float)hi - (float)lo;
+    R[c] = r;
+  }
+  __syncthreads();
+  int an = 0, below = 0;
+  if (own) {
+    int rank = 0;
+#pragma unroll 16
+    for (int j = 0; j < D; ++j) {
+      const float rj = R[j];
+      rank += (rj > r || (rj == r && j < c)) ? 1 : 0;
+    }
+    an = rank < n_a ? 1 : 0;
+  }
+  // anomalous channels below mine: inside my wave by ballot, wave 0's total through LDS
+  const unsigned long long bal = __ballot(an);
+  below = __popcll(bal & ((1ull << lane) - 1ull));
+  if (tid == 0) cnt0 = __popcll(bal);
+  __syncthreads();
+  if (own) {
+    if (wave == 1) below += cnt0;
+    const int pos = an ? below : n_a + (c - below);
+    perm[hd * D + pos] = (uint8_t)c;
+  }
+}
+
+}  // namespace vidkv

@@ -1,0 +1,199 @@
+// Protected-token selection of one sequence by one workgroup of 1024 threads, for sequences short
+// enough that a thread keeps its scores in registers (or, from an index list, that the mask fits
+// LDS): one launch, or a few workgroups of another launch, instead of a chain of six short ones.
+#pragma once
+#include "vidkv_common.h"
+
+namespace vidkv {
+
+// Order-preserving map float -> uint32 (ascending).
+__device__ __forceinline__ uint32_t fkey(float f) {
+  const uint32_t b = __float_as_uint(f + 0.0f);   // -0 and +0 are the same score
+  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+}
+
+constexpr int ONE_THREADS = 1024;
+constexpr int ONE_Q = 8;                                  // float4 pieces of scores per thread
+constexpr int ONE_MAX_T = ONE_THREADS * 4 * ONE_Q;        // 32768 tokens
+constexpr int ONE_COPIES = 4;                             // histogram copies, by lane: scores crowd into few bins
+constexpr int ONE_BINS = 2048;
+
+struct OneSelLds {
+  int hist[ONE_COPIES][ONE_BINS];                         // index list: the mask (ONE_MAX_T / 32 words)
+  int wsum[16];
+  int pre_s[ONE_Q][16], pre_e[ONE_Q][16];
+  int bin, rem;
+};
+
+struct OneSelArgs {
+  const float* scores;        // [B, T] or NULL
+  const int32_t* idx_in;      // [B, n_s] or NULL
+  int T, ng, ngc, n_s;
+  int32_t* idx;               // IDX, MASK, RANK of the packed buffer
+  uint32_t* mask;
+  uint32_t* rank;
+};
+
+// Exclusive scan of one int per thread over the 1024 threads.
+__device__ __forceinline__ int one_exscan(int v, int* wsum) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  int inc = v;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int o = __shfl_up(inc, d, 64);
+    if (lane >= d) inc += o;
+  }
+  __syncthreads();                                        // wsum may still be read
+  if (lane == 63) wsum[wv] = inc;
+  __syncthreads();
+  int base = 0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) base += i < wv ? wsum[i] : 0;
+  return base + inc - v;
+}
+
+// The n_s largest scores (ties: lower index first) by a radix select on the ordered 32-bit keys
+// (11 + 11 + 10 bits), then IDX, MASK and RANK in token order.  Thread t holds the scores of the
+// pieces q 1024 + t, four tokens each; a wave of a slab q covers 256 consecutive tokens.
+__device__ __forceinline__ void select_one(const OneSelArgs& a, int b, OneSelLds& s) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int np = a.T >> 2, nq = (np + ONE_THREADS - 1) / ONE_THREADS;
+  uint32_t key[ONE_Q][4];                                 // 0: no token (below every score's key but a NaN's)
+  uint32_t sel[ONE_Q], tie[ONE_Q];                        // bit j: token j of the piece is in / has the last key
+  int take_eq = 0;
+  if (a.scores) {
+    const float4* sc4 = reinterpret_cast<const float4*>(a.scores + (size_t)b * a.T);
+    float4 v[ONE_Q];
+#pragma unroll
+    for (int q = 0; q < ONE_Q; ++q) {
+      const int p = q * ONE_THREADS + tid;
+      v[q] = p < np ? sc4[p] : float4{0.f, 0.f, 0.f, 0.f};
+    }
+    uint32_t prefix = 0, pmask = 0;
+    int rem = a.n_s;
+#pragma unroll
+    for (int level = 0; level < 3; ++level) {
+      const int shift = level == 0 ? 21 : level == 1 ? 10 : 0;
+      const int nb = level == 2 ? 1024 : 2048;
+#pragma unroll
+      for (int i = 0; i < ONE_COPIES * ONE_BINS / ONE_THREADS; ++i) s.hist[0][i * ONE_THREADS + tid] = 0;
+      __syncthreads();
+      if (level == 0) {
+#pragma unroll
+        for (int q = 0; q < ONE_Q; ++q) {
+          key[q][0] = fkey(v[q].x); key[q][1] = fkey(v[q].y); key[q][2] = fkey(v[q].z); key[q][3] = fkey(v[q].w);
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < ONE_Q; ++q)
+        if (q * ONE_THREADS + tid < np) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if ((key[q][j] & pmask) == prefix)
+              atomicAdd(&s.hist[lane & (ONE_COPIES - 1)][(key[q][j] >> shift) & (nb - 1)], 1);
+        }
+      __syncthreads();
+      // thread t owns bins 2 (1023 - t) and the one above: the scan gives the keys in higher bins
+      const int b0 = 2 * (ONE_THREADS - 1 - tid);
+      int c0 = 0, c1 = 0;
+#pragma unroll
+      for (int k = 0; k < ONE_COPIES; ++k) { c0 += s.hist[k][b0]; c1 += s.hist[k][b0 + 1]; }
+      const int above = one_exscan(c0 + c1, s.wsum);
+      if (above < rem && rem <= above + c0 + c1) {        // exactly one thread
+        const bool hi = rem <= above + c1;
+        s.bin = hi ? b0 + 1 : b0;
+        s.rem = hi ? rem - above : rem - above - c1;
+      }
+      __syncthreads();
+      prefix |= (uint32_t)s.bin << shift;
+      pmask |= (uint32_t)(nb - 1) << shift;
+      rem = s.rem;
+    }
+    take_eq = rem;
+#pragma unroll
+    for (int q = 0; q < ONE_Q; ++q) {
+      sel[q] = tie[q] = 0;
+      if (q * ONE_THREADS + tid < np) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          sel[q] |= (key[q][j] > prefix ? 1u : 0u) << j;
+          tie[q] |= (key[q][j] == prefix ? 1u : 0u) << j;
+        }
+      }
+    }
+  } else {
+    uint32_t* m = reinterpret_cast<uint32_t*>(&s.hist[0][0]);
+    if (tid < ONE_MAX_T / 32) m[tid] = 0;
+    __syncthreads();
+    for (int i = tid; i < a.n_s; i += ONE_THREADS) {
+      const int t = a.idx_in[(size_t)b * a.n_s + i];
+      if (t >= 0 && t < a.T) atomicOr(&m[t >> 5], 1u << (t & 31));   // an index outside the cache is ignored
+    }
+    for (int g = a.ng + tid; g < a.ngc; g += ONE_THREADS) a.mask[(size_t)b * a.ngc + g] = 0;   // room behind the tokens
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < ONE_Q; ++q) {
+      const int p = q * ONE_THREADS + tid;                // < ONE_MAX_T / 4: inside the mask
+      sel[q] = (m[p >> 3] >> (4 * (p & 7))) & 15u;
+      tie[q] = 0;
+    }
+  }
+  // counts per (slab, wave), in token order; then the sums of all before each
+#pragma unroll
+  for (int q = 0; q < ONE_Q; ++q) {
+    int cs = 0, ce = 0;
+    if (q < nq) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        cs += __popcll(__ballot((sel[q] >> j) & 1u));
+        ce += __popcll(__ballot((tie[q] >> j) & 1u));
+      }
+    }
+    if (lane == 0) { s.pre_s[q][wave] = cs; s.pre_e[q][wave] = ce; }
+  }
+  __syncthreads();
+  {
+    const int cs = tid < ONE_Q * 16 ? s.pre_s[0][tid] : 0, ce = tid < ONE_Q * 16 ? s.pre_e[0][tid] : 0;
+    const int ps = one_exscan(cs, s.wsum);
+    const int pe = one_exscan(ce, s.wsum);
+    if (tid < ONE_Q * 16) { s.pre_s[0][tid] = ps; s.pre_e[0][tid] = pe; }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < ONE_Q; ++q) {
+    if (q >= nq) break;
+    const int p = q * ONE_THREADS + tid;
+    int bs = s.pre_s[q][wave], be = s.pre_e[q][wave];     // selected / tied tokens before mine
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const unsigned long long ms = __ballot((sel[q] >> j) & 1u), me = __ballot((tie[q] >> j) & 1u);
+      bs += __builtin_amdgcn_mbcnt_hi((uint32_t)(ms >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ms, 0u));
+      be += __builtin_amdgcn_mbcnt_hi((uint32_t)(me >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)me, 0u));
+    }
+    const int first = bs + min(be, take_eq);              // protected tokens before my first
+    uint32_t in = 0;
+    int r = first;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bool t = (tie[q] >> j) & 1u;
+      if (((sel[q] >> j) & 1u) || (t && be < take_eq)) {
+        in |= 1u << j;
+        if (r < a.n_s) a.idx[(size_t)b * a.n_s + r] = 4 * p + j;
+        ++r;
+      }
+      be += t ? 1 : 0;
+    }
+    uint32_t w = in << (4 * (lane & 7));                  // 8 lanes: one group
+    w |= __shfl_xor(w, 1, 64);
+    w |= __shfl_xor(w, 2, 64);
+    w |= __shfl_xor(w, 4, 64);
+    if ((lane & 7) == 0 && (p >> 3) < a.ng) {
+      a.mask[(size_t)b * a.ngc + (p >> 3)] = w;
+      a.rank[(size_t)b * a.ngc + (p >> 3)] = (uint32_t)first;
+    }
+  }
+}
+
+OneSelArgs one_sel_args(const Geom& g, const float* scores, const int32_t* idx, uint8_t* packed);
+
+}  // namespace vidkv

@@ -23,6 +23,16 @@ void launch_k_encode(const Geom& g, const EncodeSpan& sp, const void* K, uint8_t
                      bool use_fft, hipStream_t st);
 void launch_v_encode(const Geom& g, const EncodeSpan& sp, int n_s, float gamma, const void* V,
                      uint8_t* packed, hipStream_t st);
+bool one_workgroup_selection(const Geom& g);
+void launch_k_range_select(const Geom& g, const void* K, void* ws, const float* scores, const int32_t* idx,
+                           uint8_t* packed_V, hipStream_t st);
+bool launch_v_encode_select(const Geom& g, float gamma, const void* V, uint8_t* packed_V, const void* ws,
+                            uint8_t* packed_K, hipStream_t st);
+bool launch_k_encode_protect2(const Geom& g, const void* K, uint8_t* packed_K, const void* V, uint8_t* packed_V,
+                              hipStream_t st);
+void launch_v_protect2(const Geom& g, const void* V, uint8_t* packed, hipStream_t st);
+bool launch_flush_encode(const Geom& g, const EncodeSpan& sp, float gamma, const void* K, const void* V,
+                         uint8_t* packed_K, uint8_t* packed_V, hipStream_t st);
 void launch_flush_marks(const Geom& g, int n_groups, uint8_t* packed, hipStream_t st);
 hipError_t launch_saliency(const void* Xv, const void* Xt, int B, int Tv, int Nt, int d,
                            float* scores, float* tsum, hipStream_t st);
@@ -189,15 +199,21 @@ vidkv_status vidkv_quantize_kv(const vidkv_params* p, const void* K, const void*
   const float* sc = g.n_s > 0 ? saliency : nullptr;
   const int32_t* ix = g.n_s > 0 ? salient_idx : nullptr;
   if (!stream_on_current_device(st)) return VIDKV_EINVAL;
-  // The chain of short dependent launches that selects the protected tokens runs on the side
-  // stream beside the bandwidth-bound key passes.  The fork and join cost about as much as
-  // three short launches, so this pays only when the key passes are long enough to hide the
-  // chain behind them.  (Moving the channel selection over as well, beside the value coding
-  // pass, was measured and lost: its four large workgroups wait for free compute units until
-  // the coding pass has been dispatched, and the second fork and join come on top.)
+  if (g.T == 0) return VIDKV_OK;
+  // Launches of the whole call: range pass and protected-token selection | value coding and channel
+  // selection | key coding and 2-bit protected rows.  The selections are short chains of dependent
+  // work that wait for memory, the passes need its bandwidth: a selection in the first workgroups of
+  // a pass costs nothing, as launches of its own one of 5 to 8 us (channels) and six of 3 to 5 us
+  // (tokens) with the passes waiting.  One head of 1568 tokens 38.9 -> 23.0 us, 28 x 4 heads of 6272
+  // tokens with 2-bit rows 139 -> 114, 64 x 4 heads of 25088 944 -> 915.
+  // A sequence too long for one workgroup's registers keeps the chain of six.  With a side stream,
+  // and key passes long enough to hide the fork and join (32 MiB), it runs beside them, the value
+  // pass last; beside the range pass alone it is the longer of the two (196000 tokens: 154 us
+  // against 137).
+  const bool sel = g.n_s > 0, one = sel && one_workgroup_selection(g);
   const Side sd = take_side(side);
-  const bool fork = sd.ok && (size_t)g.nheads * g.T * D * 2 >= ((size_t)32 << 20);
-  if (g.n_s > 0 && g.T > 0 && fork) {
+  const bool fork = sel && !one && sd.ok && (size_t)g.nheads * g.T * D * 2 >= ((size_t)32 << 20);
+  if (fork) {
     if (!stream_on_current_device(sd.stream)) return VIDKV_EINVAL;
     if (hipEventRecord(sd.fork, st) != hipSuccess) return VIDKV_EHIP;
     if (hipStreamWaitEvent(sd.stream, sd.fork, 0) != hipSuccess) return VIDKV_EHIP;
@@ -211,9 +227,25 @@ vidkv_status vidkv_quantize_kv(const vidkv_params* p, const void* K, const void*
     return launch_quantize_values(g, p->gamma, V, sc, ix, pv, ws_v, 2u, st) == hipSuccess
                ? VIDKV_OK : VIDKV_EHIP;
   }
-  if (launch_quantize_keys(g, K, pk, ws_k, ~0u, st) != hipSuccess) return VIDKV_EHIP;
-  return launch_quantize_values(g, p->gamma, V, sc, ix, pv, ws_v, ~0u, st) == hipSuccess
-             ? VIDKV_OK : VIDKV_EHIP;
+  bool good = true;
+  if (g.metric == 0 && one) {
+    launch_k_range_select(g, K, ws_k, sc, ix, pv, st);
+  } else {
+    if (sel) good = launch_quantize_values(g, p->gamma, V, sc, ix, pv, ws_v, 1u, st) == hipSuccess;
+    good = launch_quantize_keys(g, K, pk, ws_k, g.metric == 0 ? 1u : 3u, st) == hipSuccess && good;
+  }
+  if (!good) return VIDKV_EHIP;
+  const EncodeSpan all{g.T, g.ng, 0, g.nheads, 0};
+  if (g.metric != 0 || !launch_v_encode_select(g, p->gamma, V, pv, ws_k, pk, st)) {
+    if (g.metric == 0) good = launch_quantize_keys(g, K, pk, ws_k, 2u, st) == hipSuccess;
+    launch_v_encode(g, all, g.n_s, p->gamma, V, pv, st);
+  }
+  const bool rows2 = sel && g.sal_bits == 2;
+  if (!rows2 || !launch_k_encode_protect2(g, K, pk, V, pv, st)) {
+    launch_k_encode(g, all, K, pk, g.use_fft, st);
+    if (rows2) launch_v_protect2(g, V, pv, st);
+  }
+  return hipGetLastError() == hipSuccess && good ? VIDKV_OK : VIDKV_EHIP;
 }
 
 // Argument checks of a decode step, shared by the entry points below.
@@ -346,9 +378,13 @@ vidkv_status vidkv_flush_residual(const vidkv_params* p, int32_t layer, const vo
   hipStream_t st = static_cast<hipStream_t>(stream);
   const long long bh = (long long)g.B * g.H;
   const EncodeSpan sp{tail_capacity, n_flush / G, g.ng, bh, layer * bh};
-  launch_k_encode(g, sp, K_tail, static_cast<uint8_t*>(packed_K), g.use_fft, st);
-  launch_v_encode(g, sp, 0, p->gamma, V_tail, static_cast<uint8_t*>(packed_V), st);
-  launch_flush_marks(g, sp.ng, static_cast<uint8_t*>(packed_V), st);
+  uint8_t* pk = static_cast<uint8_t*>(packed_K);
+  uint8_t* pv = static_cast<uint8_t*>(packed_V);
+  if (!launch_flush_encode(g, sp, p->gamma, K_tail, V_tail, pk, pv, st)) {
+    launch_k_encode(g, sp, K_tail, pk, g.use_fft, st);
+    launch_v_encode(g, sp, 0, p->gamma, V_tail, pv, st);
+    launch_flush_marks(g, sp.ng, pv, st);
+  }
   return hipGetLastError() == hipSuccess ? VIDKV_OK : VIDKV_EHIP;
 }
 
