@@ -75,7 +75,7 @@ def lib() -> C.CDLL:
         # loaded, so that both resolve to that one copy.  Loaded the other way round the
         # library registers its kernels with a second runtime, and every launch on a torch
         # stream fails.
-        import torch  # noqa: F401
+        import torch
         L = C.CDLL(LIB_PATH)
         PP = C.POINTER(VidkvParams)
         vp, sz, i32 = C.c_void_p, C.c_size_t, C.c_int32
@@ -116,6 +116,7 @@ def lib() -> C.CDLL:
         L.vidkv_status_string.restype = C.c_char_p
         L.vidkv_abi_version.argtypes = []
         L.vidkv_abi_version.restype = C.c_int
+        _bind_torch(torch)
         _lib = L
     return _lib
 
@@ -149,28 +150,44 @@ def workspace_bytes(p: VidkvParams, which: int) -> int:
     return lib().vidkv_workspace_bytes(C.byref(p), which)
 
 
+# A decode call marshals ten arguments and a flush eight, once per layer: what follows is kept to a
+# few attribute reads per tensor.  torch's names are looked up once, with the library.
+_Tensor = _f16 = _u8 = _f32 = _i32 = _raw_stream = _cur_device = None
+
+
+def _bind_torch(torch) -> None:
+    global _Tensor, _f16, _u8, _f32, _i32, _raw_stream, _cur_device
+    _f16, _u8, _f32, _i32 = torch.float16, torch.uint8, torch.float32, torch.int32
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    _cur_device = torch.cuda.current_device
+    _Tensor = torch.Tensor
+
+
 def _ptr(t, dtype=None, name="tensor"):
     """Device pointer of a contiguous CUDA tensor (None -> NULL)."""
     if t is None:
         return None
-    import torch
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    if not isinstance(t, _Tensor) or not t.is_cuda:
         raise TypeError(f"{name}: expected a CUDA tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name}: must be contiguous")
-    if dtype is not None and t.dtype != dtype:
+    if dtype is not None and t.dtype is not dtype:
         raise TypeError(f"{name}: expected dtype {dtype}, got {t.dtype}")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _nbytes(t) -> int:
-    return t.numel() * t.element_size()
+    return t.nbytes
 
 
 def _stream(stream):
+    """Handle of a torch stream, of the current device's current one for None."""
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None:
+        return _raw_stream(_cur_device())
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _check(status: int, where: str):
@@ -181,27 +198,27 @@ def _check(status: int, where: str):
 def quantize_keys(p: VidkvParams, K, packed_K, workspace, stream=None, stages=None) -> None:
     """vidkv_quantize_keys: K [L,B,Hkv,Tq,128] fp16 -> packed_K (uint8 buffer).
     With `stages` (bit mask) calls vidkv_quantize_keys_stages instead."""
-    import torch
-    a = [C.byref(p), _ptr(K, torch.float16, "K"), _ptr(packed_K, torch.uint8, "packed_K"),
-         _nbytes(packed_K), _ptr(workspace, torch.uint8, "workspace"), _nbytes(workspace)]
+    L = _lib or lib()
+    a = [C.byref(p), _ptr(K, _f16, "K"), _ptr(packed_K, _u8, "packed_K"),
+         _nbytes(packed_K), _ptr(workspace, _u8, "workspace"), _nbytes(workspace)]
     if stages is None:
-        _check(lib().vidkv_quantize_keys(*a, _stream(stream)), "vidkv_quantize_keys")
+        _check(L.vidkv_quantize_keys(*a, _stream(stream)), "vidkv_quantize_keys")
     else:
-        _check(lib().vidkv_quantize_keys_stages(*a, stages, _stream(stream)),
+        _check(L.vidkv_quantize_keys_stages(*a, stages, _stream(stream)),
                "vidkv_quantize_keys_stages")
 
 
 def quantize_values(p: VidkvParams, V, packed_V, workspace, saliency=None, salient_idx=None,
                     stream=None, stages=None) -> None:
     """vidkv_quantize_values: V fp16 (+ scores [B,Tq] f32 or indices [B,n_s] i32) -> packed_V."""
-    import torch
-    a = [C.byref(p), _ptr(V, torch.float16, "V"), _ptr(saliency, torch.float32, "saliency"),
-         _ptr(salient_idx, torch.int32, "salient_idx"), _ptr(packed_V, torch.uint8, "packed_V"),
-         _nbytes(packed_V), _ptr(workspace, torch.uint8, "workspace"), _nbytes(workspace)]
+    L = _lib or lib()
+    a = [C.byref(p), _ptr(V, _f16, "V"), _ptr(saliency, _f32, "saliency"),
+         _ptr(salient_idx, _i32, "salient_idx"), _ptr(packed_V, _u8, "packed_V"),
+         _nbytes(packed_V), _ptr(workspace, _u8, "workspace"), _nbytes(workspace)]
     if stages is None:
-        _check(lib().vidkv_quantize_values(*a, _stream(stream)), "vidkv_quantize_values")
+        _check(L.vidkv_quantize_values(*a, _stream(stream)), "vidkv_quantize_values")
     else:
-        _check(lib().vidkv_quantize_values_stages(*a, stages, _stream(stream)),
+        _check(L.vidkv_quantize_values_stages(*a, stages, _stream(stream)),
                "vidkv_quantize_values_stages")
 
 
@@ -210,16 +227,16 @@ def decode_attention(p: VidkvParams, layer: int, q, packed_K, packed_V, out, wor
                      stream=None, stages=None, side=None) -> None:
     """vidkv_decode_attention: one decode step of one layer -> out [B,Hq,128] fp16.
     `side`: a SideStream for the residual-token kernel of a large block, or None (in line)."""
-    import torch
-    a = [C.byref(p), layer, _ptr(q, torch.float16, "q"), _ptr(packed_K, torch.uint8, "packed_K"),
-         _ptr(packed_V, torch.uint8, "packed_V"), _ptr(K_tail, torch.float16, "K_tail"),
-         _ptr(V_tail, torch.float16, "V_tail"), tail_capacity, _ptr(tail_len, torch.int32, "tail_len"),
-         _ptr(out, torch.float16, "out"), _ptr(workspace, torch.uint8, "workspace"),
+    L = _lib or lib()
+    a = [C.byref(p), layer, _ptr(q, _f16, "q"), _ptr(packed_K, _u8, "packed_K"),
+         _ptr(packed_V, _u8, "packed_V"), _ptr(K_tail, _f16, "K_tail"),
+         _ptr(V_tail, _f16, "V_tail"), tail_capacity, _ptr(tail_len, _i32, "tail_len"),
+         _ptr(out, _f16, "out"), _ptr(workspace, _u8, "workspace"),
          _nbytes(workspace)]
     if stages is None:
-        _check(lib().vidkv_decode_attention(*a, _stream(stream), _side(side)), "vidkv_decode_attention")
+        _check(L.vidkv_decode_attention(*a, _stream(stream), _side(side)), "vidkv_decode_attention")
     else:
-        _check(lib().vidkv_decode_attention_stages(*a, stages, _stream(stream), _side(side)),
+        _check(L.vidkv_decode_attention_stages(*a, stages, _stream(stream), _side(side)),
                "vidkv_decode_attention_stages")
 
 
@@ -229,36 +246,36 @@ NOALLOC_SCRATCH_BYTES = 16 << 20     # VIDKV_NOALLOC_SCRATCH_BYTES of include/vi
 def decode_attention_noalloc(p: VidkvParams, layer: int, q, packed_K, packed_V, out, K_tail=None,
                              V_tail=None, tail_capacity: int = 0, tail_len=None, stream=None) -> None:
     """vidkv_decode_attention_noalloc: the decode step without a workspace argument."""
-    import torch
-    _check(lib().vidkv_decode_attention_noalloc(
-        C.byref(p), layer, _ptr(q, torch.float16, "q"), _ptr(packed_K, torch.uint8, "packed_K"),
-        _ptr(packed_V, torch.uint8, "packed_V"), _ptr(K_tail, torch.float16, "K_tail"),
-        _ptr(V_tail, torch.float16, "V_tail"), tail_capacity, _ptr(tail_len, torch.int32, "tail_len"),
-        _ptr(out, torch.float16, "out"), _stream(stream)), "vidkv_decode_attention_noalloc")
+    L = _lib or lib()
+    _check(L.vidkv_decode_attention_noalloc(
+        C.byref(p), layer, _ptr(q, _f16, "q"), _ptr(packed_K, _u8, "packed_K"),
+        _ptr(packed_V, _u8, "packed_V"), _ptr(K_tail, _f16, "K_tail"),
+        _ptr(V_tail, _f16, "V_tail"), tail_capacity, _ptr(tail_len, _i32, "tail_len"),
+        _ptr(out, _f16, "out"), _stream(stream)), "vidkv_decode_attention_noalloc")
 
 
 def quantize_kv(p: VidkvParams, K, V, packed_K, packed_V, workspace, saliency=None,
                 salient_idx=None, stream=None, side=None) -> None:
     """vidkv_quantize_kv: both tensors of the same tokens in one call.
     `side`: a SideStream for the protected-token selection, or None (in line)."""
-    import torch
-    _check(lib().vidkv_quantize_kv(
-        C.byref(p), _ptr(K, torch.float16, "K"), _ptr(V, torch.float16, "V"),
-        _ptr(saliency, torch.float32, "saliency"), _ptr(salient_idx, torch.int32, "salient_idx"),
-        _ptr(packed_K, torch.uint8, "packed_K"), _nbytes(packed_K),
-        _ptr(packed_V, torch.uint8, "packed_V"), _nbytes(packed_V),
-        _ptr(workspace, torch.uint8, "workspace"), _nbytes(workspace), _stream(stream), _side(side)),
+    L = _lib or lib()
+    _check(L.vidkv_quantize_kv(
+        C.byref(p), _ptr(K, _f16, "K"), _ptr(V, _f16, "V"),
+        _ptr(saliency, _f32, "saliency"), _ptr(salient_idx, _i32, "salient_idx"),
+        _ptr(packed_K, _u8, "packed_K"), _nbytes(packed_K),
+        _ptr(packed_V, _u8, "packed_V"), _nbytes(packed_V),
+        _ptr(workspace, _u8, "workspace"), _nbytes(workspace), _stream(stream), _side(side)),
         "vidkv_quantize_kv")
 
 
 def flush_residual(p: VidkvParams, layer: int, K_tail, V_tail, tail_capacity: int, n_flush: int,
                    packed_K, packed_V, stream=None) -> None:
     """vidkv_flush_residual: code the first n_flush residual tokens of one layer and append them."""
-    import torch
-    _check(lib().vidkv_flush_residual(
-        C.byref(p), layer, _ptr(K_tail, torch.float16, "K_tail"), _ptr(V_tail, torch.float16, "V_tail"),
-        tail_capacity, n_flush, _ptr(packed_K, torch.uint8, "packed_K"), _nbytes(packed_K),
-        _ptr(packed_V, torch.uint8, "packed_V"), _nbytes(packed_V), _stream(stream)),
+    L = _lib or lib()
+    _check(L.vidkv_flush_residual(
+        C.byref(p), layer, _ptr(K_tail, _f16, "K_tail"), _ptr(V_tail, _f16, "V_tail"),
+        tail_capacity, n_flush, _ptr(packed_K, _u8, "packed_K"), _nbytes(packed_K),
+        _ptr(packed_V, _u8, "packed_V"), _nbytes(packed_V), _stream(stream)),
         "vidkv_flush_residual")
 
 
@@ -268,17 +285,18 @@ def saliency_workspace_bytes(batch: int, hidden_dim: int) -> int:
 
 def saliency_scores(X_v, X_t, scores, workspace, stream=None) -> None:
     """vidkv_saliency_scores: X_v [B,Tv,d] fp16, X_t [B,Nt,d] fp16 -> scores [B,Tv] f32."""
-    import torch
+    L = _lib or lib()
     B, Tv, d = X_v.shape
     assert X_t.shape[0] == B and X_t.shape[2] == d and tuple(scores.shape) == (B, Tv)
-    _check(lib().vidkv_saliency_scores(
-        _ptr(X_v, torch.float16, "X_v"), _ptr(X_t, torch.float16, "X_t"), B, Tv, X_t.shape[1], d,
-        _ptr(scores, torch.float32, "scores"), _ptr(workspace, torch.uint8, "workspace"),
+    _check(L.vidkv_saliency_scores(
+        _ptr(X_v, _f16, "X_v"), _ptr(X_t, _f16, "X_t"), B, Tv, X_t.shape[1], d,
+        _ptr(scores, _f32, "scores"), _ptr(workspace, _u8, "workspace"),
         _nbytes(workspace), _stream(stream)), "vidkv_saliency_scores")
 
 
 def calib_copy(dst, src, stream=None) -> None:
-    _check(lib().vidkv_calib_copy(_ptr(dst, None, "dst"), _ptr(src, None, "src"), _nbytes(src),
+    L = _lib or lib()
+    _check(L.vidkv_calib_copy(_ptr(dst, None, "dst"), _ptr(src, None, "src"), _nbytes(src),
                                   _stream(stream)), "vidkv_calib_copy")
 
 

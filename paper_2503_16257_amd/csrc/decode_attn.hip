@@ -125,24 +125,26 @@ int attn_max_splits(const Geom& g) {
 // round where 512 / (B H) is no whole number, and more workgroups than needed for the same s.  This and the
 // residual tokens in the same launch: 28 layers of 6272 tokens, n_a = 64, 606 -> 402 us a step; of
 // 2 x 3136, n_a = 96, 555 -> 407.)
-static int attn_splits(const Geom& g, long long others) {
-  const long long bh = (long long)g.B * g.H, cus = device_cu_count(), npairs = (g.ng + 1) / 2;
-  const long long nmax = attn_max_splits(g);
-  long long best_n = 1, best = -1;
-  auto consider = [&](long long n) {
+static int attn_splits(const Geom& g, long long others_) {
+  // 32-bit arithmetic: the candidates' divisions are on every decode call's way
+  const int bh = (int)std::min((long long)g.B * g.H, 1LL << 20), cus = device_cu_count(), npairs = (g.ng + 1) / 2;
+  const int nmax = attn_max_splits(g), others = (int)std::min(others_, 1LL << 20);
+  int best_n = 1;
+  long long best_t = -1;
+  auto consider = [&](int n) {
     if (n < 1 || n > nmax) return;
-    const long long s = ((npairs + n - 1) / n + 3) / 4, w = n * bh + others;
-    const long long t = (w + 2 * cus - 1) / (2 * cus) * (60 + s * (w <= cus ? 22 : 35));
-    if (best < 0 || t < best) { best = t; best_n = n; }
+    const int s = ((npairs + n - 1) / n + 3) / 4, w = n * bh + others;
+    // a 64-bit product: thousands of rounds of thousands of pairs
+    const long long t = (long long)((w + 2 * cus - 1) / (2 * cus)) * (60 + (long long)s * (w <= cus ? 22 : 35));
+    if (best_t < 0 || t < best_t) { best_t = t; best_n = n; }
   };
-  const long long one_round = std::max(1LL, (2 * cus - others) / bh);
-  consider(std::min(one_round, nmax));
-  for (long long s = std::min(64LL, (npairs + 3) / 4); s >= 1; --s) {
-    const long long n = (npairs + 4 * s - 1) / (4 * s);
+  consider(std::min(std::max(1, (2 * cus - others) / bh), nmax));
+  for (int s = std::min(64, (npairs + 3) / 4); s >= 1; --s) {
+    const int n = (npairs + 4 * s - 1) / (4 * s);
     if (n > nmax) break;
     consider(n);
   }
-  return (int)best_n;
+  return best_n;
 }
 
 // A large block of residual tokens is worth a stream of its own: its kernel is short of
