@@ -17,7 +17,16 @@ __global__ __launch_bounds__(256) void sal_text_sum_kernel(const _Float16* __res
   if (c >= d) return;
   const _Float16* p = Xt + (size_t)b * Nt * d + c;
   float acc = 0.0f;
-  for (int j = 0; j < Nt; ++j) acc += (float)p[(size_t)j * d];
+  // 16 rows requested at a time, added in ascending order (a row at a time: a call of 4 x 5000 tokens,
+  // 256 text tokens 43.2 us; this 24.8)
+  for (int j0 = 0; j0 < Nt; j0 += 16) {
+    _Float16 x[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) x[u] = p[(size_t)min(j0 + u, Nt - 1) * d];
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      if (j0 + u < Nt) acc += (float)x[u];
+  }
   tsum[(size_t)b * d + c] = acc;
 }
 
