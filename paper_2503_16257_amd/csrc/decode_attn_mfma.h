@@ -539,25 +539,28 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     };
     // anomalous channels: rows = tokens, K = (channel, bit plane); the column operand is
     // zero outside my parity, so both groups add into S directly
-    auto anomalous_item = [&](int n) {
+    // scale and zero point of the anomalous K-step n, read one item ahead (n_a = 64, 28 x 8 x 12544
+    // tokens: 570 us a step with the reads in front of their use, 558 so, 551 with the constant's
+    // operands below taken from what is there)
+    auto load_sz = [&](int n, uint2& as, uint2& az) {
+      const int grp = n / (UA > 0 ? UA : 1), ua = n % (UA > 0 ? UA : 1);
+      const uint8_t* rec = stage + grp * KREC;
+      const int quad = min(4 * ua + kb, NQ - 1);
+      as = *reinterpret_cast<const uint2*>(rec + OFF_AS + quad * 8);
+      az = *reinterpret_cast<const uint2*>(rec + OFF_AZ + quad * 8);
+    };
+    auto anomalous_item = [&](int n, uint2 as, uint2 az) {
       const int grp = n / (UA > 0 ? UA : 1), ua = n % (UA > 0 ? UA : 1);
       Op s4, z4;                                             // 4 halves each (low 8 bytes used)
-      if (HOP_SZ) {
-        *reinterpret_cast<uint2*>(&s4) = hop.as[grp][ua];
-        *reinterpret_cast<uint2*>(&z4) = hop.az[grp][ua];
-      } else {
-        const uint8_t* rec = stage + grp * KREC;
-        const int quad = min(4 * ua + kb, NQ - 1);
-        *reinterpret_cast<uint2*>(&s4) = *reinterpret_cast<const uint2*>(rec + OFF_AS + quad * 8);
-        *reinterpret_cast<uint2*>(&z4) = *reinterpret_cast<const uint2*>(rec + OFF_AZ + quad * 8);
-      }
+      *reinterpret_cast<uint2*>(&s4) = HOP_SZ ? hop.as[grp][ua] : as;
+      *reinterpret_cast<uint2*>(&z4) = HOP_SZ ? hop.az[grp][ua] : az;
       uint32_t sp[4];                                        // (s/2, s) of channel r
-      Op Ac1, Ac2;
+      Op Ac1, Ac2;                                           // the constant: 1.5 s is sp itself, and (z, 0)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         sp[r] = h2_bits(h2{s4.v[r], s4.v[r]} * h2{(_Float16)0.5f, (_Float16)1.0f});
-        Ac1.p[r] = h2{z4.v[r], s4.v[r]};                     // z + s
-        Ac2.u[r] = sp[r] & 0xFFFFu;                          // + s/2
+        Ac1.u[r] = sp[r];
+        Ac2.u[r] = (r & 1) ? z4.u[r >> 1] >> 16 : z4.u[r >> 1] & 0xFFFFu;
       }
       // code bytes of my two tokens (tiles mt = 0, 1): bits (2r, 2r+1) of a byte are the
       // code of channel r, expanded like the sign words
@@ -605,14 +608,18 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     // with key item j NK / 8 (all eight at once when there are no key items)
     Op mre[2], mim[2];
     uint2 E[2][2], O[2][2];
-    if (NKN > 0) load_meta(0, mre[0], mim[0]);
+    uint2 asz[2][2];
+    if (!HOP_SZ && NKA > 0) load_sz(0, asz[0][0], asz[0][1]);
+    if (NKN > 0 && (HOP_SZ || NKA == 0)) load_meta(0, mre[0], mim[0]);
     if (DO_V) lookup(0, E[0], O[0]);
     __builtin_amdgcn_sched_barrier(0);
     constexpr int NSTEP = NK > 0 ? NK : 1;
 #pragma unroll
     for (int k = 0; k < NSTEP; ++k) {
       if (k < NKA) {
-        anomalous_item(k);
+        if (!HOP_SZ && k + 1 < NKA) load_sz(k + 1, asz[(k + 1) & 1][0], asz[(k + 1) & 1][1]);
+        if (!HOP_SZ && k + 1 == NKA && NKN > 0) load_meta(0, mre[0], mim[0]);
+        anomalous_item(k, asz[k & 1][0], asz[k & 1][1]);
       } else if (k < NK) {
         const int n = k - NKA;
         if (n + 1 < NKN) load_meta(n + 1, mre[(n + 1) & 1], mim[(n + 1) & 1]);
