@@ -10,8 +10,8 @@ namespace vidkv {
 // protected tokens (the last group may hold fewer).  One wave codes one record, lane = two adjacent
 // channels: a row is one 256-byte request of the wave, all 32 rows are requested at once, and the
 // codes of a lane pair make the record's bytes.  (A thread per channel, 2-byte loads: 11.9 us for 4480
-// records of the 28 x 6272 token cache.  With the key coding pass around it 52.5 us: 8.8 more than that
-// pass alone, 6 of them for the 36 MB it reads.)  Record: codes [32 rows][32 bytes] (channel
+// records of the 28 x 6272 token cache.  Behind the key coding pass's workgroups, in the same launch,
+// the whole call took 116.5 us; in front of them 119; as launches of their own one gap more.)  Record: codes [32 rows][32 bytes] (channel
 // 4 j + r of a row in bits 2r.. of byte j), fp16 s[128], fp16 z[128].
 struct Protect2Args {
   const _Float16* V;

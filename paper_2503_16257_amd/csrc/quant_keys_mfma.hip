@@ -70,8 +70,9 @@ static __device__ const DftTab kDftTab = make_dft_tab();
 // the record keeps its shape, bit (blk, k) e / 8 + e holds the code of channel
 // 8 blk + e at token k / 16 + k, and the two scale slots hold s = max - min and
 // z = min.
-// EXTRA: the first x_rows rows of the grid do something else of the same call, 1: code the protected
-// value rows (2 bits), 2: the value coding pass (a flush: both blocks are small, one launch).
+// EXTRA: rows of the grid that do something else of the same call, 1: from row x_rows on, code the
+// protected value rows (2 bits), 2: the first x_rows, the value coding pass (a flush: both blocks are
+// small, one launch).
 template <int NA8T, bool FFT, int EXTRA>
 __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restrict__ K,
                                                             const uint8_t* __restrict__ perm_g,
@@ -81,9 +82,9 @@ __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restr
                                                             Protect2Args p2, VEncArgs ve) {
   const int n_a = NA8T >= 0 ? 8 * NA8T : n_a_rt;
   __shared__ EncTile tile4[4];                    // per wave: the group's tile
-  if (EXTRA == 1 && (int)blockIdx.y < x_rows) {
+  if (EXTRA == 1 && (int)blockIdx.y >= x_rows) {
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const long long id = 4 * ((long long)blockIdx.y * gridDim.x + blockIdx.x) + w;
+    const long long id = 4 * ((long long)(blockIdx.y - x_rows) * gridDim.x + blockIdx.x) + w;
     if (id < p2.total) protect2_part(p2, id, reinterpret_cast<Protect2Lds*>(&tile4[0][0])[w]);
     return;
   }
@@ -92,7 +93,7 @@ __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restr
                         ve.rec_out, ve.rows_out, ve.mask, ve.rank, ve.mark_rank, blockIdx.x, blockIdx.y, tile4);
     return;
   }
-  const long long hd = blockIdx.y - (EXTRA ? x_rows : 0);
+  const long long hd = blockIdx.y - (EXTRA == 2 ? x_rows : 0);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int x16 = lane & 15, kb = lane >> 4;
@@ -318,6 +319,7 @@ __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restr
 template <int NA8T, int EXTRA>
 static void launch_one(bool use_fft, dim3 grid, hipStream_t st, const u32x4* k4, const uint8_t* perm, const Geom& g,
                        const EncodeSpan& sp, int gpb, uint8_t* rec, int rows, const Protect2Args& p2, const VEncArgs& ve) {
+  if (EXTRA == 1) rows = (int)sp.heads;
   if (use_fft)
     hipLaunchKernelGGL((k_encode_mfma_kernel<NA8T, true, EXTRA>), grid, dim3(256), 0, st, k4, perm, sp.in_tokens, sp.ng,
                        g.n_a, g.krec, gpb, g.ngc, sp.g_out0, rec, rows, p2, ve);
