@@ -20,7 +20,7 @@ struct AttnArgs {
   // p = 2^(score2 - m), l = sum p, o = sum p v
   float* part_o;             // [nsplit + tail splits, B, Hq, 128]
   float* part_ml;            // [nsplit + tail splits, B, Hq, 2]
-  int layer, B, H, Hq, rep, ng, n_a, n_n, n_s, krec_bytes, cap, nsplit, gps;
+  int layer, B, H, Hq, rep, ng, n_a, n_s, cap, nsplit, gps;
   int ngc;                   // groups of capacity: stride of the per-head record arrays
   int use_fft;               // normal key channels coded by Eq. 5 (1) or by Eq. 4 at 1 bit (0)
   int sal_bits, npg;         // protected rows kept as fp16 (16) or Eq. 4 codes (2); groups of 32 rows

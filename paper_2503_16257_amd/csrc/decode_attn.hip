@@ -7,8 +7,8 @@
 // so per 32-token group the +-s coefficients are contracted over channels first
 // (Y[h][slot]) and a single 32-point inverse real DFT per query head follows.
 //
-// This file holds the kernel for the fp16 residual tokens, the merge kernels and
-// the launcher; the MFMA kernel that reads the packed tokens is in decode_attn_mfma.h.
+// This file holds the merge kernel and the launcher; the fp16 residual tokens' part is in
+// decode_attn.h, the MFMA kernel that reads the packed tokens in decode_attn_mfma.h.
 #include "decode_attn.h"
 
 #include <algorithm>
@@ -108,12 +108,15 @@ static int device_cu_count() {
 }
 
 // The most split-T workgroups per (sequence, KV head) that attn_splits() can choose: what the
-// workspace is sized for.  Grows with the number of groups.
+// workspace is sized for.  Grows with the number of groups.  One pair per wave and two rounds of
+// workgroups, but not so many that the partials outgrow the array of the entry point without a
+// workspace - unless one round and two pairs per wave already do.
 int attn_max_splits(const Geom& g) {
   if (g.ng == 0) return 0;
-  const long long bh = (long long)g.B * g.H, npairs = (g.ng + 1) / 2;
-  const long long by_pairs = (npairs + 3) / 4, by_grid = 4LL * device_cu_count() / bh;
-  return (int)std::max(1LL, std::min(by_pairs, by_grid));
+  const long long bh = (long long)g.B * g.H, npairs = (g.ng + 1) / 2, cus = device_cu_count();
+  const long long fit = ((long long)VIDKV_NOALLOC_SCRATCH_BYTES - 512) / ((long long)g.B * g.Hq * (D + 2) * 4) - ATTN_TAIL_SPLITS;
+  const long long least = std::max(1LL, std::min((2 * cus + bh - 1) / bh, (npairs + 7) / 8));
+  return (int)std::max(least, std::min({(npairs + 3) / 4, 4 * cus / bh, fit}));
 }
 
 // Split-T workgroups per (sequence, KV head), with `others` workgroups of another kind in the same
@@ -176,7 +179,7 @@ hipError_t launch_decode_attention(const Geom& g, int layer, float scale, const 
   const bool has_tail = cap > 0 && ktail && vtail && tail_len;
   a.tail_len = has_tail ? tail_len : nullptr;
   a.layer = layer; a.B = g.B; a.H = g.H; a.Hq = g.Hq; a.rep = g.rep; a.ng = g.ng; a.ngc = g.ngc;
-  a.n_a = g.n_a; a.n_n = g.n_n; a.n_s = g.n_s; a.krec_bytes = g.krec; a.cap = cap;
+  a.n_a = g.n_a; a.n_s = g.n_s; a.cap = cap;
   a.sal_bits = g.sal_bits; a.npg = g.npg; a.use_fft = g.use_fft ? 1 : 0;
   a.scale2 = scale * 1.4426950408889634f;
   // stages: bit 0 split-T partial kernel(s), bit 1 merge

@@ -24,6 +24,15 @@ def test_workspace_does_not_depend_on_the_fill(batch, heads):
     assert full == sorted(full) and full[-1] <= max(sizes)
 
 
+@pytest.mark.parametrize("batch,heads,rep,tokens", [(51, 8, 8, 512), (128, 4, 7, 512), (128, 4, 7, 196000), (300, 1, 8, 6272),
+                                                    (64, 8, 7, 25088), (1, 1, 8, 1000000)])
+def test_more_splits_never_outgrow_the_array_of_the_call_without_a_workspace(batch, heads, rep, tokens):
+    """Shapes whose partials fit the library's array at one round of workgroups and two pairs per
+    wave keep fitting it: the finer splits are only taken where they fit too."""
+    p = vk.make_params(1, batch, heads, heads * rep, tokens, 16, 0)
+    assert vk.workspace_bytes(p, 2) <= vk.NOALLOC_SCRATCH_BYTES
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("batch,heads", [(1, 1), (9, 4), (31, 4), (43, 3), (129, 1), (130, 4)])
 @pytest.mark.parametrize("cap", [1, 40, 256])
