@@ -127,9 +127,18 @@ __device__ __forceinline__ uint32_t byte_x8(uint32_t w) {
 // FFT: normal key channels coded by Eq. 5 (true) or by Eq. 4 at 1 bit on the tokens (false);
 // in the latter case slot = token and code * s + z = (z + s/2) + sigma * s/2, sigma = +-1,
 // so the same sign-type operand serves, without the inverse DFT and with a constant term.
-// The counts of the workloads carry a probability into P V as one fp16 number; every other
-// count as fp16 hi + lo parts (two more products per value tile and group), because those
-// counts have always had their probabilities in 32 bits.
+// FULL: the counts that a kernel in 32-bit arithmetic served before this one keep its accuracy:
+//   * probabilities enter P V as three bf16 parts that add up to the fp32 number, whatever its size
+//     (fp16 hi + lo parts are 0 below 2^-25 of the running maximum, where the softmax denominator
+//     still counts the token: 196000 tokens at 2^-25.1 of one other lost 0.5 % of the output);
+//   * protected rows' probabilities as three fp16 parts, the second and third scaled by 2^11 and 2^22;
+//   * q enters as it is, or halved where the head has an element of 2^15 or more; what the other
+//     counts take as s/2 and s here is s against q and 2 q, so neither loses bits where it is subnormal;
+//   * the inverse DFT runs on v_mfma_f32_16x16x4_f32, on the fp32 sums and an fp32 matrix.
+// The other counts have always had fp16 probabilities and -q/16.  It costs 48 instead of 32 products of a
+// pair's values and 512 instead of 96 matrix-pipe cycles of its inverse DFT: n_a = 96, nothing protected, one layer of
+// 196000 tokens 30.7 -> 35.0 us, 4 x 8 x 12544 tokens 86.6 -> 96.9, 2 x 3136 tokens 11.8 both (the 32-bit
+// kernel: 309, 684, 24.2).
 // TAIL: workgroups with split >= nsplit of the grid take residual tokens.  A variant of its own,
 // since the branch costs the others 3 % (28 x 8 x 12544 tokens, n_a = 64: 597 us a step against 577).
 template <int NA8, int SAL, bool FFT, bool TAIL>
@@ -139,7 +148,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   constexpr int U = (NB + 3) / 4;            // K-steps over normal channels
   constexpr int NQ = NA / 4;                 // anomalous 4-channel quads
   constexpr int UA = (NQ + 3) / 4;           // K-steps over anomalous channels
-  constexpr bool PLO = !(NA8 == 0 || NA8 == 1 || NA8 == 2 || NA8 == 4 || NA8 == 8 || NA8 == 16);   // low parts of the probabilities too
+  constexpr bool FULL = !(NA8 == 0 || NA8 == 1 || NA8 == 2 || NA8 == 4 || NA8 == 8 || NA8 == 16);
   constexpr int KREC = 12 * NA + 8 * NN;
   constexpr int KCH = KREC / 16;             // 16-byte chunks of a key record (64 < KCH <= 96, or 64)
   constexpr int OFF_AS = 8 * NA, OFF_AZ = 10 * NA, OFF_BITS = 12 * NA, OFF_META = 12 * NA + 4 * NN;
@@ -158,8 +167,8 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   const f4 zero = f4{0.f, 0.f, 0.f, 0.f};
 
   __shared__ __align__(16) uint8_t ring[4][RING];   // per wave: 2 key stages, 2 value stages; reused for the wave's partial output
-  __shared__ uint2 t_trit[256];              // byte -> 4 halves, half i = +1 / -1 / 0 from bits 2i (nonzero), 2i+1 (negative)
-  __shared__ u32x4 w_tab[4][64];             // per lane: inverse-DFT operands Wh[0], Wh[1], Wl[0], Wl[1]
+  __shared__ uint2 t_trit[256];              // byte -> 4 fp16 (FULL: bf16) numbers, number i = +1 / -1 / 0 from bits 2i (nonzero), 2i+1 (negative)
+  __shared__ u32x4 w_tab[4][64];             // per lane: inverse-DFT operands Wh[0], Wh[1], Wl[0], Wl[1] (FULL: fp32, token tile 0 Re, tile 1 Re, tile 0 Im, tile 1 Im)
   // q and the channel permutation are needed only until the constant operands are built;
   // the lists of the protected tokens' probabilities take their place afterwards
   constexpr int PL_BYTES = (SAL != 0) ? 4 * LCAP * 8 * 4 : 0;
@@ -179,7 +188,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const uint32_t f = ((uint32_t)tid >> (2 * i)) & 3u;
-      h[i] = (f & 1u) ? ((f & 2u) ? 0xBC00u : 0x3C00u) : 0u;
+      h[i] = (f & 1u) ? ((f & 2u) ? 0x8000u : 0u) | (FULL ? 0x3F80u : 0x3C00u) : 0u;
     }
     t_trit[tid] = uint2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
     // 16 * (inverse real DFT matrix) as fp16 hi + lo parts: row t = 16 mt + x, k-slot (kb, i):
@@ -200,17 +209,27 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       v = i == 7 ? cos32(7) : v; v = i == 8 ? 0.0f : v;
       return neg ? -v : v;
     };
-    Op W;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    auto idft16 = [&](int i) -> float {
       const int k = 4 * wkb + (i & 3);
-      float w;
-      if (i < 4) w = (k == 0) ? 0.5f : cos_rt(k * wt);
-      else       w = (k == 0) ? ((wt & 1) ? -0.5f : 0.5f) : -cos_rt(k * wt + 24);
-      const _Float16 hi = (_Float16)w;
-      W.v[i] = wlo ? (_Float16)(w - (float)hi) : hi;
+      if (i < 4) return (k == 0) ? 0.5f : cos_rt(k * wt);
+      return (k == 0) ? ((wt & 1) ? -0.5f : 0.5f) : -cos_rt(k * wt + 24);
+    };
+    if (FULL) {
+      // 2 * the matrix in fp32, row t, k-slots i of the Re half (wlo = 0) or the Im half
+      f4 W;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) W[i] = idft16(4 * wlo + i) * 0.125f;
+      w_tab[2 * wlo + wmt][wl] = __builtin_bit_cast(u32x4, W);
+    } else {
+      Op W;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float w = idft16(i);
+        const _Float16 hi = (_Float16)w;
+        W.v[i] = wlo ? (_Float16)(w - (float)hi) : hi;
+      }
+      w_tab[2 * wlo + wmt][wl] = W.q;
     }
-    w_tab[2 * wlo + wmt][wl] = W.q;
   }
 
   if (TAIL && split >= a.nsplit) {
@@ -360,8 +379,9 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   // The permutation bytes of my channel blocks and quads come in one LDS read each, then
   // every q element in one batch of independent reads (no branch around a read: absent
   // blocks read a valid block and are zeroed afterwards).
-  Op Bn[2][U > 0 ? U : 1];                   // normal channels: -q/16 (FFT) or -q/2 at channels 8 (4u+kb) + e, only in my parity
-  Op Ba[2][UA > 0 ? UA : 1];                 // anomalous: (-q, -q) per channel, only in my parity
+  Op Bn[2][U > 0 ? U : 1];                   // normal channels: -q/16 (FFT) or -q/2 (FULL: -q h) at channels 8 (4u+kb) + e, only in my parity
+  Op Ba[2][UA > 0 ? UA : 1];                 // anomalous: (-q, -q) (FULL: (-q h, -2 q h)) per channel, only in my parity
+  float sc2 = a.scale2;                      // sum -> score in the exp2 domain (FULL: the sums are 2 h times the scores')
   {
     uint2 pb[U > 0 ? U : 1];
     uint32_t pq[UA > 0 ? UA : 1];
@@ -380,7 +400,23 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     for (int ua = 0; ua < UA; ++ua)
 #pragma unroll
       for (int r = 0; r < 4; ++r) qa[ua][r] = qrow[(pq[ua] >> (8 * r)) & 0xFFu];
-    const _Float16 cn = (_Float16)(FFT ? -0.0625f : -0.5f);
+    _Float16 cn = (_Float16)(FFT ? -0.0625f : -0.5f), ca0 = (_Float16)-1.0f, ca1 = (_Float16)-1.0f;
+    if (FULL) {
+      // h = 1, or 1/2 for a head with an element whose double is no fp16 number
+      float mx = 0.0f;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf((float)qn[u][e]));
+#pragma unroll
+      for (int ua = 0; ua < UA; ++ua)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mx = fmaxf(mx, fabsf((float)qa[ua][r]));
+      const bool big = swap_max16(swap_max32(mx)) >= 32768.0f;
+      cn = ca0 = (_Float16)(big ? -0.5f : -1.0f);
+      ca1 = (_Float16)(big ? -1.0f : -2.0f);
+      sc2 *= big ? 1.0f : 0.5f;
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const bool ok = hv && (4 * u + kb) < NB;
@@ -396,8 +432,8 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       const bool ok = hv && (4 * ua + kb) < NQ;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const _Float16 v = ok ? (_Float16)(-qa[ua][r]) : (_Float16)0.0f;
-        const uint32_t pr = h2_bits(h2{v, v});
+        const _Float16 v = ok ? qa[ua][r] : (_Float16)0.0f;
+        const uint32_t pr = h2_bits(h2{(_Float16)(v * ca0), (_Float16)(v * ca1)});
         Ba[0][ua].u[r] = par ? 0u : pr;
         Ba[1][ua].u[r] = par ? pr : 0u;
       }
@@ -416,7 +452,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   for (int m = 0; m < 8; ++m) o[m] = zero;
   float m_run = -INFINITY, l_run = 0.0f;     // of my column (shared by both parities of a head)
   uint32_t pp[4] = {0u, 0u, 0u, 0u};         // probabilities of the pair whose values come next
-  uint32_t pq[4] = {0u, 0u, 0u, 0u};         // ... their low parts (PLO)
+  uint32_t pm[4] = {0u, 0u, 0u, 0u}, pl[4] = {0u, 0u, 0u, 0u};   // ... their second and third parts (FULL)
 
   // ---------------- the pieces of one step.  Stage numbers are compile-time constants (the
   // loop alternates two instances of the step) so that every LDS address of the records is a
@@ -481,7 +517,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     const uint32_t (&wi)[2][U > 0 ? U : 1] = hop.wi;
     const uint32_t (&wa)[2][UA > 0 ? UA : 1][2] = hop.wa;
     u32x4 vw[2];
-    Op sv, Ap[2], Aq[2];                         // sv: Eq. 6 scales of channels 16 m + x16, my rows' group
+    Op sv, Ap[2];                                // sv: Eq. 6 scales of channels 16 m + x16, my rows' group
     if (DO_V) {
       vw[0] = hop.vw[0];
       vw[1] = hop.vw[1];
@@ -490,11 +526,10 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       for (int r = 0; r < 4; ++r) {
         Ap[0].u[r] = pp[r] & keep0;
         Ap[1].u[r] = pp[r] & keep1;
-        if (PLO) { Aq[0].u[r] = pq[r] & keep0; Aq[1].u[r] = pq[r] & keep1; }
       }
     }
     S[0] = zero; S[1] = zero;
-    f4 accRe = zero, accIm = zero, accCn = zero, accC = zero;   // my column's group only: the operands are masked
+    f4 accRe = zero, accIm = zero, accCn = zero, accCs = zero, accC = zero;   // my column's group only: the operands are masked
 
     // ---- the work items
     // scales of the normal K-step n = (group, u)
@@ -531,10 +566,11 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           Az.u[r] = zq.u[r] ^ 0x80008000u;
-          As.u[r] = h2_bits(sre.p[r] * h2{(_Float16)0.5f, (_Float16)0.5f}) ^ 0x80008000u;
+          As.u[r] = FULL ? sre.u[r] ^ 0x80008000u : h2_bits(sre.p[r] * h2{(_Float16)0.5f, (_Float16)0.5f}) ^ 0x80008000u;
         }
         accCn = mma(Az, Bn[grp][u], accCn);
-        accCn = mma(As, Bn[grp][u], accCn);
+        if (FULL) accCs = mma(As, Bn[grp][u], accCs);        // z and s apart: the score takes 2 z + s
+        else accCn = mma(As, Bn[grp][u], accCn);
       }
     };
     // anomalous channels: rows = tokens, K = (channel, bit plane); the column operand is
@@ -554,13 +590,20 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       Op s4, z4;                                             // 4 halves each (low 8 bytes used)
       *reinterpret_cast<uint2*>(&s4) = HOP_SZ ? hop.as[grp][ua] : as;
       *reinterpret_cast<uint2*>(&z4) = HOP_SZ ? hop.az[grp][ua] : az;
-      uint32_t sp[4];                                        // (s/2, s) of channel r
-      Op Ac1, Ac2;                                           // the constant: 1.5 s is sp itself, and (z, 0)
+      uint32_t sp[4];                                        // (s/2, s) (FULL: (s, s)) of channel r
+      // the constant z + 1.5 s: 1.5 s is sp itself, and (z, 0).  FULL, twice that against (q, 2 q): (s, z) and (0, s)
+      Op Ac1, Ac2;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        sp[r] = h2_bits(h2{s4.v[r], s4.v[r]} * h2{(_Float16)0.5f, (_Float16)1.0f});
-        Ac1.u[r] = sp[r];
-        Ac2.u[r] = (r & 1) ? z4.u[r >> 1] >> 16 : z4.u[r >> 1] & 0xFFFFu;
+        if (FULL) {
+          sp[r] = h2_bits(h2{s4.v[r], s4.v[r]});
+          Ac1.p[r] = h2{s4.v[r], z4.v[r]};
+          Ac2.u[r] = sp[r] & 0xFFFF0000u;
+        } else {
+          sp[r] = h2_bits(h2{s4.v[r], s4.v[r]} * h2{(_Float16)0.5f, (_Float16)1.0f});
+          Ac1.u[r] = sp[r];
+          Ac2.u[r] = (r & 1) ? z4.u[r >> 1] >> 16 : z4.u[r >> 1] & 0xFFFFu;
+        }
       }
       // code bytes of my two tokens (tiles mt = 0, 1): bits (2r, 2r+1) of a byte are the
       // code of channel r, expanded like the sign words
@@ -592,12 +635,29 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     // P V of tile m: C[column][channel 16 m + x16] = sum_t p * code, then o += s * C
     auto value_tile = [&](int m, const uint2 (&E)[2], const uint2 (&O)[2]) {
       f4 C = zero;
+      if (FULL) {
+        // every row times either group's values; my rows' parity says which of the two counts
+        f4 Cg[2] = {zero, zero};
 #pragma unroll
-      for (int grp = 0; grp < 2; ++grp) {
-        Op Bv;
-        Bv.u[0] = E[grp].x; Bv.u[1] = E[grp].y; Bv.u[2] = O[grp].x; Bv.u[3] = O[grp].y;
-        C = mma(Ap[grp], Bv, C);
-        if (PLO) C = mma(Aq[grp], Bv, C);
+        for (int grp = 0; grp < 2; ++grp) {
+          Op Bv, P3;
+          Bv.u[0] = E[grp].x; Bv.u[1] = E[grp].y; Bv.u[2] = O[grp].x; Bv.u[3] = O[grp].y;
+          P3.q = u32x4{pl[0], pl[1], pl[2], pl[3]};
+          Cg[grp] = mma_bf16(P3, Bv, Cg[grp]);
+          P3.q = u32x4{pm[0], pm[1], pm[2], pm[3]};
+          Cg[grp] = mma_bf16(P3, Bv, Cg[grp]);
+          P3.q = u32x4{pp[0], pp[1], pp[2], pp[3]};
+          Cg[grp] = mma_bf16(P3, Bv, Cg[grp]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) C[i] = (kb >> 1) ? Cg[1][i] : Cg[0][i];
+      } else {
+#pragma unroll
+        for (int grp = 0; grp < 2; ++grp) {
+          Op Bv;
+          Bv.u[0] = E[grp].x; Bv.u[1] = E[grp].y; Bv.u[2] = O[grp].x; Bv.u[3] = O[grp].y;
+          C = mma(Ap[grp], Bv, C);
+        }
       }
       const float sc = (float)sv.v[m];
 #pragma unroll
@@ -646,9 +706,21 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
           S[0][i] += accRe[i];
           S[1][i] += accIm[i];
         }
-        cst_n = 2.0f * accCn[0];
+        cst_n = FULL ? 2.0f * accCn[0] + accCs[0] : 2.0f * accCn[0];
       }
-      if (U > 0 && FFT) {
+      if (U > 0 && FFT && FULL) {
+        // k-slot (kb, i) of the matrix against row 4 kb + i of the sums, one i at a time
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+#pragma unroll
+          for (int mt = 0; mt < 2; ++mt) {
+            const f4 W = __builtin_bit_cast(f4, w_tab[2 * half + mt][lane]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              S[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(W[i], half ? accIm[i] : accRe[i], S[mt], 0, 0, 0);
+          }
+      }
+      if (U > 0 && FFT && !FULL) {
         // split Y/16 into fp16 hi + lo, then the inverse DFT
         Op Yh, Yl, Wh[2], Wl[2];
         Wh[0].q = w_tab[0][lane]; Wh[1].q = w_tab[1][lane];
@@ -669,7 +741,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
           S[mt] = mma(Wh[mt], Yl, S[mt]);
         }
       }
-      if (UA > 0) cst = accC[0];                 // = -(sum q (z + 1.5 s))
+      if (UA > 0) cst = accC[0];                 // = -(sum q (z + 1.5 s)) (FULL: 2 h times it, like S and cst_n)
       if (!FFT) cst -= cst_n;
     }
   };
@@ -690,19 +762,26 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   };
   // one batch: entries lfirst .. min(lcnt, BS) - 1 of the list against the rows in rowbuf (which
   // have landed), then the next batch's rows are requested.  Operand rows 0-7 are the heads'
-  // probabilities rounded to fp16, rows 8-15 what the rounding left.
-  auto batch = [&]() {
+  // probabilities rounded to fp16, rows 8-15 what the rounding left.  (FULL: rows 8-15 are 0, and a second
+  // operand holds what the first rounding left, times 2^11, in rows 0-7 and what the second left, times
+  // 2^22, in rows 8-15: 33 bits, and nothing is lost above 2^-47.)
+  auto batch = [&]() __attribute__((always_inline)) {   // (a call would put the running sums into memory)
     const int n = min(lcnt, BS);
     // lane numbers of its own, so that no address of a batch occupies a register between batches
     uint32_t ln = lane;
     asm volatile("" : "+v"(ln));
     const int x16 = ln & 15, kb = ln >> 4, hcol = x16 & 7, par = x16 >> 3;
-    auto entry = [&](int idx) -> _Float16 {
+    auto entry = [&](int idx, _Float16& second) -> _Float16 {
       float v = plist[wave][lpos + idx][hcol];
       v = (unsigned)(idx - lfirst) < (unsigned)(n - lfirst) ? v : 0.0f;
       const _Float16 hi = (_Float16)v;
-      return par ? (_Float16)(v - (float)hi) : hi;
+      if (!FULL) return par ? (_Float16)(v - (float)hi) : hi;
+      const float r1 = (v - (float)hi) * 2048.0f;
+      const _Float16 mid = (_Float16)r1;
+      second = par ? (_Float16)((r1 - (float)mid) * 2048.0f) : mid;
+      return par ? (_Float16)0.0f : hi;
     };
+    const float unit2 = (kb >> 1) ? 0x1p-22f : 0x1p-11f;     // of the second operand's products in my rows
     if (SAL == 1) {
       if (n < BS) {
         // rows without an entry count 0 times, and must not hold a NaN (a last batch only)
@@ -711,9 +790,9 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
           if (4 * j + kb >= n) *reinterpret_cast<u32x4*>(&rowbuf[wave][j * 1024 + ln * 16]) = u32x4{0u, 0u, 0u, 0u};
         asm volatile("" ::: "memory");
       }
-      h4 A;                                  // k-slots: rows 4 kb + i
+      h4 A, A2;                              // k-slots: rows 4 kb + i
 #pragma unroll
-      for (int i = 0; i < 4; ++i) A[i] = entry(4 * kb + i);
+      for (int i = 0; i < 4; ++i) { _Float16 e2 = (_Float16)0.0f; A[i] = entry(4 * kb + i, e2); A2[i] = e2; }
       // a transposing read hands lane x16 of kb the rows 4 kb .. 4 kb + 3 of channel 16 m + x16
       const int r = 4 * kb + (x16 >> 2);
       const uint32_t at = rowbuf_lds + r * 2 * D + (r & 7) * 32 + (x16 & 3) * 8;
@@ -722,15 +801,30 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
         const h4 B = __builtin_bit_cast(h4, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
             reinterpret_cast<__attribute__((address_space(3))) s16x4*>(at ^ (m * 32))));
         o[m] = __builtin_amdgcn_mfma_f32_16x16x16f16(A, B, o[m], 0, 0, 0);
+        if (FULL) {
+          const f4 C2 = __builtin_amdgcn_mfma_f32_16x16x16f16(A2, B, zero, 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[m][i] = fmaf(unit2, C2[i], o[m][i]);
+        }
       }
     } else {
       const uint8_t* rec = &rowbuf[wave][0];
-      Op A, one;                             // k-slots: rows kb + 4 i
+      Op A, A2, one;                         // k-slots: rows kb + 4 i
 #pragma unroll
-      for (int i = 0; i < 8; ++i) A.v[i] = entry(kb + 4 * i);
+      for (int i = 0; i < 8; ++i) { _Float16 e2 = (_Float16)0.0f; A.v[i] = entry(kb + 4 * i, e2); A2.v[i] = e2; }
 #pragma unroll
       for (int i = 0; i < 4; ++i) one.u[i] = 0x3C003C00u;
-      const f4 P = mma(A, one, zero);
+      // sum over the batch's rows of probability x B
+      auto times = [&](const Op& B) -> f4 {
+        f4 C = mma(A, B, zero);
+        if (FULL) {
+          const f4 C2 = mma(A2, B, zero);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) C[i] = fmaf(unit2, C2[i], C[i]);
+        }
+        return C;
+      };
+      const f4 P = times(one);
       // channel 16 m + x16 is field x16 % 4 of byte 4 m + x16 / 4 of a row; the code stays where
       // it is: as an fp16 number code 2^(2 (x16 % 4) - 24), here times 2^15
       const uint8_t* codes = rec + kb * 32 + (x16 >> 2);
@@ -743,7 +837,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
         for (int i = 0; i < 4; ++i)
           B.p[i] = bits_h2(((uint32_t)codes[256 * i + 4 * m] | ((uint32_t)codes[256 * i + 128 + 4 * m] << 16)) & field) *
                    h2{(_Float16)32768.0f, (_Float16)32768.0f};
-        const f4 C = mma(A, B, zero);
+        const f4 C = times(B);
         const float sc = (float)reinterpret_cast<const _Float16*>(rec + 1024)[16 * m + x16] * unit;
         const float zc = (float)reinterpret_cast<const _Float16*>(rec + 1280)[16 * m + x16];
 #pragma unroll
@@ -765,13 +859,13 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     // t = score - running maximum, in the exp2 domain, for my column at token slot i
     // (i < 4: token 4kb+i, else 16+4kb+i-4); a column without a group gets -inf
     const bool dead = par && !v1ok;
-    const float c0 = dead ? -INFINITY : -cst * a.scale2;
+    const float c0 = dead ? -INFINITY : -cst * sc2;
     float c1 = c0 - m_run;
     float t[8];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      t[i] = fmaf(S[0][i], a.scale2, c1);
-      t[4 + i] = fmaf(S[1][i], a.scale2, c1);
+      t[i] = fmaf(S[0][i], sc2, c1);
+      t[4 + i] = fmaf(S[1][i], sc2, c1);
     }
     // The running maximum is raised lazily: only when some score exceeds it by more than 8
     // (p stays below 2^8), which needs no cross-lane traffic in the common case.
@@ -782,8 +876,8 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       if (m_run == -INFINITY) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          t[i] = fmaf(S[0][i], a.scale2, c0);
-          t[4 + i] = fmaf(S[1][i], a.scale2, c0);
+          t[i] = fmaf(S[0][i], sc2, c0);
+          t[4 + i] = fmaf(S[1][i], sc2, c0);
         }
         smax = t[0];
 #pragma unroll
@@ -829,17 +923,23 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     // probabilities as the A operand of P V (row = my column).  The k-slots of that product
     // are ordered (0,2), (4,6), (1,3), (5,7) in token-slot numbers: the order in which two
     // trit bytes expand (even slots, then odd slots).
-    pp[0] = pk_rne(pr[0], pr[2]);
-    pp[1] = pk_rne(pr[4], pr[6]);
-    pp[2] = pk_rne(pr[1], pr[3]);
-    pp[3] = pk_rne(pr[5], pr[7]);
-    if (PLO) {
+    if (FULL) {
+      // 24 bits = 3 x 8: the upper halves of p, of what they leave, and what is left then
+      auto upper2 = [](float x, float y) -> uint32_t { return __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u); };
+      auto rest = [](float x) -> float { return x - __uint_as_float(__float_as_uint(x) & 0xFFFF0000u); };
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int i = (r & 1) * 4 + (r >> 1);            // slots (0,2) (4,6) (1,3) (5,7)
-        const h2 hi = bits_h2(pp[r]);
-        pq[r] = pk_rne(pr[i] - (float)hi[0], pr[i + 2] - (float)hi[1]);
+        const float x1 = rest(pr[i]), y1 = rest(pr[i + 2]);
+        pp[r] = upper2(pr[i], pr[i + 2]);
+        pm[r] = upper2(x1, y1);
+        pl[r] = upper2(rest(x1), rest(y1));
       }
+    } else {
+      pp[0] = pk_rne(pr[0], pr[2]);
+      pp[1] = pk_rne(pr[4], pr[6]);
+      pp[2] = pk_rne(pr[1], pr[3]);
+      pp[3] = pk_rne(pr[5], pr[7]);
     }
     if ((SAL != 0) && stage_pl) {
       uint32_t ln = lane;

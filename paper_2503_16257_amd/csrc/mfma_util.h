@@ -26,6 +26,12 @@ __device__ __forceinline__ f4 mma(const Op& a, const Op& b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(a.v, b.v, c, 0, 0, 0);
 }
 
+// the same product of bf16 operands
+typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ f4 mma_bf16(const Op& a, const Op& b, f4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(b8, a.q), __builtin_bit_cast(b8, b.q), c, 0, 0, 0);
+}
+
 __device__ __forceinline__ uint32_t h2_bits(h2 x) { return __builtin_bit_cast(uint32_t, x); }
 __device__ __forceinline__ h2 bits_h2(uint32_t x) { return __builtin_bit_cast(h2, x); }
 
