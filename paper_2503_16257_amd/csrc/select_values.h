@@ -15,12 +15,12 @@ __device__ __forceinline__ uint32_t fkey(float f) {
 constexpr int ONE_THREADS = 1024;
 constexpr int ONE_Q = 8;                                  // float4 pieces of scores per thread
 constexpr int ONE_MAX_T = ONE_THREADS * 4 * ONE_Q;        // 32768 tokens
-constexpr int ONE_COPIES = 4;                             // histogram copies, by lane: scores crowd into few bins
-constexpr int ONE_BINS = 2048;
+constexpr int ONE_COPIES = 32;                            // histogram copies, by lane: one for each bank
+constexpr int ONE_BINS = 256;
 
 struct OneSelLds {
-  int hist[ONE_COPIES][ONE_BINS];                         // index list: the mask (ONE_MAX_T / 32 words)
-  int wsum[16];
+  int hist[ONE_BINS][ONE_COPIES];                         // index list: the mask (ONE_MAX_T / 32 words)
+  int wsum[16], lsum[2][16];
   int pre_s[ONE_Q][16], pre_e[ONE_Q][16];
   int bin, rem;
 };
@@ -34,15 +34,26 @@ struct OneSelArgs {
   uint32_t* rank;
 };
 
+// Inclusive scan over the lanes of a wave, all of them active: inside rows of 16 lanes, then the totals
+// of the rows before (register moves: with the exchanges through LDS the selection of 1568 tokens took 10.1 us).
+// STEP = 4: v is the same in each four lanes and counts once.
+template <int STEP>
+__device__ __forceinline__ int wave_scan(int v) {
+  if (STEP == 1) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);   // from lane - 1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);   // - 2
+  }
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);     // - 4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);     // - 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);    // rows 1 and 3: lane 15 of the row before
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);    // rows 2 and 3: lane 31
+  return v;
+}
+
 // Exclusive scan of one int per thread over the 1024 threads.
 __device__ __forceinline__ int one_exscan(int v, int* wsum) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  int inc = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int o = __shfl_up(inc, d, 64);
-    if (lane >= d) inc += o;
-  }
+  const int inc = wave_scan<1>(v);
   __syncthreads();                                        // wsum may still be read
   if (lane == 63) wsum[wv] = inc;
   __syncthreads();
@@ -53,12 +64,17 @@ __device__ __forceinline__ int one_exscan(int v, int* wsum) {
 }
 
 // The n_s largest scores (ties: lower index first) by a radix select on the ordered 32-bit keys
-// (11 + 11 + 10 bits), then IDX, MASK and RANK in token order.  Thread t holds the scores of the
+// (four digits of 8 bits), then IDX, MASK and RANK in token order.  Thread t holds the scores of the
 // pieces q 1024 + t, four tokens each; a wave of a slab q covers 256 consecutive tokens.
+// A digit's copies lie in the 32 banks, so that at most two lanes of a wave add to one word, whatever the
+// scores are: saliency scores crowd into few digits, and equal, clipped or coarse ones (padding) into one.
+// A launch of its own takes 8.8 us at 1568 tokens, 20.9 at 32768 with scattered scores and 19.4 with equal ones.
+// (Three digits of 11, 11 and 10 bits, four copies that shared a bank: 8.9, 22.8 and 56; the six-launch
+// chain: 22.5, 23.6 and 25.5.)
 __device__ __forceinline__ void select_one(const OneSelArgs& a, int b, OneSelLds& s) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int np = a.T >> 2, nq = (np + ONE_THREADS - 1) / ONE_THREADS;
-  uint32_t key[ONE_Q][4];                                 // 0: no token (below every score's key but a NaN's)
+  uint32_t key[ONE_Q][4];                                 // of a piece without tokens: never looked at (p < np)
   uint32_t sel[ONE_Q], tie[ONE_Q];                        // bit j: token j of the piece is in / has the last key
   int take_eq = 0;
   if (a.scores) {
@@ -69,44 +85,48 @@ __device__ __forceinline__ void select_one(const OneSelArgs& a, int b, OneSelLds
       const int p = q * ONE_THREADS + tid;
       v[q] = p < np ? sc4[p] : float4{0.f, 0.f, 0.f, 0.f};
     }
+    // my eight words of the histogram: those of bin 255 - t / 4 (bins descend with t), copies 8 (t % 4) ..
+    const int bin = ONE_BINS - 1 - (tid >> 2);
+    int4* mine = reinterpret_cast<int4*>(&s.hist[bin][8 * (tid & 3)]);
+    mine[0] = mine[1] = int4{0, 0, 0, 0};
     uint32_t prefix = 0, pmask = 0;
     int rem = a.n_s;
+    __syncthreads();
 #pragma unroll
-    for (int level = 0; level < 3; ++level) {
-      const int shift = level == 0 ? 21 : level == 1 ? 10 : 0;
-      const int nb = level == 2 ? 1024 : 2048;
+    for (int q = 0; q < ONE_Q; ++q) {
+      key[q][0] = fkey(v[q].x); key[q][1] = fkey(v[q].y); key[q][2] = fkey(v[q].z); key[q][3] = fkey(v[q].w);
+    }
 #pragma unroll
-      for (int i = 0; i < ONE_COPIES * ONE_BINS / ONE_THREADS; ++i) s.hist[0][i * ONE_THREADS + tid] = 0;
-      __syncthreads();
-      if (level == 0) {
-#pragma unroll
-        for (int q = 0; q < ONE_Q; ++q) {
-          key[q][0] = fkey(v[q].x); key[q][1] = fkey(v[q].y); key[q][2] = fkey(v[q].z); key[q][3] = fkey(v[q].w);
-        }
-      }
+    for (int level = 0; level < 4; ++level) {
+      const int shift = 24 - 8 * level;
 #pragma unroll
       for (int q = 0; q < ONE_Q; ++q)
         if (q * ONE_THREADS + tid < np) {
 #pragma unroll
           for (int j = 0; j < 4; ++j)
             if ((key[q][j] & pmask) == prefix)
-              atomicAdd(&s.hist[lane & (ONE_COPIES - 1)][(key[q][j] >> shift) & (nb - 1)], 1);
+              atomicAdd(&s.hist[(key[q][j] >> shift) & (ONE_BINS - 1)][lane & (ONE_COPIES - 1)], 1);
         }
       __syncthreads();
-      // thread t owns bins 2 (1023 - t) and the one above: the scan gives the keys in higher bins
-      const int b0 = 2 * (ONE_THREADS - 1 - tid);
-      int c0 = 0, c1 = 0;
+      // the bin's count, its words cleared for the next level; then the keys in higher bins
+      const int4 x = mine[0], y = mine[1];
+      mine[0] = mine[1] = int4{0, 0, 0, 0};
+      int c = x.x + x.y + x.z + x.w + y.x + y.y + y.z + y.w;
+      c += __builtin_amdgcn_update_dpp(0, c, 0xB1, 0xF, 0xF, true);   // the lane beside
+      c += __builtin_amdgcn_update_dpp(0, c, 0x4E, 0xF, 0xF, true);   // the pair beside
+      const int inc = wave_scan<4>(c);                    // over the 16 bins of my wave, 4 lanes each
+      if (lane == 63) s.lsum[level & 1][wave] = inc;
+      __syncthreads();
+      int above = inc - c;
 #pragma unroll
-      for (int k = 0; k < ONE_COPIES; ++k) { c0 += s.hist[k][b0]; c1 += s.hist[k][b0 + 1]; }
-      const int above = one_exscan(c0 + c1, s.wsum);
-      if (above < rem && rem <= above + c0 + c1) {        // exactly one thread
-        const bool hi = rem <= above + c1;
-        s.bin = hi ? b0 + 1 : b0;
-        s.rem = hi ? rem - above : rem - above - c1;
+      for (int i = 0; i < 16; ++i) above += i < wave ? s.lsum[level & 1][i] : 0;
+      if ((tid & 3) == 0 && above < rem && rem <= above + c) {   // exactly one thread
+        s.bin = bin;
+        s.rem = rem - above;
       }
       __syncthreads();
       prefix |= (uint32_t)s.bin << shift;
-      pmask |= (uint32_t)(nb - 1) << shift;
+      pmask |= (uint32_t)(ONE_BINS - 1) << shift;
       rem = s.rem;
     }
     take_eq = rem;

@@ -60,3 +60,49 @@ def test_selection(T, fused):
                 np.testing.assert_array_equal(r[:ng], np.concatenate([[0], np.cumsum(flag.reshape(ng, 32).sum(1))[:-1]]))
                 # room behind the tokens: cleared for an index list, left alone for scores
                 assert (m[ng:] == (0 if kind == "index" else 0x5A5A5A5A)).all()
+
+
+@pytest.mark.parametrize("T", [1568, 32768])
+def test_scores_that_differ_in_one_digit(T):
+    """Infinities, and scores whose ordered keys differ only in the highest, a middle or the lowest bits."""
+    rng = np.random.default_rng(T)
+    for kind in ("infinite", "high", "middle", "low"):
+        if kind == "infinite":
+            sc = rng.choice(np.array([-np.inf, -1.0, 0.0, 1.0, np.inf], np.float32), (2, T))
+        else:
+            shift = {"high": 24, "middle": 12, "low": 0}[kind]
+            sc = (np.uint32(0x3F000000) + (rng.integers(0, 16, (2, T)).astype(np.uint32) << np.uint32(shift))).view(np.float32)
+        for n_s in (1, T // 3, T - 1):
+            print(f"[case] T {T} n_s {n_s} {kind}", flush=True)
+            p = vk.make_params(1, 2, 1, 1, T, 16, n_s)
+            V = torch.zeros((1, 2, 1, T, 128), dtype=torch.float16, device=DEV)
+            pv, ws = vk.alloc_bytes(vk.packed_values_bytes(p)), vk.alloc_bytes(vk.workspace_bytes(p, 1))
+            vk.quantize_values(p, V, pv, ws, saliency=torch.from_numpy(sc).to(DEV))
+            off = LY.value_sections(1, 2, 1, T, n_s)["idx"]
+            got = pv[off:off + 8 * n_s].cpu().numpy().view("<i4").reshape(2, n_s)
+            for b in range(2):
+                np.testing.assert_array_equal(got[b], O.select_salient_tokens(sc[b], n_s))
+
+
+def test_equal_scores_take_no_longer():
+    """The longest sequence of one workgroup, all scores equal (padding) against scattered ones.  A
+    histogram whose counters for one digit share a bank takes 2.4 times as long, one that spreads them 0.93."""
+    T = 32768
+    p = vk.make_params(1, 1, 1, 1, T, 16, T // 10)
+    V = torch.zeros((1, 1, 1, T, 128), dtype=torch.float16, device=DEV)
+    pv, ws = vk.alloc_bytes(vk.packed_values_bytes(p)), vk.alloc_bytes(vk.workspace_bytes(p, 1))
+    scattered = torch.rand((1, T), device=DEV)
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+
+    def best(sc):
+        t = []
+        for _ in range(7):
+            e0.record()
+            for _ in range(50):
+                vk.quantize_values(p, V, pv, ws, saliency=sc, stages=1)
+            e1.record()
+            torch.cuda.synchronize()
+            t.append(e0.elapsed_time(e1))
+        return min(t)
+
+    assert best(torch.full_like(scattered, 0.25)) < 1.5 * best(scattered)
