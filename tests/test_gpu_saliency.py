@@ -84,3 +84,18 @@ def test_full_size_rows_sampled():
     err = np.abs(got[torch.from_numpy(rows).to(DEV)].cpu().numpy().astype(np.float64) - ref)
     assert np.all(err <= _bound(xs, xt)), f"max err {err.max():.3e}"
     assert torch.isfinite(got).all()
+
+
+def test_every_number_of_last_text_rows():
+    """The text rows are summed 16 at a time, the last ones in shorter runs: every remainder, rows
+    that are all different, and a large value behind the last one that must not be read into the sum."""
+    d = 40
+    r = np.random.default_rng(11)
+    for Nt in list(range(1, 35)) + [255, 256, 257]:
+        buf = torch.full((Nt + 16, d), 30000.0, dtype=torch.float16, device=DEV)
+        Xt = r.standard_normal((1, Nt, d)).astype(np.float16)
+        buf[:Nt] = torch.from_numpy(Xt[0]).to(DEV)
+        Xv = r.standard_normal((1, 66, d)).astype(np.float16)
+        got = _run(torch.from_numpy(Xv).to(DEV), buf[:Nt][None]).cpu().numpy()[0]
+        err = np.abs(got.astype(np.float64) - O.saliency_scores(Xv[0], Xt[0]))
+        assert np.all(err <= _bound(Xv[0], Xt[0])), f"{Nt} text rows: max err {err.max():.3e}"
