@@ -107,20 +107,26 @@ static int device_cu_count() {
   return n;
 }
 
-// The most split-T workgroups per (sequence, KV head) that attn_splits() can choose: what the
-// workspace is sized for.  Grows with the number of groups.  One pair per wave and two rounds of
-// workgroups, but not so many that the partials outgrow the array of the entry point without a
-// workspace - unless one round and two pairs per wave already do.
+// Split-T workgroups per (sequence, KV head) that every accepted workspace has room for: one round
+// of workgroups, two pairs per wave.
+int attn_least_splits(const Geom& g) {
+  if (g.ng == 0) return 0;
+  const long long bh = (long long)g.B * g.H, npairs = (g.ng + 1) / 2, cus = device_cu_count();
+  return (int)std::max(1LL, std::min((2 * cus + bh - 1) / bh, (npairs + 7) / 8));
+}
+
+// The most that attn_splits() can choose: what the workspace is sized for.  Grows with the number of
+// groups.  One pair per wave and two rounds of workgroups, but not so many that the partials outgrow
+// the array of the entry point without a workspace - unless the least number already does.
 int attn_max_splits(const Geom& g) {
   if (g.ng == 0) return 0;
   const long long bh = (long long)g.B * g.H, npairs = (g.ng + 1) / 2, cus = device_cu_count();
   const long long fit = ((long long)VIDKV_NOALLOC_SCRATCH_BYTES - 512) / ((long long)g.B * g.Hq * (D + 2) * 4) - ATTN_TAIL_SPLITS;
-  const long long least = std::max(1LL, std::min((2 * cus + bh - 1) / bh, (npairs + 7) / 8));
-  return (int)std::max(least, std::min({(npairs + 3) / 4, 4 * cus / bh, fit}));
+  return (int)std::max((long long)attn_least_splits(g), std::min({(npairs + 3) / 4, 4 * cus / bh, fit}));
 }
 
-// Split-T workgroups per (sequence, KV head), with `others` workgroups of another kind in the same
-// launch.  4 waves per workgroup, each takes s pairs of groups one after another; two workgroups
+// Split-T workgroups per (sequence, KV head), nmax at most, with `others` workgroups of another kind in
+// the same launch.  4 waves per workgroup, each takes s pairs of groups one after another; two workgroups
 // are resident per compute unit.  Tried are all s up to 64, then the even split over one round.
 // Time of a round, measured for n_a = 64: 6 us to get going and finish, 2.2 us per pair where a
 // compute unit has one workgroup, 3.5 where it has two.  (A fixed aim of two workgroups per unit
@@ -128,10 +134,10 @@ int attn_max_splits(const Geom& g) {
 // round where 512 / (B H) is no whole number, and more workgroups than needed for the same s.  This and the
 // residual tokens in the same launch: 28 layers of 6272 tokens, n_a = 64, 606 -> 402 us a step; of
 // 2 x 3136, n_a = 96, 555 -> 407.)
-static int attn_splits(const Geom& g, long long others_) {
+static int attn_splits(const Geom& g, int nmax, long long others_) {
   // 32-bit arithmetic: the candidates' divisions are on every decode call's way
   const int bh = (int)std::min((long long)g.B * g.H, 1LL << 20), cus = device_cu_count(), npairs = (g.ng + 1) / 2;
-  const int nmax = attn_max_splits(g), others = (int)std::min(others_, 1LL << 20);
+  const int others = (int)std::min(others_, 1LL << 20);
   int best_n = 1;
   long long best_t = -1;
   auto consider = [&](int n) {
@@ -161,10 +167,11 @@ bool attn_tail_beside(const Geom& g, int cap) {
 
 // side / fork / join: when side is not null (and there are residual tokens for the MFMA
 // path) the residual-token kernel is forked onto that stream and joined before the merge.
+// ws_bytes: room for attn_least_splits() + ATTN_TAIL_SPLITS parts at least.
 hipError_t launch_decode_attention(const Geom& g, int layer, float scale, const void* q,
                                    const uint8_t* pk, const uint8_t* pv, const void* ktail,
                                    const void* vtail, int cap, const int32_t* tail_len, void* out,
-                                   void* ws, unsigned stages, hipStream_t st, hipStream_t side,
+                                   void* ws, size_t ws_bytes, unsigned stages, hipStream_t st, hipStream_t side,
                                    hipEvent_t fork, hipEvent_t join) {
   AttnArgs a;
   a.q = reinterpret_cast<const _Float16*>(q);
@@ -191,16 +198,18 @@ hipError_t launch_decode_attention(const Geom& g, int layer, float scale, const 
   const long long bh = (long long)g.B * g.H, slots = 2LL * device_cu_count();
   const int tail_iters = has_tail ? (cap + 31) / 32 : 0;
   int ntail = std::min(tail_iters, ATTN_TAIL_SPLITS);
+  const long long fit = (long long)(ws_bytes / ((size_t)g.B * g.Hq * (D + 2) * sizeof(float))) - ATTN_TAIL_SPLITS;
+  const int nmax = (int)std::min((long long)attn_max_splits(g), fit);
   bool along = false;
   a.nsplit = 0;
   if (g.ng > 0) {
     if (has_tail && !attn_tail_beside(g, cap)) {   // (not by whether a side stream is there: the result is the same with and without)
       const int nt = std::min((tail_iters + (bh * tail_iters <= 64 ? 0 : 3)) / (bh * tail_iters <= 64 ? 1 : 4), ATTN_TAIL_SPLITS);
-      a.nsplit = attn_splits(g, bh * nt);
+      a.nsplit = attn_splits(g, nmax, bh * nt);
       along = bh * (a.nsplit + nt) <= slots;
       if (along) ntail = nt;
     }
-    if (!along) a.nsplit = attn_splits(g, 0);
+    if (!along) a.nsplit = attn_splits(g, nmax, 0);
   } else if (ntail == 0) {
     ntail = 1;
   }

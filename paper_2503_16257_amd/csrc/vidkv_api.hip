@@ -15,9 +15,10 @@ size_t values_ws_bytes(const Geom& g);
 hipError_t launch_decode_attention(const Geom& g, int layer, float scale, const void* q,
                                    const uint8_t* pk, const uint8_t* pv, const void* ktail,
                                    const void* vtail, int cap, const int32_t* tail_len, void* out,
-                                   void* ws, unsigned stages, hipStream_t st, hipStream_t side,
+                                   void* ws, size_t ws_bytes, unsigned stages, hipStream_t st, hipStream_t side,
                                    hipEvent_t fork, hipEvent_t join);
 bool attn_tail_beside(const Geom& g, int cap);
+int attn_least_splits(const Geom& g);
 int attn_max_splits(const Geom& g);
 void launch_k_encode(const Geom& g, const EncodeSpan& sp, const void* K, uint8_t* packed,
                      bool use_fft, hipStream_t st);
@@ -43,14 +44,13 @@ static size_t ws_keys(const Geom& g) {
   return align256((size_t)g.nheads * g.range_chunks * 2 * D * sizeof(_Float16)) + 256;
 }
 static size_t ws_values(const Geom& g) { return values_ws_bytes(g); }
-static size_t ws_attn(const Geom& g) {
+static size_t ws_attn(const Geom& g, int (*splits)(const Geom&) = attn_max_splits) {
   // sized for the capacity, so that a workspace allocated once stays large enough
   // while residual flushes make the packed cache longer
   Geom c = g;
   c.T = g.Tcap;
   c.ng = g.ngc;
-  const int ns = attn_max_splits(c);
-  return align256((size_t)(ns + ATTN_TAIL_SPLITS) * g.B * g.Hq * (D + 2) * sizeof(float)) + 256;
+  return align256((size_t)(splits(c) + ATTN_TAIL_SPLITS) * g.B * g.Hq * (D + 2) * sizeof(float)) + 256;
 }
 static bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
@@ -279,7 +279,9 @@ vidkv_status vidkv_decode_attention_stages(const vidkv_params* p, int32_t layer,
                                         tail_capacity, tail_len, out);
   if (chk != VIDKV_OK) return chk;
   if (!aligned(ws, 256)) return VIDKV_EINVAL;
-  if (ws_bytes < ws_attn(g)) return VIDKV_ENOSPACE;
+  // ws_attn(g) has room for the finest split; a workspace of the size that this call asked for when it only
+  // knew the coarsest is taken as before, and the split fits it
+  if (ws_bytes < ws_attn(g, attn_least_splits)) return VIDKV_ENOSPACE;
   const uint8_t* pk = static_cast<const uint8_t*>(packed_K);
   const uint8_t* pv = static_cast<const uint8_t*>(packed_V);
   hipStream_t st = static_cast<hipStream_t>(stream);
@@ -288,11 +290,11 @@ vidkv_status vidkv_decode_attention_stages(const vidkv_params* p, int32_t layer,
   if (sd.ok && K_tail && V_tail && tail_len && (stages & 1u) && attn_tail_beside(g, tail_capacity)) {
     if (!stream_on_current_device(sd.stream)) return VIDKV_EINVAL;
     return launch_decode_attention(g, layer, p->softmax_scale, q, pk, pv, K_tail, V_tail,
-                                   tail_capacity, tail_len, out, ws, stages, st, sd.stream,
+                                   tail_capacity, tail_len, out, ws, ws_bytes, stages, st, sd.stream,
                                    sd.fork, sd.join) == hipSuccess ? VIDKV_OK : VIDKV_EHIP;
   }
   const hipError_t e = launch_decode_attention(g, layer, p->softmax_scale, q, pk, pv, K_tail, V_tail,
-                                               tail_capacity, tail_len, out, ws, stages, st,
+                                               tail_capacity, tail_len, out, ws, ws_bytes, stages, st,
                                                nullptr, nullptr, nullptr);
   return e == hipSuccess ? VIDKV_OK : VIDKV_EHIP;
 }
@@ -353,7 +355,8 @@ vidkv_status vidkv_decode_attention_noalloc(const vidkv_params* p, int32_t layer
   // only the parts that this call's kernels wrote before it.
   const hipError_t e = launch_decode_attention(
       g, layer, p->softmax_scale, q, static_cast<const uint8_t*>(packed_K),
-      static_cast<const uint8_t*>(packed_V), K_tail, V_tail, tail_capacity, tail_len, out, ws, ~0u,
+      static_cast<const uint8_t*>(packed_V), K_tail, V_tail, tail_capacity, tail_len, out, ws,
+      VIDKV_NOALLOC_SCRATCH_BYTES, ~0u,
       static_cast<hipStream_t>(stream), nullptr, nullptr, nullptr);
   return e == hipSuccess ? VIDKV_OK : VIDKV_EHIP;
 }

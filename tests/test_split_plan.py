@@ -52,3 +52,36 @@ def test_grids_around_one_round(batch, heads, cap):
         n = int(tl[b])
         ref = P.oracle_attention(run, 0, b, q[b], Kt[b, :, :n].cpu().numpy(), Vt[b, :, :n].cpu().numpy())
         P.assert_out_close(out[b], ref, f"seq {b}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("batch,heads,cap", [(1, 4, 0), (1, 4, 128), (2, 1, 40), (16, 4, 256)])
+def test_a_workspace_for_the_coarsest_split_is_still_taken(batch, heads, cap):
+    """The size for one round of workgroups and two pairs per wave, which the query once reported: such a
+    buffer is accepted, nothing behind it is touched, and one byte less is refused."""
+    w = dataclasses.replace(synth.reduced(synth.WORKLOADS["c3_stack"], 32, L=1, B=batch), Hkv=heads, Hq=7 * heads)
+    run = P.GpuRun(w, DEV)
+    bh, npairs, cus = batch * heads, (w.T // 32 + 1) // 2, torch.cuda.get_device_properties(0).multi_processor_count
+    splits = max(1, min(-(-2 * cus // bh), (npairs + 7) // 8))
+    size = -(-(splits + 8) * batch * w.Hq * 130 * 4 // 256) * 256 + 256
+    assert size <= vk.workspace_bytes(run.p, 2)
+    if bh <= 4:
+        assert size < vk.workspace_bytes(run.p, 2)
+    big = torch.full((size + 4096,), 0xCC, dtype=torch.uint8, device=DEV)
+    Kt = Vt = tl = None
+    if cap:
+        g = torch.Generator(device=DEV); g.manual_seed(cap)
+        Kt, Vt = (torch.randn((batch, heads, cap, 128), generator=g, device=DEV).to(torch.float16) for _ in range(2))
+        tl = torch.full((batch,), cap, dtype=torch.int32, device=DEV)
+    q = synth.query(w, 0)
+    qd = torch.from_numpy(q).to(DEV)
+    out = torch.empty((batch, w.Hq, 128), dtype=torch.float16, device=DEV)
+    kw = dict(K_tail=Kt, V_tail=Vt, tail_capacity=cap, tail_len=tl)
+    vk.decode_attention(run.p, 0, qd, run.pk, run.pv, out, big[:size], **kw)
+    torch.cuda.synchronize()
+    assert (big[size:] == 0xCC).all()
+    b = batch - 1
+    ref = P.oracle_attention(run, 0, b, q[b], *((Kt[b].cpu().numpy(), Vt[b].cpu().numpy()) if cap else ()))
+    P.assert_out_close(out[b].cpu().numpy(), ref, f"seq {b}")
+    with pytest.raises(RuntimeError, match="too small"):
+        vk.decode_attention(run.p, 0, qd, run.pk, run.pv, out, big[:size - 1], **kw)
