@@ -29,7 +29,7 @@ struct AttnArgs {
   float scale2;              // softmax scale * log2(e): scores live in the exp2 domain
 };
 
-struct TailLds {
+struct alignas(16) TailLds {              // (16: q and P are read four at a time)
   float q[MAX_REP][D];
   float P[MAX_REP][32];
   float alpha[MAX_REP];

@@ -15,14 +15,17 @@ from paper_2503_16257_amd import build as B
 SRC = os.path.join(B.CSRC, "decode_attn_mfma.hip")
 
 
-@pytest.fixture(scope="module")
-def attention_isa(tmp_path_factory):
-    out = tmp_path_factory.mktemp("isa") / "decode_attn_mfma.s"
+def _isa(src, out):
     flags = [f for f in B.FLAGS if f not in ("-fPIC", "-Wall", "-Wno-unused-function")]
-    cmd = [B._hipcc(), *flags, "-w", "-S", "--cuda-device-only", SRC, "-o", str(out)]
+    cmd = [B._hipcc(), *flags, "-w", "-S", "--cuda-device-only", src, "-o", str(out)]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
     return out.read_text()
+
+
+@pytest.fixture(scope="module")
+def attention_isa(tmp_path_factory):
+    return _isa(SRC, tmp_path_factory.mktemp("isa") / "decode_attn_mfma.s")
 
 
 def test_m0_is_written_only_by_the_transfer_statements(attention_isa):
@@ -45,3 +48,11 @@ def test_no_register_spills_in_the_headline_variants(attention_isa):
             found += 1
             assert spills == 0, (name, spills)
     assert found == 3
+
+
+def test_residual_tokens_read_lds_16_bytes_at_a_time(tmp_path):
+    """q and the probabilities come in quads only where the compiler knows their alignment."""
+    isa = _isa(os.path.join(B.CSRC, "decode_attn.hip"), tmp_path / "decode_attn.s")
+    m = re.search(r"^\S*attn_tail_kernel\S*:.*?s_endpgm", isa, re.S | re.M)
+    assert len(re.findall(r"^\s*ds_read_b128\b", m.group(0), re.M)) >= 64
+    assert not re.search(r"^\s*ds_read2", m.group(0), re.M)
