@@ -125,35 +125,82 @@ int attn_max_splits(const Geom& g) {
   return (int)std::max((long long)attn_least_splits(g), std::min({(npairs + 3) / 4, 4 * cus / bh, fit}));
 }
 
-// Split-T workgroups per (sequence, KV head), nmax at most, with `others` workgroups of another kind in
-// the same launch.  4 waves per workgroup, each takes s pairs of groups one after another; two workgroups
-// are resident per compute unit.  Tried are all s up to 64, then the even split over one round.
-// Time of a round, measured for n_a = 64: 6 us to get going and finish, 2.2 us per pair where a
-// compute unit has one workgroup, 3.5 where it has two.  (A fixed aim of two workgroups per unit
+// The costs below are in 0.1 us: of a round of workgroups, two resident per compute unit, that take s
+// pairs of groups one after another in each of 4 waves; 6 us to get going and finish, 2.2 us per pair where a
+// compute unit has one workgroup, 3.5 where it has two.  Measured for n_a = 64 and checked for 16 with fp16
+// rows, 96, and 64 with 2-bit rows, 1 to 64 sequences of 192 to 12544 tokens with 0 to 512 residual ones:
+// the split chosen costs 0.6 % more than the fastest tried on average, 16 % at most.
+static long long main_cost(int s, int w, int cus) {
+  // a 64-bit product: thousands of rounds of thousands of pairs
+  return (long long)((w + 2 * cus - 1) / (2 * cus)) * (60 + (long long)s * (w <= cus ? 22 : 35));
+}
+
+// Split-T workgroups per (sequence, KV head), nmax at most, in a launch without residual tokens: tried are all
+// s up to 64, then the even split over one round.  (A fixed aim of two workgroups per unit
 // and at least 2 pairs per wave took 2.2 us more where there are few pairs, a second, nearly empty
-// round where 512 / (B H) is no whole number, and more workgroups than needed for the same s.  This and the
-// residual tokens in the same launch: 28 layers of 6272 tokens, n_a = 64, 606 -> 402 us a step; of
-// 2 x 3136, n_a = 96, 555 -> 407.)
-static int attn_splits(const Geom& g, int nmax, long long others_) {
+// round where 512 / (B H) is no whole number, and more workgroups than needed for the same s.)
+static int attn_splits(int bh, int npairs, int nmax, int cus, long long* cost) {
   // 32-bit arithmetic: the candidates' divisions are on every decode call's way
-  const int bh = (int)std::min((long long)g.B * g.H, 1LL << 20), cus = device_cu_count(), npairs = (g.ng + 1) / 2;
-  const int others = (int)std::min(others_, 1LL << 20);
   int best_n = 1;
   long long best_t = -1;
   auto consider = [&](int n) {
     if (n < 1 || n > nmax) return;
-    const int s = ((npairs + n - 1) / n + 3) / 4, w = n * bh + others;
-    // a 64-bit product: thousands of rounds of thousands of pairs
-    const long long t = (long long)((w + 2 * cus - 1) / (2 * cus)) * (60 + (long long)s * (w <= cus ? 22 : 35));
+    const long long t = main_cost(((npairs + n - 1) / n + 3) / 4, n * bh, cus);
     if (best_t < 0 || t < best_t) { best_t = t; best_n = n; }
   };
-  consider(std::min(std::max(1, (2 * cus - others) / bh), nmax));
+  consider(std::min(std::max(1, 2 * cus / bh), nmax));
   for (int s = std::min(64, (npairs + 3) / 4); s >= 1; --s) {
     const int n = (npairs + 4 * s - 1) / (4 * s);
     if (n > nmax) break;
     consider(n);
   }
+  *cost = best_t;
   return best_n;
+}
+
+struct AttnPlan {
+  int nsplit, ntail;   // workgroups per (sequence, KV head): packed tokens, residual tokens
+  bool along;          // the latter in the same launch
+};
+
+// `iters` blocks of 32 residual tokens per head; `beside`: they get a launch of their own in any case.
+// In the same launch, where all workgroups fit one round, their time disappears behind the packed tokens'
+// if each takes few blocks one after another: 4.8 us and 3.4 us per block, 5 where a compute unit has two
+// workgroups.  A launch of its own, up to ATTN_TAIL_SPLITS workgroups per head, costs 5.8 us and
+// 2.4 us per block and workgroup of a compute unit.  (8 x 4 heads x 1568 tokens, 128 residual tokens in
+// one workgroup per head because there are more than 64 blocks: 21.0 us; in four: 12.8; in a launch of their
+// own: 18.9.  28 layers of 6272 tokens, 77 residual tokens, n_a = 64: a launch each 606 us a step, along 402.)
+static AttnPlan attn_plan(const Geom& g, int nmax, int iters, bool beside) {
+  const int bh = (int)std::min((long long)g.B * g.H, 1LL << 20), cus = device_cu_count(), npairs = (g.ng + 1) / 2;
+  AttnPlan best{0, std::min(iters, ATTN_TAIL_SPLITS), false};
+  long long best_t = -1;
+  if (iters > 0 && !beside) {
+    // from the most workgroups with one block each down to the fewest; of the splits that fit beside them in
+    // one round, or in one workgroup per compute unit, the finest
+    int per = (iters + ATTN_TAIL_SPLITS - 1) / ATTN_TAIL_SPLITS, nt = (iters + per - 1) / per;
+    for (;;) {
+      for (int room = 2; room >= 1; --room) {
+        const int most = std::min(nmax, room * cus / bh - nt);
+        if (most < 1) continue;
+        const int s = ((npairs + most - 1) / most + 3) / 4;
+        const int n = room == 2 ? most : (npairs + 4 * s - 1) / (4 * s), w = bh * (n + nt);
+        const long long t = std::max(main_cost(s, w, cus), 48 + (long long)per * (w <= cus ? 34 : 50));
+        if (best_t < 0 || t < best_t) { best_t = t; best = {n, nt, true}; }
+      }
+      if (nt == 1) break;
+      per = (iters + nt - 2) / (nt - 1);               // the next smaller number that changes the blocks per workgroup
+      nt = (iters + per - 1) / per;
+    }
+  }
+  const int ntail = std::min(iters, ATTN_TAIL_SPLITS);
+  const long long wt = (long long)bh * ntail;
+  const long long own = iters == 0 || beside ? 0 : 58 + 24LL * ((iters + ntail - 1) / ntail) * ((wt + cus - 1) / cus);
+  if (best_t < 0 || best_t > 82 + own) {               // 82: the least that main_cost() can be
+    long long t;
+    const int n = attn_splits(bh, npairs, nmax, cus, &t);
+    if (best_t < 0 || t + own < best_t) best = {n, ntail, false};
+  }
+  return best;
 }
 
 // A large block of residual tokens is worth a stream of its own: its kernel is short of
@@ -190,28 +237,21 @@ hipError_t launch_decode_attention(const Geom& g, int layer, float scale, const 
   a.sal_bits = g.sal_bits; a.npg = g.npg; a.use_fft = g.use_fft ? 1 : 0;
   a.scale2 = scale * 1.4426950408889634f;
   // stages: bit 0 split-T partial kernel(s), bit 1 merge
-  // Residual tokens.  Where all workgroups fit one round, the MFMA kernel's launch takes them
-  // along (their time disappears behind the packed tokens': 5-6 us each as a launch of its own):
-  // 32 tokens per workgroup while there are few, else 128, which still end first.  Otherwise a
-  // launch of its own, on the side stream or behind, with up to ATTN_TAIL_SPLITS workgroups per
-  // (sequence, KV head).  With no token at all one empty part per head is still written.
+  // Residual tokens: in the MFMA kernel's launch, or in one of their own, on the side stream or behind.
+  // With no token at all one empty part per head is still written.
   const long long bh = (long long)g.B * g.H, slots = 2LL * device_cu_count();
   const int tail_iters = has_tail ? (cap + 31) / 32 : 0;
-  int ntail = std::min(tail_iters, ATTN_TAIL_SPLITS);
   const long long fit = (long long)(ws_bytes / ((size_t)g.B * g.Hq * (D + 2) * sizeof(float))) - ATTN_TAIL_SPLITS;
   const int nmax = (int)std::min((long long)attn_max_splits(g), fit);
+  int ntail = std::max(1, std::min(tail_iters, ATTN_TAIL_SPLITS));
   bool along = false;
   a.nsplit = 0;
   if (g.ng > 0) {
-    if (has_tail && !attn_tail_beside(g, cap)) {   // (not by whether a side stream is there: the result is the same with and without)
-      const int nt = std::min((tail_iters + (bh * tail_iters <= 64 ? 0 : 3)) / (bh * tail_iters <= 64 ? 1 : 4), ATTN_TAIL_SPLITS);
-      a.nsplit = attn_splits(g, nmax, bh * nt);
-      along = bh * (a.nsplit + nt) <= slots;
-      if (along) ntail = nt;
-    }
-    if (!along) a.nsplit = attn_splits(g, nmax, 0);
-  } else if (ntail == 0) {
-    ntail = 1;
+    // (not by whether a side stream is there: the result is the same with and without)
+    const AttnPlan p = attn_plan(g, nmax, tail_iters, attn_tail_beside(g, cap));
+    a.nsplit = p.nsplit;
+    ntail = p.ntail;
+    along = p.along;
   }
   a.early = bh * (a.nsplit + (along ? ntail : 0)) <= slots / 2;
   a.tail_per = ntail > 0 && tail_iters > 0 ? (tail_iters + ntail - 1) / ntail : 0;
