@@ -131,14 +131,16 @@ __device__ __forceinline__ uint32_t byte_x8(uint32_t w) {
 //   * probabilities enter P V as three bf16 parts that add up to the fp32 number, whatever its size
 //     (fp16 hi + lo parts are 0 below 2^-25 of the running maximum, where the softmax denominator
 //     still counts the token: 196000 tokens at 2^-25.1 of one other lost 0.5 % of the output);
-//   * protected rows' probabilities as three fp16 parts, the second and third scaled by 2^11 and 2^22;
+//   * protected rows' probabilities as hi + 2^-18 lo, two fp16 numbers;
 //   * q enters as it is, or halved where the head has an element of 2^15 or more; what the other
 //     counts take as s/2 and s here is s against q and 2 q, so neither loses bits where it is subnormal;
 //   * the inverse DFT runs on v_mfma_f32_16x16x4_f32, on the fp32 sums and an fp32 matrix.
-// The other counts have always had fp16 probabilities and -q/16.  It costs 48 instead of 32 products of a
-// pair's values and 512 instead of 96 matrix-pipe cycles of its inverse DFT: n_a = 96, nothing protected, one layer of
-// 196000 tokens 30.7 -> 35.0 us, 4 x 8 x 12544 tokens 86.6 -> 96.9, 2 x 3136 tokens 11.8 both (the 32-bit
-// kernel: 309, 684, 24.2).
+// The other counts have always had fp16 probabilities and -q/16.  What it costs is 48 instead of 32 products
+// of a pair's values (the three parts are used as they are, in all rows: with the operand rows masked by parity, and
+// the second part in the rows that the mask leaves, a third fewer products took more registers than there are) and
+// 256 instead of 96 matrix-pipe cycles of its inverse DFT: n_a = 96, nothing protected, one layer of 196000 tokens
+// 30.7 -> 33.7 us, 4 x 8 x 12544 tokens 86.6 -> 94.4, 2 x 3136 tokens 11.7 -> 11.5 (the 32-bit kernel: 309, 684, 24.2).
+// (The DFT's products between the anomalous items instead of behind them: 34.0, 95.1.)
 // TAIL: workgroups with split >= nsplit of the grid take residual tokens.  A variant of its own,
 // since the branch costs the others 3 % (28 x 8 x 12544 tokens, n_a = 64: 597 us a step against 577).
 template <int NA8, int SAL, bool FFT, bool TAIL>
@@ -168,7 +170,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
 
   __shared__ __align__(16) uint8_t ring[4][RING];   // per wave: 2 key stages, 2 value stages; reused for the wave's partial output
   __shared__ uint2 t_trit[256];              // byte -> 4 fp16 (FULL: bf16) numbers, number i = +1 / -1 / 0 from bits 2i (nonzero), 2i+1 (negative)
-  __shared__ u32x4 w_tab[4][64];             // per lane: inverse-DFT operands Wh[0], Wh[1], Wl[0], Wl[1] (FULL: fp32, token tile 0 Re, tile 1 Re, tile 0 Im, tile 1 Im)
+  __shared__ u32x4 w_tab[4][64];             // per lane: inverse-DFT operands Wh[0], Wh[1], Wl[0], Wl[1] (FULL: fp32, [0] the Re half, [2] the Im half, of the first 16 tokens)
   // q and the channel permutation are needed only until the constant operands are built;
   // the lists of the protected tokens' probabilities take their place afterwards
   constexpr int PL_BYTES = (SAL != 0) ? 4 * LCAP * 8 * 4 : 0;
@@ -215,7 +217,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       return (k == 0) ? ((wt & 1) ? -0.5f : 0.5f) : -cos_rt(k * wt + 24);
     };
     if (FULL) {
-      // 2 * the matrix in fp32, row t, k-slots i of the Re half (wlo = 0) or the Im half
+      // 2 * the matrix in fp32, row t (those below 16 are used), k-slots i of the Re half (wlo = 0) or the Im half
       f4 W;
 #pragma unroll
       for (int i = 0; i < 4; ++i) W[i] = idft16(4 * wlo + i) * 0.125f;
@@ -709,16 +711,23 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
         cst_n = FULL ? 2.0f * accCn[0] + accCs[0] : 2.0f * accCn[0];
       }
       if (U > 0 && FFT && FULL) {
-        // k-slot (kb, i) of the matrix against row 4 kb + i of the sums, one i at a time
+        // k-slot (kb, i) of the matrix against row 4 kb + i of the sums, one i at a time.  Coefficient 4 kb + i is
+        // even where i is; from token t to t + 16 the even ones stay and the odd ones change their sign, so the
+        // products for the first 16 tokens serve both halves
+        const f4 Wr = __builtin_bit_cast(f4, w_tab[0][lane]), Wi = __builtin_bit_cast(f4, w_tab[2][lane]);
+        f4 ev = zero, od = zero;
 #pragma unroll
-        for (int half = 0; half < 2; ++half)
+        for (int i = 0; i < 4; i += 2) {
+          ev = __builtin_amdgcn_mfma_f32_16x16x4f32(Wr[i], accRe[i], ev, 0, 0, 0);
+          od = __builtin_amdgcn_mfma_f32_16x16x4f32(Wr[i + 1], accRe[i + 1], od, 0, 0, 0);
+          ev = __builtin_amdgcn_mfma_f32_16x16x4f32(Wi[i], accIm[i], ev, 0, 0, 0);
+          od = __builtin_amdgcn_mfma_f32_16x16x4f32(Wi[i + 1], accIm[i + 1], od, 0, 0, 0);
+        }
 #pragma unroll
-          for (int mt = 0; mt < 2; ++mt) {
-            const f4 W = __builtin_bit_cast(f4, w_tab[2 * half + mt][lane]);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              S[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(W[i], half ? accIm[i] : accRe[i], S[mt], 0, 0, 0);
-          }
+        for (int i = 0; i < 4; ++i) {
+          S[0][i] += ev[i] + od[i];
+          S[1][i] += ev[i] - od[i];
+        }
       }
       if (U > 0 && FFT && !FULL) {
         // split Y/16 into fp16 hi + lo, then the inverse DFT
@@ -762,26 +771,21 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   };
   // one batch: entries lfirst .. min(lcnt, BS) - 1 of the list against the rows in rowbuf (which
   // have landed), then the next batch's rows are requested.  Operand rows 0-7 are the heads'
-  // probabilities rounded to fp16, rows 8-15 what the rounding left.  (FULL: rows 8-15 are 0, and a second
-  // operand holds what the first rounding left, times 2^11, in rows 0-7 and what the second left, times
-  // 2^22, in rows 8-15: 33 bits, and nothing is lost above 2^-47.)
+  // probabilities rounded to fp16, rows 8-15 what the rounding left (FULL: times 2^18, so that the two
+  // carry 22 bits and nothing is lost above 2^-43).
   auto batch = [&]() __attribute__((always_inline)) {   // (a call would put the running sums into memory)
     const int n = min(lcnt, BS);
     // lane numbers of its own, so that no address of a batch occupies a register between batches
     uint32_t ln = lane;
     asm volatile("" : "+v"(ln));
     const int x16 = ln & 15, kb = ln >> 4, hcol = x16 & 7, par = x16 >> 3;
-    auto entry = [&](int idx, _Float16& second) -> _Float16 {
+    auto entry = [&](int idx) -> _Float16 {
       float v = plist[wave][lpos + idx][hcol];
       v = (unsigned)(idx - lfirst) < (unsigned)(n - lfirst) ? v : 0.0f;
       const _Float16 hi = (_Float16)v;
-      if (!FULL) return par ? (_Float16)(v - (float)hi) : hi;
-      const float r1 = (v - (float)hi) * 2048.0f;
-      const _Float16 mid = (_Float16)r1;
-      second = par ? (_Float16)((r1 - (float)mid) * 2048.0f) : mid;
-      return par ? (_Float16)0.0f : hi;
+      return par ? (_Float16)(FULL ? (v - (float)hi) * 0x1p18f : v - (float)hi) : hi;
     };
-    const float unit2 = (kb >> 1) ? 0x1p-22f : 0x1p-11f;     // of the second operand's products in my rows
+    const float lo_row = FULL && (kb >> 1) ? 0x1p-18f : 1.0f;   // of my rows' products
     if (SAL == 1) {
       if (n < BS) {
         // rows without an entry count 0 times, and must not hold a NaN (a last batch only)
@@ -790,9 +794,9 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
           if (4 * j + kb >= n) *reinterpret_cast<u32x4*>(&rowbuf[wave][j * 1024 + ln * 16]) = u32x4{0u, 0u, 0u, 0u};
         asm volatile("" ::: "memory");
       }
-      h4 A, A2;                              // k-slots: rows 4 kb + i
+      h4 A;                                  // k-slots: rows 4 kb + i
 #pragma unroll
-      for (int i = 0; i < 4; ++i) { _Float16 e2 = (_Float16)0.0f; A[i] = entry(4 * kb + i, e2); A2[i] = e2; }
+      for (int i = 0; i < 4; ++i) A[i] = entry(4 * kb + i);
       // a transposing read hands lane x16 of kb the rows 4 kb .. 4 kb + 3 of channel 16 m + x16
       const int r = 4 * kb + (x16 >> 2);
       const uint32_t at = rowbuf_lds + r * 2 * D + (r & 7) * 32 + (x16 & 3) * 8;
@@ -800,36 +804,28 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       for (int m = 0; m < 8; ++m) {
         const h4 B = __builtin_bit_cast(h4, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
             reinterpret_cast<__attribute__((address_space(3))) s16x4*>(at ^ (m * 32))));
-        o[m] = __builtin_amdgcn_mfma_f32_16x16x16f16(A, B, o[m], 0, 0, 0);
         if (FULL) {
-          const f4 C2 = __builtin_amdgcn_mfma_f32_16x16x16f16(A2, B, zero, 0, 0, 0);
+          const f4 C = __builtin_amdgcn_mfma_f32_16x16x16f16(A, B, zero, 0, 0, 0);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) o[m][i] = fmaf(unit2, C2[i], o[m][i]);
+          for (int i = 0; i < 4; ++i) o[m][i] = fmaf(lo_row, C[i], o[m][i]);
+        } else {
+          o[m] = __builtin_amdgcn_mfma_f32_16x16x16f16(A, B, o[m], 0, 0, 0);
         }
       }
     } else {
       const uint8_t* rec = &rowbuf[wave][0];
-      Op A, A2, one;                         // k-slots: rows kb + 4 i
+      Op A, one;                             // k-slots: rows kb + 4 i
 #pragma unroll
-      for (int i = 0; i < 8; ++i) { _Float16 e2 = (_Float16)0.0f; A.v[i] = entry(kb + 4 * i, e2); A2.v[i] = e2; }
+      for (int i = 0; i < 8; ++i) A.v[i] = entry(kb + 4 * i);
 #pragma unroll
       for (int i = 0; i < 4; ++i) one.u[i] = 0x3C003C00u;
-      // sum over the batch's rows of probability x B
-      auto times = [&](const Op& B) -> f4 {
-        f4 C = mma(A, B, zero);
-        if (FULL) {
-          const f4 C2 = mma(A2, B, zero);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) C[i] = fmaf(unit2, C2[i], C[i]);
-        }
-        return C;
-      };
-      const f4 P = times(one);
+      f4 P = mma(A, one, zero);
+      if (FULL) P *= lo_row;
       // channel 16 m + x16 is field x16 % 4 of byte 4 m + x16 / 4 of a row; the code stays where
       // it is: as an fp16 number code 2^(2 (x16 % 4) - 24), here times 2^15
       const uint8_t* codes = rec + kb * 32 + (x16 >> 2);
       const uint32_t field = 0x00030003u << (2 * (x16 & 3));
-      const float unit = (float)(1 << 9) / (float)(1 << (2 * (x16 & 3)));
+      const float unit = lo_row * ((float)(1 << 9) / (float)(1 << (2 * (x16 & 3))));
 #pragma unroll
       for (int m = 0; m < 8; ++m) {
         Op B;
@@ -837,7 +833,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
         for (int i = 0; i < 4; ++i)
           B.p[i] = bits_h2(((uint32_t)codes[256 * i + 4 * m] | ((uint32_t)codes[256 * i + 128 + 4 * m] << 16)) & field) *
                    h2{(_Float16)32768.0f, (_Float16)32768.0f};
-        const f4 C = times(B);
+        const f4 C = mma(A, B, zero);
         const float sc = (float)reinterpret_cast<const _Float16*>(rec + 1024)[16 * m + x16] * unit;
         const float zc = (float)reinterpret_cast<const _Float16*>(rec + 1280)[16 * m + x16];
 #pragma unroll

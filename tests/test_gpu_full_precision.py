@@ -58,7 +58,9 @@ def test_probabilities_far_below_the_largest(n_a, rows):
         V[:, :, :, 777] = 0.0
         q = np.zeros((1, w.Hq, 128), np.float16)
         q[:, :, 0] = d * np.log(2.0) * np.sqrt(128.0) / 8.0
-        _check(w, K, V, q, 1e-3, f"n_a {n_a} {rows} 2^-{d}", idx=idx, bits=2 if rows == "2bit" else 16)
+        # a protected row's probability is held to 2^-22 of itself, and to 2^-43 of the largest
+        tol = 1e-3 + (0.0 if rows == "none" else 2.0 ** (d - 43))
+        _check(w, K, V, q, tol, f"n_a {n_a} {rows} 2^-{d}", idx=idx, bits=2 if rows == "2bit" else 16)
 
 
 @pytest.mark.parametrize("fft", [1, 0])
