@@ -8,6 +8,7 @@ import pytest
 import torch
 
 import parity as P
+from oracle import vidkv_oracle as O
 from paper_2503_16257_amd import synth
 
 pytestmark = pytest.mark.gpu
@@ -30,6 +31,17 @@ def test_runs_of_protected_tokens(n, bits):
     P.assert_out_close(out[0], P.oracle_attention(run, 0, 0, q[0]), f"{n} protected in a row, {bits} bits")
 
 
+def _oracle(run, w, q, n):
+    """The oracle's attention from the packed bytes, with the first n entries of IDX and their rows only."""
+    K, V = [], []
+    for h in range(w.Hkv):
+        K.append(O.dequantize_keys_head(run.key_record(h)))
+        v = run.value_record(h)
+        V.append(O.ternary_dequant(v["codes"], v["s16"], v["idx"][:n], v["rows"][:n]))
+    none = np.zeros((w.Hkv, 0, 128), np.float16)
+    return O.decode_attention(q, np.stack(K), np.stack(V), none, none, float(run.p.softmax_scale))
+
+
 @pytest.mark.parametrize("bits", [16, 2])
 def test_dropped_entries_and_a_flush_behind_them(bits):
     """Entries outside the cache are dropped: the rows behind the last protected token are never
@@ -40,16 +52,26 @@ def test_dropped_entries_and_a_flush_behind_them(bits):
     if bits == 16:
         rows = run.pv[sec["rows"]:sec["rows"] + w.n_heads * w.n_salient * 256].view(w.n_heads, w.n_salient, 256)
         rows[:, 9:] = 0xFF
-    q = torch.from_numpy(synth.query(w, 0)).to(DEV)
+    else:                                          # 36 entries: the second record holds none of the nine
+        recs = run.pv[sec["rows"]:sec["rows"] + w.n_heads * 2 * P.LY.PREC].view(w.n_heads, 2, P.LY.PREC)
+        recs[:, 1:] = 0xFF
+    qn = synth.query(w, 0)
+    q = torch.from_numpy(qn).to(DEV)
     a = run.attention(0, q)
-    assert torch.isfinite(a).all()
+    P.assert_out_close(a.cpu().numpy()[0], _oracle(run, w, qn[0], 9), f"{bits} bits")
     Kt = np.stack([synth.tail_heads(w, 0, b, 32)[0] for b in range(w.B)])
     Vt = np.stack([synth.tail_heads(w, 0, b, 32)[1] for b in range(w.B)])
-    run.flush(0, torch.from_numpy(Kt).to(DEV), torch.from_numpy(Vt).to(DEV), 32, 32)
+    Kd, Vd = torch.from_numpy(Kt).to(DEV), torch.from_numpy(Vt).to(DEV)
+    run.flush(0, Kd, Vd, 32, 32)
     run.advance(32)
     b = run.attention(0, q)
-    assert torch.isfinite(b).all()
-    # the same cache with exactly the nine tokens protected gives the same attention
-    ref, _ = _run(idx[:9], bits)
+    P.assert_out_close(b.cpu().numpy()[0], _oracle(run, w, qn[0], 9), f"{bits} bits, flushed")
+    # the same cache with exactly the nine tokens protected gives the same attention, before the
+    # flush and behind it
+    ref, _ = _run(idx[:9], bits, t_capacity=1568 + 32)
     if bits == 16:
         assert torch.equal(a, ref.attention(0, q))
+    ref.flush(0, Kd, Vd, 32, 32)
+    ref.advance(32)
+    if bits == 16:
+        assert torch.equal(b, ref.attention(0, q))
