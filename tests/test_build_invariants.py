@@ -4,6 +4,7 @@ transfers rely on (CPU only: hipcc cross-compiles the device code to assembly).
 The transfer statement writes M0 itself and the kernel assumes that nothing else does:
 no register-indirect indexing (v_movrel / s_movrel set M0), no other M0 user in between.
 """
+import concurrent.futures as cf
 import os
 import re
 import subprocess
@@ -12,7 +13,7 @@ import pytest
 
 from paper_2503_16257_amd import build as B
 
-SRC = os.path.join(B.CSRC, "decode_attn_mfma.hip")
+SOURCES = [f for f in B.SOURCES if f.startswith("decode_attn_mfma")]   # every instantiation of the kernel
 
 
 def _isa(src, out):
@@ -25,29 +26,36 @@ def _isa(src, out):
 
 @pytest.fixture(scope="module")
 def attention_isa(tmp_path_factory):
-    return _isa(SRC, tmp_path_factory.mktemp("isa") / "decode_attn_mfma.s")
+    d = tmp_path_factory.mktemp("isa")
+    with cf.ThreadPoolExecutor(max_workers=4) as ex:
+        return dict(zip(SOURCES, ex.map(lambda f: _isa(os.path.join(B.CSRC, f), d / (f + ".s")), SOURCES)))
 
 
-def test_m0_is_written_only_by_the_transfer_statements(attention_isa):
-    transfers = len(re.findall(r"^\s*global_load_lds_dwordx4\b", attention_isa, re.M))
-    m0_lines = [l for l in attention_isa.splitlines() if re.search(r"\bm0\b", l) and not l.lstrip().startswith(";")]
+@pytest.mark.parametrize("src", SOURCES)
+def test_m0_is_written_only_by_the_transfer_statements(attention_isa, src):
+    isa = attention_isa[src]
+    transfers = len(re.findall(r"^\s*global_load_lds_dwordx4\b", isa, re.M))
+    m0_lines = [l for l in isa.splitlines() if re.search(r"\bm0\b", l) and not l.lstrip().startswith(";")]
     assert transfers > 0
     # every mention of M0 is the s_mov of one transfer statement
     assert all(re.match(r"\s*s_mov_b32 m0, s\d+", l) for l in m0_lines), \
         [l for l in m0_lines if not re.match(r"\s*s_mov_b32 m0, s\d+", l)][:5]
     assert len(m0_lines) == transfers
-    assert "movrel" not in attention_isa
+    assert "movrel" not in isa
 
 
-def test_no_register_spills_in_the_headline_variants(attention_isa):
-    """n_a = 16 (the long-video and serving shapes), all three protected-row modes."""
-    found = 0
-    for m in re.finditer(r"\.name:\s+(\S+).*?\.vgpr_spill_count:\s+(\d+)", attention_isa, re.S):
-        name, spills = m.group(1), int(m.group(2))
-        if re.search(r"attn_mfma_kernelILi2ELi[012]ELb1E", name):
-            found += 1
-            assert spills == 0, (name, spills)
-    assert found == 3
+def test_no_variant_spills_vector_registers(attention_isa):
+    """Every anomalous-channel count (n_a / 8 is the first template argument), the three protected-row
+    modes, both key codes, without and with workgroups for residual tokens."""
+    found = set()
+    for isa in attention_isa.values():
+        for m in re.finditer(r"\.name:\s+(\S+).*?\.private_segment_fixed_size:\s+(\d+).*?\.vgpr_spill_count:\s+(\d+)", isa, re.S):
+            v = re.search(r"attn_mfma_kernelILi(\d+)ELi(\d)ELb(\d)ELb(\d)E", m.group(1))
+            assert (m.group(2), m.group(3)) == ("0", "0"), m.groups()
+            found.add(tuple(int(x) for x in v.groups()))
+    both = {0, 1, 2, 4, 8, 12}                     # a variant without the residual part as well
+    assert found == {(n, s, f, t) for n in range(17) for s in range(3) for f in (0, 1)
+                     for t in ((0, 1) if n in both else (1,))}
 
 
 def test_residual_tokens_read_lds_16_bytes_at_a_time(tmp_path):
