@@ -175,9 +175,10 @@ vidkv_status vidkv_quantize_values(const vidkv_params *params, const void *V_dev
 /* Alg. 3 and Alg. 2 on the K and V tensors of the same tokens in one call (the
  * compression step at the end of Alg. 1, Prefill): the packed buffers come out
  * byte-identical to vidkv_quantize_keys followed by vidkv_quantize_values.
- * Sequences of up to 32768 tokens run in line in three launches.  For longer
- * ones the protected-token selection is a chain of short dependent launches;
- * with a side stream it is enqueued there so that it runs beside the key
+ * Sequences of up to 32768 tokens run in line, in three launches with the
+ * range metric (more with the two others, and with some 33000 heads or more).
+ * For longer ones the protected-token selection is a chain of short dependent
+ * launches; with a side stream it is enqueued there so that it runs beside the key
  * passes (only when the key tensor is 32 MiB or more; smaller inputs run in
  * line), and joined back before the value coding pass.
  * Arguments as for the two separate calls;
@@ -206,7 +207,10 @@ vidkv_status vidkv_quantize_kv(const vidkv_params *params, const void *K_dev,
  *   tail_len_dev in : [B] int32, each 0..tail_capacity; NULL means all zero
  *   out_dev     out : [B, Hq, 128] fp16 (fp32 accumulation, RNE at the end)
  *   workspace_dev   : >= vidkv_workspace_bytes(params, 2) bytes (the size
- *                     depends on t_capacity, not on t_quant)
+ *                     depends on t_capacity, not on t_quant).  It holds the
+ *                     finest split of the cache; earlier builds reported, and
+ *                     this one still takes, the size of a coarser one, which
+ *                     the call then uses
  * With Tq == 0 this is plain attention over the residual tokens; a sequence
  * with no token at all gets zeros.
  * With a side stream, a large residual block (32-token blocks over all

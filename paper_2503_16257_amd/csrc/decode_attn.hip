@@ -185,7 +185,8 @@ static AttnPlan attn_plan(const Geom& g, int nmax, int iters, bool beside) {
         const int s = ((npairs + most - 1) / most + 3) / 4;
         const int n = room == 2 ? most : (npairs + 4 * s - 1) / (4 * s), w = bh * (n + nt);
         const long long t = std::max(main_cost(s, w, cus), 48 + (long long)per * (w <= cus ? 34 : 50));
-        if (best_t < 0 || t < best_t) { best_t = t; best = {n, nt, true}; }
+        // of equal costs the finer split: fewer of its waves take the last of the s pairs
+        if (best_t < 0 || t < best_t || (t == best_t && n > best.nsplit)) { best_t = t; best = {n, nt, true}; }
       }
       if (nt == 1) break;
       per = (iters + nt - 2) / (nt - 1);               // the next smaller number that changes the blocks per workgroup

@@ -152,7 +152,6 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   constexpr int UA = (NQ + 3) / 4;           // K-steps over anomalous channels
   constexpr bool FULL = !(NA8 == 0 || NA8 == 1 || NA8 == 2 || NA8 == 4 || NA8 == 8 || NA8 == 16);
   constexpr int KREC = 12 * NA + 8 * NN;
-  constexpr int KCH = KREC / 16;             // 16-byte chunks of a key record (64 < KCH <= 96, or 64)
   constexpr int OFF_AS = 8 * NA, OFF_AZ = 10 * NA, OFF_BITS = 12 * NA, OFF_META = 12 * NA + 4 * NN;
   constexpr int RING = 4 * KREC + 4 * VREC;  // a wave's ring: two stages of a pair's key records, two of its value records
   constexpr int BS = (SAL == 2) ? 32 : 16;   // protected rows multiplied at a time: a 2-bit record, or 16 fp16 rows

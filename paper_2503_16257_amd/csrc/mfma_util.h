@@ -41,11 +41,4 @@ __device__ __forceinline__ int slot_token(int kb, int i) {
   return (i < 4) ? 4 * kb + i : 16 + 4 * kb + (i - 4);
 }
 
-// cos(2 pi j / 32), j = 0..31, rounded to fp32 (quarter-turn values exact).
-static __device__ const float kCosT[32] = {
-    cos32(0),  cos32(1),  cos32(2),  cos32(3),  cos32(4),  cos32(5),  cos32(6),  cos32(7),
-    cos32(8),  cos32(9),  cos32(10), cos32(11), cos32(12), cos32(13), cos32(14), cos32(15),
-    cos32(16), cos32(17), cos32(18), cos32(19), cos32(20), cos32(21), cos32(22), cos32(23),
-    cos32(24), cos32(25), cos32(26), cos32(27), cos32(28), cos32(29), cos32(30), cos32(31)};
-
 }  // namespace vidkv

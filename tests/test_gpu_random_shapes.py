@@ -1,5 +1,5 @@
 """GPU parity on seeded random configurations: head counts, GQA ratios, anomalous-channel
-counts (MFMA and generic attention kernels), protected-token counts from none to all, both
+counts (fp16 and full-precision attention variants), protected-token counts from none to all, both
 key codes, both protected-row formats, all three channel metrics, ragged residual lengths."""
 import dataclasses
 
