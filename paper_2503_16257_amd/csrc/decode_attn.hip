@@ -169,7 +169,7 @@ struct AttnPlan {
 // workgroups.  A launch of its own, up to ATTN_TAIL_SPLITS workgroups per head, costs 5.8 us and
 // 2.4 us per block and workgroup of a compute unit.  (8 x 4 heads x 1568 tokens, 128 residual tokens in
 // one workgroup per head because there are more than 64 blocks: 21.0 us; in four: 12.8; in a launch of their
-// own: 18.9.  28 layers of 6272 tokens, 77 residual tokens, n_a = 64: a launch each 606 us a step, along 402.)
+// own: 18.9.  28 layers of 6272 tokens, 77 residual tokens, n_a = 64: a launch each 606 us a step, along 397.)
 static AttnPlan attn_plan(const Geom& g, int nmax, int iters, bool beside) {
   const int bh = (int)std::min((long long)g.B * g.H, 1LL << 20), cus = device_cu_count(), npairs = (g.ng + 1) / 2;
   AttnPlan best{0, std::min(iters, ATTN_TAIL_SPLITS), false};
