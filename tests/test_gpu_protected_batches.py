@@ -22,10 +22,11 @@ def _run(idx, bits, t_capacity=0, n_a=16):
     return P.GpuRun(w, DEV, salient_idx=d, salient_bits=bits, t_capacity=t_capacity), w
 
 
+@pytest.mark.parametrize("n_a", [16, 96])
 @pytest.mark.parametrize("bits", [16, 2])
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 31, 32, 33, 95, 129, 700])
-def test_runs_of_protected_tokens(n, bits):
-    run, w = _run(list(range(45, 45 + n)) + [w for w in (1200, 1567) if w >= 45 + n], bits)
+def test_runs_of_protected_tokens(n, bits, n_a):
+    run, w = _run(list(range(45, 45 + n)) + [w for w in (1200, 1567) if w >= 45 + n], bits, n_a=n_a)
     q = synth.query(w, 0)
     out = run.attention(0, torch.from_numpy(q).to(DEV)).cpu().numpy()
     P.assert_out_close(out[0], P.oracle_attention(run, 0, 0, q[0]), f"{n} protected in a row, {bits} bits")
