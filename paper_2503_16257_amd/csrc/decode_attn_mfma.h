@@ -158,6 +158,12 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   constexpr int LCAP = 96;                   // a wave's list of protected probabilities: 32 waiting + a pair's 64
   constexpr int ROWB = (SAL == 2) ? PREC : BS * 2 * D;
 
+  // Every argument that the way to the first requests needs, asked for at once: left to itself the compiler
+  // loads each where it is used and waits for it, a cache miss per 64 bytes of arguments one after another
+  // (from a wave's start to its last request 1.9 us, 0.9 so: 4 heads x 6272 tokens, n_a = 64, 2-bit rows).
+  asm volatile("" :: "s"(a.q), "s"(a.kperm), "s"(a.krec), "s"(a.vrec), "s"(a.layer), "s"(a.B), "s"(a.H), "s"(a.Hq),
+               "s"(a.rep), "s"(a.ng), "s"(a.ngc), "s"(a.gps), "s"(a.nsplit), "s"(a.early));
+  if (SAL != 0) asm volatile("" :: "s"(a.vmask), "s"(a.vrank), "s"(a.vrows), "s"(a.n_s), "s"(a.npg));
   const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform
@@ -180,58 +186,8 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   float (*plist)[LCAP][8] = reinterpret_cast<float (*)[LCAP][8]>(pre_s);   // per wave, a ring: probabilities [protected token][head]
   __shared__ __align__(256) uint8_t rowbuf[(SAL != 0) ? 4 : 1][(SAL != 0) ? ROWB : 16];   // per wave: the rows of the next batch
   __shared__ __align__(16) float al16[4][16];   // per wave: rescale factors per column
-  __shared__ float mw[4][8], lw[4][8];
+  __shared__ __align__(16) float mw[8][4], lw[8][4];   // [head][wave]
   static_assert(sizeof(float) * 8 * D <= RING, "a wave's partial output must fit its ring");
-
-  // ---------------- the expansion table of the value operands, the inverse-DFT operands
-  {
-    uint32_t h[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t f = ((uint32_t)tid >> (2 * i)) & 3u;
-      h[i] = (f & 1u) ? ((f & 2u) ? 0x8000u : 0u) | (FULL ? 0x3F80u : 0x3C00u) : 0u;
-    }
-    t_trit[tid] = uint2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
-    // 16 * (inverse real DFT matrix) as fp16 hi + lo parts: row t = 16 mt + x, k-slot (kb, i):
-    // i < 4 -> Re X[4kb+i], i >= 4 -> Im X[4kb+i-4] (Re X[16] when that index is 0)
-    const int wl = tid & 63, wmt = (tid >> 6) & 1, wlo = tid >> 7;
-    const int wt = 16 * wmt + (wl & 15), wkb = wl >> 4;
-    // cos(2 pi j / 32) from the first-octant constants by the symmetries (no memory access:
-    // this runs before anything has arrived, and a load would only put its latency in front
-    // of the first transfers)
-    auto cos_rt = [](int j) -> float {
-      j &= 31;
-      if (j > 16) j = 32 - j;
-      const bool neg = j > 8;
-      const int i = neg ? 16 - j : j;
-      float v = cos32(0);
-      v = i == 1 ? cos32(1) : v; v = i == 2 ? cos32(2) : v; v = i == 3 ? cos32(3) : v;
-      v = i == 4 ? cos32(4) : v; v = i == 5 ? cos32(5) : v; v = i == 6 ? cos32(6) : v;
-      v = i == 7 ? cos32(7) : v; v = i == 8 ? 0.0f : v;
-      return neg ? -v : v;
-    };
-    auto idft16 = [&](int i) -> float {
-      const int k = 4 * wkb + (i & 3);
-      if (i < 4) return (k == 0) ? 0.5f : cos_rt(k * wt);
-      return (k == 0) ? ((wt & 1) ? -0.5f : 0.5f) : -cos_rt(k * wt + 24);
-    };
-    if (FULL) {
-      // 2 * the matrix in fp32, row t (those below 16 are used), k-slots i of the Re half (wlo = 0) or the Im half
-      f4 W;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) W[i] = idft16(4 * wlo + i) * 0.125f;
-      w_tab[2 * wlo + wmt][wl] = __builtin_bit_cast(u32x4, W);
-    } else {
-      Op W;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float w = idft16(i);
-        const _Float16 hi = (_Float16)w;
-        W.v[i] = wlo ? (_Float16)(w - (float)hi) : hi;
-      }
-      w_tab[2 * wlo + wmt][wl] = W.q;
-    }
-  }
 
   if (TAIL && split >= a.nsplit) {
     // (arguments read anew here, so that the main path's registers do not hold them)
@@ -314,15 +270,6 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   };
   int rb = 0, rk_end = 0;                    // rank of the first row of the batch being filled; end of the wave's rows
   int lpos = 0, lcnt = 0, lfirst = 0;        // where that batch starts in the ring, entries in it and behind it, first valid entry
-  if ((SAL != 0) && p_begin < p_end) {
-    const size_t g0 = (size_t)b * a.ngc + 2 * p_begin, g1 = (size_t)b * a.ngc + min(2 * p_end, a.ng) - 1;
-    rb = (int)((const cu32*)a.vrank)[g0];
-    rk_end = (int)((const cu32*)a.vrank)[g1] + __popc(((const cu32*)a.vmask)[g1]);
-    if (SAL == 2) {                          // batches are whole records
-      lfirst = lcnt = rb & 31;
-      rb &= ~31;
-    }
-  }
   const uint32_t rowbuf_lds = (uint32_t)reinterpret_cast<uintptr_t>(&rowbuf[(SAL != 0) ? wave : 0][0]);
   auto fetch_rows = [&]() {
     if (SAL == 1) {
@@ -351,11 +298,15 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     const uint8_t* qsrc = reinterpret_cast<const uint8_t*>(a.q + ((long long)b * a.Hq + kvh * R) * D);
     const uint32_t q_lds = (uint32_t)reinterpret_cast<uintptr_t>(pre_s);
     const int qbytes = R * D * 2;
+    // head r keeps its 16-byte pieces in the order piece ^ 2 r: one channel of the 8 heads, read by the 16
+    // columns of a wave at a time, lies in 8 different groups of banks (in the same one: the operands of
+    // q took 0.95 us, 1.4 with eight waves on a compute unit; now 0.5 and 0.75)
+    const int q_off = (lane * 16) ^ ((lane >> 4) * 32);
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                 :: "s"(q_lds), "v"(qsrc + (lane * 16 < qbytes ? lane * 16 : 0)) : "memory", "m0");
+                 :: "s"(q_lds), "v"(qsrc + (lane * 16 < qbytes ? q_off : 0)) : "memory", "m0");
     if (1024 + lane * 16 < qbytes)
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                   :: "s"(q_lds + 1024u), "v"(qsrc + 1024 + lane * 16) : "memory", "m0");
+                   :: "s"(q_lds + 1024u), "v"(qsrc + 1024 + (q_off ^ 128)) : "memory", "m0");
     if (lane < D / 16)
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
                    :: "s"(q_lds + 8u * D * 2u), "v"(a.kperm + hd * D + lane * 16) : "memory", "m0");
@@ -364,10 +315,70 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     fetch_keys(p, 0);
     if (a.early) fetch_values(p, 0);
   }
+  // (these loads are waited for all together: behind the transfers' requests)
+  if ((SAL != 0) && p_begin < p_end) {
+    const size_t g0 = (size_t)b * a.ngc + 2 * p_begin, g1 = (size_t)b * a.ngc + min(2 * p_end, a.ng) - 1;
+    rb = (int)((const cu32*)a.vrank)[g0];
+    rk_end = (int)((const cu32*)a.vrank)[g1] + __popc(((const cu32*)a.vmask)[g1]);
+    if (SAL == 2) {                          // batches are whole records
+      lfirst = lcnt = rb & 31;
+      rb &= ~31;
+    }
+  }
   if ((SAL != 0)) {
     load_masks(p, sm0c, sm1c);
     load_masks(p + 1, sm0n, sm1n);
   }
+  // ---------------- the expansion table of the value operands, the inverse-DFT operands
+  // (behind the first requests, whose latency they fill)
+  {
+    uint32_t h[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t f = ((uint32_t)tid >> (2 * i)) & 3u;
+      h[i] = (f & 1u) ? ((f & 2u) ? 0x8000u : 0u) | (FULL ? 0x3F80u : 0x3C00u) : 0u;
+    }
+    t_trit[tid] = uint2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+    // 16 * (inverse real DFT matrix) as fp16 hi + lo parts: row t = 16 mt + x, k-slot (kb, i):
+    // i < 4 -> Re X[4kb+i], i >= 4 -> Im X[4kb+i-4] (Re X[16] when that index is 0)
+    const int wl = tid & 63, wmt = (tid >> 6) & 1, wlo = tid >> 7;
+    const int wt = 16 * wmt + (wl & 15), wkb = wl >> 4;
+    // cos(2 pi j / 32) from the first-octant constants by the symmetries (no memory access, whose
+    // latency would come on top of the first transfers')
+    auto cos_rt = [](int j) -> float {
+      j &= 31;
+      if (j > 16) j = 32 - j;
+      const bool neg = j > 8;
+      const int i = neg ? 16 - j : j;
+      float v = cos32(0);
+      v = i == 1 ? cos32(1) : v; v = i == 2 ? cos32(2) : v; v = i == 3 ? cos32(3) : v;
+      v = i == 4 ? cos32(4) : v; v = i == 5 ? cos32(5) : v; v = i == 6 ? cos32(6) : v;
+      v = i == 7 ? cos32(7) : v; v = i == 8 ? 0.0f : v;
+      return neg ? -v : v;
+    };
+    auto idft16 = [&](int i) -> float {
+      const int k = 4 * wkb + (i & 3);
+      if (i < 4) return (k == 0) ? 0.5f : cos_rt(k * wt);
+      return (k == 0) ? ((wt & 1) ? -0.5f : 0.5f) : -cos_rt(k * wt + 24);
+    };
+    if (FULL) {
+      // 2 * the matrix in fp32, row t (those below 16 are used), k-slots i of the Re half (wlo = 0) or the Im half
+      f4 W;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) W[i] = idft16(4 * wlo + i) * 0.125f;
+      w_tab[2 * wlo + wmt][wl] = __builtin_bit_cast(u32x4, W);
+    } else {
+      Op W;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float w = idft16(i);
+        const _Float16 hi = (_Float16)w;
+        W.v[i] = wlo ? (_Float16)(w - (float)hi) : hi;
+      }
+      w_tab[2 * wlo + wmt][wl] = W.q;
+    }
+  }
+
   if (wave == 0) {
     if (p < p_end && a.early) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NDMA_K + NDMA_V) : "memory");
     else if (p < p_end) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NDMA_K) : "memory");
@@ -377,6 +388,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   if (SAL != 0) fetch_rows();
   const bool hv = hcol < R;
   const _Float16* qrow = &qs[hv ? hcol : 0][0];
+  const uint32_t qswz = hv ? hcol * 0x10101010u : 0u;        // (four channels' numbers at a time)
   // The permutation bytes of my channel blocks and quads come in one LDS read each, then
   // every q element in one batch of independent reads (no branch around a read: absent
   // blocks read a valid block and are zeroed afterwards).
@@ -388,10 +400,14 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     uint32_t pq[UA > 0 ? UA : 1];
 #pragma unroll
     for (int u = 0; u < U; ++u)
+    {
       pb[u] = *reinterpret_cast<const uint2*>(&perm_s[NA + 8 * min(4 * u + kb, NB - 1)]);
+      pb[u].x ^= qswz;
+      pb[u].y ^= qswz;
+    }
 #pragma unroll
     for (int ua = 0; ua < UA; ++ua)
-      pq[ua] = *reinterpret_cast<const uint32_t*>(&perm_s[4 * min(4 * ua + kb, NQ - 1)]);
+      pq[ua] = *reinterpret_cast<const uint32_t*>(&perm_s[4 * min(4 * ua + kb, NQ - 1)]) ^ qswz;
     _Float16 qn[U > 0 ? U : 1][8], qa[UA > 0 ? UA : 1][4];
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -1041,27 +1057,32 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       const float s = __uint_as_float(r[0]) + __uint_as_float(r[1]);
       ow[(4 * (kb & 1) + i) * D + 16 * (m + 4 * (kb >> 1)) + x16] = s;
     }
-  if (kb == 0 && par == 0) { mw[wave][hcol] = m_run; lw[wave][hcol] = l_run; }
+  if (kb == 0 && par == 0) { mw[hcol][wave] = m_run; lw[hcol][wave] = l_run; }
   __syncthreads();
-  // ---------------- workgroup merge of the 4 waves, then the split partial
+  // ---------------- workgroup merge of the 4 waves, then the split partial: four channels of one head
+  // a thread, everything read at once (one channel of four heads one after another, each behind the reads of
+  // the maxima: 1.2 to 1.5 us; now 0.4)
   {
-    const int c = tid & 127, hh = tid >> 7;
-    for (int h = hh; h < R; h += 2) {
-      float M = fmaxf(fmaxf(mw[0][h], mw[1][h]), fmaxf(mw[2][h], mw[3][h]));
-      float acc = 0.0f, L = 0.0f;
-      if (M != -INFINITY) {
+    const int h = tid >> 5, c4 = tid & 31;
+    const f4 m4 = *reinterpret_cast<const f4*>(&mw[h][0]), l4 = *reinterpret_cast<const f4*>(&lw[h][0]);
+    f4 x[4];
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          const float mi = mw[w][h];
-          if (mi == -INFINITY) continue;
-          const float f = exp2f(mi - M);
-          acc += f * reinterpret_cast<const float*>(&ring[w][0])[h * D + c];
-          L += f * lw[w][h];
-        }
-      }
+    for (int w = 0; w < 4; ++w) x[w] = *reinterpret_cast<const f4*>(&ring[w][(h * D + 4 * c4) * sizeof(float)]);
+    const float M = fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]));
+    f4 acc = zero;
+    float L = 0.0f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const bool any = m4[w] != -INFINITY;                      // an empty wave's sums are never looked at
+      const float f = any ? exp2f(m4[w] - M) : 0.0f;
+      L += any ? f * l4[w] : 0.0f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[i] += any ? f * x[w][i] : 0.0f;
+    }
+    if (h < R) {
       const long long row = ((long long)split * a.B + b) * a.Hq + kvh * R + h;
-      a.part_o[row * D + c] = acc;
-      if (c == 0) { a.part_ml[row * 2] = M; a.part_ml[row * 2 + 1] = L; }
+      *reinterpret_cast<f4*>(a.part_o + row * D + 4 * c4) = acc;
+      if (c4 == 0) *reinterpret_cast<float2*>(a.part_ml + row * 2) = float2{M, L};
     }
   }
 }
