@@ -12,11 +12,9 @@
 //  3. Normal channels: the DFT matrix, split in three fp16 parts (exact products,
 //     fp32 accumulation), times X (32 tokens x 16 channels), as [slot][channel]:
 //     each lane gets 8 coefficients of one channel, so the mean-|.| scales need
-//     only a 4-lane sum, and a wave-wide ballot of "coefficient >= 0" per
-//     accumulator register holds, byte by byte, the record's sign words (8
-//     channels of one slot per byte).  One orientation serves both: the key
-//     coding pass is limited by what the SIMDs can sustain, not by HBM alone, and
-//     a second orientation for the sign bits cost 40 % more MFMA work.
+//     only a 4-lane sum, and the 8 channels' signs of a slot, a byte of the
+//     record's sign words, are or-ed together by register moves between lanes.  One
+//     orientation serves both: a second one for the sign bits cost 40 % more MFMA work.
 //  4. Anomalous channels: min / max over the 32 tokens, codes, 4 channels per
 //     byte assembled inside lane quads.
 // The record is assembled in LDS and written with 16-byte stores.
@@ -64,6 +62,33 @@ constexpr DftTab make_dft_tab() {
 
 static __device__ const DftTab kDftTab = make_dft_tab();
 
+// v | v of the lane that DPP control CTRL names (one instruction)
+template <int CTRL>
+__device__ __forceinline__ uint32_t or_dpp(uint32_t v) {
+  return v | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_ROR4 = 0x124, DPP_ROR8 = 0x128;
+// the sign bits of four floats, bit 7 of four bytes
+__device__ __forceinline__ uint32_t signs4(f4 a) {
+  const uint32_t lo = __builtin_amdgcn_perm(__float_as_uint(a[1]), __float_as_uint(a[0]), 0x0C0C0703u);
+  const uint32_t hi = __builtin_amdgcn_perm(__float_as_uint(a[3]), __float_as_uint(a[2]), 0x07030C0Cu);
+  return lo | hi;
+}
+// The sign words of the two 8-channel blocks of a tile.  lo, hi: my channel's bits at slots 4 kb .. 4 kb + 3 of
+// the first and the second slot tile, at bit 7 of a byte each.  Eight lanes' bits are put at their channel's place
+// and or-ed together, so that every lane of a block holds the block's bytes; the first writes 8 of them.
+// (As wave-wide ballots whose bytes 32 lanes then selected this took 55 vector instructions a tile, 18 so, in a
+// pass whose vector units were 71 % busy.)
+__device__ __forceinline__ void put_sign_words(uint8_t* words, uint32_t lo, uint32_t hi, int x16, int kb, bool ok) {
+  const uint32_t sh = 7u - (x16 & 7);
+  lo = or_dpp<DPP_HALF_MIRROR>(or_dpp<DPP_XOR2>(or_dpp<DPP_XOR1>((lo & 0x80808080u) >> sh)));
+  hi = or_dpp<DPP_HALF_MIRROR>(or_dpp<DPP_XOR2>(or_dpp<DPP_XOR1>((hi & 0x80808080u) >> sh)));
+  asm("" : "+v"(lo), "+v"(hi));                      // (the last "or" stays outside the branch, one instruction with its move)
+  if ((x16 & 7) == 0 && ok)
+    *reinterpret_cast<uint2*>(words + (x16 >> 3) * 32 + kb * 8) =
+        uint2{__builtin_amdgcn_perm(hi, lo, 0x05010400u), __builtin_amdgcn_perm(hi, lo, 0x07030602u)};
+}
+
 // NA8T >= 0 fixes n_a = 8 * NA8T at compile time (tile loop fully unrolled);
 // NA8T < 0 takes n_a at run time.  FFT = false codes the normal channels with
 // Eq. 4 at 1 bit on the tokens themselves (the non-FFT 1-bit path of Alg. 3):
@@ -76,7 +101,7 @@ static __device__ const DftTab kDftTab = make_dft_tab();
 template <int NA8T, bool FFT, int EXTRA>
 __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restrict__ K,
                                                             const uint8_t* __restrict__ perm_g,
-                                                            int T, int ng, int n_a_rt, int krec, int gpb,
+                                                            int T, int ng, int n_a_rt, int krec,
                                                             int ngc, int g_out0,
                                                             uint8_t* __restrict__ rec_out, int x_rows,
                                                             Protect2Args p2, VEncArgs ve) {
@@ -108,19 +133,15 @@ __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restr
 
   // the first tile is requested before anything else so that its latency
   // overlaps the set-up below
-  const int g_begin = blockIdx.x * gpb;
-  const int g_end = min(ng, g_begin + gpb);
+  const int g = blockIdx.x * 4 + wave;               // one group per wave: see launch_k_encode
+  if (g >= ng) return;                               // (no barrier in this kernel: everything is per wave)
   const u32x4* head = K + hd * (long long)T * 16;
 
   // coalesced tile load: lane reads 16 bytes of row (lane >> 4) + 4 i, i = 0..7
   u32x4 pre[8];
-  auto prefetch = [&](int g) {
-    const u32x4* src = head + (long long)g * G * 16 + lane;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) pre[i] = __builtin_nontemporal_load(src + 64 * i);
-  };
-  int g = g_begin + wave;
-  if (g < g_end) prefetch(g);
+  for (int i = 0; i < 8; ++i) pre[i] = __builtin_nontemporal_load(head + (long long)g * G * 16 + lane + 64 * i);
+  __builtin_amdgcn_sched_barrier(0);                 // (these first, and their first use behind the set-up: 128.2 us against 127.0)
 
   // Channel tile j: anomalous tiles first (16 anomalous channels each, in PERM
   // order), then normal tiles.  My column's channel in every tile, as a byte
@@ -149,216 +170,201 @@ __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restr
   const int bits_h = 6 * n_a;                        // half-word offsets inside the record
   const int meta_h = 6 * n_a + 2 * n_n;
   const int nblk = n_n >> 3;
+  float one = 1.0f;                                  // (a 1 that the compiler does not see)
+  asm("" : "+v"(one));
   // my 8 token slots start at row 4*kb (slots 0-3) and 16 + 4*kb (slots 4-7)
   const uint8_t* tcol = reinterpret_cast<const uint8_t*>(&tile4[wave][0]) + 4 * kb * ENC_ROW;
 
-  for (; g < g_end; g += 4) {
-    {
-      uint8_t* wdst = reinterpret_cast<uint8_t*>(&tile4[wave][0]) + kb * ENC_ROW + x16 * 16;
+  __builtin_amdgcn_sched_barrier(0);
+  {
+    uint8_t* wdst = reinterpret_cast<uint8_t*>(&tile4[wave][0]) + kb * ENC_ROW + x16 * 16;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4*>(wdst + 4 * i * ENC_ROW) = pre[i];
-    }
-    if (g + 4 < g_end) prefetch(g + 4);
+    for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4*>(wdst + 4 * i * ENC_ROW) = pre[i];
+  }
 
 #pragma unroll
-    for (int j = 0; j < ENC_MAXT; ++j) {
-      if (j >= NT) break;
-      // my column's channel at my 8 token slots: 16-bit LDS loads into register halves
-      Op X;
-      const uint8_t* cp = tcol + chofs[j];
+  for (int j = 0; j < ENC_MAXT; ++j) {
+    if (j >= NT) break;
+    // my column's channel at my 8 token slots: 16-bit LDS loads into register halves
+    Op X;
+    const uint8_t* cp = tcol + chofs[j];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int row = (i < 4) ? i : 12 + i;          // relative to row 4*kb
+      X.v[i] = *reinterpret_cast<const _Float16*>(cp + row * ENC_ROW);
+    }
+
+    if (j < NTa) {
+      // ---------------- Eq. 4, 2 bits: z = min, s = (max - min) / 3 over the 32 tokens
+      const h2 mn2 = __builtin_elementwise_minimum(__builtin_elementwise_minimum(X.p[0], X.p[1]),
+                                                   __builtin_elementwise_minimum(X.p[2], X.p[3]));
+      const h2 mx2 = __builtin_elementwise_maximum(__builtin_elementwise_maximum(X.p[0], X.p[1]),
+                                                   __builtin_elementwise_maximum(X.p[2], X.p[3]));
+      // min and -max over the 4 lane groups: both are "min" reductions, so one
+      // swap pair serves the two values; a last swap hands both to every lane
+      float lo_f = fminf((float)mn2[0], (float)mn2[1]);
+      float nh_f = -fmaxf((float)mx2[0], (float)mx2[1]);
+      {
+        auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo_f), __float_as_uint(nh_f), false, false);
+        const float t = __builtin_elementwise_minimum(__uint_as_float(r[0]), __uint_as_float(r[1]));
+        auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(t), __float_as_uint(t), false, false);
+        const float u = __builtin_elementwise_minimum(__uint_as_float(q[0]), __uint_as_float(q[1]));   // rows 0,1: min; rows 2,3: -max
+        auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(u), __float_as_uint(u), false, false);
+        lo_f = __uint_as_float(w[0]);
+        nh_f = __uint_as_float(w[1]);
+      }
+      const float mnf = lo_f, rng = -nh_f - lo_f;
+      const float inv = rng > 0.0f ? 3.0f / rng : 0.0f;
+      uint32_t w0 = 0, w1 = 0;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const int row = (i < 4) ? i : 12 + i;          // relative to row 4*kb
-        X.v[i] = *reinterpret_cast<const _Float16*>(cp + row * ENC_ROW);
+        // between 0 and a little over 3, whatever the rounding: nothing to clamp.  (x - min as x * 1 + (-min): a
+        // multiply-add takes the 16-bit operand as it is)
+        const float u = rintf(__builtin_fmaf((float)X.v[i], one, -mnf) * inv);
+        if (i < 4) w0 = __builtin_amdgcn_cvt_pk_u8_f32(u, i, w0); else w1 = __builtin_amdgcn_cvt_pk_u8_f32(u, i - 4, w1);
       }
-
-      if (j < NTa) {
-        // ---------------- Eq. 4, 2 bits: z = min, s = (max - min) / 3 over the 32 tokens
-        h2 mn2 = __builtin_elementwise_min(__builtin_elementwise_min(X.p[0], X.p[1]),
-                                           __builtin_elementwise_min(X.p[2], X.p[3]));
-        h2 mx2 = __builtin_elementwise_max(__builtin_elementwise_max(X.p[0], X.p[1]),
-                                           __builtin_elementwise_max(X.p[2], X.p[3]));
-        // min and -max over the 4 lane groups: both are "min" reductions, so one
-        // swap pair serves the two values; a last swap hands both to every lane
-        float lo_f = fminf((float)mn2[0], (float)mn2[1]);
-        float nh_f = -fmaxf((float)mx2[0], (float)mx2[1]);
-        {
-          auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo_f), __float_as_uint(nh_f), false, false);
-          const float t = fminf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-          auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(t), __float_as_uint(t), false, false);
-          const float u = fminf(__uint_as_float(q[0]), __uint_as_float(q[1]));   // rows 0,1: min; rows 2,3: -max
-          auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(u), __float_as_uint(u), false, false);
-          lo_f = __uint_as_float(w[0]);
-          nh_f = __uint_as_float(w[1]);
+      // 4 channels of a quad (adjacent lanes) share a byte: channel r in bits 2r, 2r+1
+      const int ja = 16 * j + x16;                 // anomalous index of my column
+      w0 <<= 2 * (x16 & 3);
+      w1 <<= 2 * (x16 & 3);
+      if (ja >= n_a) { w0 = 0; w1 = 0; }
+      w0 = or_dpp<DPP_XOR2>(or_dpp<DPP_XOR1>(w0));
+      w1 = or_dpp<DPP_XOR2>(or_dpp<DPP_XOR1>(w1));
+      // the quads' bytes of a token are neighbours: lane (quad, r) takes token r's byte to its quad's place, and the
+      // four quads' are or-ed (8 single bytes from every fourth lane before)
+      const uint32_t to_place = 0x0C0C0C0Cu ^ ((0x0Cu ^ (x16 & 3)) << (2 * (x16 & 12)));
+      w0 = or_dpp<DPP_ROR8>(or_dpp<DPP_ROR4>(__builtin_amdgcn_perm(0u, w0, to_place)));
+      w1 = or_dpp<DPP_ROR8>(or_dpp<DPP_ROR4>(__builtin_amdgcn_perm(0u, w1, to_place)));
+      if (x16 < 8) {                               // quad 0: the first four slots' tokens, quad 1: the others
+        uint8_t* at = rec8 + ((x16 & 4 ? 16 : 0) + 4 * kb + (x16 & 3)) * nq + 4 * j;
+        const uint32_t v = x16 & 4 ? w1 : w0;
+        if ((nq & 3) == 0) {
+          *reinterpret_cast<uint32_t*>(at) = v;
+        } else {                                   // n_a = 8 mod 16: rows of codes are 2-byte aligned, the last tile half full
+          *reinterpret_cast<uint16_t*>(at) = (uint16_t)v;
+          if (16 * j + 16 <= n_a) *reinterpret_cast<uint16_t*>(at + 2) = (uint16_t)(v >> 16);
         }
-        const float mnf = lo_f, rng = -nh_f - lo_f;
-        const float inv = rng > 0.0f ? 3.0f / rng : 0.0f;
-        uint32_t w0 = 0, w1 = 0;
+      }
+      if (kb == 0 && ja < n_a) {
+        // rng / 3, correctly rounded: the product with the rounded 1/3 and one correction
+        const float q3 = rng * (1.0f / 3.0f);
+        const float s = __builtin_fmaf(__builtin_fmaf(-3.0f, q3, rng), 1.0f / 3.0f, q3);
+        reinterpret_cast<_Float16*>(rec16)[4 * n_a + ja] = (_Float16)s;
+        reinterpret_cast<_Float16*>(rec16)[5 * n_a + ja] = (_Float16)lo_f;
+      }
+    } else if (!FFT) {
+      // ---------------- Eq. 4, 1 bit: z = min, s = max - min over the 32 tokens
+      const int jn = j - NTa;
+      const h2 mn2 = __builtin_elementwise_minimum(__builtin_elementwise_minimum(X.p[0], X.p[1]),
+                                                   __builtin_elementwise_minimum(X.p[2], X.p[3]));
+      const h2 mx2 = __builtin_elementwise_maximum(__builtin_elementwise_maximum(X.p[0], X.p[1]),
+                                                   __builtin_elementwise_maximum(X.p[2], X.p[3]));
+      float lo_f = fminf((float)mn2[0], (float)mn2[1]);
+      float nh_f = -fmaxf((float)mx2[0], (float)mx2[1]);
+      {
+        auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo_f), __float_as_uint(nh_f), false, false);
+        const float t = __builtin_elementwise_minimum(__uint_as_float(r[0]), __uint_as_float(r[1]));
+        auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(t), __float_as_uint(t), false, false);
+        const float u = __builtin_elementwise_minimum(__uint_as_float(q[0]), __uint_as_float(q[1]));   // rows 0,1: min; rows 2,3: -max
+        auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(u), __float_as_uint(u), false, false);
+        lo_f = __uint_as_float(w[0]);
+        nh_f = __uint_as_float(w[1]);
+      }
+      const float rng = -nh_f - lo_f;
+      // code = round-half-even((x - z) / s) in {0, 1} = [x above the midpoint]; a tie codes 0
+      const float mid = 0.5f * (lo_f - nh_f);
+      const int nidx = 16 * jn + x16;              // normal index of my column
+      // x above the midpoint = x above the largest fp16 number that is not above the midpoint = the sign of their
+      // difference.  That number: the midpoint (+ 0: no -0, whose difference to +0 would be negative) rounded
+      // toward zero, and where that went up, the next one down
+      const float mid0 = mid + 0.0f;
+      uint32_t t = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(mid0, mid0));
+      t += (float)bits_h2(t)[0] > mid0 ? 0x00010001u : 0u;
+      uint32_t d[4];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          float u = ((float)X.v[i] - mnf) * inv;
-          u = fminf(fmaxf(rintf(u), 0.0f), 3.0f);
-          const uint32_t c = (uint32_t)u;
-          if (i < 4) w0 |= c << (8 * i); else w1 |= c << (8 * (i - 4));
-        }
-        // 4 channels of a quad (adjacent lanes) share a byte: channel r in bits 2r, 2r+1
-        w0 <<= 2 * (x16 & 3);
-        w1 <<= 2 * (x16 & 3);
-        const int ja = 16 * j + x16;                 // anomalous index of my column
-        if (ja >= n_a) { w0 = 0; w1 = 0; }
-        w0 |= __shfl_xor(w0, 1, 64);  w1 |= __shfl_xor(w1, 1, 64);
-        w0 |= __shfl_xor(w0, 2, 64);  w1 |= __shfl_xor(w1, 2, 64);
-        if (ja < n_a) {
-          const int quad = ja >> 2;
-          if ((x16 & 3) == 0) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              rec8[(4 * kb + i) * nq + quad] = (uint8_t)(w0 >> (8 * i));
-              rec8[(16 + 4 * kb + i) * nq + quad] = (uint8_t)(w1 >> (8 * i));
-            }
-          }
-          if (kb == 0) {
-            reinterpret_cast<_Float16*>(rec16)[4 * n_a + ja] = (_Float16)(rng / 3.0f);
-            reinterpret_cast<_Float16*>(rec16)[5 * n_a + ja] = (_Float16)lo_f;
-          }
-        }
-      } else if (!FFT) {
-        // ---------------- Eq. 4, 1 bit: z = min, s = max - min over the 32 tokens
-        const int jn = j - NTa;
-        h2 mn2 = __builtin_elementwise_min(__builtin_elementwise_min(X.p[0], X.p[1]),
-                                           __builtin_elementwise_min(X.p[2], X.p[3]));
-        h2 mx2 = __builtin_elementwise_max(__builtin_elementwise_max(X.p[0], X.p[1]),
-                                           __builtin_elementwise_max(X.p[2], X.p[3]));
-        float lo_f = fminf((float)mn2[0], (float)mn2[1]);
-        float nh_f = -fmaxf((float)mx2[0], (float)mx2[1]);
-        {
-          auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo_f), __float_as_uint(nh_f), false, false);
-          const float t = fminf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-          auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(t), __float_as_uint(t), false, false);
-          const float u = fminf(__uint_as_float(q[0]), __uint_as_float(q[1]));   // rows 0,1: min; rows 2,3: -max
-          auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(u), __float_as_uint(u), false, false);
-          lo_f = __uint_as_float(w[0]);
-          nh_f = __uint_as_float(w[1]);
-        }
-        const float rng = -nh_f - lo_f;
-        // code = round-half-even((x - z) / s) in {0, 1} = [x above the midpoint]; a tie codes 0
-        const float mid = 0.5f * (lo_f - nh_f);
-        const int nidx = 16 * jn + x16;              // normal index of my column
-        // ballot i: bit 16 kb + 8 h + e = code of channel 8 (2 jn + h) + e at token slot (kb, i)
-        unsigned long long bal[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) bal[i] = __ballot(nidx < n_n && (float)X.v[i] > mid);
-        // lane (h = lane / 16, k = lane % 16) < 32 assembles word (blk 2 jn + h, k): low byte =
-        // token k = slot (k / 4, k % 4), high byte = token 16 + k = slot (k / 4, 4 + k % 4)
-        {
-          const int k = x16, h = kb & 1, ii = k & 3;
-          unsigned long long lo8 = ii == 0 ? bal[0] : ii == 1 ? bal[1] : ii == 2 ? bal[2] : bal[3];
-          unsigned long long hi8 = ii == 0 ? bal[4] : ii == 1 ? bal[5] : ii == 2 ? bal[6] : bal[7];
-          const int sh = 8 * (2 * (k >> 2) + h);
-          const uint32_t w16 = (uint32_t)((lo8 >> sh) & 0xFFull) | ((uint32_t)((hi8 >> sh) & 0xFFull) << 8);
-          const int blk = 2 * jn + h;
-          if (kb < 2 && blk < nblk) rec16[bits_h + blk * 16 + k] = (uint16_t)w16;
-        }
-        if ((kb & 1) == 0 && nidx < n_n) {
-          const int b8 = nidx >> 3, e = nidx & 7;
-          reinterpret_cast<_Float16*>(rec16)[meta_h + (b8 * 2 + (kb >> 1)) * 8 + e] =
-              (kb >> 1) ? (_Float16)lo_f : (_Float16)rng;
-        }
-      } else {
-        // ---------------- Eq. 5: 32-point DFT along tokens, sign bits and mean-|.| scales
-        const int jn = j - NTa;
-        const f4 zero = f4{0.f, 0.f, 0.f, 0.f};
-        // [slot][channel]: my column = channel x16, my rows = slots 4kb + i of the two slot
-        // tiles (Re X[0..15]; Re X[16], Im X[1..15]); three exact partial products each
-        f4 aRe = mma(F[0][0], X, zero), aIm = mma(F[1][0], X, zero);
-        aRe = mma(F[0][1], X, aRe);  aIm = mma(F[1][1], X, aIm);
-        aRe = mma(F[0][2], X, aRe);  aIm = mma(F[1][2], X, aIm);
-        const int nidx = 16 * jn + x16;              // normal index of my column
-        // sign bits (bit = coefficient >= 0): ballot i, bit 16 kb + 8 h + e = channel
-        // 8 (2 jn + h) + e at slot 4 kb + i
-        unsigned long long bre[4], bim[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          bre[i] = __ballot(nidx < n_n && aRe[i] >= 0.0f);
-          bim[i] = __ballot(nidx < n_n && aIm[i] >= 0.0f);
-        }
-        // lane (h = lane / 16, k = lane % 16) < 32 assembles word (blk 2 jn + h, k): low byte
-        // = first slot tile at slot k = (k / 4, k % 4), high byte = second slot tile
-        {
-          const int k = x16, h = kb & 1, ii = k & 3;
-          const unsigned long long lo8 = ii == 0 ? bre[0] : ii == 1 ? bre[1] : ii == 2 ? bre[2] : bre[3];
-          const unsigned long long hi8 = ii == 0 ? bim[0] : ii == 1 ? bim[1] : ii == 2 ? bim[2] : bim[3];
-          const int sh = 8 * (2 * (k >> 2) + h);
-          const uint32_t w16 = (uint32_t)((lo8 >> sh) & 0xFFull) | ((uint32_t)((hi8 >> sh) & 0xFFull) << 8);
-          const int blk = 2 * jn + h;
-          if (kb < 2 && blk < nblk) rec16[bits_h + blk * 16 + k] = (uint16_t)w16;
-        }
-        // scales: Re X[16] sits in row 0 of the second tile and counts for the real view
-        float sr = fabsf(aRe[0]) + fabsf(aRe[1]) + fabsf(aRe[2]) + fabsf(aRe[3]);
-        float si = fabsf(aIm[0]) + fabsf(aIm[1]) + fabsf(aIm[2]) + fabsf(aIm[3]);
-        if (kb == 0) { sr += fabsf(aIm[0]); si -= fabsf(aIm[0]); }
-        // sum over the 4 lane groups: afterwards rows 0,1 hold the Re total, rows 2,3 the Im total
-        auto r32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(sr), __float_as_uint(si), false, false);
-        const float t2 = __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
-        auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(t2), __float_as_uint(t2), false, false);
-        const float tot = (__uint_as_float(r16[0]) + __uint_as_float(r16[1])) * (1.0f / 1024.0f);
-        if ((kb & 1) == 0 && nidx < n_n) {
-          const int b8 = nidx >> 3, e = nidx & 7;
-          reinterpret_cast<_Float16*>(rec16)[meta_h + (b8 * 2 + (kb >> 1)) * 8 + e] = (_Float16)tot;
-        }
+      for (int i = 0; i < 4; ++i) d[i] = h2_bits(bits_h2(t) - X.p[i]);
+      // slots (0, 1), (2, 3): tokens 4 kb + i; slots (4, 5), (6, 7): tokens 16 + 4 kb + i
+      put_sign_words(rec8 + 2 * bits_h + 64 * jn, __builtin_amdgcn_perm(d[1], d[0], 0x07050301u),
+                     __builtin_amdgcn_perm(d[3], d[2], 0x07050301u), x16, kb, 2 * jn + (x16 >> 3) < nblk);
+      if ((kb & 1) == 0 && nidx < n_n) {
+        const int b8 = nidx >> 3, e = nidx & 7;
+        reinterpret_cast<_Float16*>(rec16)[meta_h + (b8 * 2 + (kb >> 1)) * 8 + e] =
+            (kb >> 1) ? (_Float16)lo_f : (_Float16)rng;
+      }
+    } else {
+      // ---------------- Eq. 5: 32-point DFT along tokens, sign bits and mean-|.| scales
+      const int jn = j - NTa;
+      const f4 zero = f4{0.f, 0.f, 0.f, 0.f};
+      // [slot][channel]: my column = channel x16, my rows = slots 4kb + i of the two slot
+      // tiles (Re X[0..15]; Re X[16], Im X[1..15]); three exact partial products each
+      f4 aRe = mma(F[0][0], X, zero), aIm = mma(F[1][0], X, zero);
+      aRe = mma(F[0][1], X, aRe);  aIm = mma(F[1][1], X, aIm);
+      aRe = mma(F[0][2], X, aRe);  aIm = mma(F[1][2], X, aIm);
+      const int nidx = 16 * jn + x16;              // normal index of my column
+      // sign bits (bit = coefficient >= 0; a sum that starts at +0 is never -0)
+      put_sign_words(rec8 + 2 * bits_h + 64 * jn, ~signs4(aRe), ~signs4(aIm), x16, kb, 2 * jn + (x16 >> 3) < nblk);
+      // scales: Re X[16] sits in row 0 of the second tile and counts for the real view
+      float sr = fabsf(aRe[0]) + fabsf(aRe[1]) + fabsf(aRe[2]) + fabsf(aRe[3]);
+      float si = fabsf(aIm[0]) + fabsf(aIm[1]) + fabsf(aIm[2]) + fabsf(aIm[3]);
+      if (kb == 0) { sr += fabsf(aIm[0]); si -= fabsf(aIm[0]); }
+      // sum over the 4 lane groups: afterwards rows 0,1 hold the Re total, rows 2,3 the Im total
+      auto r32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(sr), __float_as_uint(si), false, false);
+      const float t2 = __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
+      auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(t2), __float_as_uint(t2), false, false);
+      const float tot = (__uint_as_float(r16[0]) + __uint_as_float(r16[1])) * (1.0f / 1024.0f);
+      if ((kb & 1) == 0 && nidx < n_n) {
+        const int b8 = nidx >> 3, e = nidx & 7;
+        reinterpret_cast<_Float16*>(rec16)[meta_h + (b8 * 2 + (kb >> 1)) * 8 + e] = (_Float16)tot;
       }
     }
-    // ---- the finished record: LDS -> global, 16 bytes per lane
-    u32x4* dst = reinterpret_cast<u32x4*>(rec_out + (hd * ngc + g_out0 + g) * (long long)krec);
-    const int nch = krec >> 4;
-    if (lane < nch) __builtin_nontemporal_store(recbuf[wave][lane], dst + lane);
-    if (lane + 64 < nch) __builtin_nontemporal_store(recbuf[wave][lane + 64], dst + lane + 64);
   }
+  // ---- the finished record: LDS -> global, 16 bytes per lane
+  u32x4* dst = reinterpret_cast<u32x4*>(rec_out + (hd * ngc + g_out0 + g) * (long long)krec);
+  const int nch = krec >> 4;
+  if (lane < nch) __builtin_nontemporal_store(recbuf[wave][lane], dst + lane);
+  if (lane + 64 < nch) __builtin_nontemporal_store(recbuf[wave][lane + 64], dst + lane + 64);
 }
 
 template <int NA8T, int EXTRA>
 static void launch_one(bool use_fft, dim3 grid, hipStream_t st, const u32x4* k4, const uint8_t* perm, const Geom& g,
-                       const EncodeSpan& sp, int gpb, uint8_t* rec, int rows, const Protect2Args& p2, const VEncArgs& ve) {
+                       const EncodeSpan& sp, uint8_t* rec, int rows, const Protect2Args& p2, const VEncArgs& ve) {
   if (EXTRA == 1) rows = (int)sp.heads;
   if (use_fft)
     hipLaunchKernelGGL((k_encode_mfma_kernel<NA8T, true, EXTRA>), grid, dim3(256), 0, st, k4, perm, sp.in_tokens, sp.ng,
-                       g.n_a, g.krec, gpb, g.ngc, sp.g_out0, rec, rows, p2, ve);
+                       g.n_a, g.krec, g.ngc, sp.g_out0, rec, rows, p2, ve);
   else
     hipLaunchKernelGGL((k_encode_mfma_kernel<NA8T, false, EXTRA>), grid, dim3(256), 0, st, k4, perm, sp.in_tokens, sp.ng,
-                       g.n_a, g.krec, gpb, g.ngc, sp.g_out0, rec, rows, p2, ve);
+                       g.n_a, g.krec, g.ngc, sp.g_out0, rec, rows, p2, ve);
 }
 
 template <int EXTRA>
-static void launch_any(const Geom& g, const EncodeSpan& sp, int gpb, int gx, const void* K, uint8_t* packed, bool use_fft,
+static void launch_any(const Geom& g, const EncodeSpan& sp, int gx, const void* K, uint8_t* packed, bool use_fft,
                        hipStream_t st, int rows, const Protect2Args& p2, const VEncArgs& ve) {
   const dim3 grid(gx, (unsigned)(sp.heads + rows));
   const u32x4* k4 = reinterpret_cast<const u32x4*>(K);
   const uint8_t* perm = packed + g.k_perm + sp.head0 * D;
   uint8_t* rec = packed + g.k_rec + (size_t)sp.head0 * g.ngc * g.krec;
   switch (g.n_a) {
-    case 8:  launch_one<1, EXTRA>(use_fft, grid, st, k4, perm, g, sp, gpb, rec, rows, p2, ve); break;
-    case 16: launch_one<2, EXTRA>(use_fft, grid, st, k4, perm, g, sp, gpb, rec, rows, p2, ve); break;
-    case 32: launch_one<4, EXTRA>(use_fft, grid, st, k4, perm, g, sp, gpb, rec, rows, p2, ve); break;
-    case 64: launch_one<8, EXTRA>(use_fft, grid, st, k4, perm, g, sp, gpb, rec, rows, p2, ve); break;
-    case 0: launch_one<0, EXTRA>(use_fft, grid, st, k4, perm, g, sp, gpb, rec, rows, p2, ve); break;
-    case 96: launch_one<12, EXTRA>(use_fft, grid, st, k4, perm, g, sp, gpb, rec, rows, p2, ve); break;
-    case 128: launch_one<16, EXTRA>(use_fft, grid, st, k4, perm, g, sp, gpb, rec, rows, p2, ve); break;
-    default: launch_one<-1, EXTRA>(use_fft, grid, st, k4, perm, g, sp, gpb, rec, rows, p2, ve); break;
+    case 8:  launch_one<1, EXTRA>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
+    case 16: launch_one<2, EXTRA>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
+    case 32: launch_one<4, EXTRA>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
+    case 64: launch_one<8, EXTRA>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
+    case 0: launch_one<0, EXTRA>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
+    case 96: launch_one<12, EXTRA>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
+    case 128: launch_one<16, EXTRA>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
+    default: launch_one<-1, EXTRA>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
   }
 }
 
-// two groups per wave: short-lived workgroups keep the memory system evenly loaded,
-// and the second group's load overlaps the first group's arithmetic
-constexpr int K_GPB = 8;
-
-// ... and one where that leaves compute units without a workgroup: the second group's time is then
-// simply added (one head of 1568 tokens, whole call: 23.2 us against 20.4)
-static int key_gpb(const EncodeSpan& sp) { return sp.heads * ((sp.ng + K_GPB - 1) / K_GPB) < 256 ? 4 : K_GPB; }
+// Four groups per workgroup, one per wave: short-lived workgroups keep the memory system evenly loaded.  (Two per
+// wave, the second's load beside the first's arithmetic, were better while the arithmetic took most of the time:
+// 64 x 4 heads x 25088 tokens, n_a = 32, plain code, whole call: 920 us against 891; 4 heads x 196000 130.6 against
+// 127.9; 28 x 4 x 6272, n_a = 64 108.6 either way.)
+constexpr int K_GPB = 4;
 
 void launch_k_encode(const Geom& g, const EncodeSpan& sp, const void* K, uint8_t* packed,
                      bool use_fft, hipStream_t st) {
-  const int gpb = key_gpb(sp);
-  launch_any<0>(g, sp, gpb, (sp.ng + gpb - 1) / gpb, K, packed, use_fft, st, 0, Protect2Args{}, VEncArgs{});
+  launch_any<0>(g, sp, (sp.ng + K_GPB - 1) / K_GPB, K, packed, use_fft, st, 0, Protect2Args{}, VEncArgs{});
 }
 
 // false: too many heads for one grid, nothing done
@@ -366,10 +372,9 @@ bool launch_k_encode_protect2(const Geom& g, const void* K, uint8_t* packed_K, c
                               hipStream_t st) {
   const Protect2Args p2 = protect2_args(g, V, packed_V);
   const EncodeSpan sp{g.T, g.ng, 0, g.nheads, 0};
-  const int gpb = key_gpb(sp);
-  const long long gx = (g.ng + gpb - 1) / gpb, rows = ((p2.total + 3) / 4 + gx - 1) / gx;
+  const long long gx = (g.ng + K_GPB - 1) / K_GPB, rows = ((p2.total + 3) / 4 + gx - 1) / gx;
   if (g.nheads + rows > 65535) return false;
-  launch_any<1>(g, sp, gpb, (int)gx, K, packed_K, g.use_fft, st, (int)rows, p2, VEncArgs{});
+  launch_any<1>(g, sp, (int)gx, K, packed_K, g.use_fft, st, (int)rows, p2, VEncArgs{});
   return true;
 }
 
@@ -380,8 +385,9 @@ bool launch_flush_encode(const Geom& g, const EncodeSpan& sp, float gamma, const
                          uint8_t* packed_K, uint8_t* packed_V, hipStream_t st) {
   if (2 * sp.heads > 65535) return false;
   VEncArgs ve = v_encode_args(g, sp, 0, gamma, V, packed_V);
+  ve.gpb = K_GPB;                                    // one grid for both
   if (g.n_s > 0) ve.mark_rank = g.n_s;
-  launch_any<2>(g, sp, ve.gpb, (sp.ng + ve.gpb - 1) / ve.gpb, K, packed_K, g.use_fft, st, (int)sp.heads, Protect2Args{}, ve);
+  launch_any<2>(g, sp, (sp.ng + K_GPB - 1) / K_GPB, K, packed_K, g.use_fft, st, (int)sp.heads, Protect2Args{}, ve);
   return true;
 }
 
