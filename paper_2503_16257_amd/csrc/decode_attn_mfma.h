@@ -72,6 +72,7 @@
 // against 13.9 for 28 query heads x 6272 tokens, n_a = 64, 20 % at 2 bits; 180 against 152
 // for 64 sequences x 25088 tokens, n_a = 16, 5 % in fp16; 29.8 against 27.7 for one of 196000.)
 #pragma once
+#include <cstddef>
 #include <type_traits>
 
 #include "decode_attn.h"
@@ -98,6 +99,9 @@ __device__ __forceinline__ float swap_max16(float v) {
   auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
+__device__ __forceinline__ float from_xor8(float v) {        // v(lane ^ 8): within a row of 16, 8 lanes on
+  return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x128, 0xF, 0xF, true));
+}
 // two floats -> packed fp16 pair, round to nearest even
 __device__ __forceinline__ uint32_t pk_rne(float a, float b) {
   return h2_bits(__builtin_convertvector(f2{a, b}, h2));
@@ -123,6 +127,33 @@ template <int B>
 __device__ __forceinline__ uint32_t byte_x8(uint32_t w, uint32_t three) {
   return ((w >> (8 * B)) & 0xFFu) << three;
 }
+
+// Inverse-DFT operands.  split: 16 * (inverse real DFT matrix) as fp16 hi + lo parts, [2 lo + mt][lane][8 halves]: row
+// t = 16 mt + x, k-slot (kb, i): i < 4 -> Re X[4kb+i], i >= 4 -> Im X[4kb+i-4] (Re X[16] when that index is 0).
+// full: twice the matrix in fp32, [2 half + mt][lane][4]: k-slots i of the Re half (0) or the Im half (1).
+// (Loaded: computed by every workgroup they took longer, 0.84 us, than q takes to arrive, where only one workgroup
+// runs on a compute unit, and 250 vector instructions a wave beside others.)
+struct IdftTab { uint32_t split[4][64][4]; float full[4][64][4]; };
+
+constexpr IdftTab make_idft_tab() {
+  IdftTab tab{};
+  for (int n = 0; n < 4; ++n)
+    for (int lane = 0; lane < 64; ++lane) {
+      const int kb = lane >> 4, t = 16 * (n & 1) + (lane & 15);
+      float w[8] = {};
+      for (int i = 0; i < 8; ++i) {
+        const int k = 4 * kb + (i & 3);
+        w[i] = i < 4 ? (k == 0 ? 0.5f : cos32(k * t)) : k == 0 ? ((t & 1) ? -0.5f : 0.5f) : -cos32(k * t + 24);
+        const _Float16 hi = (_Float16)w[i];
+        const _Float16 v = (n >> 1) ? (_Float16)(w[i] - (float)hi) : hi;
+        tab.split[n][lane][i >> 1] |= (uint32_t)__builtin_bit_cast(uint16_t, v) << (16 * (i & 1));
+      }
+      for (int i = 0; i < 4; ++i) tab.full[n][lane][i] = w[4 * (n >> 1) + i] * 0.125f;
+    }
+  return tab;
+}
+
+static __device__ const __align__(256) IdftTab kIdftTab = make_idft_tab();
 
 // SAL: 0 no protected tokens, 1 protected rows in fp16, 2 protected rows as 2-bit records.
 // FFT: normal key channels coded by Eq. 5 (true) or by Eq. 4 at 1 bit on the tokens (false);
@@ -338,9 +369,28 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   };
   int p = p_begin;
 
-  // ---------------- set-up: q and the channel permutation go straight to LDS (wave 0 asks for
+  // What the wave has to know of its protected tokens, asked for in front of the transfers and looked at behind
+  // the first barrier (behind the transfers, with a wait at once, it held up the rows' request by 0.4 us)
+  uint32_t rank0 = 0, rank1 = 0, mask1 = 0, mk0 = 0, mk1 = 0, mk2 = 0, mk3 = 0;
+  if (SAL != 0) {
+    const cu32* rk = (const cu32*)a.vrank + (size_t)b * a.ngc;
+    const cu32* mk = (const cu32*)a.vmask + (size_t)b * a.ngc;
+    const int last = a.ng - 1, g0 = 2 * p_begin, g1 = max(0, min(2 * p_end - 1, last));
+    rank0 = rk[min(g0, last)]; rank1 = rk[g1]; mask1 = mk[g1];
+    mk0 = mk[min(g0, last)]; mk1 = mk[min(g0 + 1, last)];
+    mk2 = mk[min(g0 + 2, last)]; mk3 = mk[min(g0 + 3, last)];
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
+  // ---------------- set-up: the inverse-DFT operands (1 KB each wave), q and the channel permutation go straight to LDS (wave 0 asks for
   // them), the first pair's key records are requested right behind them, and only the
   // former are waited for: the operands are built while the records are on their way
+  {
+    const uint32_t at = lane16;
+    asm volatile(VIDKV_DMA("%0", "%1", "%2", "0")
+                 :: "s"((uint32_t)reinterpret_cast<uintptr_t>(&w_tab[0][0]) + 1024u * wave), "v"(at),
+                    "s"(reinterpret_cast<const uint8_t*>(&kIdftTab) + (FULL ? offsetof(IdftTab, full) : 0) + 1024 * wave) : "memory", "m0");
+  }
   if (wave == 0) {
     const uint8_t* qsrc = reinterpret_cast<const uint8_t*>(a.q + ((long long)b * a.Hq + kvh * R) * D);
     const uint32_t q_lds = (uint32_t)reinterpret_cast<uintptr_t>(pre_s);
@@ -360,22 +410,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   }
   fetch_keys(p, 0, p < p_end);
   fetch_values(p, 0, p < p_end && a.early);
-  // (these loads are waited for all together: behind the transfers' requests)
-  if ((SAL != 0) && p_begin < p_end) {
-    const size_t g0 = (size_t)b * a.ngc + 2 * p_begin, g1 = (size_t)b * a.ngc + min(2 * p_end, a.ng) - 1;
-    rb = (int)((const cu32*)a.vrank)[g0];
-    rk_end = (int)((const cu32*)a.vrank)[g1] + __popc(((const cu32*)a.vmask)[g1]);
-    if (SAL == 2) {                          // batches are whole records
-      lfirst = lcnt = rb & 31;
-      rb &= ~31;
-    }
-  }
-  if ((SAL != 0)) {
-    load_masks(p, sm0c, sm1c);
-    load_masks(p + 1, sm0n, sm1n);
-  }
-  // ---------------- the expansion table of the value operands, the inverse-DFT operands
-  // (behind the first requests, whose latency they fill)
+  // ---------------- the expansion table of the value operands (behind the first requests, whose latency it fills)
   {
     uint32_t h[4];
 #pragma unroll
@@ -384,53 +419,29 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       h[i] = (f & 1u) ? ((f & 2u) ? 0x8000u : 0u) | (FULL ? 0x3F80u : 0x3C00u) : 0u;
     }
     t_trit[tid] = uint2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
-    // 16 * (inverse real DFT matrix) as fp16 hi + lo parts: row t = 16 mt + x, k-slot (kb, i):
-    // i < 4 -> Re X[4kb+i], i >= 4 -> Im X[4kb+i-4] (Re X[16] when that index is 0)
-    const int wl = tid & 63, wmt = (tid >> 6) & 1, wlo = tid >> 7;
-    const int wt = 16 * wmt + (wl & 15), wkb = wl >> 4;
-    // cos(2 pi j / 32) from the first-octant constants by the symmetries (no memory access, whose
-    // latency would come on top of the first transfers')
-    auto cos_rt = [](int j) -> float {
-      j &= 31;
-      if (j > 16) j = 32 - j;
-      const bool neg = j > 8;
-      const int i = neg ? 16 - j : j;
-      float v = cos32(0);
-      v = i == 1 ? cos32(1) : v; v = i == 2 ? cos32(2) : v; v = i == 3 ? cos32(3) : v;
-      v = i == 4 ? cos32(4) : v; v = i == 5 ? cos32(5) : v; v = i == 6 ? cos32(6) : v;
-      v = i == 7 ? cos32(7) : v; v = i == 8 ? 0.0f : v;
-      return neg ? -v : v;
-    };
-    auto idft16 = [&](int i) -> float {
-      const int k = 4 * wkb + (i & 3);
-      if (i < 4) return (k == 0) ? 0.5f : cos_rt(k * wt);
-      return (k == 0) ? ((wt & 1) ? -0.5f : 0.5f) : -cos_rt(k * wt + 24);
-    };
-    if (FULL) {
-      // 2 * the matrix in fp32, row t (those below 16 are used), k-slots i of the Re half (wlo = 0) or the Im half
-      f4 W;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) W[i] = idft16(4 * wlo + i) * 0.125f;
-      w_tab[2 * wlo + wmt][wl] = __builtin_bit_cast(u32x4, W);
-    } else {
-      Op W;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float w = idft16(i);
-        const _Float16 hi = (_Float16)w;
-        W.v[i] = wlo ? (_Float16)(w - (float)hi) : hi;
-      }
-      w_tab[2 * wlo + wmt][wl] = W.q;
-    }
   }
 
-  if (wave == 0) {
-    if (p < p_end && a.early) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NDMA_K + NDMA_V) : "memory");
-    else if (p < p_end) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NDMA_K) : "memory");
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  }
+  // the inverse-DFT operands, q and the permutation have landed: at least this many transfers were asked for later
+  if (p < p_end && a.early) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NDMA_K + NDMA_V) : "memory");
+  else if (p < p_end) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NDMA_K) : "memory");
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (SAL != 0) fetch_rows();
+  if (SAL != 0) {
+    if (p_begin < p_end) {
+      rb = (int)rank0;
+      rk_end = (int)rank1 + __popc(mask1);
+      if (SAL == 2) {                        // batches are whole records
+        lfirst = lcnt = rb & 31;
+        rb &= ~31;
+      }
+      sm0c = mk0;
+      sm1c = 2 * p + 1 < a.ng ? mk1 : 0u;
+    }
+    if (p_begin + 1 < p_end) {
+      sm0n = mk2;
+      sm1n = 2 * p + 3 < a.ng ? mk3 : 0u;
+    }
+  }
   const bool hv = hcol < R;
   const _Float16* qrow = &qs[hv ? hcol : 0][0];
   const uint32_t qswz = hv ? hcol * 0x10101010u : 0u;        // (four channels' numbers at a time)
@@ -942,12 +953,14 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   // online softmax of the pair's scores: updates m_run, l_run (and rescales the running
   // sums and the listed probabilities when the maximum is raised), leaves the packed
   // probabilities in pp and, when the pair has protected tokens, stages them at stg as [token][head]
-  auto softmax = [&](const f4 (&S)[2], float cst, bool v1ok, bool stage_pl, uint8_t* stg) {
+  // (first: no score came before, there is nothing to rescale)
+  auto softmax = [&](auto first_c, const f4 (&S)[2], float cst, bool v1ok, bool stage_pl, uint8_t* stg) {
+    constexpr bool FIRST = decltype(first_c)::value;
     // t = score - running maximum, in the exp2 domain, for my column at token slot i
     // (i < 4: token 4kb+i, else 16+4kb+i-4); a column without a group gets -inf
     const bool dead = par && !v1ok;
     const float c0 = dead ? -INFINITY : -cst * sc2;
-    float c1 = c0 - m_run;
+    float c1 = FIRST ? c0 : c0 - m_run;
     float t[8];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -957,7 +970,12 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     // The running maximum is raised lazily: only when some score exceeds it by more than 8
     // (p stays below 2^8), which needs no cross-lane traffic in the common case.
     float mx = fmaxf(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3])), fmaxf(fmaxf(t[4], t[5]), fmaxf(t[6], t[7])));
-    if (__any(mx > 8.0f || m_run == -INFINITY)) {
+    if (FIRST) {
+      const float smax = swap_max16(swap_max32(mx)), m_new = fmaxf(smax, from_xor8(smax));
+#pragma unroll
+      for (int i = 0; i < 8; ++i) t[i] -= m_new;
+      m_run = m_new;
+    } else if (__any(mx > 8.0f || m_run == -INFINITY)) {
       // true scores again; maximum over the 4 k-blocks and the 2 parities of the head
       float smax;
       if (m_run == -INFINITY) {
@@ -974,7 +992,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       }
       smax = swap_max32(smax);
       smax = swap_max16(smax);
-      smax = fmaxf(smax, __shfl_xor(smax, 8, 64));
+      smax = fmaxf(smax, from_xor8(smax));
       const float m_new = fmaxf(m_run, smax);
       const float al = (m_run == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(m_run - m_new);
       const float shift = (m_run == -INFINITY) ? -m_new : m_run - m_new;
@@ -1068,10 +1086,13 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     __builtin_amdgcn_sched_barrier(0);
     fetch_keys(p + PSTEP, KS ^ 1, p + PSTEP < p_end);
     fetch_values(p, KS, !FIRST || !a.early);             // (early: requested at the start)
+    // (the first rows here: in front of the operands of q, whose LDS reads then wait for the transfer, they cost
+    // 0.4 us, at the end of the step 0.3)
+    if (SAL != 0 && FIRST) fetch_rows();
     f4 S[2];
     float cst;
     scores_and_values(ks_c, std::true_type{}, std::integral_constant<bool, !FIRST>{}, hop, S, cst);
-    softmax(S, cst, v1ok, (sm0c | sm1c) != 0, &ring[wave][0] + KS * 2 * KREC);
+    softmax(first_c, S, cst, v1ok, (sm0c | sm1c) != 0, &ring[wave][0] + KS * 2 * KREC);
     if ((SAL != 0)) {
       sm0v = sm0c; sm1v = sm1c;
       sm0c = sm0n; sm1c = sm1n;
@@ -1119,7 +1140,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   // l: 4 k-blocks and 2 parities of each head
   l_run = swap_sum32(l_run);
   l_run = swap_sum16(l_run);
-  l_run += __shfl_xor(l_run, 8, 64);
+  l_run += from_xor8(l_run);
   // o: rows 4kb+i; the parity 1 rows of a head live 32 lanes away from its parity 0 rows.
   // One lane-half swap of the register pair (tile m, tile m + 4) and one addition leave the
   // sums of tile m in lanes 0..31 and those of tile m + 4 in lanes 32..63.
