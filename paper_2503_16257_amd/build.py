@@ -1,15 +1,18 @@
-"""Build libvidkv.so (gfx950) in-tree with hipcc.  `python -m paper_2503_16257_amd.build`."""
+"""Build libvidkv.so (gfx950, hipcc) and the binding's native call layer (host, g++) in-tree.
+`python -m paper_2503_16257_amd.build`."""
 from __future__ import annotations
 
 import concurrent.futures as cf
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libvidkv.so")
+MARSHAL = os.path.join(HERE, "vidkv_marshal.so")
 
 SOURCES = ["vidkv_api.hip", "quant_keys.hip", "quant_keys_mfma.hip", "quant_values.hip",
            "quant_values_enc.hip", "decode_attn.hip", "decode_attn_mfma.hip", "decode_attn_mfma_b.hip",
@@ -43,16 +46,32 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_marshal() -> None:
+    """csrc/marshal.cpp: a CPython extension that reads torch tensors (host code, no device code)."""
+    import torch
+    t = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-I{sysconfig.get_paths()['include']}",
+           "-isystem", f"{t}/include", "-isystem", f"{t}/include/torch/csrc/api/include",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL,
+           f"-L{t}/lib", "-ltorch_python", "-ltorch_cpu", "-lc10", f"-Wl,-rpath,{t}/lib"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on marshal.cpp:\n{r.stderr}")
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with cf.ThreadPoolExecutor(max_workers=8) as ex:
+        marshal = ex.submit(_build_marshal)
         objs = list(ex.map(_compile, SOURCES))
+        marshal.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stderr}")
     if verbose:
-        print(f"built {LIB}")
+        print(f"built {LIB} and {MARSHAL}")
     return LIB
 
 
