@@ -98,7 +98,11 @@ __device__ __forceinline__ void put_sign_words(uint8_t* words, uint32_t lo, uint
 // EXTRA: rows of the grid that do something else of the same call, 1: from row x_rows on, code the
 // protected value rows (2 bits), 2: the first x_rows, the value coding pass (a flush: both blocks are
 // small, one launch).
-template <int NA8T, bool FFT, int EXTRA>
+// SPLIT: one group per workgroup, its tiles shared out among the four waves (and a flush's values likewise), for
+// calls that leave compute units idle anyway: a group's tiles one after another are then most of the kernel
+// after the first load.  (Whole calls: one head x 1568 tokens 18.4 us, 17.0 so; 28 flushes of 4 heads x 128 tokens
+// 119 against 113.  The value pass of a prefill shared out likewise gains nothing beside its channel selection.)
+template <int NA8T, bool FFT, int EXTRA, bool SPLIT>
 __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restrict__ K,
                                                             const uint8_t* __restrict__ perm_g,
                                                             int T, int ng, int n_a_rt, int krec,
@@ -114,7 +118,7 @@ __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restr
     return;
   }
   if (EXTRA == 2 && (int)blockIdx.y < x_rows) {
-    v_encode_part<true>(ve.V, ve.T, ve.ng, ve.B, ve.H, ve.n_s, ve.gamma, ve.gpb, ve.ngc, ve.g_out0, ve.mask, ve.rank,
+    v_encode_part<true, SPLIT>(ve.V, ve.T, ve.ng, ve.B, ve.H, ve.n_s, ve.gamma, ve.gpb, ve.ngc, ve.g_out0, ve.mask, ve.rank,
                         ve.rec_out, ve.rows_out, ve.mask, ve.rank, ve.mark_rank, blockIdx.x, blockIdx.y, tile4);
     return;
   }
@@ -133,26 +137,31 @@ __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restr
 
   // the first tile is requested before anything else so that its latency
   // overlaps the set-up below
-  const int g = blockIdx.x * 4 + wave;               // one group per wave: see launch_k_encode
-  if (g >= ng) return;                               // (no barrier in this kernel: everything is per wave)
+  const int g = SPLIT ? blockIdx.x : blockIdx.x * 4 + wave;
+  if (g >= ng) return;                               // (unless SPLIT there is no barrier below: everything is per wave)
+  const int slot = SPLIT ? 0 : wave;                 // which tile and record buffer
   const u32x4* head = K + hd * (long long)T * 16;
 
   // coalesced tile load: lane reads 16 bytes of row (lane >> 4) + 4 i, i = 0..7
-  u32x4 pre[8];
+  constexpr int NPRE = SPLIT ? 2 : 8;                // SPLIT: my wave's rows are 8 wave ..
+  const int row0 = SPLIT ? 8 * wave : 0;
+  u32x4 pre[NPRE];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) pre[i] = __builtin_nontemporal_load(head + (long long)g * G * 16 + lane + 64 * i);
+  for (int i = 0; i < NPRE; ++i) pre[i] = __builtin_nontemporal_load(head + ((long long)g * G + row0) * 16 + lane + 64 * i);
   __builtin_amdgcn_sched_barrier(0);                 // (these first, and their first use behind the set-up: 128.2 us against 127.0)
 
   // Channel tile j: anomalous tiles first (16 anomalous channels each, in PERM
   // order), then normal tiles.  My column's channel in every tile, as a byte
   // offset inside a token row (an absent column reads channel 0 and is ignored).
-  int chofs[ENC_MAXT];
+  constexpr int NMY = SPLIT ? (ENC_MAXT + 3) / 4 : ENC_MAXT;
+  int chofs[NMY];
 #pragma unroll
-  for (int j = 0; j < ENC_MAXT; ++j) {
+  for (int jj = 0; jj < NMY; ++jj) {
+    const int j = SPLIT ? 4 * jj + wave : jj;
     const bool an = j < NTa;
     const int off = an ? 16 * j + x16 : 16 * (j - NTa) + x16;
     const bool valid = j < NT && (an ? off < n_a : off < n_n);
-    chofs[j] = valid ? 2 * (int)perm_g[hd * D + (an ? off : n_a + off)] : 0;
+    chofs[jj] = valid ? 2 * (int)perm_g[hd * D + (an ? off : n_a + off)] : 0;
   }
 
   // DFT operand from the precomputed table: slot x16 of tile tt, k-slots = tokens
@@ -165,7 +174,7 @@ __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restr
         F[tt][part].q = *reinterpret_cast<const u32x4*>(&kDftTab.w[tt][part][lane][0]);
   }
 
-  uint8_t* rec8 = reinterpret_cast<uint8_t*>(&recbuf[wave][0]);
+  uint8_t* rec8 = reinterpret_cast<uint8_t*>(&recbuf[slot][0]);
   uint16_t* rec16 = reinterpret_cast<uint16_t*>(rec8);
   const int bits_h = 6 * n_a;                        // half-word offsets inside the record
   const int meta_h = 6 * n_a + 2 * n_n;
@@ -173,21 +182,23 @@ __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restr
   float one = 1.0f;                                  // (a 1 that the compiler does not see)
   asm("" : "+v"(one));
   // my 8 token slots start at row 4*kb (slots 0-3) and 16 + 4*kb (slots 4-7)
-  const uint8_t* tcol = reinterpret_cast<const uint8_t*>(&tile4[wave][0]) + 4 * kb * ENC_ROW;
+  const uint8_t* tcol = reinterpret_cast<const uint8_t*>(&tile4[slot][0]) + 4 * kb * ENC_ROW;
 
   __builtin_amdgcn_sched_barrier(0);
   {
-    uint8_t* wdst = reinterpret_cast<uint8_t*>(&tile4[wave][0]) + kb * ENC_ROW + x16 * 16;
+    uint8_t* wdst = reinterpret_cast<uint8_t*>(&tile4[slot][0]) + (row0 + kb) * ENC_ROW + x16 * 16;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4*>(wdst + 4 * i * ENC_ROW) = pre[i];
+    for (int i = 0; i < NPRE; ++i) *reinterpret_cast<u32x4*>(wdst + 4 * i * ENC_ROW) = pre[i];
   }
+  if (SPLIT) __syncthreads();
 
 #pragma unroll
-  for (int j = 0; j < ENC_MAXT; ++j) {
+  for (int jj = 0; jj < NMY; ++jj) {
+    const int j = SPLIT ? 4 * jj + wave : jj;
     if (j >= NT) break;
     // my column's channel at my 8 token slots: 16-bit LDS loads into register halves
     Op X;
-    const uint8_t* cp = tcol + chofs[j];
+    const uint8_t* cp = tcol + chofs[jj];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int row = (i < 4) ? i : 12 + i;          // relative to row 4*kb
@@ -321,23 +332,28 @@ __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restr
   // ---- the finished record: LDS -> global, 16 bytes per lane
   u32x4* dst = reinterpret_cast<u32x4*>(rec_out + (hd * ngc + g_out0 + g) * (long long)krec);
   const int nch = krec >> 4;
-  if (lane < nch) __builtin_nontemporal_store(recbuf[wave][lane], dst + lane);
-  if (lane + 64 < nch) __builtin_nontemporal_store(recbuf[wave][lane + 64], dst + lane + 64);
+  if (SPLIT) {
+    __syncthreads();
+    if (tid < nch) __builtin_nontemporal_store(recbuf[0][tid], dst + tid);
+  } else {
+    if (lane < nch) __builtin_nontemporal_store(recbuf[wave][lane], dst + lane);
+    if (lane + 64 < nch) __builtin_nontemporal_store(recbuf[wave][lane + 64], dst + lane + 64);
+  }
 }
 
-template <int NA8T, int EXTRA>
+template <int NA8T, int EXTRA, bool SPLIT>
 static void launch_one(bool use_fft, dim3 grid, hipStream_t st, const u32x4* k4, const uint8_t* perm, const Geom& g,
                        const EncodeSpan& sp, uint8_t* rec, int rows, const Protect2Args& p2, const VEncArgs& ve) {
   if (EXTRA == 1) rows = (int)sp.heads;
   if (use_fft)
-    hipLaunchKernelGGL((k_encode_mfma_kernel<NA8T, true, EXTRA>), grid, dim3(256), 0, st, k4, perm, sp.in_tokens, sp.ng,
+    hipLaunchKernelGGL((k_encode_mfma_kernel<NA8T, true, EXTRA, SPLIT>), grid, dim3(256), 0, st, k4, perm, sp.in_tokens, sp.ng,
                        g.n_a, g.krec, g.ngc, sp.g_out0, rec, rows, p2, ve);
   else
-    hipLaunchKernelGGL((k_encode_mfma_kernel<NA8T, false, EXTRA>), grid, dim3(256), 0, st, k4, perm, sp.in_tokens, sp.ng,
+    hipLaunchKernelGGL((k_encode_mfma_kernel<NA8T, false, EXTRA, SPLIT>), grid, dim3(256), 0, st, k4, perm, sp.in_tokens, sp.ng,
                        g.n_a, g.krec, g.ngc, sp.g_out0, rec, rows, p2, ve);
 }
 
-template <int EXTRA>
+template <int EXTRA, bool SPLIT>
 static void launch_any(const Geom& g, const EncodeSpan& sp, int gx, const void* K, uint8_t* packed, bool use_fft,
                        hipStream_t st, int rows, const Protect2Args& p2, const VEncArgs& ve) {
   const dim3 grid(gx, (unsigned)(sp.heads + rows));
@@ -345,14 +361,14 @@ static void launch_any(const Geom& g, const EncodeSpan& sp, int gx, const void* 
   const uint8_t* perm = packed + g.k_perm + sp.head0 * D;
   uint8_t* rec = packed + g.k_rec + (size_t)sp.head0 * g.ngc * g.krec;
   switch (g.n_a) {
-    case 8:  launch_one<1, EXTRA>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
-    case 16: launch_one<2, EXTRA>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
-    case 32: launch_one<4, EXTRA>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
-    case 64: launch_one<8, EXTRA>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
-    case 0: launch_one<0, EXTRA>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
-    case 96: launch_one<12, EXTRA>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
-    case 128: launch_one<16, EXTRA>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
-    default: launch_one<-1, EXTRA>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
+    case 8:  launch_one<1, EXTRA, SPLIT>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
+    case 16: launch_one<2, EXTRA, SPLIT>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
+    case 32: launch_one<4, EXTRA, SPLIT>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
+    case 64: launch_one<8, EXTRA, SPLIT>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
+    case 0: launch_one<0, EXTRA, SPLIT>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
+    case 96: launch_one<12, EXTRA, SPLIT>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
+    case 128: launch_one<16, EXTRA, SPLIT>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
+    default: launch_one<-1, EXTRA, SPLIT>(use_fft, grid, st, k4, perm, g, sp, rec, rows, p2, ve); break;
   }
 }
 
@@ -362,9 +378,16 @@ static void launch_any(const Geom& g, const EncodeSpan& sp, int gx, const void* 
 // 127.9; 28 x 4 x 6272, n_a = 64 108.6 either way.)
 constexpr int K_GPB = 4;
 
+// One group per workgroup: where that leaves no compute unit with more than one workgroup (of 256; more of them than
+// that would only queue up behind their barriers).
+static bool split_groups(long long groups) { return groups <= 256; }
+
 void launch_k_encode(const Geom& g, const EncodeSpan& sp, const void* K, uint8_t* packed,
                      bool use_fft, hipStream_t st) {
-  launch_any<0>(g, sp, (sp.ng + K_GPB - 1) / K_GPB, K, packed, use_fft, st, 0, Protect2Args{}, VEncArgs{});
+  if (split_groups(sp.heads * sp.ng))
+    launch_any<0, true>(g, sp, sp.ng, K, packed, use_fft, st, 0, Protect2Args{}, VEncArgs{});
+  else
+    launch_any<0, false>(g, sp, (sp.ng + K_GPB - 1) / K_GPB, K, packed, use_fft, st, 0, Protect2Args{}, VEncArgs{});
 }
 
 // false: too many heads for one grid, nothing done
@@ -374,7 +397,7 @@ bool launch_k_encode_protect2(const Geom& g, const void* K, uint8_t* packed_K, c
   const EncodeSpan sp{g.T, g.ng, 0, g.nheads, 0};
   const long long gx = (g.ng + K_GPB - 1) / K_GPB, rows = ((p2.total + 3) / 4 + gx - 1) / gx;
   if (g.nheads + rows > 65535) return false;
-  launch_any<1>(g, sp, (int)gx, K, packed_K, g.use_fft, st, (int)rows, p2, VEncArgs{});
+  launch_any<1, false>(g, sp, (int)gx, K, packed_K, g.use_fft, st, (int)rows, p2, VEncArgs{});
   return true;
 }
 
@@ -387,7 +410,10 @@ bool launch_flush_encode(const Geom& g, const EncodeSpan& sp, float gamma, const
   VEncArgs ve = v_encode_args(g, sp, 0, gamma, V, packed_V);
   ve.gpb = K_GPB;                                    // one grid for both
   if (g.n_s > 0) ve.mark_rank = g.n_s;
-  launch_any<2>(g, sp, (sp.ng + K_GPB - 1) / K_GPB, K, packed_K, g.use_fft, st, (int)sp.heads, Protect2Args{}, ve);
+  if (split_groups(2 * sp.heads * sp.ng))
+    launch_any<2, true>(g, sp, sp.ng, K, packed_K, g.use_fft, st, (int)sp.heads, Protect2Args{}, ve);
+  else
+    launch_any<2, false>(g, sp, (sp.ng + K_GPB - 1) / K_GPB, K, packed_K, g.use_fft, st, (int)sp.heads, Protect2Args{}, ve);
   return true;
 }
 

@@ -42,8 +42,8 @@ struct VEncArgs {
 typedef u32x4 EncTile[32 * VENC_ROW / 16];
 
 // The groups of workgroup bx of head hd (256 threads).  MARK: also MASK = 0 and RANK = mark_rank of the
-// groups when mark_rank >= 0 (a flushed block).
-template <bool MARK>
+// groups when mark_rank >= 0 (a flushed block).  SPLIT: group bx alone, a quarter of its channels each wave.
+template <bool MARK, bool SPLIT = false>
 __device__ __forceinline__ void v_encode_part(const u32x4* __restrict__ V, int T, int ng, int B, int H, int n_s,
                                               float gamma, int gpb, int ngc, int g_out0,
                                               const uint32_t* __restrict__ mask, const uint32_t* __restrict__ rank,
@@ -58,28 +58,31 @@ __device__ __forceinline__ void v_encode_part(const u32x4* __restrict__ V, int T
   // tile4: per wave, the group's tile
   // my 8 token slots start at row 4*kb (slots 0-3) and 16 + 4*kb (slots 4-7); my channel
   // of tile m is 16 m + x16
-  const uint8_t* tcol = reinterpret_cast<const uint8_t*>(&tile4[wave][0]) + 4 * kb * VENC_ROW + 2 * x16;
+  const uint8_t* tcol = reinterpret_cast<const uint8_t*>(&tile4[SPLIT ? 0 : wave][0]) + 4 * kb * VENC_ROW + 2 * x16;
 
-  const int g_begin = bx * gpb;
-  const int g_end = min(ng, g_begin + gpb);
+  const int g_begin = SPLIT ? bx : bx * gpb;
+  const int g_end = min(ng, g_begin + (SPLIT ? 1 : gpb));
   const u32x4* head = V + hd * (long long)T * 16;
 
-  u32x4 pre[8];
+  constexpr int NPRE = SPLIT ? 2 : 8;                      // SPLIT: my wave's rows are 8 wave ..
+  const int row0 = SPLIT ? 8 * wave : 0;
+  u32x4 pre[NPRE];
   auto prefetch = [&](int g) {
-    const u32x4* src = head + (long long)g * G * 16 + lane;
+    const u32x4* src = head + ((long long)g * G + row0) * 16 + lane;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) pre[i] = __builtin_nontemporal_load(src + 64 * i);
+    for (int i = 0; i < NPRE; ++i) pre[i] = __builtin_nontemporal_load(src + 64 * i);
   };
-  int g = g_begin + wave;
+  int g = SPLIT ? g_begin : g_begin + wave;
   if (g < g_end) prefetch(g);
 
   for (; g < g_end; g += 4) {
     {
-      uint8_t* wdst = reinterpret_cast<uint8_t*>(&tile4[wave][0]) + kb * VENC_ROW + x16 * 16;
+      uint8_t* wdst = reinterpret_cast<uint8_t*>(&tile4[SPLIT ? 0 : wave][0]) + (row0 + kb) * VENC_ROW + x16 * 16;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4*>(wdst + 4 * i * VENC_ROW) = pre[i];
+      for (int i = 0; i < NPRE; ++i) *reinterpret_cast<u32x4*>(wdst + 4 * i * VENC_ROW) = pre[i];
     }
-    if (g + 4 < g_end) prefetch(g + 4);
+    if (SPLIT) __syncthreads();                            // (the whole workgroup is here: g is its only group)
+    else if (g + 4 < g_end) prefetch(g + 4);
 
     uint32_t m = 0, r0 = 0;
     if (n_s > 0) {
@@ -102,6 +105,7 @@ __device__ __forceinline__ void v_encode_part(const u32x4* __restrict__ V, int T
     uint32_t sc16[4];                          // 8 fp16 scales: tile m in half (m & 1) of sc16[m >> 1]
 #pragma unroll
     for (int mp = 0; mp < 4; ++mp) {
+      if (SPLIT && mp != wave) continue;
       Op X[2];
       float part[2];
 #pragma unroll
@@ -150,11 +154,20 @@ __device__ __forceinline__ void v_encode_part(const u32x4* __restrict__ V, int T
       words[mp] = word;
       sc16[mp] = h2_bits(h2{s16[0], s16[1]});
     }
-    if (MARK && mark_rank >= 0 && hd % H == 0 && lane == 0) {
+    if (MARK && mark_rank >= 0 && hd % H == 0 && lane == 0 && (!SPLIT || wave == 0)) {
       mark_mask[(size_t)b * ngc + g_out0 + g] = 0;
       mark_ranks[(size_t)b * ngc + g_out0 + g] = (uint32_t)mark_rank;
     }
     uint8_t* rec = rec_out + (hd * ngc + g_out0 + g) * (long long)VREC;
+    if (SPLIT) {
+#pragma unroll
+      for (int mp = 0; mp < 4; ++mp)
+        if (mp == wave) {
+          reinterpret_cast<uint32_t*>(rec)[4 * lane + mp] = words[mp];
+          if (kb == 0) reinterpret_cast<uint32_t*>(rec + 1024)[4 * x16 + mp] = sc16[mp];
+        }
+      continue;                                            // (a flushed block has no protected rows)
+    }
     u32x4 wv;
     wv[0] = words[0]; wv[1] = words[1]; wv[2] = words[2]; wv[3] = words[3];
     __builtin_nontemporal_store(wv, reinterpret_cast<u32x4*>(rec) + lane);                 // word (kb, x16, mp) at byte 16 lane + 4 mp

@@ -49,3 +49,24 @@ def test_key_codes(fft, kind, n_a):
     stats = {}
     for hd in range(w.Hkv):
         P.check_keys_head(run, hd, K[0, 0, hd], stats)
+
+
+@pytest.mark.parametrize("fft", [1, 0])
+@pytest.mark.parametrize("n_a", [0, 8, 24, 64, 128])
+@pytest.mark.parametrize("heads", [5, 6])
+def test_groups_shared_out_and_not(heads, n_a, fft):
+    """49 groups a head: 5 heads are coded one group per workgroup, 6 heads one per wave; a flush of 2 groups likewise
+    and, of 6 heads x 22 groups (264 workgroups with the values), one per wave."""
+    import test_gpu_flush as F
+    w = dataclasses.replace(synth.reduced(synth.WORKLOADS["c4_long"], 8), Hkv=heads, Hq=heads, n_anom=n_a, n_salient=0)
+    n = 64 if heads == 5 else 704
+    run = P.GpuRun(w, DEV, use_fft=fft, t_capacity=w.T + n)
+    stats = {}
+    for hd in range(heads):
+        P.check_keys_head(run, hd, synth.key_head(w, hd), stats)
+    Kt, Vt = synth.tail_heads(w, 0, 0, n)
+    run.flush(0, torch.from_numpy(Kt[None]).to(DEV), torch.from_numpy(Vt[None]).to(DEV), n, n)
+    run.advance(n)
+    for h in range(heads):
+        F._check_block(run, h, w.T // 32, Kt[h], Vt[h], stats)
+    P.check_near_budget(stats)
