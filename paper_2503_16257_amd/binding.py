@@ -124,7 +124,8 @@ def lib() -> C.CDLL:
         _bind_torch(torch)
         from . import vidkv_marshal
         vidkv_marshal.bind(*(C.cast(f, vp).value for f in (
-            L.vidkv_decode_attention, L.vidkv_decode_attention_noalloc, L.vidkv_flush_residual)))
+            L.vidkv_decode_attention, L.vidkv_decode_attention_noalloc, L.vidkv_flush_residual)),
+            VidkvParams, VidkvSideStream)
         _native = vidkv_marshal
         _lib = L
     return _lib

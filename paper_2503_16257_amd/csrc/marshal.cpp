@@ -2,9 +2,9 @@
 // Python the checks and pointers of its tensors took 2.5 us of a call whose two launches take 6.
 //
 // What a call does is what binding.py does for it - tensor type, device, contiguity and dtype checked, then the
-// C entry point - for plain torch.Tensor arguments that pass; anything else returns None, and binding.py's own
-// path takes the call and raises what it always raised.  Nothing is kept between calls but the entry points'
-// addresses, which bind() hands over once.
+// C entry point - for plain torch.Tensor arguments that pass and structures of binding.py's own classes; anything
+// else returns None, and binding.py's own path takes the call and raises what it always raised.  Nothing is kept
+// between calls but the entry points' addresses and the two classes, which bind() hands over once.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -17,11 +17,15 @@ namespace {
 decltype(&vidkv_decode_attention) g_decode;
 decltype(&vidkv_decode_attention_noalloc) g_decode_noalloc;
 decltype(&vidkv_flush_residual) g_flush;
+PyTypeObject* g_params_type;         // binding.VidkvParams
+PyTypeObject* g_side_type;           // binding.VidkvSideStream
 
-// Memory of a ctypes structure of exactly `size` bytes.
+// Memory of a ctypes structure of class `type` and exactly `size` bytes (ctypes refuses other objects, whatever
+// buffer they have).
 class Struct {
  public:
-  Struct(PyObject* o, size_t size) {
+  Struct(PyObject* o, PyTypeObject* type, size_t size) {
+    if (!PyObject_TypeCheck(o, type)) return;
     if (PyObject_GetBuffer(o, &view_, PyBUF_SIMPLE) != 0) { PyErr_Clear(); return; }
     held_ = true;
     if ((size_t)view_.len == size) ptr_ = view_.buf;
@@ -96,12 +100,12 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n) {
         !integer(a[7], &cap) || !tensor(a[8], at::kInt, true, &tl) || !tensor(a[9], at::kHalf, true, &out) ||
         !tensor(a[10], at::kByte, false, &ws, &wsb))
       Py_RETURN_NONE;
-    const Struct p(a[0], sizeof(vidkv_params));
+    const Struct p(a[0], g_params_type, sizeof(vidkv_params));
     if (!p.get()) Py_RETURN_NONE;
     vidkv_side_stream side;
     const bool has_side = a[13] != Py_None;
     if (has_side) {
-      const Struct s(a[13], sizeof(side));
+      const Struct s(a[13], g_side_type, sizeof(side));
       if (!s.get()) Py_RETURN_NONE;
       side = *static_cast<const vidkv_side_stream*>(s.get());
     }
@@ -127,7 +131,7 @@ PyObject* decode_noalloc(PyObject*, PyObject* const* a, Py_ssize_t n) {
         !tensor(a[4], at::kByte, true, &pv) || !tensor(a[5], at::kHalf, true, &kt) || !tensor(a[6], at::kHalf, true, &vt) ||
         !integer(a[7], &cap) || !tensor(a[8], at::kInt, true, &tl) || !tensor(a[9], at::kHalf, true, &out))
       Py_RETURN_NONE;
-    const Struct p(a[0], sizeof(vidkv_params));
+    const Struct p(a[0], g_params_type, sizeof(vidkv_params));
     if (!p.get()) Py_RETURN_NONE;
     const int got = stream_handle(a[10], a[11], &stream);
     if (got < 0) return nullptr;
@@ -152,7 +156,7 @@ PyObject* flush(PyObject*, PyObject* const* a, Py_ssize_t n) {
         !integer(a[4], &cap) || !integer(a[5], &nf) || !tensor(a[6], at::kByte, false, &pk, &kb) ||
         !tensor(a[7], at::kByte, false, &pv, &vb))
       Py_RETURN_NONE;
-    const Struct p(a[0], sizeof(vidkv_params));
+    const Struct p(a[0], g_params_type, sizeof(vidkv_params));
     if (!p.get()) Py_RETURN_NONE;
     const int got = stream_handle(a[8], a[9], &stream);
     if (got < 0) return nullptr;
@@ -165,13 +169,19 @@ PyObject* flush(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
-// (addresses of vidkv_decode_attention, vidkv_decode_attention_noalloc, vidkv_flush_residual)
+// (addresses of vidkv_decode_attention, vidkv_decode_attention_noalloc, vidkv_flush_residual; the classes of
+// vidkv_params and vidkv_side_stream)
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
   void* f[3];
-  if (n != 3 || !handle(a[0], &f[0]) || !handle(a[1], &f[1]) || !handle(a[2], &f[2])) {
-    PyErr_SetString(PyExc_TypeError, "bind: three addresses");
+  if (n != 5 || !handle(a[0], &f[0]) || !handle(a[1], &f[1]) || !handle(a[2], &f[2]) || !PyType_Check(a[3]) ||
+      !PyType_Check(a[4])) {
+    PyErr_SetString(PyExc_TypeError, "bind: three addresses and two classes");
     return nullptr;
   }
+  Py_INCREF(a[3]);                                     // (kept, with the module, for as long as the process)
+  Py_INCREF(a[4]);
+  g_params_type = reinterpret_cast<PyTypeObject*>(a[3]);
+  g_side_type = reinterpret_cast<PyTypeObject*>(a[4]);
   g_decode = reinterpret_cast<decltype(g_decode)>(f[0]);
   g_decode_noalloc = reinterpret_cast<decltype(g_decode_noalloc)>(f[1]);
   g_flush = reinterpret_cast<decltype(g_flush)>(f[2]);

@@ -1,11 +1,28 @@
 """The native call layer takes plain arguments only and leaves every refusal to the Python path: the errors are
-the same with and without it, and no exception of C++ leaves it (CPU: nothing here reaches a launch)."""
+the same with and without it, and no exception of C++ leaves it (nothing here reaches a launch)."""
 import ctypes as C
+import types
 
 import pytest
 import torch
 
 from paper_2503_16257_amd import binding as vk
+
+PARAM_BYTES, SIDE_BYTES = C.sizeof(vk.VidkvParams), C.sizeof(vk.VidkvSideStream)
+
+
+class ForeignParams(C.Structure):
+    _fields_ = [("words", C.c_int32 * (PARAM_BYTES // 4))]
+
+
+class ForeignSide(C.Structure):
+    _fields_ = [("words", C.c_void_p * (SIDE_BYTES // 8))]
+
+
+FOREIGN_PARAMS = [bytes(PARAM_BYTES), bytearray(PARAM_BYTES), memoryview(bytes(PARAM_BYTES)), (C.c_int32 * (PARAM_BYTES // 4))(),
+                  ForeignParams()]
+FOREIGN_SIDES = [bytes(SIDE_BYTES), bytearray(SIDE_BYTES), (C.c_void_p * (SIDE_BYTES // 8))(), ForeignSide()]
+REFUSED = (TypeError, C.ArgumentError)                 # what ctypes raises
 
 
 def _args(**kw):
@@ -64,3 +81,43 @@ def test_odd_arguments_are_left_to_the_python_path():
     assert n.decode_attention_noalloc(*null, lambda s: "no handle", None) is None
     with pytest.raises(ZeroDivisionError):
         n.decode_attention_noalloc(*null, lambda s: 1 // 0, None)
+
+
+@pytest.mark.parametrize("foreign", FOREIGN_PARAMS, ids=lambda f: type(f).__name__)
+def test_a_buffer_of_the_size_of_the_parameters_is_refused(foreign):
+    with pytest.raises(REFUSED):
+        vk.decode_attention_noalloc(foreign, 0, None, None, None, None, stream=types.SimpleNamespace(cuda_stream=0))
+    assert vk._native.decode_attention_noalloc(foreign, 0, *[None] * 5, 0, None, None, lambda s: 0, None) is None
+
+
+def test_a_structure_derived_from_the_parameters_is_taken_where_it_adds_nothing():
+    class Same(vk.VidkvParams):
+        pass
+
+    class Longer(vk.VidkvParams):
+        _fields_ = [("more", C.c_int32)]
+
+    vk.lib()
+    args = (0, *[None] * 5, 0, None, None, lambda s: 0, None)
+    assert vk._native.decode_attention_noalloc(Same(), *args) == vk.EINVAL
+    assert vk._native.decode_attention_noalloc(Longer(), *args) is None
+    # (the Python path takes it, as a pointer to its first part)
+    with pytest.raises(vk.VidkvError):
+        vk.decode_attention_noalloc(Longer(), 0, None, None, None, None, stream=types.SimpleNamespace(cuda_stream=0))
+
+
+@pytest.mark.gpu
+def test_foreign_structures_are_refused_with_tensors_in_place():
+    """Parameters and side stream of each call, everything else in order (no launch: refused in front of the library)."""
+    z = lambda n, t: torch.zeros(n, dtype=t, device="cuda:0")
+    p = vk.make_params(1, 1, 1, 2, 32, 16, 0, t_capacity=64)
+    q, tail, pk = z((1, 2, 128), torch.float16), z((1, 1, 32, 128), torch.float16), z(vk.packed_keys_bytes(p), torch.uint8)
+    pv, ws = z(vk.packed_values_bytes(p), torch.uint8), z(vk.workspace_bytes(p, 2), torch.uint8)
+    for f in FOREIGN_PARAMS:
+        for call in (lambda: vk.decode_attention(f, 0, q, pk, pv, q, ws), lambda: vk.decode_attention_noalloc(f, 0, q, pk, pv, q),
+                     lambda: vk.flush_residual(f, 0, tail, tail, 32, 32, pk, pv)):
+            with pytest.raises(REFUSED):
+                call()
+    for f in FOREIGN_SIDES:
+        with pytest.raises(REFUSED):
+            vk.decode_attention(p, 0, q, pk, pv, q, ws, side=types.SimpleNamespace(c=f))
