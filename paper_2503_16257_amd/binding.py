@@ -6,17 +6,19 @@ stream, and turns a non-zero status into an exception.  If the library has not
 been built the first call raises: there is no fallback.  The calls that are made
 once per layer go through vidkv_marshal.so (csrc/marshal.cpp), which does the same
 natively for plain tensors that pass the checks and leaves everything else to
-this module.
+this module; where it is missing or was built for another Python or torch, this
+module takes every call.
 """
 from __future__ import annotations
 
 import ctypes as C
+import logging
 import math
 import os
+import sys
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libvidkv.so")
-MARSHAL_PATH = os.path.join(_HERE, "vidkv_marshal.so")
 
 OK, EINVAL, ESHAPE, ENOSPACE, EHIP = 0, 1, 2, 3, 4
 
@@ -72,10 +74,9 @@ def lib() -> C.CDLL:
     """Load the shared library (once).  Raises if it is not built."""
     global _lib, _native
     if _lib is None:
-        for path in (LIB_PATH, MARSHAL_PATH):
-            if not os.path.exists(path):
-                raise RuntimeError(
-                    f"{path} is missing: build it with `python -m paper_2503_16257_amd.build`")
+        if not os.path.exists(LIB_PATH):
+            raise RuntimeError(
+                f"{LIB_PATH} is missing: build it with `python -m paper_2503_16257_amd.build`")
         # PyTorch ships its own HIP runtime; it must be in the process before this library is
         # loaded, so that both resolve to that one copy.  Loaded the other way round the
         # library registers its kernels with a second runtime, and every launch on a torch
@@ -122,13 +123,33 @@ def lib() -> C.CDLL:
         L.vidkv_abi_version.argtypes = []
         L.vidkv_abi_version.restype = C.c_int
         _bind_torch(torch)
-        from . import vidkv_marshal
-        vidkv_marshal.bind(*(C.cast(f, vp).value for f in (
-            L.vidkv_decode_attention, L.vidkv_decode_attention_noalloc, L.vidkv_flush_residual)),
-            VidkvParams, VidkvSideStream)
-        _native = vidkv_marshal
+        _native = _load_native(L)
         _lib = L
     return _lib
+
+
+def native_tag() -> str:
+    """What a build of the native call layer belongs to: it reads CPython's and torch's structures."""
+    import torch
+    return f"{sys.implementation.cache_tag} torch {torch.__version__}"
+
+
+def _load_native(L):
+    """The native call layer, or None: then every call takes the Python path."""
+    try:
+        from . import vidkv_marshal as m
+        built_for = getattr(m, "built_for", None)
+        if built_for != native_tag():
+            raise ImportError(f"it was built for {built_for}, this is {native_tag()}")
+    except ImportError as e:
+        logging.getLogger(__name__).warning(
+            "vidkv_marshal.so is not used (%s): each call costs a few us more on the host; build it with "
+            "`python -m paper_2503_16257_amd.build`", e)
+        return None
+    m.bind(*(C.cast(f, C.c_void_p).value for f in (
+        L.vidkv_decode_attention, L.vidkv_decode_attention_noalloc, L.vidkv_flush_residual)),
+        VidkvParams, VidkvSideStream)
+    return m
 
 
 def make_params(n_layers, batch, n_kv_heads, n_q_heads, t_quant, n_anom, n_salient,
@@ -239,7 +260,7 @@ def decode_attention(p: VidkvParams, layer: int, q, packed_K, packed_V, out, wor
     """vidkv_decode_attention: one decode step of one layer -> out [B,Hq,128] fp16.
     `side`: a SideStream for the residual-token kernel of a large block, or None (in line)."""
     L = _lib or lib()
-    if stages is None:
+    if stages is None and _native is not None:
         st = _native.decode_attention(p, layer, q, packed_K, packed_V, K_tail, V_tail, tail_capacity, tail_len, out,
                                       workspace, _stream, stream, None if side is None else side.c)
         if st is not None:
@@ -265,10 +286,11 @@ def decode_attention_noalloc(p: VidkvParams, layer: int, q, packed_K, packed_V, 
                              V_tail=None, tail_capacity: int = 0, tail_len=None, stream=None) -> None:
     """vidkv_decode_attention_noalloc: the decode step without a workspace argument."""
     L = _lib or lib()
-    st = _native.decode_attention_noalloc(p, layer, q, packed_K, packed_V, K_tail, V_tail, tail_capacity, tail_len, out,
-                                          _stream, stream)
-    if st is not None:
-        return _check(st, "vidkv_decode_attention_noalloc")
+    if _native is not None:
+        st = _native.decode_attention_noalloc(p, layer, q, packed_K, packed_V, K_tail, V_tail, tail_capacity, tail_len, out,
+                                              _stream, stream)
+        if st is not None:
+            return _check(st, "vidkv_decode_attention_noalloc")
     _check(L.vidkv_decode_attention_noalloc(
         C.byref(p), layer, _ptr(q, _f16, "q"), _ptr(packed_K, _u8, "packed_K"),
         _ptr(packed_V, _u8, "packed_V"), _ptr(K_tail, _f16, "K_tail"),
@@ -294,9 +316,10 @@ def flush_residual(p: VidkvParams, layer: int, K_tail, V_tail, tail_capacity: in
                    packed_K, packed_V, stream=None) -> None:
     """vidkv_flush_residual: code the first n_flush residual tokens of one layer and append them."""
     L = _lib or lib()
-    st = _native.flush_residual(p, layer, K_tail, V_tail, tail_capacity, n_flush, packed_K, packed_V, _stream, stream)
-    if st is not None:
-        return _check(st, "vidkv_flush_residual")
+    if _native is not None:
+        st = _native.flush_residual(p, layer, K_tail, V_tail, tail_capacity, n_flush, packed_K, packed_V, _stream, stream)
+        if st is not None:
+            return _check(st, "vidkv_flush_residual")
     _check(L.vidkv_flush_residual(
         C.byref(p), layer, _ptr(K_tail, _f16, "K_tail"), _ptr(V_tail, _f16, "V_tail"),
         tail_capacity, n_flush, _ptr(packed_K, _u8, "packed_K"), _nbytes(packed_K),

@@ -1,5 +1,5 @@
-"""Build libvidkv.so (gfx950, hipcc) and the binding's native call layer (host, g++) in-tree.
-`python -m paper_2503_16257_amd.build`."""
+"""Build libvidkv.so (gfx950, hipcc) and, where there are a g++ and the headers of Python and torch, the binding's
+native call layer (host) in-tree.  `python -m paper_2503_16257_amd.build`."""
 from __future__ import annotations
 
 import concurrent.futures as cf
@@ -49,10 +49,11 @@ def _compile(src: str) -> str:
 def _build_marshal() -> None:
     """csrc/marshal.cpp: a CPython extension that reads torch tensors (host code, no device code)."""
     import torch
+    from .binding import native_tag
     t = os.path.dirname(torch.__file__)
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-I{sysconfig.get_paths()['include']}",
            "-isystem", f"{t}/include", "-isystem", f"{t}/include/torch/csrc/api/include",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DVIDKV_BUILT_FOR="{native_tag()}"',
            os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL,
            f"-L{t}/lib", "-ltorch_python", "-ltorch_cpu", "-lc10", f"-Wl,-rpath,{t}/lib"]
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -65,13 +66,20 @@ def build(verbose: bool = True) -> str:
     with cf.ThreadPoolExecutor(max_workers=8) as ex:
         marshal = ex.submit(_build_marshal)
         objs = list(ex.map(_compile, SOURCES))
+    built = [LIB]
+    try:
         marshal.result()
+        built.append(MARSHAL)
+    except (ImportError, OSError, RuntimeError) as e:          # the binding works without it
+        if os.path.exists(MARSHAL):
+            os.remove(MARSHAL)                                 # (nor is one of an older source left)
+        print(f"vidkv_marshal.so was not built, calls are marshalled in Python: {e}", file=sys.stderr)
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stderr}")
     if verbose:
-        print(f"built {LIB} and {MARSHAL}")
+        print(f"built {' and '.join(built)}")
     return LIB
 
 

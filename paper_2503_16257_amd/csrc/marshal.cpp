@@ -198,4 +198,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "vidkv_marshal", nullptr, -1, metho
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit_vidkv_marshal(void) { return PyModule_Create(&module); }
+// built_for: the Python and the torch that this was compiled against (binding.py uses it with no other)
+PyMODINIT_FUNC PyInit_vidkv_marshal(void) {
+  PyObject* m = PyModule_Create(&module);
+  if (m && PyModule_AddStringConstant(m, "built_for", VIDKV_BUILT_FOR) != 0) Py_CLEAR(m);
+  return m;
+}

@@ -1,12 +1,17 @@
 """The native call layer takes plain arguments only and leaves every refusal to the Python path: the errors are
 the same with and without it, and no exception of C++ leaves it (nothing here reaches a launch)."""
 import ctypes as C
+import importlib
+import os
+import shutil
+import sys
 import types
 
 import pytest
 import torch
 
 from paper_2503_16257_amd import binding as vk
+from paper_2503_16257_amd import build as B
 
 PARAM_BYTES, SIDE_BYTES = C.sizeof(vk.VidkvParams), C.sizeof(vk.VidkvSideStream)
 
@@ -121,3 +126,64 @@ def test_foreign_structures_are_refused_with_tensors_in_place():
     for f in FOREIGN_SIDES:
         with pytest.raises(REFUSED):
             vk.decode_attention(p, 0, q, pk, pv, q, ws, side=types.SimpleNamespace(c=f))
+
+
+@pytest.mark.parametrize("layer", ["missing", "not loadable", "of another torch", "of older source"])
+def test_without_the_layer_every_call_takes_the_python_path(layer, tmp_path, monkeypatch):
+    """A package that holds the library and no native layer that fits: everything works as it did before there was one."""
+    name = "vidkv_copy_" + layer.replace(" ", "_")
+    d = tmp_path / name
+    d.mkdir()
+    here = os.path.dirname(vk.__file__)
+    shutil.copy(os.path.join(here, "binding.py"), d)
+    (d / "__init__.py").write_text("")
+    os.symlink(vk.LIB_PATH, d / "libvidkv.so")
+    if layer == "not loadable":
+        (d / "vidkv_marshal.so").write_bytes(b"no shared object")
+    elif layer != "missing":
+        tag = 'built_for = "cpython-00 torch 0.0"\n' if layer == "of another torch" else ""
+        (d / "vidkv_marshal.py").write_text(tag + "def bind(*a):\n    raise RuntimeError('taken')\n")
+    monkeypatch.syspath_prepend(str(tmp_path))
+    try:
+        v = importlib.import_module(name + ".binding")
+        p = v.make_params(1, 1, 1, 2, 32, 16, 0)
+        assert v.packed_keys_bytes(p) == vk.packed_keys_bytes(vk.make_params(1, 1, 1, 2, 32, 16, 0)) > 0
+        assert v._native is None
+        s = types.SimpleNamespace(cuda_stream=0)
+        with pytest.raises(v.VidkvError, match="invalid argument"):
+            v.decode_attention_noalloc(p, 0, None, None, None, None, stream=s)
+        cpu = torch.zeros((1, 2, 128), dtype=torch.float16)
+        for call in (lambda: v.decode_attention(p, 0, cpu, None, None, None, cpu, stream=s),
+                     lambda: v.decode_attention_noalloc(p, 0, cpu, None, None, None, stream=s),
+                     lambda: v.flush_residual(p, 0, cpu, cpu, 32, 32, cpu, cpu, stream=s)):
+            with pytest.raises(TypeError, match="expected a CUDA tensor"):
+                call()
+    finally:
+        for m in [m for m in sys.modules if m == name or m.startswith(name + ".")]:
+            del sys.modules[m]
+
+
+def test_the_layer_built_here_is_used():
+    vk.lib()
+    assert vk._native is not None and vk._native.built_for == vk.native_tag()
+
+
+def test_the_library_is_built_where_the_layer_cannot_be(tmp_path, monkeypatch, capsys):
+    """No torch or Python headers, no g++: the library alone, and no layer of an older build beside it."""
+    stale = tmp_path / "vidkv_marshal.so"
+    stale.write_bytes(b"")
+    monkeypatch.setattr(B, "MARSHAL", str(stale))
+    monkeypatch.setattr(B, "OBJ", str(tmp_path))
+    monkeypatch.setattr(B, "_compile", lambda src: str(tmp_path / src))
+    ran = []
+
+    def run(cmd, **kw):
+        ran.append(cmd)
+        if cmd[0] == "g++":
+            raise FileNotFoundError("g++")
+        return types.SimpleNamespace(returncode=0, stderr="")
+
+    monkeypatch.setattr(B.subprocess, "run", run)
+    assert B.build(verbose=False) == B.LIB
+    assert [c[0] for c in ran].count("g++") == 1 and len(ran) == 2 and not stale.exists()
+    assert "vidkv_marshal.so" in capsys.readouterr().err
