@@ -89,6 +89,27 @@ __device__ __forceinline__ void put_sign_words(uint8_t* words, uint32_t lo, uint
         uint2{__builtin_amdgcn_perm(hi, lo, 0x05010400u), __builtin_amdgcn_perm(hi, lo, 0x07030602u)};
 }
 
+// lo, nh: min and -max of my column over the 32 tokens, of which X holds 8.  A NaN counts for nothing (a column of
+// nothing else: +infinity, both), so that the other tokens are coded as without it and no code leaves its field.
+// (Eight more vector instructions a tile than with minima that pass a NaN on: 28 layers x 4 heads x 6272 tokens,
+// n_a = 64, whole call: 107.8 us against 107.2; 64 x 4 x 25088, n_a = 32, plain code: 881 against 886.)
+__device__ __forceinline__ void range32(const Op& X, float& lo, float& nh) {
+  const h2 mn2 = __builtin_elementwise_min(__builtin_elementwise_min(X.p[0], X.p[1]), __builtin_elementwise_min(X.p[2], X.p[3]));
+  const h2 mx2 = __builtin_elementwise_max(__builtin_elementwise_max(X.p[0], X.p[1]), __builtin_elementwise_max(X.p[2], X.p[3]));
+  // (against infinity: no NaN from here on, so that the minima across lanes need no canonicalisation)
+  lo = fminf(fminf((float)mn2[0], (float)mn2[1]), INFINITY);
+  nh = fminf(fminf(-(float)mx2[0], -(float)mx2[1]), INFINITY);
+  // both are "min" reductions over the 4 lane groups, so one swap pair serves the two values; a last
+  // swap hands both to every lane
+  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(nh), false, false);
+  const float t = __builtin_elementwise_minimum(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(t), __float_as_uint(t), false, false);
+  const float u = __builtin_elementwise_minimum(__uint_as_float(q[0]), __uint_as_float(q[1]));   // rows 0,1: min; rows 2,3: -max
+  auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(u), __float_as_uint(u), false, false);
+  lo = __uint_as_float(w[0]);
+  nh = __uint_as_float(w[1]);
+}
+
 // NA8T >= 0 fixes n_a = 8 * NA8T at compile time (tile loop fully unrolled);
 // NA8T < 0 takes n_a at run time.  FFT = false codes the normal channels with
 // Eq. 4 at 1 bit on the tokens themselves (the non-FFT 1-bit path of Alg. 3):
@@ -207,30 +228,15 @@ __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restr
 
     if (j < NTa) {
       // ---------------- Eq. 4, 2 bits: z = min, s = (max - min) / 3 over the 32 tokens
-      const h2 mn2 = __builtin_elementwise_minimum(__builtin_elementwise_minimum(X.p[0], X.p[1]),
-                                                   __builtin_elementwise_minimum(X.p[2], X.p[3]));
-      const h2 mx2 = __builtin_elementwise_maximum(__builtin_elementwise_maximum(X.p[0], X.p[1]),
-                                                   __builtin_elementwise_maximum(X.p[2], X.p[3]));
-      // min and -max over the 4 lane groups: both are "min" reductions, so one
-      // swap pair serves the two values; a last swap hands both to every lane
-      float lo_f = fminf((float)mn2[0], (float)mn2[1]);
-      float nh_f = -fmaxf((float)mx2[0], (float)mx2[1]);
-      {
-        auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo_f), __float_as_uint(nh_f), false, false);
-        const float t = __builtin_elementwise_minimum(__uint_as_float(r[0]), __uint_as_float(r[1]));
-        auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(t), __float_as_uint(t), false, false);
-        const float u = __builtin_elementwise_minimum(__uint_as_float(q[0]), __uint_as_float(q[1]));   // rows 0,1: min; rows 2,3: -max
-        auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(u), __float_as_uint(u), false, false);
-        lo_f = __uint_as_float(w[0]);
-        nh_f = __uint_as_float(w[1]);
-      }
+      float lo_f, nh_f;
+      range32(X, lo_f, nh_f);
       const float mnf = lo_f, rng = -nh_f - lo_f;
       const float inv = rng > 0.0f ? 3.0f / rng : 0.0f;
       uint32_t w0 = 0, w1 = 0;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        // between 0 and a little over 3, whatever the rounding: nothing to clamp.  (x - min as x * 1 + (-min): a
-        // multiply-add takes the 16-bit operand as it is)
+        // between 0 and a little over 3, whatever the rounding, or a NaN, whose code is 0: nothing to clamp.
+        // (x - min as x * 1 + (-min): a multiply-add takes the 16-bit operand as it is)
         const float u = rintf(__builtin_fmaf((float)X.v[i], one, -mnf) * inv);
         if (i < 4) w0 = __builtin_amdgcn_cvt_pk_u8_f32(u, i, w0); else w1 = __builtin_amdgcn_cvt_pk_u8_f32(u, i - 4, w1);
       }
@@ -266,21 +272,8 @@ __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restr
     } else if (!FFT) {
       // ---------------- Eq. 4, 1 bit: z = min, s = max - min over the 32 tokens
       const int jn = j - NTa;
-      const h2 mn2 = __builtin_elementwise_minimum(__builtin_elementwise_minimum(X.p[0], X.p[1]),
-                                                   __builtin_elementwise_minimum(X.p[2], X.p[3]));
-      const h2 mx2 = __builtin_elementwise_maximum(__builtin_elementwise_maximum(X.p[0], X.p[1]),
-                                                   __builtin_elementwise_maximum(X.p[2], X.p[3]));
-      float lo_f = fminf((float)mn2[0], (float)mn2[1]);
-      float nh_f = -fmaxf((float)mx2[0], (float)mx2[1]);
-      {
-        auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo_f), __float_as_uint(nh_f), false, false);
-        const float t = __builtin_elementwise_minimum(__uint_as_float(r[0]), __uint_as_float(r[1]));
-        auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(t), __float_as_uint(t), false, false);
-        const float u = __builtin_elementwise_minimum(__uint_as_float(q[0]), __uint_as_float(q[1]));   // rows 0,1: min; rows 2,3: -max
-        auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(u), __float_as_uint(u), false, false);
-        lo_f = __uint_as_float(w[0]);
-        nh_f = __uint_as_float(w[1]);
-      }
+      float lo_f, nh_f;
+      range32(X, lo_f, nh_f);
       const float rng = -nh_f - lo_f;
       // code = round-half-even((x - z) / s) in {0, 1} = [x above the midpoint]; a tie codes 0
       const float mid = 0.5f * (lo_f - nh_f);

@@ -8,6 +8,7 @@ import pytest
 import torch
 
 import parity as P
+from paper_2503_16257_amd import binding as vk
 from paper_2503_16257_amd import synth
 
 pytestmark = pytest.mark.gpu
@@ -70,3 +71,35 @@ def test_groups_shared_out_and_not(heads, n_a, fft):
     for h in range(heads):
         F._check_block(run, h, w.T // 32, Kt[h], Vt[h], stats)
     P.check_near_budget(stats)
+
+
+@pytest.mark.parametrize("bits", [0x7E00, 0xFE01, 0x7D00], ids=["quiet", "negative", "signalling"])
+@pytest.mark.parametrize("n_a", [0, 24, 64, 128])
+@pytest.mark.parametrize("tokens", [[3], [0, 2], [0, 2, 16, 18], list(range(31))], ids=["one", "pair", "lane", "all but one"])
+def test_a_nan_costs_nothing_but_its_own_code(tokens, n_a, bits):
+    """NaN elements of a group (one lane's tokens 0 .. 3 and 16 .. 19 of a channel among them) against the same keys with the
+    group's minimum in their place, whose code is 0: equal bytes, but for the NaN elements' own 1-bit codes.  Eq. 4 at 2 bits,
+    and at 1 bit (a sum over 32 tokens, the DFT, passes a NaN on to its channel)."""
+    H, T = 2, 96
+    print(f"[case] NaN {bits:#x} at {len(tokens)} tokens, n_a {n_a}", flush=True)
+    g = np.random.default_rng(11)
+    clean = (g.standard_normal((1, 1, H, T, 128)) * (1 + g.random(128))).astype(np.float16)
+    count = 0
+    for ch in (1, 6, 64, 127):
+        group = clean[0, 0, :, 32:64, ch]
+        # (the channel's widest two numbers stand outside the group: which channels are 2-bit ones stays as it is)
+        clean[0, 0, :, 0, ch], clean[0, 0, :, 1, ch] = -9.0, 9.0
+        rest = np.delete(group, tokens, axis=1)
+        group[:, tokens] = rest.min(axis=1, keepdims=True)
+        count += H * len(tokens)
+    bad = clean.copy()
+    for ch in (1, 6, 64, 127):
+        bad.view(np.uint16)[0, 0, :, 32:64, ch][:, tokens] = bits
+    p = vk.make_params(1, 1, H, H, T, n_a, 0, use_fft=0)
+    packed = []
+    for K in (clean, bad):
+        pk = torch.zeros(vk.packed_keys_bytes(p), dtype=torch.uint8, device=DEV)
+        vk.quantize_keys(p, torch.from_numpy(K).to(DEV), pk, vk.alloc_bytes(vk.workspace_bytes(p, 0), DEV))
+        packed.append(pk.cpu().numpy())
+    differ = int(np.unpackbits(packed[0] ^ packed[1]).sum())
+    assert differ <= (0 if n_a == 128 else count), f"{differ} bits differ"
