@@ -387,7 +387,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   // former are waited for: the operands are built while the records are on their way
   {
     const uint32_t at = lane16;
-    asm volatile(VIDKV_DMA("%0", "%1", "%2", "0")
+    asm volatile("s_nop 1\n\t" VIDKV_DMA("%0", "%1", "%2", "0")
                  :: "s"((uint32_t)reinterpret_cast<uintptr_t>(&w_tab[0][0]) + 1024u * wave), "v"(at),
                     "s"(reinterpret_cast<const uint8_t*>(&kIdftTab) + (FULL ? offsetof(IdftTab, full) : 0) + 1024 * wave) : "memory", "m0");
   }

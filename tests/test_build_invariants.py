@@ -44,6 +44,41 @@ def test_m0_is_written_only_by_the_transfer_statements(attention_isa, src):
     assert "movrel" not in isa
 
 
+def _states_before_first_transfer(lines):
+    """Fewest wait states between the beginning of an assembly statement and a transfer with a scalar base, over
+    its paths; None if a path has none."""
+    labels = {l.rstrip(":"): i for i, l in enumerate(lines) if l.endswith(":")}
+    best, todo = None, [(0, 0)]
+    while todo:
+        i, n = todo.pop()
+        while i < len(lines):
+            l = lines[i]
+            if re.match(r"global_load_lds_dwordx4 v\d+, s\[", l):
+                best = n if best is None else min(best, n)
+                break
+            if m := re.match(r"s_c?branch\S* (\S+)", l):
+                todo.append((labels[m.group(1)], n + 1))
+                if l.startswith("s_branch"):
+                    break
+            m = re.match(r"s_nop (\d+)", l)
+            n += int(m.group(1)) + 1 if m else 0 if l.startswith(".") or l.endswith(":") else 1
+            i += 1
+    return best
+
+
+@pytest.mark.parametrize("src", SOURCES)
+def test_a_transfer_stands_five_wait_states_behind_its_statements_beginning(attention_isa, src):
+    """A vector instruction may have written the scalar base right in front of the statement: then a memory
+    instruction has to stand five wait states behind it, and the compiler does not look into the statement."""
+    found = []
+    for m in re.finditer(r"^\s*;;#ASMSTART$(.*?)^\s*;;#ASMEND$", attention_isa[src], re.S | re.M):
+        lines = [l.split(";")[0].strip() for l in m.group(1).splitlines()]
+        n = _states_before_first_transfer([l for l in lines if l])
+        if n is not None:
+            found.append(n)
+    assert len(found) > 100 and min(found) >= 5, (len(found), min(found, default=None))
+
+
 def test_no_variant_spills_vector_registers(attention_isa):
     """Every anomalous-channel count (n_a / 8 is the first template argument), the three protected-row
     modes, both key codes, without and with workgroups for residual tokens."""
