@@ -183,6 +183,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   constexpr int NQ = NA / 4;                 // anomalous 4-channel quads
   constexpr int UA = (NQ + 3) / 4;           // K-steps over anomalous channels
   constexpr bool FULL = !(NA8 == 0 || NA8 == 1 || NA8 == 2 || NA8 == 4 || NA8 == 8 || NA8 == 16);
+  constexpr bool IDFT = FFT && U > 0;        // scores of normal channels come through the inverse DFT
   constexpr int KREC = 12 * NA + 8 * NN;
   constexpr int OFF_AS = 8 * NA, OFF_AZ = 10 * NA, OFF_BITS = 12 * NA, OFF_META = 12 * NA + 4 * NN;
   constexpr int RING = 4 * KREC + 4 * VREC;  // a wave's ring: two stages of a pair's key records, two of its value records
@@ -382,10 +383,10 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     __builtin_amdgcn_sched_barrier(0);
   }
 
-  // ---------------- set-up: the inverse-DFT operands (1 KB each wave), q and the channel permutation go straight to LDS (wave 0 asks for
-  // them), the first pair's key records are requested right behind them, and only the
-  // former are waited for: the operands are built while the records are on their way
-  {
+  // ---------------- set-up: the inverse-DFT operands (1 KB each wave, where there are any), q and the channel
+  // permutation (wave 0 asks for them) go straight to LDS, the first pair's key records are requested right behind
+  // them, and only the former are waited for: the operands are built while the records are on their way
+  if (IDFT) {
     const uint32_t at = lane16;
     asm volatile("s_nop 1\n\t" VIDKV_DMA("%0", "%1", "%2", "0")
                  :: "s"((uint32_t)reinterpret_cast<uintptr_t>(&w_tab[0][0]) + 1024u * wave), "v"(at),
@@ -790,7 +791,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
         }
         cst_n = FULL ? 2.0f * accCn[0] + accCs[0] : 2.0f * accCn[0];
       }
-      if (U > 0 && FFT && FULL) {
+      if (IDFT && FULL) {
         // k-slot (kb, i) of the matrix against row 4 kb + i of the sums, one i at a time.  Coefficient 4 kb + i is
         // even where i is; from token t to t + 16 the even ones stay and the odd ones change their sign, so the
         // products for the first 16 tokens serve both halves
@@ -809,7 +810,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
           S[1][i] += ev[i] - od[i];
         }
       }
-      if (U > 0 && FFT && !FULL) {
+      if (IDFT && !FULL) {
         // split Y/16 into fp16 hi + lo, then the inverse DFT
         Op Yh, Yl, Wh[2], Wl[2];
         Wh[0].q = w_tab[0][lane]; Wh[1].q = w_tab[1][lane];

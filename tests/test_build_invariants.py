@@ -93,6 +93,16 @@ def test_no_variant_spills_vector_registers(attention_isa):
                      for t in ((0, 1) if n in both else (1,))}
 
 
+def test_only_the_variants_with_an_inverse_dft_load_its_operands(attention_isa):
+    """(Eq. 5 on at least one channel: the others would fetch 4 KB a workgroup and wait for it, and read none of it.)"""
+    seen = set()
+    for isa in attention_isa.values():
+        for m in re.finditer(r"^_ZN\S*attn_mfma_kernelILi(\d+)ELi(\d)ELb(\d)ELb(\d)E\S*:.*?^\.Lfunc_end", isa, re.S | re.M):
+            assert ("kIdftTab" in m.group(0)) == (m.group(3) == "1" and m.group(1) != "16"), m.groups()
+            seen.add(m.groups())
+    assert len(seen) >= 17 * 3 * 2
+
+
 def test_residual_tokens_read_lds_16_bytes_at_a_time(tmp_path):
     """q and the probabilities come in quads only where the compiler knows their alignment."""
     isa = _isa(os.path.join(B.CSRC, "decode_attn.hip"), tmp_path / "decode_attn.s")
