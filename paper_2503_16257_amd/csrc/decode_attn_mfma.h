@@ -976,27 +976,12 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) t[i] -= m_new;
       m_run = m_new;
-    } else if (__any(mx > 8.0f || m_run == -INFINITY)) {
-      // true scores again; maximum over the 4 k-blocks and the 2 parities of the head
-      float smax;
-      if (m_run == -INFINITY) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          t[i] = fmaf(S[0][i], sc2, c0);
-          t[4 + i] = fmaf(S[1][i], sc2, c0);
-        }
-        smax = t[0];
-#pragma unroll
-        for (int i = 1; i < 8; ++i) smax = fmaxf(smax, t[i]);
-      } else {
-        smax = mx + m_run;
-      }
-      smax = swap_max32(smax);
-      smax = swap_max16(smax);
+    } else if (__any(mx > 8.0f)) {
+      // maximum over the 4 k-blocks and the 2 parities of the head (the first step has left a finite one)
+      float smax = swap_max16(swap_max32(mx + m_run));
       smax = fmaxf(smax, from_xor8(smax));
       const float m_new = fmaxf(m_run, smax);
-      const float al = (m_run == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(m_run - m_new);
-      const float shift = (m_run == -INFINITY) ? -m_new : m_run - m_new;
+      const float shift = m_run - m_new, al = __builtin_amdgcn_exp2f(shift);
 #pragma unroll
       for (int i = 0; i < 8; ++i) t[i] += shift;
       l_run *= al;
