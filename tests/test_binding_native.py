@@ -187,3 +187,49 @@ def test_the_library_is_built_where_the_layer_cannot_be(tmp_path, monkeypatch, c
     assert B.build(verbose=False) == B.LIB
     assert [c[0] for c in ran].count("g++") == 1 and len(ran) == 2 and not stale.exists()
     assert "vidkv_marshal.so" in capsys.readouterr().err
+
+
+_DTYPE = {"q": torch.float16, "pk": torch.uint8, "pv": torch.uint8, "Kt": torch.float16, "Vt": torch.float16,
+          "tl": torch.int32, "out": torch.float16, "ws": torch.uint8}
+_OF_CALL = {"decode_attention": ["q", "pk", "pv", "Kt", "Vt", "tl", "out", "ws"],
+            "decode_attention_noalloc": ["q", "pk", "pv", "Kt", "Vt", "tl", "out"],
+            "flush_residual": ["Kt", "Vt", "pk", "pv"]}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("call,name", [(c, n) for c, names in _OF_CALL.items() for n in names])
+def test_device_tensors_that_do_not_fit_are_refused(call, name):
+    """One tensor of a call that would pass is of another type, not contiguous, or not on the device (raised in front of
+    any launch); the call itself passes, and leaves what the Python path leaves."""
+    p = vk.make_params(1, 1, 1, 2, 32, 16, 0, t_capacity=64)
+    size = {"pk": (vk.packed_keys_bytes(p),), "pv": (vk.packed_values_bytes(p),), "ws": (vk.workspace_bytes(p, 2),), "tl": (1,),
+            "q": (1, 2, 128), "out": (1, 2, 128), "Kt": (1, 1, 32, 128), "Vt": (1, 1, 32, 128)}
+    good = {n: torch.zeros(size[n], dtype=t, device="cuda:0") for n, t in _DTYPE.items()}
+
+    def run(t):
+        if call == "flush_residual":
+            vk.flush_residual(p, 0, t["Kt"], t["Vt"], 32, 32, t["pk"], t["pv"])
+        else:
+            ws = (t["ws"],) if call == "decode_attention" else ()
+            getattr(vk, call)(p, 0, t["q"], t["pk"], t["pv"], t["out"], *ws, K_tail=t["Kt"], V_tail=t["Vt"], tail_capacity=32,
+                              tail_len=t["tl"])
+
+    other = {torch.float16: (torch.bfloat16, torch.float32), torch.uint8: (torch.int8, torch.float16),
+             torch.int32: (torch.int64, torch.float32)}[_DTYPE[name]]
+    for t in other:
+        with pytest.raises(TypeError, match="expected dtype"):
+            run({**good, name: torch.zeros(size[name], dtype=t, device="cuda:0")})
+    # (one element is contiguous whatever its stride: two, every other one of four)
+    strided = torch.zeros(size[name][:-1] + (2 * max(size[name][-1], 2),), dtype=_DTYPE[name], device="cuda:0")[..., ::2]
+    with pytest.raises(ValueError, match="must be contiguous"):
+        run({**good, name: strided})
+    with pytest.raises(TypeError, match="expected a CUDA tensor"):
+        run({**good, name: good[name].cpu()})
+    run(good)
+    native, vk._native = vk._native, None
+    try:
+        again = {n: torch.zeros_like(t) for n, t in good.items()}
+        run(again)
+    finally:
+        vk._native = native
+    assert all(torch.equal(good[n], again[n]) for n in ("pk", "pv", "out"))
