@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
 
 // Compute units of the current device, asked once per device. A process with no usable
 // device (a size query on a build host) gets the MI355X figure, 256.
-static int device_cu_count() {
+int device_cu_count() {
   constexpr int MAXDEV = 64;
   static std::atomic<int> cached[MAXDEV];
   int dev = 0;

@@ -371,9 +371,12 @@ static void launch_any(const Geom& g, const EncodeSpan& sp, int gx, const void* 
 // 127.9; 28 x 4 x 6272, n_a = 64 108.6 either way.)
 constexpr int K_GPB = 4;
 
-// One group per workgroup: where that leaves no compute unit with more than one workgroup (of 256; more of them than
-// that would only queue up behind their barriers).
-static bool split_groups(long long groups) { return groups <= 256; }
+// One group per workgroup, its tiles among the four waves: where no compute unit gets more than one such workgroup.
+// (The kernel alone, one group per wave against shared out, n_a = 64: 49 groups 4.6 us against 3.1, 128 4.7 against
+// 3.3, 200 5.0 against 3.5, 256 5.0 against 3.6, whether of one head or of eight; n_a = 16: 4.6 against 3.4 to 4.9 against 3.6;
+// a flush with its values: 32 groups 4.6 against 3.2, 256 4.7 against 3.6.  Beyond the compute units the difference falls:
+// 300 groups 5.0 against 3.9, 512 5.2 against 4.2; not looked at in whole calls.)
+static bool split_groups(long long groups) { return groups <= device_cu_count(); }
 
 void launch_k_encode(const Geom& g, const EncodeSpan& sp, const void* K, uint8_t* packed,
                      bool use_fft, hipStream_t st) {
@@ -394,9 +397,9 @@ bool launch_k_encode_protect2(const Geom& g, const void* K, uint8_t* packed_K, c
   return true;
 }
 
-// Key and value coding passes of a residual block, MASK and RANK of its groups: one launch, one group
-// per wave.  As three (5.6 + 4.0 + 1.3 us and their gaps at 4 heads x 128 tokens) 28 layers took 446 us,
-// as one (5.8 us) 269, most of it the caller's.
+// Key and value coding passes of a residual block, MASK and RANK of its groups: one launch, one group per workgroup
+// or, from split_groups() on, per wave.  (As three, 5.6 + 4.0 + 1.3 us and their gaps at 4 heads x 128 tokens, 28 layers took
+// 446 us; as one of 5.8, 269; with the kernel at 3.2 and the calls marshalled natively 115 to 132, nearly all of it the host.)
 bool launch_flush_encode(const Geom& g, const EncodeSpan& sp, float gamma, const void* K, const void* V,
                          uint8_t* packed_K, uint8_t* packed_V, hipStream_t st) {
   if (2 * sp.heads > 65535) return false;

@@ -69,6 +69,9 @@ struct EncodeSpan {
   long long head0;    // first of them inside the packed buffer
 };
 
+// Compute units of the current device (decode_attn.hip).
+int device_cu_count();
+
 __host__ __device__ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 inline bool make_geom(const vidkv_params* p, Geom* g) {
