@@ -182,8 +182,9 @@ def workspace_bytes(p: VidkvParams, which: int) -> int:
 
 
 # A decode call marshals ten arguments and a flush eight, once per layer: natively where the arguments are
-# plain (9.6 -> 6.2 us a decode call on the host, 5.5 -> 3.3 a flush; the launches are 3 us each), and what follows
-# is kept to a few attribute reads per tensor.  torch's names are looked up once, with the library.
+# plain (host time with and without, in turn in one process: 6.9 against 9.0 us a decode call, 3.5 against 5.7 a flush, in
+# another 7.8 against 10.0 and 4.2 against 5.8; the launches are 3 us each), and what follows is kept to a few
+# attribute reads per tensor.  torch's names are looked up once, with the library.
 _Tensor = _f16 = _u8 = _f32 = _i32 = _raw_stream = _cur_device = None
 
 

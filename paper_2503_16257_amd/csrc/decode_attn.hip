@@ -25,10 +25,12 @@ __global__ __launch_bounds__(256) void attn_tail_kernel(AttnArgs a) {
 
 // Merge of the split partials: out = sum_i o_i 2^{m_i - M} / sum_i l_i 2^{m_i - M}.
 // grid (Hq, B), block 256 = 32 channel quads x 8 slices of the list of parts.  What takes time is
-// latency - the launch, one round trip to memory, the reduction - so up to 8 MAXU parts are
-// requested before the first is used, 16 bytes of a part per thread (a block of 128 threads that
-// held 16 or 32 parts as single floats: 3.6 and 5.4 us, 6.4 at 1792 (sequence, head) rows; of 1024
-// threads up to 136 parts: 5.8; this: 3.2, 3.3, 4.6 and 4.6).
+// latency - the launch, the round trips to memory, the reduction - so the source asks for up to 8 MAXU
+// parts before it uses the first, 16 bytes of a part per thread.  The compiler does not keep that order:
+// arguments in two steps, then (m, l) - of 2 parts, at MAXU 9 two at a time, at 17 all of them - waited for in front
+// of the sums, and the first part's sums only behind the maximum: three to about ten round trips, not one.  (A block of
+// 128 threads that held 16 or 32 parts as single floats: 3.6 and 5.4 us, 6.4 at 1792 (sequence, head) rows; of 1024
+// threads up to 136 parts: 5.8; this: 3.2, 3.3, 4.6 and 4.6.)
 template <int MAXU>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ part_o,
                                                          const float2* __restrict__ part_ml,
@@ -127,9 +129,12 @@ int attn_max_splits(const Geom& g) {
 
 // The costs below are in 0.1 us: of a round of workgroups, two resident per compute unit, that take s
 // pairs of groups one after another in each of 4 waves; 6 us to get going and finish, 2.2 us per pair where a
-// compute unit has one workgroup, 3.5 where it has two.  Measured for n_a = 64 and checked for 16 with fp16
-// rows, 96, and 64 with 2-bit rows, 1 to 64 sequences of 192 to 12544 tokens with 0 to 512 residual ones:
-// the split chosen costs 0.6 % more than the fastest tried on average, 16 % at most.
+// compute unit has one workgroup, 3.5 where it has two.  Fitted at n_a = 64 to a kernel that took that long (the
+// split chosen cost 0.6 % more than the fastest tried on average, 16 % at most) and kept: the present one gets
+// going 1.4 us earlier and spends fewer instructions on a pair.  On it, n_a = 64, 16 with fp16 rows, 96, and 64 with 2-bit rows, 1 to 64
+// sequences x 4 heads of 192 to 12544 tokens with 0 to 512 residual ones, 420 shapes: 1.8 % on average, more than 10 % at
+// 28 of them, 44 % at most (40 sequences x 1568 tokens with 256 residual ones: 39.2 us, 27.3 with all of it in
+// one launch); none of the 420 is slower than on the kernel it was fitted to, 13 % less on average.
 static long long main_cost(int s, int w, int cus) {
   // a 64-bit product: thousands of rounds of thousands of pairs
   return (long long)((w + 2 * cus - 1) / (2 * cus)) * (60 + (long long)s * (w <= cus ? 22 : 35));

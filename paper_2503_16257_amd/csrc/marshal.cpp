@@ -1,5 +1,5 @@
 // The per-layer calls of the binding, marshalled natively: a decode step makes one call per layer, and in
-// Python the checks and pointers of its tensors took 2.5 us of a call whose two launches take 6.
+// Python the checks and pointers of its tensors cost 2 us and more of it (both sides in binding.py).
 //
 // What a call does is what binding.py does for it - tensor type, device, contiguity and dtype checked, then the
 // C entry point - for plain torch.Tensor arguments that pass and structures of binding.py's own classes; anything

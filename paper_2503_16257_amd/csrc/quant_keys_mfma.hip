@@ -121,8 +121,8 @@ __device__ __forceinline__ void range32(const Op& X, float& lo, float& nh) {
 // small, one launch).
 // SPLIT: one group per workgroup, its tiles shared out among the four waves (and a flush's values likewise), for
 // calls that leave compute units idle anyway: a group's tiles one after another are then most of the kernel
-// after the first load.  (Whole calls: one head x 1568 tokens 18.4 us, 17.0 so; 28 flushes of 4 heads x 128 tokens
-// 119 against 113.  The value pass of a prefill shared out likewise gains nothing beside its channel selection.)
+// after the first load.  (Whole calls: one head x 1568 tokens 18.4 us, 17.0 so; 28 flushes of 4 heads x 128 tokens 5 %
+// less.  The value pass of a prefill shared out likewise gains nothing beside its channel selection.)
 template <int NA8T, bool FFT, int EXTRA, bool SPLIT>
 __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restrict__ K,
                                                             const uint8_t* __restrict__ perm_g,
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restr
   u32x4 pre[NPRE];
 #pragma unroll
   for (int i = 0; i < NPRE; ++i) pre[i] = __builtin_nontemporal_load(head + ((long long)g * G + row0) * 16 + lane + 64 * i);
-  __builtin_amdgcn_sched_barrier(0);                 // (these first, and their first use behind the set-up: 128.2 us against 127.0)
+  __builtin_amdgcn_sched_barrier(0);                 // (these first, and their first use behind the set-up: 1 % of a call with 4 heads x 196000)
 
   // Channel tile j: anomalous tiles first (16 anomalous channels each, in PERM
   // order), then normal tiles.  My column's channel in every tile, as a byte
@@ -366,13 +366,13 @@ static void launch_any(const Geom& g, const EncodeSpan& sp, int gx, const void* 
 }
 
 // Four groups per workgroup, one per wave: short-lived workgroups keep the memory system evenly loaded.  (Two per
-// wave, the second's load beside the first's arithmetic, were better while the arithmetic took most of the time:
-// 64 x 4 heads x 25088 tokens, n_a = 32, plain code, whole call: 920 us against 891; 4 heads x 196000 130.6 against
-// 127.9; 28 x 4 x 6272, n_a = 64 108.6 either way.)
+// wave, the second's load beside the first's arithmetic, were better while the arithmetic took most of the time.  When
+// it no longer did, whole calls on one card: 64 x 4 heads x 25088 tokens, n_a = 32, plain code, 3 % slower than this,
+// 4 heads x 196000 2 %, 28 x 4 x 6272, n_a = 64, the same.)
 constexpr int K_GPB = 4;
 
 // One group per workgroup, its tiles among the four waves: where no compute unit gets more than one such workgroup.
-// (The kernel alone, one group per wave against shared out, n_a = 64: 49 groups 4.6 us against 3.1, 128 4.7 against
+// (The kernel alone, inputs in the caches, one group per wave against shared out, n_a = 64: 49 groups 4.6 us against 3.1, 128 4.7 against
 // 3.3, 200 5.0 against 3.5, 256 5.0 against 3.6, whether of one head or of eight; n_a = 16: 4.6 against 3.4 to 4.9 against 3.6;
 // a flush with its values: 32 groups 4.6 against 3.2, 256 4.7 against 3.6.  Beyond the compute units the difference falls:
 // 300 groups 5.0 against 3.9, 512 5.2 against 4.2; not looked at in whole calls.)
@@ -399,7 +399,7 @@ bool launch_k_encode_protect2(const Geom& g, const void* K, uint8_t* packed_K, c
 
 // Key and value coding passes of a residual block, MASK and RANK of its groups: one launch, one group per workgroup
 // or, from split_groups() on, per wave.  (As three, 5.6 + 4.0 + 1.3 us and their gaps at 4 heads x 128 tokens, 28 layers took
-// 446 us; as one of 5.8, 269; with the kernel at 3.2 and the calls marshalled natively 115 to 132, nearly all of it the host.)
+// 446 us; as one of 5.8, 269; shared out, 3.5, and with the calls marshalled natively 115 to 132 on different hosts, whose time it is.)
 bool launch_flush_encode(const Geom& g, const EncodeSpan& sp, float gamma, const void* K, const void* V,
                          uint8_t* packed_K, uint8_t* packed_V, hipStream_t st) {
   if (2 * sp.heads > 65535) return false;
