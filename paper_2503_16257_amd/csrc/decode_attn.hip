@@ -25,49 +25,55 @@ __global__ __launch_bounds__(256) void attn_tail_kernel(AttnArgs a) {
 
 // Merge of the split partials: out = sum_i o_i 2^{m_i - M} / sum_i l_i 2^{m_i - M}.
 // grid (Hq, B), block 256 = 32 channel quads x 8 slices of the list of parts.  What takes time is
-// latency - the launch, the round trips to memory, the reduction - so the source asks for up to 8 MAXU
-// parts before it uses the first, 16 bytes of a part per thread.  The compiler does not keep that order:
-// arguments in two steps, then (m, l) - of 2 parts, at MAXU 9 two at a time, at 17 all of them - waited for in front
-// of the sums, and the first part's sums only behind the maximum: three to about ten round trips, not one.  (A block of
-// 128 threads that held 16 or 32 parts as single floats: 3.6 and 5.4 us, 6.4 at 1792 (sequence, head) rows; of 1024
-// threads up to 136 parts: 5.8; this: 3.2, 3.3, 4.6 and 4.6.)
-template <int MAXU>
+// latency - the launch, the round trips to memory, the reduction - so everything is asked for at once: the
+// arguments, then up to 8 U parts, 16 bytes of a part per thread, and their (m, l), before any is waited for.
+// (As the compiler orders it by itself - arguments in two steps, (m, l) waited for in front of the sums, the sums behind
+// the maximum, three to ten round trips - the kernel took 3.4 us at 28 rows x 26 parts and 4.2 at 28 x 129 x 7; so 2.8 and
+// 3.8: a step of 28 layers x 6272 tokens 314 -> 299 us, one layer of 196000 28.3 -> 27.4, 28 x 8 x 12544 485 -> 476.)
+template <int U>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ part_o,
                                                          const float2* __restrict__ part_ml,
                                                          int nparts, int BHq,
                                                          _Float16* __restrict__ out) {
+  asm volatile("" :: "s"(part_o), "s"(part_ml), "s"(nparts), "s"(BHq), "s"(out));
   const int row = blockIdx.y * gridDim.x + blockIdx.x;             // (sequence, query head)
   const int c4 = threadIdx.x & 31, sl = threadIdx.x >> 5;
   __shared__ f4 so[8][32];
   __shared__ float sl_[8], sM[8];
   const f4* po = reinterpret_cast<const f4*>(part_o) + (size_t)row * (D / 4) + c4;
+  const float2* pm = part_ml + row;
   f4 o = f4{0.f, 0.f, 0.f, 0.f};
   float l = 0.0f, M = -INFINITY;
   // slice sl takes parts sl, sl + 8, ...; its sums are relative to its own running maximum
-  for (int i0 = sl; i0 < nparts; i0 += 8 * MAXU) {
-    f4 oi[MAXU];
-    float2 ml[MAXU];
+  for (int i0 = sl; i0 < nparts; i0 += 8 * U) {
+    f4 oi[U];
+    float2 ml[U];
 #pragma unroll
-    for (int u = 0; u < MAXU; ++u) {
-      const int i = i0 + 8 * u, ii = i < nparts ? i : i0;
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + 8 * u, ii = i < nparts ? i : i0;          // (past the end: a part again, not counted)
+      ml[u] = pm[(size_t)ii * BHq];
       oi[u] = po[(size_t)ii * BHq * (D / 4)];
-      ml[u] = part_ml[(size_t)ii * BHq + row];
-      if (i >= nparts) ml[u].x = -INFINITY;
     }
+    // (left to itself the compiler waits for (m, l) first, and for the sums only behind the maximum)
+#pragma unroll
+    for (int u = 0; u < U; ++u) asm volatile("" : "+v"(oi[u]), "+v"(ml[u].x), "+v"(ml[u].y));
     float Mn = M;
 #pragma unroll
-    for (int u = 0; u < MAXU; ++u) Mn = fmaxf(Mn, ml[u].x);
-    const float w0 = M == -INFINITY ? 0.0f : exp2f(M - Mn);
+    for (int u = 0; u < U; ++u) {
+      if (i0 + 8 * u >= nparts) ml[u].x = -INFINITY;
+      Mn = fmaxf(Mn, ml[u].x);
+    }
+    const float w0 = M == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(M - Mn);
     o *= w0;
     l *= w0;
     M = Mn;
 #pragma unroll
-    for (int u = 0; u < MAXU; ++u) {
-      const float w = ml[u].x == -INFINITY ? 0.0f : exp2f(ml[u].x - M);
-      if (w != 0.0f) {                       // an empty part's sums are never looked at
-        o += w * oi[u];
-        l += w * ml[u].y;
-      }
+    for (int u = 0; u < U; ++u) {
+      const float w = ml[u].x == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(ml[u].x - M);
+      const bool any = w != 0.0f;                                  // an empty part's sums are never looked at
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] += any ? w * oi[u][e] : 0.0f;
+      l += any ? w * ml[u].y : 0.0f;
     }
   }
   so[sl][c4] = o;
