@@ -19,8 +19,8 @@
  *    as void*, NULL = the default stream), which must belong to the current
  *    device (else VIDKV_EINVAL).  The library creates no stream and no event
  *    and keeps no state between calls (the one exception is the device array
- *    of vidkv_decode_attention_noalloc).  vidkv_quantize_kv and
- *    vidkv_decode_attention can run part of a large call beside the rest on a
+ *    of vidkv_decode_attention_noalloc).  vidkv_quantize_kv can run part of a
+ *    large call beside the rest on a
  *    second stream that the caller hands in (vidkv_side_stream below); without
  *    one, everything runs in line on `hip_stream`.
  *  - All arguments are checked on the host before anything is launched; a
@@ -213,11 +213,10 @@ vidkv_status vidkv_quantize_kv(const vidkv_params *params, const void *K_dev,
  *                     the call then uses
  * With Tq == 0 this is plain attention over the residual tokens; a sequence
  * with no token at all gets zeros.
- * With a side stream, a large residual block (32-token blocks over all
- * sequences and KV heads, at most 8 counted per head, numbering four times
- * the device's compute units or more) is read by a kernel that is forked onto
- * it and joined before the split partials are merged.
- *   side            : NULL, or the caller's side stream and events           */
+ * Everything runs in line on `hip_stream`, with and without a side stream (a
+ * large residual block no longer gains from one).
+ *   side            : NULL, or the caller's side stream and events: checked,
+ *                     not used                                               */
 vidkv_status vidkv_decode_attention(const vidkv_params *params, int32_t layer,
                                     const void *q_dev, const void *packed_K_dev,
                                     const void *packed_V_dev, const void *K_tail_dev,

@@ -174,39 +174,38 @@ struct AttnPlan {
   bool along;          // the latter in the same launch
 };
 
-// `iters` blocks of 32 residual tokens per head; `beside`: they get a launch of their own in any case.
-// In the same launch, where all workgroups fit one round, their time disappears behind the packed tokens'
-// if each takes few blocks one after another: 4.8 us and 3.4 us per block, 5 where a compute unit has two
-// workgroups.  A launch of its own, up to ATTN_TAIL_SPLITS workgroups per head, costs 5.8 us and
-// 2.4 us per block and workgroup of a compute unit.  (8 x 4 heads x 1568 tokens, 128 residual tokens in
-// one workgroup per head because there are more than 64 blocks: 21.0 us; in four: 12.8; in a launch of their
-// own: 18.9.  28 layers of 6272 tokens, 77 residual tokens, n_a = 64: a launch each 606 us a step, along 397.)
-static AttnPlan attn_plan(const Geom& g, int nmax, int iters, bool beside) {
+// `iters` blocks of 32 residual tokens per head, a wave of a residual workgroup one or more of them, `turns` one
+// after another.  In the same launch, where all workgroups fit one round, their time disappears behind the packed
+// tokens': 3.5 us and 2.2 us a turn, 3.2 where a compute unit has two workgroups.  A launch of its own costs 7.0 us
+// and 2.8 us a turn and round of three workgroups a compute unit.  Fitted to 780 shapes (1 to 64 sequences x 1 to 8
+// heads of 192 to 12544 tokens, 32 to 1024 residual ones, four variants), main_cost() as it is: 1.3 % over the fastest split tried on
+// average, 29 % at most.  Large blocks, too (64 x 4 heads x 25088 tokens, 256 residual ones: the launch takes 7.7 us; on a
+// stream of its own beside the packed tokens' the call took 147 us, behind them 140).
+static AttnPlan attn_plan(const Geom& g, int nmax, int iters) {
   const int bh = (int)std::min((long long)g.B * g.H, 1LL << 20), cus = device_cu_count(), npairs = (g.ng + 1) / 2;
-  AttnPlan best{0, std::min(iters, ATTN_TAIL_SPLITS), false};
-  long long best_t = -1;
-  if (iters > 0 && !beside) {
-    // from the most workgroups with one block each down to the fewest; of the splits that fit beside them in
+  const int ntail = std::min((iters + 3) / 4, ATTN_TAIL_SPLITS);
+  AttnPlan best{0, ntail, false};
+  long long best_t = -1, own = 0;
+  if (iters > 0) {
+    const int turns0 = (iters + 4 * ntail - 1) / (4 * ntail);
+    own = 70 + 28LL * turns0 * (((long long)bh * ntail + 3 * cus - 1) / (3 * cus));
+    // from the most workgroups down to the fewest; of the splits that fit beside them in
     // one round, or in one workgroup per compute unit, the finest
-    int per = (iters + ATTN_TAIL_SPLITS - 1) / ATTN_TAIL_SPLITS, nt = (iters + per - 1) / per;
-    for (;;) {
+    for (int nt = ntail, turns = turns0;;) {
       for (int room = 2; room >= 1; --room) {
         const int most = std::min(nmax, room * cus / bh - nt);
         if (most < 1) continue;
         const int s = ((npairs + most - 1) / most + 3) / 4;
         const int n = room == 2 ? most : (npairs + 4 * s - 1) / (4 * s), w = bh * (n + nt);
-        const long long t = std::max(main_cost(s, w, cus), 48 + (long long)per * (w <= cus ? 34 : 50));
+        const long long t = std::max(main_cost(s, w, cus), 35 + (long long)turns * (w <= cus ? 22 : 32));
         // of equal costs the finer split: fewer of its waves take the last of the s pairs
         if (best_t < 0 || t < best_t || (t == best_t && n > best.nsplit)) { best_t = t; best = {n, nt, true}; }
       }
       if (nt == 1) break;
-      per = (iters + nt - 2) / (nt - 1);               // the next smaller number that changes the blocks per workgroup
-      nt = (iters + per - 1) / per;
+      turns = (iters + 4 * (nt - 1) - 1) / (4 * (nt - 1));   // the next smaller number that changes the blocks per wave
+      nt = (iters + 4 * turns - 1) / (4 * turns);
     }
   }
-  const int ntail = std::min(iters, ATTN_TAIL_SPLITS);
-  const long long wt = (long long)bh * ntail;
-  const long long own = iters == 0 || beside ? 0 : 58 + 24LL * ((iters + ntail - 1) / ntail) * ((wt + cus - 1) / cus);
   if (best_t < 0 || best_t > 82 + own) {               // 82: the least that main_cost() can be
     long long t;
     const int n = attn_splits(bh, npairs, nmax, cus, &t);
@@ -215,23 +214,11 @@ static AttnPlan attn_plan(const Geom& g, int nmax, int iters, bool beside) {
   return best;
 }
 
-// A large block of residual tokens is worth a stream of its own: its kernel is short of
-// memory parallelism, not of arithmetic, and runs well beside the MFMA kernel.
-bool attn_tail_beside(const Geom& g, int cap) {
-  if (cap <= 0 || g.ng == 0) return false;
-  const int iters = (cap + 31) / 32;
-  const long long wgs = (long long)(iters < ATTN_TAIL_SPLITS ? iters : ATTN_TAIL_SPLITS) * g.B * g.H;
-  return wgs >= 4LL * device_cu_count();
-}
-
-// side / fork / join: when side is not null (and there are residual tokens for the MFMA
-// path) the residual-token kernel is forked onto that stream and joined before the merge.
 // ws_bytes: room for attn_least_splits() + ATTN_TAIL_SPLITS parts at least.
 hipError_t launch_decode_attention(const Geom& g, int layer, float scale, const void* q,
                                    const uint8_t* pk, const uint8_t* pv, const void* ktail,
                                    const void* vtail, int cap, const int32_t* tail_len, void* out,
-                                   void* ws, size_t ws_bytes, unsigned stages, hipStream_t st, hipStream_t side,
-                                   hipEvent_t fork, hipEvent_t join) {
+                                   void* ws, size_t ws_bytes, unsigned stages, hipStream_t st) {
   AttnArgs a;
   a.q = reinterpret_cast<const _Float16*>(q);
   a.kperm = pk + g.k_perm;
@@ -249,18 +236,17 @@ hipError_t launch_decode_attention(const Geom& g, int layer, float scale, const 
   a.sal_bits = g.sal_bits; a.npg = g.npg; a.use_fft = g.use_fft ? 1 : 0;
   a.scale2 = scale * 1.4426950408889634f;
   // stages: bit 0 split-T partial kernel(s), bit 1 merge
-  // Residual tokens: in the MFMA kernel's launch, or in one of their own, on the side stream or behind.
+  // Residual tokens: in the MFMA kernel's launch, or in one of their own behind it.
   // With no token at all one empty part per head is still written.
   const long long bh = (long long)g.B * g.H, slots = 2LL * device_cu_count();
   const int tail_iters = has_tail ? (cap + 31) / 32 : 0;
   const long long fit = (long long)(ws_bytes / ((size_t)g.B * g.Hq * (D + 2) * sizeof(float))) - ATTN_TAIL_SPLITS;
   const int nmax = (int)std::min((long long)attn_max_splits(g), fit);
-  int ntail = std::max(1, std::min(tail_iters, ATTN_TAIL_SPLITS));
+  int ntail = std::max(1, std::min((tail_iters + 3) / 4, ATTN_TAIL_SPLITS));
   bool along = false;
   a.nsplit = 0;
   if (g.ng > 0) {
-    // (not by whether a side stream is there: the result is the same with and without)
-    const AttnPlan p = attn_plan(g, nmax, tail_iters, attn_tail_beside(g, cap));
+    const AttnPlan p = attn_plan(g, nmax, tail_iters);
     a.nsplit = p.nsplit;
     ntail = p.ntail;
     along = p.along;
@@ -274,19 +260,8 @@ hipError_t launch_decode_attention(const Geom& g, int layer, float scale, const 
     const int npairs = (g.ng + 1) / 2;
     a.gps = a.nsplit > 0 ? (npairs + a.nsplit - 1) / a.nsplit : 0;   // pairs per split
     const dim3 gtail(ntail, g.H, g.B), gmain(a.nsplit + (along ? ntail : 0), g.H, g.B);
-    if (has_tail && side && a.nsplit > 0) {
-      if (hipEventRecord(fork, st) != hipSuccess) return hipErrorUnknown;
-      if (hipStreamWaitEvent(side, fork, 0) != hipSuccess) return hipErrorUnknown;
-      // the side stream now depends on `st`: it is joined back whatever fails below
-      hipLaunchKernelGGL(attn_tail_kernel, gtail, dim3(256), 0, side, a);
-      const bool rec = hipEventRecord(join, side) == hipSuccess;
-      launch_attn_mfma(a, gmain, st);
-      const bool joined = hipStreamWaitEvent(st, join, 0) == hipSuccess;
-      if (!rec || !joined) return hipErrorUnknown;
-    } else {
-      if (a.nsplit > 0) launch_attn_mfma(a, gmain, st);
-      if (ntail > 0 && !along) hipLaunchKernelGGL(attn_tail_kernel, gtail, dim3(256), 0, st, a);
-    }
+    if (a.nsplit > 0) launch_attn_mfma(a, gmain, st);
+    if (ntail > 0 && !along) hipLaunchKernelGGL(attn_tail_kernel, gtail, dim3(256), 0, st, a);
   }
   if (stages & 2u) {
     _Float16* o16 = reinterpret_cast<_Float16*>(out);

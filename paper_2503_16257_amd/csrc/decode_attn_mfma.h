@@ -79,26 +79,8 @@
 
 namespace vidkv {
 
-typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(4))) uint32_t cu32;   // read with scalar loads
 
-__device__ __forceinline__ float swap_sum32(float v) {       // v(lane) + v(lane ^ 32)
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float swap_sum16(float v) {       // v(lane) + v(lane ^ 16)
-  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float swap_max32(float v) {
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float swap_max16(float v) {
-  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
 __device__ __forceinline__ float from_xor8(float v) {        // v(lane ^ 8): within a row of 16, 8 lanes on
   return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x128, 0xF, 0xF, true));
 }
@@ -219,7 +201,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     float al16[4][16];             // per wave: rescale factors per column
     float mw[8][4], lw[8][4];      // [head][wave]
     alignas(256) uint8_t rowbuf[(SAL != 0) ? 4 : 1][(SAL != 0) ? ROWB : 16];   // per wave: the rows of the next batch
-    alignas(16) uint8_t ring[4][RING];   // per wave: 2 key stages, 2 value stages; reused for the wave's partial output
+    alignas(256) uint8_t ring[4][RING];  // per wave: 2 key stages, 2 value stages; reused for the wave's partial output
     alignas(16) uint8_t pre_s[PRE_BYTES > PL_BYTES ? PRE_BYTES : PL_BYTES];
   };
   __shared__ __align__(256) Lds lds;
@@ -241,6 +223,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     const __attribute__((address_space(4))) AttnArgs* ap =
         (const __attribute__((address_space(4))) AttnArgs*)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(ap));
+    static_assert(sizeof(TailLds) <= sizeof(lds.ring), "the residual part must fit the rings");
     attn_tail_part(*(const AttnArgs*)ap, split - ap->nsplit, kvh, b, *reinterpret_cast<TailLds*>(&ring[0][0]));
     return;
   }
@@ -1127,47 +1110,12 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   l_run = swap_sum32(l_run);
   l_run = swap_sum16(l_run);
   l_run += from_xor8(l_run);
-  // o: rows 4kb+i; the parity 1 rows of a head live 32 lanes away from its parity 0 rows.
-  // One lane-half swap of the register pair (tile m, tile m + 4) and one addition leave the
-  // sums of tile m in lanes 0..31 and those of tile m + 4 in lanes 32..63.
-  float* ow = reinterpret_cast<float*>(&ring[wave][0]);        // [8 heads][128 channels]
+  // o: rows 4kb+i, (parity, head)
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                // no transfer into the ring is left
-#pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(o[m][i]), __float_as_uint(o[m + 4][i]), false, false);
-      const float s = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-      ow[(4 * (kb & 1) + i) * D + 16 * (m + 4 * (kb >> 1)) + x16] = s;
-    }
+  put_wave_sums(o, reinterpret_cast<float*>(&ring[wave][0]), x16, kb);
   if (kb == 0 && par == 0) { mw[hcol][wave] = m_run; lw[hcol][wave] = l_run; }
   __syncthreads();
-  // ---------------- workgroup merge of the 4 waves, then the split partial: four channels of one head
-  // a thread, everything read at once (one channel of four heads one after another, each behind the reads of
-  // the maxima: 1.2 to 1.5 us; now 0.4)
-  {
-    const int h = tid >> 5, c4 = tid & 31;
-    const f4 m4 = *reinterpret_cast<const f4*>(&mw[h][0]), l4 = *reinterpret_cast<const f4*>(&lw[h][0]);
-    f4 x[4];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) x[w] = *reinterpret_cast<const f4*>(&ring[w][(h * D + 4 * c4) * sizeof(float)]);
-    const float M = fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]));
-    f4 acc = zero;
-    float L = 0.0f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const bool any = m4[w] != -INFINITY;                      // an empty wave's sums are never looked at
-      const float f = any ? exp2f(m4[w] - M) : 0.0f;
-      L += any ? f * l4[w] : 0.0f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[i] += any ? f * x[w][i] : 0.0f;
-    }
-    if (h < R) {
-      const long long row = ((long long)split * a.B + b) * a.Hq + kvh * R + h;
-      *reinterpret_cast<f4*>(a.part_o + row * D + 4 * c4) = acc;
-      if (c4 == 0) *reinterpret_cast<float2*>(a.part_ml + row * 2) = float2{M, L};
-    }
-  }
+  put_partial(a, split, kvh, b, tid, mw, lw, &ring[0][0], RING);
 }
 
 #undef VIDKV_DMA

@@ -1,6 +1,7 @@
 // C ABI of the VidKV library: argument validation on the host, then kernel
 // launches on the caller's stream (and, for two calls, on a second stream that the
 // caller hands in).  Nothing here allocates, synchronizes, or creates streams or events.
+#include <algorithm>
 #include <mutex>
 
 #include "vidkv_common.h"
@@ -15,9 +16,8 @@ size_t values_ws_bytes(const Geom& g);
 hipError_t launch_decode_attention(const Geom& g, int layer, float scale, const void* q,
                                    const uint8_t* pk, const uint8_t* pv, const void* ktail,
                                    const void* vtail, int cap, const int32_t* tail_len, void* out,
-                                   void* ws, size_t ws_bytes, unsigned stages, hipStream_t st, hipStream_t side,
-                                   hipEvent_t fork, hipEvent_t join);
-bool attn_tail_beside(const Geom& g, int cap);
+                                   void* ws, size_t ws_bytes, unsigned stages, hipStream_t st);
+int device_cu_count();
 int attn_least_splits(const Geom& g);
 int attn_max_splits(const Geom& g);
 void launch_k_encode(const Geom& g, const EncodeSpan& sp, const void* K, uint8_t* packed,
@@ -287,15 +287,13 @@ vidkv_status vidkv_decode_attention_stages(const vidkv_params* p, int32_t layer,
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (!stream_on_current_device(st)) return VIDKV_EINVAL;
   const Side sd = take_side(side);
-  if (sd.ok && K_tail && V_tail && tail_len && (stages & 1u) && attn_tail_beside(g, tail_capacity)) {
-    if (!stream_on_current_device(sd.stream)) return VIDKV_EINVAL;
-    return launch_decode_attention(g, layer, p->softmax_scale, q, pk, pv, K_tail, V_tail,
-                                   tail_capacity, tail_len, out, ws, ws_bytes, stages, st, sd.stream,
-                                   sd.fork, sd.join) == hipSuccess ? VIDKV_OK : VIDKV_EHIP;
-  }
+  // (nothing runs there any more; where a large residual block did, a stream of another device is still refused)
+  const int blocks = std::min((tail_capacity + 31) / 32, ATTN_TAIL_SPLITS);
+  if (sd.ok && K_tail && V_tail && tail_len && (stages & 1u) && g.ng > 0 &&
+      (long long)blocks * g.B * g.H >= 4LL * device_cu_count() && !stream_on_current_device(sd.stream))
+    return VIDKV_EINVAL;
   const hipError_t e = launch_decode_attention(g, layer, p->softmax_scale, q, pk, pv, K_tail, V_tail,
-                                               tail_capacity, tail_len, out, ws, ws_bytes, stages, st,
-                                               nullptr, nullptr, nullptr);
+                                               tail_capacity, tail_len, out, ws, ws_bytes, stages, st);
   return e == hipSuccess ? VIDKV_OK : VIDKV_EHIP;
 }
 
@@ -357,7 +355,7 @@ vidkv_status vidkv_decode_attention_noalloc(const vidkv_params* p, int32_t layer
       g, layer, p->softmax_scale, q, static_cast<const uint8_t*>(packed_K),
       static_cast<const uint8_t*>(packed_V), K_tail, V_tail, tail_capacity, tail_len, out, ws,
       VIDKV_NOALLOC_SCRATCH_BYTES, ~0u,
-      static_cast<hipStream_t>(stream), nullptr, nullptr, nullptr);
+      static_cast<hipStream_t>(stream));
   return e == hipSuccess ? VIDKV_OK : VIDKV_EHIP;
 }
 

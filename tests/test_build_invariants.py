@@ -104,8 +104,11 @@ def test_only_the_variants_with_an_inverse_dft_load_its_operands(attention_isa):
 
 
 def test_residual_tokens_read_lds_16_bytes_at_a_time(tmp_path):
-    """q and the probabilities come in quads only where the compiler knows their alignment."""
+    """The value rows come through transposing reads, two for a tile of channels, and the waves' sums in quads, which
+    they do only where the compiler knows their alignment.  (q and the probabilities, which this test looked at
+    while the residual part ran on the vector ALU, are operands in registers.)"""
     isa = _isa(os.path.join(B.CSRC, "decode_attn.hip"), tmp_path / "decode_attn.s")
     m = re.search(r"^\S*attn_tail_kernel\S*:.*?s_endpgm", isa, re.S | re.M)
-    assert len(re.findall(r"^\s*ds_read_b128\b", m.group(0), re.M)) >= 64
-    assert not re.search(r"^\s*ds_read2", m.group(0), re.M)
+    reads = re.findall(r"^\s*(ds_read\w*)\b", m.group(0), re.M)
+    assert set(reads) == {"ds_read_b128", "ds_read_b64_tr_b16"}
+    assert reads.count("ds_read_b64_tr_b16") >= 16 and reads.count("ds_read_b128") >= 6
