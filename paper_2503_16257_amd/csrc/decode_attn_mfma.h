@@ -433,7 +433,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   // every q element in one batch of independent reads (no branch around a read: absent
   // blocks read a valid block and are zeroed afterwards).
   Op Bn[2][U > 0 ? U : 1];                   // normal channels: -q/16 (FFT) or -q/2 (FULL: -q h) at channels 8 (4u+kb) + e, only in my parity
-  Op Ba[2][UA > 0 ? UA : 1];                 // anomalous: (-q, -q) (FULL: (-q h, -2 q h)) per channel, only in my parity
+  Op Ba[2][UA > 0 ? UA : 1];                 // anomalous: -q h of a quad's 4 channels, then -2 q h (h = 1/2 unless FULL), only in my parity
   float sc2 = a.scale2;                      // sum -> score in the exp2 domain (FULL: the sums are 2 h times the scores')
   {
     uint2 pb[U > 0 ? U : 1];
@@ -457,7 +457,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     for (int ua = 0; ua < UA; ++ua)
 #pragma unroll
       for (int r = 0; r < 4; ++r) qa[ua][r] = qrow[(pq[ua] >> (8 * r)) & 0xFFu];
-    _Float16 cn = (_Float16)(FFT ? -0.0625f : -0.5f), ca0 = (_Float16)-1.0f, ca1 = (_Float16)-1.0f;
+    _Float16 cn = (_Float16)(FFT ? -0.0625f : -0.5f), ca0 = (_Float16)-0.5f, ca1 = (_Float16)-1.0f;
     if (FULL) {
       // h = 1, or 1/2 for a head with an element whose double is no fp16 number
       float mx = 0.0f;
@@ -490,9 +490,12 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const _Float16 v = ok ? qa[ua][r] : (_Float16)0.0f;
-        const uint32_t pr = h2_bits(h2{(_Float16)(v * ca0), (_Float16)(v * ca1)});
-        Ba[0][ua].u[r] = par ? 0u : pr;
-        Ba[1][ua].u[r] = par ? pr : 0u;
+#pragma unroll
+        for (int plane = 0; plane < 2; ++plane) {
+          const _Float16 x = (_Float16)(v * (plane ? ca1 : ca0));
+          Ba[0][ua].v[4 * plane + r] = par ? (_Float16)0.0f : x;
+          Ba[1][ua].v[4 * plane + r] = par ? x : (_Float16)0.0f;
+        }
       }
     }
   }
@@ -617,26 +620,19 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       accRe = mma(Are, Bn[grp][u], accRe);
       accIm = mma(Aim, Bn[grp][u], accIm);
       if (!FFT) {
-        // constant term, rows all equal: (-z)(-q/2) + (-s/2)(-q/2) = q (z + s/2) / 2
+        // constant term, rows all equal: z and s against -q/2 (FULL: -q h), apart: the score takes 2 z + s
         const uint8_t* rec = stage + grp * KREC;
         const int blk = min(4 * u + kb, NB - 1);
-        Op zq, Az, As;
+        Op zq;
         zq.q = *reinterpret_cast<const u32x4*>(rec + OFF_META + (blk * 2 + 1) * 16);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          Az.u[r] = zq.u[r] ^ 0x80008000u;
-          As.u[r] = FULL ? sre.u[r] ^ 0x80008000u : h2_bits(sre.p[r] * h2{(_Float16)0.5f, (_Float16)0.5f}) ^ 0x80008000u;
-        }
-        accCn = mma(Az, Bn[grp][u], accCn);
-        if (FULL) accCs = mma(As, Bn[grp][u], accCs);        // z and s apart: the score takes 2 z + s
-        else accCn = mma(As, Bn[grp][u], accCn);
+        accCn = mma(zq, Bn[grp][u], accCn);
+        accCs = mma(sre, Bn[grp][u], accCs);
       }
     };
-    // anomalous channels: rows = tokens, K = (channel, bit plane); the column operand is
+    // anomalous channels: rows = tokens, K = (bit plane, channel); the column operand is
     // zero outside my parity, so both groups add into S directly
     // scale and zero point of the anomalous K-step n, read one item ahead (n_a = 64, 28 x 8 x 12544
-    // tokens: 570 us a step with the reads in front of their use, 558 so, 551 with the constant's
-    // operands below taken from what is there)
+    // tokens: 570 us a step with the reads in front of their use, 558 so)
     auto load_sz = [&](int n, uint2& as, uint2& az) {
       const int grp = n / (UA > 0 ? UA : 1), ua = n % (UA > 0 ? UA : 1);
       const uint8_t* rec = stage + grp * KREC;
@@ -646,38 +642,28 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     };
     auto anomalous_item = [&](int n, uint2 as, uint2 az) {
       const int grp = n / (UA > 0 ? UA : 1), ua = n % (UA > 0 ? UA : 1);
-      Op s4, z4;                                             // 4 halves each (low 8 bytes used)
-      *reinterpret_cast<uint2*>(&s4) = HOP_SZ ? hop.as[grp][ua] : as;
-      *reinterpret_cast<uint2*>(&z4) = HOP_SZ ? hop.az[grp][ua] : az;
-      uint32_t sp[4];                                        // (s/2, s) (FULL: (s, s)) of channel r
-      // the constant z + 1.5 s: 1.5 s is sp itself, and (z, 0).  FULL, twice that against (q, 2 q): (s, z) and (0, s)
-      Op Ac1, Ac2;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        if (FULL) {
-          sp[r] = h2_bits(h2{s4.v[r], s4.v[r]});
-          Ac1.p[r] = h2{s4.v[r], z4.v[r]};
-          Ac2.u[r] = sp[r] & 0xFFFF0000u;
-        } else {
-          sp[r] = h2_bits(h2{s4.v[r], s4.v[r]} * h2{(_Float16)0.5f, (_Float16)1.0f});
-          Ac1.u[r] = sp[r];
-          Ac2.u[r] = (r & 1) ? z4.u[r >> 1] >> 16 : z4.u[r >> 1] & 0xFFFFu;
-        }
-      }
-      // code bytes of my two tokens (tiles mt = 0, 1): bits (2r, 2r+1) of a byte are the
-      // code of channel r, expanded like the sign words
+      const uint2 s4 = HOP_SZ ? hop.as[grp][ua] : as, z4 = HOP_SZ ? hop.az[grp][ua] : az;   // of the quad's 4 channels
+      // Code bytes of my two tokens (tiles mt = 0, 1): bits (2r, 2r+1) of a byte are the code of channel r.  In
+      // x | x << 14 one plane's bits of channels (0, 1) lie 16 apart, and (2, 3) likewise 4 further up; from
+      // there as with the sign words.  By plane and not by channel, so that scales and zero points are operands as they
+      // stand in the record: an instruction for each of (s/2, s) and (z, 0) before, 64 of a pair's 380 at n_a = 64.
       const uint32_t w0 = wa[grp][ua][0], w1 = wa[grp][ua][1];
-      const uint64_t x2 = ((uint64_t)(w1 | (w1 << 15)) << 32) | (w0 | (w0 << 15));
+      const uint64_t x2 = ((uint64_t)(w1 | (w1 << 14)) << 32) | (w0 | (w0 << 14));
       Op A0, A1;
-      const uint64_t s0 = shl64<15>(x2), s1 = shl64<13>(x2), s2 = shl64<11>(x2), s3 = shl64<9>(x2);
-      A0.u[0] = ((uint32_t)s0 & 0x80008000u) | sp[0]; A1.u[0] = ((uint32_t)(s0 >> 32) & 0x80008000u) | sp[0];
-      A0.u[1] = ((uint32_t)s1 & 0x80008000u) | sp[1]; A1.u[1] = ((uint32_t)(s1 >> 32) & 0x80008000u) | sp[1];
-      A0.u[2] = ((uint32_t)s2 & 0x80008000u) | sp[2]; A1.u[2] = ((uint32_t)(s2 >> 32) & 0x80008000u) | sp[2];
-      A0.u[3] = ((uint32_t)s3 & 0x80008000u) | sp[3]; A1.u[3] = ((uint32_t)(s3 >> 32) & 0x80008000u) | sp[3];
+      const uint64_t s0 = shl64<15>(x2), s1 = shl64<11>(x2), s2 = shl64<14>(x2), s3 = shl64<10>(x2);
+      A0.u[0] = ((uint32_t)s0 & 0x80008000u) | s4.x; A1.u[0] = ((uint32_t)(s0 >> 32) & 0x80008000u) | s4.x;
+      A0.u[1] = ((uint32_t)s1 & 0x80008000u) | s4.y; A1.u[1] = ((uint32_t)(s1 >> 32) & 0x80008000u) | s4.y;
+      A0.u[2] = ((uint32_t)s2 & 0x80008000u) | s4.x; A1.u[2] = ((uint32_t)(s2 >> 32) & 0x80008000u) | s4.x;
+      A0.u[3] = ((uint32_t)s3 & 0x80008000u) | s4.y; A1.u[3] = ((uint32_t)(s3 >> 32) & 0x80008000u) | s4.y;
       S[0] = mma(A0, Ba[grp][ua], S[0]);
       S[1] = mma(A1, Ba[grp][ua], S[1]);
-      accC = mma(Ac1, Ba[grp][ua], accC);                    // rows all equal
-      accC = mma(Ac2, Ba[grp][ua], accC);
+      // the constant z + 1.5 s (FULL, twice h times it): rows all equal, s against both planes' operands, z against the second's
+      const h8 q8 = Ba[grp][ua].v;
+      const h4 q1 = __builtin_shufflevector(q8, q8, 0, 1, 2, 3), q2 = __builtin_shufflevector(q8, q8, 4, 5, 6, 7);
+      const h4 sv4 = __builtin_bit_cast(h4, s4), zv4 = __builtin_bit_cast(h4, z4);
+      accC = __builtin_amdgcn_mfma_f32_16x16x16f16(sv4, q1, accC, 0, 0, 0);
+      accC = __builtin_amdgcn_mfma_f32_16x16x16f16(sv4, q2, accC, 0, 0, 0);
+      accC = __builtin_amdgcn_mfma_f32_16x16x16f16(zv4, q2, accC, 0, 0, 0);
     };
     // table entries of value tile m, both groups: byte (m & 1) of word m >> 1 holds the even
     // token slots 0, 2, 4, 6, byte 2 + (m & 1) the odd slots 1, 3, 5, 7
@@ -772,7 +758,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
           S[0][i] += accRe[i];
           S[1][i] += accIm[i];
         }
-        cst_n = FULL ? 2.0f * accCn[0] + accCs[0] : 2.0f * accCn[0];
+        cst_n = -fmaf(2.0f, accCn[0], accCs[0]);
       }
       if (IDFT && FULL) {
         // k-slot (kb, i) of the matrix against row 4 kb + i of the sums, one i at a time.  Coefficient 4 kb + i is
