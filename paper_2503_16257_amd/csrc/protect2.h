@@ -1,7 +1,7 @@
 // Protected value rows at 2 bits (Alg. 2, STPQuant), as a piece that a launch of its own or a part
 // of another one runs.
 #pragma once
-#include "vidkv_common.h"
+#include "select_values.h"
 
 namespace vidkv {
 
@@ -19,20 +19,56 @@ struct Protect2Args {
   const int32_t* idx;
   uint8_t* out;
   long long total;            // records
+  const uint32_t* mask;       // where IDX is not there yet
+  int ngc;
 };
 
 typedef u32x4 Protect2Lds[64];       // the 1024 bytes of codes of a wave's record
 
+// FROM_MASK (up to FEW_MAX_GROUPS groups a sequence): the record's tokens are found in MASK.
+template <bool FROM_MASK = false>
 __device__ __forceinline__ void protect2_part(const Protect2Args& a, long long rec_id, Protect2Lds& lds) {
   const int lane = threadIdx.x & 63;
   const long long hd = rec_id / a.npg;
   const int pg = (int)(rec_id - hd * a.npg);
   const int b = (int)((hd / a.H) % a.B);
   const int cnt = min(G, a.n_s - pg * G);
+  int32_t* found = reinterpret_cast<int32_t*>(&lds[0]);
+  if (FROM_MASK) {
+    constexpr int W = FEW_MAX_GROUPS / 64;             // my words: W lane ..
+    const uint32_t* mk = a.mask + (size_t)b * a.ngc;
+    const int ng = a.T / G;
+    uint32_t w[W];
+    int c = 0;
+#pragma unroll
+    for (int i = 0; i < W; ++i) w[i] = mk[min(W * lane + i, ng - 1)];
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+      if (W * lane + i >= ng) w[i] = 0u;
+      c += __popc(w[i]);
+    }
+    int r = wave_scan<1>(c) - c - pg * G;              // rank of my first protected token inside the record
+    if (lane < G) found[lane] = a.T;                   // (a list with repeats has fewer tokens: clamped below)
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+      uint32_t m = r + __popc(w[i]) > 0 && r < G ? w[i] : 0u;
+      int at = r;
+      while (m) {
+        const int t = __ffs(m) - 1;
+        m &= m - 1;
+        if (at >= 0 && at < G) found[at] = (W * lane + i) * G + t;
+        ++at;
+      }
+      r += __popc(w[i]);
+    }
+    asm volatile("" ::: "memory");
+  }
   // rows beyond the last one repeat it: every load is valid and changes neither min nor max
   // (an index list with repeated or out-of-range entries leaves the end of IDX unwritten:
   // whatever is there is clamped into the tensor, such rows are never read back)
-  const int tok = min(max(a.idx[(size_t)b * a.n_s + pg * G + min(lane & 31, cnt - 1)], 0), a.T - 1);
+  const int last = min(lane & 31, cnt - 1);
+  const int tok = min(max(FROM_MASK ? found[last] : a.idx[(size_t)b * a.n_s + pg * G + last], 0), a.T - 1);
   const uint32_t* head = reinterpret_cast<const uint32_t*>(a.V + hd * (long long)a.T * D) + lane;
   uint32_t xr[G];
 #pragma unroll

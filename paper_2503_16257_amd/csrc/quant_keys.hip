@@ -32,6 +32,20 @@ __global__ __launch_bounds__(1024, 8) void k_range_select_kernel(const u32x4* __
   range_part(K, T, chunks, ws, on ? id % chunks : 0, on ? id / chunks : 0, threadIdx.x & 255, on, lds.range[sub]);
 }
 
+// Calls with few groups: the ranges of all chunks, and a workgroup for the protected tokens of each group (or
+// each sequence's list), in one launch.
+__global__ __launch_bounds__(1024) void k_few_first_kernel(const u32x4* __restrict__ K, int T, int chunks, int nsel,
+                                                           _Float16* __restrict__ ws, OneSelArgs sel) {
+  __shared__ union { FewRangeLds range; FewSelLds sel; } lds;
+  const int id = blockIdx.x;
+  if (id < nsel) {
+    if (sel.scores) few_select(sel, id / sel.ng, id % sel.ng, lds.sel);
+    else few_list(sel, id, lds.sel);
+    return;
+  }
+  few_range(K, T, chunks, ws, (id - nsel) % chunks, (id - nsel) / chunks, lds.range);
+}
+
 // Channel selection as a launch of its own.  grid nheads, block 1024.
 __global__ __launch_bounds__(1024) void k_select_kernel(const _Float16* __restrict__ ws,
                                                         int chunks, int n_a,
@@ -178,6 +192,14 @@ void launch_k_range_select(const Geom& g, const void* K, void* ws, const float* 
   hipLaunchKernelGGL(k_range_select_kernel, dim3(g.B + (total + 3) / 4), dim3(1024), 0, st,
                      reinterpret_cast<const u32x4*>(K), g.T, g.range_chunks, total, g.B,
                      reinterpret_cast<_Float16*>(ws), one_sel_args(g, scores, idx, packed_V));
+}
+
+void launch_k_few_first(const Geom& g, const void* K, void* ws, const float* scores, const int32_t* idx,
+                        uint8_t* packed_V, hipStream_t st) {
+  const int nsel = g.n_s == 0 ? 0 : scores ? g.B * g.ng : g.B;
+  hipLaunchKernelGGL(k_few_first_kernel, dim3(nsel + (unsigned)(g.nheads * g.range_chunks)), dim3(1024), 0, st,
+                     reinterpret_cast<const u32x4*>(K), g.T, g.range_chunks, nsel, reinterpret_cast<_Float16*>(ws),
+                     one_sel_args(g, scores, idx, packed_V));
 }
 
 // ---------------------------------------------------------------------------

@@ -20,6 +20,7 @@
 // The record is assembled in LDS and written with 16-byte stores.
 #include "protect2.h"
 #include "quant_values_enc.h"
+#include "select_keys.h"
 
 namespace vidkv {
 
@@ -118,7 +119,8 @@ __device__ __forceinline__ void range32(const Op& X, float& lo, float& nh) {
 // z = min.
 // EXTRA: rows of the grid that do something else of the same call, 1: from row x_rows on, code the
 // protected value rows (2 bits), 2: the first x_rows, the value coding pass (a flush: both blocks are
-// small, one launch).
+// small, one launch), 3: the first x_rows, the value coding pass of a call with few groups, the next as many the keys, whose
+// workgroups select their head's channels themselves, then the protected value rows (2 bits).
 // SPLIT: one group per workgroup, its tiles shared out among the four waves (and a flush's values likewise), for
 // calls that leave compute units idle anyway: a group's tiles one after another are then most of the kernel
 // after the first load.  (Whole calls: one head x 1568 tokens 18.4 us, 17.0 so; 28 flushes of 4 heads x 128 tokens 5 %
@@ -143,7 +145,18 @@ __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restr
                         ve.rec_out, ve.rows_out, ve.mask, ve.rank, ve.mark_rank, blockIdx.x, blockIdx.y, tile4);
     return;
   }
-  const long long hd = blockIdx.y - (EXTRA == 2 ? x_rows : 0);
+  if (EXTRA == 3 && (int)blockIdx.y >= 2 * x_rows) {
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long long id = 4 * ((long long)(blockIdx.y - 2 * x_rows) * gridDim.x + blockIdx.x) + w;
+    if (id < p2.total) protect2_part<true>(p2, id, reinterpret_cast<Protect2Lds*>(&tile4[0][0])[w]);
+    return;
+  }
+  if (EXTRA == 3 && (int)blockIdx.y < x_rows) {
+    v_encode_part<false, true, true>(ve.V, ve.T, ve.ng, ve.B, ve.H, ve.n_s, ve.gamma, 1, ve.ngc, 0, ve.mask, ve.rank,
+                        ve.rec_out, ve.rows_out, nullptr, ve.rank, -1, blockIdx.x, blockIdx.y, tile4, ve.idx);
+    return;
+  }
+  const long long hd = blockIdx.y - (EXTRA >= 2 ? x_rows : 0);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int x16 = lane & 15, kb = lane >> 4;
@@ -169,6 +182,12 @@ __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restr
   u32x4 pre[NPRE];
 #pragma unroll
   for (int i = 0; i < NPRE; ++i) pre[i] = __builtin_nontemporal_load(head + ((long long)g * G + row0) * 16 + lane + 64 * i);
+  FewChanLds& chan = reinterpret_cast<FewChanLds&>(tile4[1]);
+  static_assert(sizeof(FewChanLds) <= 3 * sizeof(EncTile), "beside the one tile that is in use");
+  if (EXTRA == 3) {
+    few_channels(ve.range_ws, ve.chunks, n_a, g == 0 ? const_cast<uint8_t*>(perm_g) : nullptr, hd, chan);
+    __syncthreads();
+  }
   __builtin_amdgcn_sched_barrier(0);                 // (these first, and their first use behind the set-up: 1 % of a call with 4 heads x 196000)
 
   // Channel tile j: anomalous tiles first (16 anomalous channels each, in PERM
@@ -182,7 +201,8 @@ __global__ __launch_bounds__(256) void k_encode_mfma_kernel(const u32x4* __restr
     const bool an = j < NTa;
     const int off = an ? 16 * j + x16 : 16 * (j - NTa) + x16;
     const bool valid = j < NT && (an ? off < n_a : off < n_n);
-    chofs[jj] = valid ? 2 * (int)perm_g[hd * D + (an ? off : n_a + off)] : 0;
+    const int at = an ? off : n_a + off;
+    chofs[jj] = valid ? 2 * (int)(EXTRA == 3 ? chan.perm[at] : perm_g[hd * D + at]) : 0;
   }
 
   // DFT operand from the precomputed table: slot x16 of tile tt, k-slots = tokens
@@ -348,8 +368,8 @@ static void launch_one(bool use_fft, dim3 grid, hipStream_t st, const u32x4* k4,
 
 template <int EXTRA, bool SPLIT>
 static void launch_any(const Geom& g, const EncodeSpan& sp, int gx, const void* K, uint8_t* packed, bool use_fft,
-                       hipStream_t st, int rows, const Protect2Args& p2, const VEncArgs& ve) {
-  const dim3 grid(gx, (unsigned)(sp.heads + rows));
+                       hipStream_t st, int rows, const Protect2Args& p2, const VEncArgs& ve, int more = 0) {
+  const dim3 grid(gx, (unsigned)(sp.heads + rows + more));
   const u32x4* k4 = reinterpret_cast<const u32x4*>(K);
   const uint8_t* perm = packed + g.k_perm + sp.head0 * D;
   uint8_t* rec = packed + g.k_rec + (size_t)sp.head0 * g.ngc * g.krec;
@@ -410,6 +430,35 @@ bool launch_flush_encode(const Geom& g, const EncodeSpan& sp, float gamma, const
     launch_any<2, true>(g, sp, sp.ng, K, packed_K, g.use_fft, st, (int)sp.heads, Protect2Args{}, ve);
   else
     launch_any<2, false>(g, sp, (sp.ng + K_GPB - 1) / K_GPB, K, packed_K, g.use_fft, st, (int)sp.heads, Protect2Args{}, ve);
+  return true;
+}
+
+// A whole call with few groups in two launches: ranges and MASK, then both coding passes and 2-bit rows, whose
+// workgroups count ranks and select channels for themselves.  What bounds such a call is launches and latencies one after
+// another: of three launches and 17.3 us for one head x 1568 tokens, 10 % fp16 rows, the token selection by one workgroup
+// took 9; so 10.9 (4.1 + 7.2 on their own).  2-bit rows 18.7 -> 11.2; 4 heads x 3136 tokens 21.1 -> 13.6, 4 x 6272 22.6 -> 19.2, nothing protected
+// 17.3 -> 14.8; 1008 groups 21.3 -> 16.5.  Every workgroup's own selection costs more than it saves from about five groups a
+// compute unit on (1372 groups: 22.5 against 22.7, without rows 19.2 against 21.5; 1568: 24.8 against 28.6), and the
+// counting, quadratic in the sequence, from about 8192 tokens on each compute unit's share (256 groups of one sequence 20.2 -> 17.0, of two
+// 22.4 -> 22.9).  false: too many, nothing done.
+void launch_k_few_first(const Geom& g, const void* K, void* ws, const float* scores, const int32_t* idx,
+                        uint8_t* packed_V, hipStream_t st);
+
+bool launch_few_groups(const Geom& g, float gamma, const void* K, const void* V, void* ws, const float* scores,
+                       const int32_t* idx, uint8_t* packed_K, uint8_t* packed_V, hipStream_t st) {
+  const long long cus = device_cu_count();
+  if (g.ng > FEW_MAX_GROUPS || g.nheads * g.ng > 4 * cus) return false;
+  if (g.n_s > 0 && scores && (long long)g.B * g.ng * g.T > 8192 * cus) return false;
+  launch_k_few_first(g, K, ws, scores, idx, packed_V, st);
+  const EncodeSpan all{g.T, g.ng, 0, g.nheads, 0};
+  VEncArgs ve = v_encode_args(g, all, g.n_s, gamma, V, packed_V);
+  ve.range_ws = reinterpret_cast<const _Float16*>(ws);
+  ve.chunks = g.range_chunks;
+  ve.idx = reinterpret_cast<int32_t*>(packed_V + g.v_idx);
+  const bool rows2 = g.n_s > 0 && g.sal_bits == 2;
+  const Protect2Args p2 = rows2 ? protect2_args(g, V, packed_V) : Protect2Args{};
+  const long long more = rows2 ? ((p2.total + 3) / 4 + g.ng - 1) / g.ng : 0;
+  launch_any<3, true>(g, all, g.ng, K, packed_K, g.use_fft, st, (int)g.nheads, p2, ve, (int)more);
   return true;
 }
 

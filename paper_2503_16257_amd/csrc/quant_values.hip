@@ -300,7 +300,8 @@ __global__ __launch_bounds__(256) void v_protect2_kernel(Protect2Args a) {
 
 Protect2Args protect2_args(const Geom& g, const void* V, uint8_t* packed) {
   return Protect2Args{reinterpret_cast<const _Float16*>(V), g.T, g.B, g.H, g.n_s, g.npg,
-                      reinterpret_cast<const int32_t*>(packed + g.v_idx), packed + g.v_rows, g.nheads * g.npg};
+                      reinterpret_cast<const int32_t*>(packed + g.v_idx), packed + g.v_rows, g.nheads * g.npg,
+                      reinterpret_cast<const uint32_t*>(packed + g.v_mask), g.ngc};
 }
 
 // MASK and RANK of groups appended behind the prefill tokens: none of their

@@ -16,6 +16,7 @@
 //   v < -alpha   : that flag AND the sign bit of v
 #pragma once
 #include "mfma_util.h"
+#include "select_values.h"
 
 namespace vidkv {
 
@@ -37,19 +38,24 @@ struct VEncArgs {
   uint8_t* rec_out;
   u32x4* rows_out;            // NULL: protected rows are not copied
   int mark_rank;              // >= 0: also write MASK = 0 and RANK = mark_rank of the groups
+  // calls with few groups: the partial ranges of the keys of the same call, IDX
+  const _Float16* range_ws;
+  int chunks;
+  int32_t* idx;
 };
 
 typedef u32x4 EncTile[32 * VENC_ROW / 16];
 
 // The groups of workgroup bx of head hd (256 threads).  MARK: also MASK = 0 and RANK = mark_rank of the
 // groups when mark_rank >= 0 (a flushed block).  SPLIT: group bx alone, a quarter of its channels each wave.
-template <bool MARK, bool SPLIT = false>
+// FEW (with SPLIT): only MASK is there yet; the rank of the group is counted, RANK and IDX are written.
+template <bool MARK, bool SPLIT = false, bool FEW = false>
 __device__ __forceinline__ void v_encode_part(const u32x4* __restrict__ V, int T, int ng, int B, int H, int n_s,
                                               float gamma, int gpb, int ngc, int g_out0,
                                               const uint32_t* __restrict__ mask, const uint32_t* __restrict__ rank,
                                               uint8_t* __restrict__ rec_out, u32x4* __restrict__ rows_out,
                                               uint32_t* mark_mask, uint32_t* mark_ranks, int mark_rank, int bx,
-                                              long long hd, EncTile (&tile4)[4]) {
+                                              long long hd, EncTile (&tile4)[4], int32_t* idx = nullptr) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int x16 = lane & 15, kb = lane >> 4;
@@ -75,6 +81,19 @@ __device__ __forceinline__ void v_encode_part(const u32x4* __restrict__ V, int T
   int g = SPLIT ? g_begin : g_begin + wave;
   if (g < g_end) prefetch(g);
 
+  uint32_t few_m = 0, few_r0 = 0;
+  if (FEW && n_s > 0) {                                    // (asked for behind the tile, looked at in front of it)
+    const uint32_t* mk = mask + (size_t)b * ngc;
+    uint32_t w[FEW_MAX_GROUPS / 64];
+    few_m = mk[g];
+#pragma unroll
+    for (int i = 0; i < FEW_MAX_GROUPS / 64; ++i) w[i] = mk[min(64 * i + lane, g)];
+    int c = 0;
+#pragma unroll
+    for (int i = 0; i < FEW_MAX_GROUPS / 64; ++i) c += 64 * i + lane < g ? __popc(w[i]) : 0;
+    few_r0 = __builtin_amdgcn_readlane(wave_scan<1>(c), 63);
+  }
+
   for (; g < g_end; g += 4) {
     {
       uint8_t* wdst = reinterpret_cast<uint8_t*>(&tile4[SPLIT ? 0 : wave][0]) + (row0 + kb) * VENC_ROW + x16 * 16;
@@ -85,7 +104,10 @@ __device__ __forceinline__ void v_encode_part(const u32x4* __restrict__ V, int T
     else if (g + 4 < g_end) prefetch(g + 4);
 
     uint32_t m = 0, r0 = 0;
-    if (n_s > 0) {
+    if (FEW) {
+      m = __builtin_amdgcn_readfirstlane(few_m);
+      r0 = few_r0;
+    } else if (n_s > 0) {
       m = __builtin_amdgcn_readfirstlane(mask[(size_t)b * ngc + g]);
       r0 = __builtin_amdgcn_readfirstlane(rank[(size_t)b * ngc + g]);
     }
@@ -166,7 +188,23 @@ __device__ __forceinline__ void v_encode_part(const u32x4* __restrict__ V, int T
           reinterpret_cast<uint32_t*>(rec)[4 * lane + mp] = words[mp];
           if (kb == 0) reinterpret_cast<uint32_t*>(rec + 1024)[4 * x16 + mp] = sc16[mp];
         }
-      continue;                                            // (a flushed block has no protected rows)
+      if (!FEW) continue;                                  // (a flushed block has no protected rows)
+      if (n_s > 0 && wave == 0 && hd % H == 0 && hd / H < B) {
+        if (lane == 0) mark_ranks[(size_t)b * ngc + g] = r0;
+        const int at = (int)r0 + __popc(m & ((1u << (lane & 31)) - 1u));
+        if (lane < 32 && ((m >> lane) & 1u) && at < n_s) idx[(size_t)b * n_s + at] = g * G + lane;
+      }
+      // protected rows among the eight that my wave brought
+      uint32_t w = rows_out ? (m >> row0) & 0xFFu : 0u, r = r0 + __popc(m & ((1u << row0) - 1u));
+      while (w) {
+        const int t = row0 + __ffs(w) - 1;
+        w &= w - 1;
+        if (lane < 16)
+          *(rows_out + (hd * n_s + r) * 16 + lane) =
+              *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint8_t*>(&tile4[0][0]) + t * VENC_ROW + lane * 16);
+        ++r;
+      }
+      continue;
     }
     u32x4 wv;
     wv[0] = words[0]; wv[1] = words[1]; wv[2] = words[2]; wv[3] = words[3];

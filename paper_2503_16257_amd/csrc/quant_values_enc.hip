@@ -37,7 +37,7 @@ VEncArgs v_encode_args(const Geom& g, const EncodeSpan& sp, int n_s, float gamma
   return VEncArgs{reinterpret_cast<const u32x4*>(V), sp.in_tokens, sp.ng, g.B, g.H, n_s, gamma, 4, g.ngc, sp.g_out0,
                   reinterpret_cast<uint32_t*>(packed + g.v_mask), reinterpret_cast<uint32_t*>(packed + g.v_rank),
                   packed + g.v_rec + (size_t)sp.head0 * g.ngc * VREC,
-                  g.sal_bits == 16 ? reinterpret_cast<u32x4*>(packed + g.v_rows) : nullptr, -1};
+                  g.sal_bits == 16 ? reinterpret_cast<u32x4*>(packed + g.v_rows) : nullptr, -1, nullptr, 0, nullptr};
 }
 
 void launch_v_encode(const Geom& g, const EncodeSpan& sp, int n_s, float gamma, const void* V,

@@ -78,6 +78,55 @@ __device__ __forceinline__ void range_part(const u32x4* __restrict__ K, int T, i
   }
 }
 
+// The same by 1024 threads, 8 pieces in flight each: a chunk in one go, for calls with few of them.
+struct FewRangeLds {
+  h2 mn[16][16][4], mx[16][16][4];
+};
+
+__device__ __forceinline__ void few_range(const u32x4* __restrict__ K, int T, int chunks, _Float16* __restrict__ ws,
+                                          int chunk, long long hd, FewRangeLds& lds) {
+  const int tid = threadIdx.x, col = tid & 15, row = tid >> 4;
+  const int t0 = chunk * RANGE_CHUNK, t1 = min(T, t0 + RANGE_CHUNK);
+  const u32x4* base = K + (hd * T) * 16 + col;
+  const _Float16 big = (_Float16)65504.0f;
+  U4H x[RANGE_CHUNK / 64];
+#pragma unroll
+  for (int k = 0; k < RANGE_CHUNK / 64; ++k)         // (a row past the end repeats the first one)
+    x[k].u = base[(long long)(t0 + row + 64 * k < t1 ? t0 + row + 64 * k : t0) * 16];
+  h2 mn[4], mx[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { mn[i] = h2{big, big}; mx[i] = h2{-big, -big}; }
+#pragma unroll
+  for (int k = 0; k < RANGE_CHUNK / 64; ++k)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      mn[i] = __builtin_elementwise_min(mn[i], x[k].h[i]);
+      mx[i] = __builtin_elementwise_max(mx[i], x[k].h[i]);
+    }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int d = 16; d <= 32; d <<= 1) {
+      mn[i] = __builtin_elementwise_min(mn[i], __builtin_bit_cast(h2, __shfl_xor(__builtin_bit_cast(int, mn[i]), d, 64)));
+      mx[i] = __builtin_elementwise_max(mx[i], __builtin_bit_cast(h2, __shfl_xor(__builtin_bit_cast(int, mx[i]), d, 64)));
+    }
+  if ((tid & 63) < 16) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { lds.mn[tid >> 6][col][i] = mn[i]; lds.mx[tid >> 6][col][i] = mx[i]; }
+  }
+  __syncthreads();
+  if (tid < 128) {                                   // two channels' minima, or maxima
+    const int c2 = tid & 63;
+    h2 v = tid < 64 ? h2{big, big} : h2{-big, -big};
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      const h2 y = (tid < 64 ? lds.mn : lds.mx)[w][c2 >> 2][c2 & 3];
+      v = tid < 64 ? __builtin_elementwise_min(v, y) : __builtin_elementwise_max(v, y);
+    }
+    *reinterpret_cast<h2*>(ws + ((hd * chunks + chunk) * 2) * D + 2 * tid) = v;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Channel selection: R_c = float(max) - float(min); the n_a largest (ties to
 // the lower channel) are anomalous.  perm = anomalous ascending, then normal
@@ -176,6 +225,76 @@ __device__ __forceinline__ void select_channels(const _Float16* __restrict__ ws,
     if (wave == 1) below += cnt0;
     const int pos = an ? below : n_a + (c - below);
     perm[hd * D + pos] = (uint8_t)c;
+  }
+}
+
+// The same by 256 threads where a head has few chunks: into LDS, for a workgroup that goes on with it, and to perm where
+// that is not null.  The caller's barrier lies behind it.
+struct FewChanLds {
+  h2 mn[16][16][4], mx[16][16][4];
+  float R[D];
+  int rank[2][D];
+  int cnt0;
+  uint8_t perm[D];
+};
+
+__device__ __forceinline__ void few_channels(const _Float16* __restrict__ ws, int chunks, int n_a, uint8_t* perm,
+                                             long long hd, FewChanLds& lds) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = tid & 15, slice = tid >> 4;
+  const u32x4* p4 = reinterpret_cast<const u32x4*>(ws + hd * chunks * 2 * D) + col;
+  const _Float16 big = (_Float16)65504.0f;
+  h2 mn[4], mx[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { mn[i] = h2{big, big}; mx[i] = h2{-big, -big}; }
+  for (int k = slice; k < chunks; k += 16) {         // (once, but for a device of many compute units)
+    U4H a, b;
+    a.u = p4[(k * 2) * 16];
+    b.u = p4[(k * 2 + 1) * 16];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      mn[i] = __builtin_elementwise_min(mn[i], a.h[i]);
+      mx[i] = __builtin_elementwise_max(mx[i], b.h[i]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { lds.mn[slice][col][i] = mn[i]; lds.mx[slice][col][i] = mx[i]; }
+  __syncthreads();
+  const int c = tid & (D - 1), half = tid >> 7;
+  if (half == 0) {
+    const int c8 = c >> 3, e = c & 7;
+    _Float16 lo = big, hi = -big;
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+      const _Float16 a = lds.mn[s][c8][e >> 1][e & 1];
+      const _Float16 b = lds.mx[s][c8][e >> 1][e & 1];
+      lo = a < lo ? a : lo;
+      hi = b > hi ? b : hi;
+    }
+    lds.R[c] = (float)hi - (float)lo;
+  }
+  __syncthreads();
+  const float r = lds.R[c];
+  int rank = 0;
+#pragma unroll
+  for (int j = 0; j < D / 2; j += 4) {
+    const float4 rj = *reinterpret_cast<const float4*>(&lds.R[64 * half + j]);
+    const float x[4] = {rj.x, rj.y, rj.z, rj.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) rank += (x[e] > r || (x[e] == r && 64 * half + j + e < c)) ? 1 : 0;
+  }
+  lds.rank[half][c] = rank;
+  __syncthreads();
+  int an = 0;
+  if (half == 0) an = lds.rank[0][c] + lds.rank[1][c] < n_a ? 1 : 0;
+  const unsigned long long bal = __ballot(an);
+  int below = __popcll(bal & ((1ull << lane) - 1ull));
+  if (tid == 0) lds.cnt0 = __popcll(bal);
+  __syncthreads();
+  if (half == 0) {
+    if (wave == 1) below += lds.cnt0;
+    const int pos = an ? below : n_a + (c - below);
+    lds.perm[pos] = (uint8_t)c;
+    if (perm) perm[hd * D + pos] = (uint8_t)c;
   }
 }
 

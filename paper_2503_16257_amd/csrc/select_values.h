@@ -18,6 +18,8 @@ constexpr int ONE_MAX_T = ONE_THREADS * 4 * ONE_Q;        // 32768 tokens
 constexpr int ONE_COPIES = 32;                            // histogram copies, by lane: one for each bank
 constexpr int ONE_BINS = 256;
 
+constexpr int FEW_MAX_GROUPS = 256;                       // of a sequence, where a call has few groups in all
+
 struct OneSelLds {
   int hist[ONE_BINS][ONE_COPIES];                         // index list: the mask (ONE_MAX_T / 32 words)
   int wsum[16], lsum[2][16];
@@ -212,6 +214,70 @@ __device__ __forceinline__ void select_one(const OneSelArgs& a, int b, OneSelLds
       a.rank[(size_t)b * a.ngc + (p >> 3)] = (uint32_t)first;
     }
   }
+}
+
+// The same for few groups, one workgroup of 1024 threads each: the rank of every token of group g by counting, 32 tokens
+// against 32 parts of the keys.  Only MASK is written; RANK and IDX come with the value coding.  Quadratic, but spread over as
+// many workgroups as there are groups, and one pass instead of four digits' and their barriers by a single one:
+// (1568 tokens: the launch with the range pass of one head 9.0 us with select_one, 4.1 so.)
+struct FewSelLds {
+  u32x4 key[FEW_MAX_GROUPS * 8];
+  int cnt[16][32];
+};
+
+__device__ __forceinline__ void few_select(const OneSelArgs& a, int b, int g, FewSelLds& s) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int np = a.T >> 2;
+  const float4* sc4 = reinterpret_cast<const float4*>(a.scores + (size_t)b * a.T);
+  for (int p = tid; p < np; p += ONE_THREADS) {
+    const float4 v = sc4[p];
+    s.key[p] = u32x4{fkey(v.x), fkey(v.y), fkey(v.z), fkey(v.w)};
+  }
+  __syncthreads();
+  const int t = 32 * g + (lane & 31), part = 2 * wave + (lane >> 5), at = g >> 2;
+  const uint32_t k = reinterpret_cast<const uint32_t*>(&s.key[0])[t];
+  // tokens before mine that have my key or a larger one, tokens behind it that have a larger one.  Of pieces part + 32 i
+  // those with i < at lie before the group, those with i > at behind it
+  int c = 0;
+  for (int i = 0; i < at; ++i) {
+    const u32x4 v = s.key[part + 32 * i];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c += v[e] >= k ? 1 : 0;
+  }
+  if (part + 32 * at < np) {
+    const u32x4 v = s.key[part + 32 * at];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c += v[e] > k || (v[e] == k && 4 * (part + 32 * at) + e < t) ? 1 : 0;
+  }
+  for (int p = part + 32 * (at + 1); p < np; p += 32) {
+    const u32x4 v = s.key[p];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c += v[e] > k ? 1 : 0;
+  }
+  c += __shfl_xor(c, 32, 64);
+  if (lane < 32) s.cnt[wave][lane] = c;
+  __syncthreads();
+  if (wave == 0) {
+    int r = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) r += s.cnt[i][lane & 31];
+    const uint32_t w = (uint32_t)__ballot(r < a.n_s);
+    if (lane == 0) a.mask[(size_t)b * a.ngc + g] = w;
+  }
+}
+
+// MASK of sequence b from its index list (an index outside the cache is ignored), 0 in the room behind the tokens.
+__device__ __forceinline__ void few_list(const OneSelArgs& a, int b, FewSelLds& s) {
+  uint32_t* m = reinterpret_cast<uint32_t*>(&s.key[0]);
+  const int tid = threadIdx.x;
+  if (tid < FEW_MAX_GROUPS) m[tid] = 0;
+  __syncthreads();
+  for (int i = tid; i < a.n_s; i += ONE_THREADS) {
+    const int t = a.idx_in[(size_t)b * a.n_s + i];
+    if (t >= 0 && t < a.T) atomicOr(&m[t >> 5], 1u << (t & 31));
+  }
+  __syncthreads();
+  for (int g = tid; g < a.ngc; g += ONE_THREADS) a.mask[(size_t)b * a.ngc + g] = g < a.ng ? m[g] : 0u;
 }
 
 OneSelArgs one_sel_args(const Geom& g, const float* scores, const int32_t* idx, uint8_t* packed);

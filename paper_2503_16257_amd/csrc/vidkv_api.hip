@@ -29,6 +29,8 @@ void launch_k_range_select(const Geom& g, const void* K, void* ws, const float* 
                            uint8_t* packed_V, hipStream_t st);
 bool launch_v_encode_select(const Geom& g, float gamma, const void* V, uint8_t* packed_V, const void* ws,
                             uint8_t* packed_K, hipStream_t st);
+bool launch_few_groups(const Geom& g, float gamma, const void* K, const void* V, void* ws, const float* scores,
+                       const int32_t* idx, uint8_t* packed_K, uint8_t* packed_V, hipStream_t st);
 bool launch_k_encode_protect2(const Geom& g, const void* K, uint8_t* packed_K, const void* V, uint8_t* packed_V,
                               hipStream_t st);
 void launch_v_protect2(const Geom& g, const void* V, uint8_t* packed, hipStream_t st);
@@ -227,6 +229,8 @@ vidkv_status vidkv_quantize_kv(const vidkv_params* p, const void* K, const void*
     return launch_quantize_values(g, p->gamma, V, sc, ix, pv, ws_v, 2u, st) == hipSuccess
                ? VIDKV_OK : VIDKV_EHIP;
   }
+  if (g.metric == 0 && launch_few_groups(g, p->gamma, K, V, ws_k, sc, ix, pk, pv, st))
+    return hipGetLastError() == hipSuccess ? VIDKV_OK : VIDKV_EHIP;
   bool good = true;
   if (g.metric == 0 && one) {
     launch_k_range_select(g, K, ws_k, sc, ix, pv, st);
