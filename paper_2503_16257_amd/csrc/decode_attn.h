@@ -78,7 +78,7 @@ __device__ __forceinline__ void put_partial(const AttnArgs& a, int split, int kv
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
     const bool any = m4[w] != -INFINITY;                      // an empty wave's sums are never looked at
-    const float f = any ? exp2f(m4[w] - M) : 0.0f;
+    const float f = any ? __builtin_amdgcn_exp2f(m4[w] - M) : 0.0f;
     L += any ? f * l4[w] : 0.0f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[i] += any ? f * x[w][i] : 0.0f;

@@ -87,7 +87,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
     float acc = 0.0f, L = 0.0f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const float w = sM[i] == -INFINITY ? 0.0f : exp2f(sM[i] - Mx);
+      const float w = sM[i] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(sM[i] - Mx);
       acc += w * so[i][c >> 2][c & 3];
       L += w * sl_[i];
     }

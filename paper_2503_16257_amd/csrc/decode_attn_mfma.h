@@ -591,7 +591,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       }
     }
     S[0] = zero; S[1] = zero;
-    f4 accRe = zero, accIm = zero, accCn = zero, accCs = zero, accC = zero;   // my column's group only: the operands are masked
+    f4 accRe = zero, accIm = zero, accCn = zero, accCs = zero, accC[3] = {zero, zero, zero};   // my column's group only: the operands are masked
 
     // ---- the work items
     // scales of the normal K-step n = (group, u)
@@ -661,9 +661,10 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       const h8 q8 = Ba[grp][ua].v;
       const h4 q1 = __builtin_shufflevector(q8, q8, 0, 1, 2, 3), q2 = __builtin_shufflevector(q8, q8, 4, 5, 6, 7);
       const h4 sv4 = __builtin_bit_cast(h4, s4), zv4 = __builtin_bit_cast(h4, z4);
-      accC = __builtin_amdgcn_mfma_f32_16x16x16f16(sv4, q1, accC, 0, 0, 0);
-      accC = __builtin_amdgcn_mfma_f32_16x16x16f16(sv4, q2, accC, 0, 0, 0);
-      accC = __builtin_amdgcn_mfma_f32_16x16x16f16(zv4, q2, accC, 0, 0, 0);
+      // (three sums, so that none waits for the product in front of it)
+      accC[0] = __builtin_amdgcn_mfma_f32_16x16x16f16(sv4, q1, accC[0], 0, 0, 0);
+      accC[1] = __builtin_amdgcn_mfma_f32_16x16x16f16(sv4, q2, accC[1], 0, 0, 0);
+      accC[2] = __builtin_amdgcn_mfma_f32_16x16x16f16(zv4, q2, accC[2], 0, 0, 0);
     };
     // table entries of value tile m, both groups: byte (m & 1) of word m >> 1 holds the even
     // token slots 0, 2, 4, 6, byte 2 + (m & 1) the odd slots 1, 3, 5, 7
@@ -800,7 +801,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
           S[mt] = mma(Wh[mt], Yl, S[mt]);
         }
       }
-      if (UA > 0) cst = accC[0];                 // = -(sum q (z + 1.5 s)) (FULL: 2 h times it, like S and cst_n)
+      if (UA > 0) cst = accC[0][0] + accC[1][0] + accC[2][0];                 // = -(sum q (z + 1.5 s)) (FULL: 2 h times it, like S and cst_n)
       if (!FFT) cst -= cst_n;
     }
   };
@@ -978,8 +979,8 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       pr[i] = __builtin_amdgcn_exp2f(t[i]);
-      l_run += pr[i];
     }
+    l_run += ((pr[0] + pr[1]) + (pr[2] + pr[3])) + ((pr[4] + pr[5]) + (pr[6] + pr[7]));
     // probabilities as the A operand of P V (row = my column).  The k-slots of that product
     // are ordered (0,2), (4,6), (1,3), (5,7) in token-slot numbers: the order in which two
     // trit bytes expand (even slots, then odd slots).
