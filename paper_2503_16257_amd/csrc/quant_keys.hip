@@ -2,48 +2,46 @@
 // top-n_a channel selection, and per 32-token group the 2-bit uniform code
 // (Eq. 4) of the selected channels and the sign bits of a 32-point real DFT
 // (Eq. 5) of the others.
+#include <algorithm>
+
 #include "select_keys.h"
 #include "select_values.h"
 
 namespace vidkv {
 
-// Pass 1 as a launch of its own.  grid (range_chunks, nheads), block 256.
-__global__ __launch_bounds__(256) void k_range_kernel(const u32x4* __restrict__ K, int T,
-                                                      int chunks, _Float16* __restrict__ ws) {
-  __shared__ RangeLds lds;
-  range_part(K, T, chunks, ws, blockIdx.x, blockIdx.y, threadIdx.x, true, lds);
+// Pass 1 as a launch of its own.  grid (range_chunks, nheads).  (256 threads, a quarter of a chunk's pieces at a time: 4 heads
+// x 196000 tokens 131.5 us a whole call, 128.8 so; 28 x 4 x 6272 103.5 and 100.8.)
+__global__ __launch_bounds__(1024, 8) void k_range_kernel(const u32x4* __restrict__ K, int T,
+                                                          int chunks, _Float16* __restrict__ ws) {
+  __shared__ ChunkRangeLds lds;
+  range_chunk(K, T, chunks, ws, blockIdx.x, blockIdx.y, lds);
 }
 
-// Pass 1 with the protected-token selection of the same call in the first B workgroups: a chain of
-// dependent work that needs no bandwidth, beside a pass that needs nothing else.  Workgroups of
-// 1024 threads, four chunks each.
-// (28 x 6272 tokens: range pass 29 us, then six selection launches of 4.7 us; both in one 31.4.)
-__global__ __launch_bounds__(1024, 8) void k_range_select_kernel(const u32x4* __restrict__ K, int T,
-                                                                 int chunks, int total, int B,
+// Pass 1 with the protected-token selection of the same call in the first nsel workgroups: a chain of
+// dependent work that needs no bandwidth, beside a pass that needs nothing else.  few: a workgroup for the tokens of each
+// group (or each sequence's list), which leaves RANK and IDX to the value coding; otherwise one a sequence.  Workgroups of
+// 1024 threads, a chunk each, asked for in one go; four: four chunks each, a quarter of the requests at a time.
+// (Whole calls, four chunks each and one: 28 x 4 heads x 6272 tokens, 20 % 2-bit rows 112.8 -> 107; 28 x 4 x 1568 37.4 -> 36.3.)
+__global__ __launch_bounds__(1024, 8) void k_range_select_kernel(const u32x4* __restrict__ K, int T, int chunks, int total,
+                                                                 int nsel, int few, int four,
                                                                  _Float16* __restrict__ ws, OneSelArgs sel) {
-  __shared__ union { RangeLds range[4]; OneSelLds one; } lds;
-  if ((int)blockIdx.x < B) {
-    select_one(sel, blockIdx.x, lds.one);
-    return;
-  }
-  const int sub = threadIdx.x >> 8;
-  const int id = (blockIdx.x - B) * 4 + sub;
-  const bool on = id < total;
-  range_part(K, T, chunks, ws, on ? id % chunks : 0, on ? id / chunks : 0, threadIdx.x & 255, on, lds.range[sub]);
-}
-
-// Calls with few groups: the ranges of all chunks, and a workgroup for the protected tokens of each group (or
-// each sequence's list), in one launch.
-__global__ __launch_bounds__(1024) void k_few_first_kernel(const u32x4* __restrict__ K, int T, int chunks, int nsel,
-                                                           _Float16* __restrict__ ws, OneSelArgs sel) {
-  __shared__ union { FewRangeLds range; FewSelLds sel; } lds;
+  __shared__ union { ChunkRangeLds range; RangeLds range4[4]; FewSelLds few; OneSelLds one; } lds;
   const int id = blockIdx.x;
   if (id < nsel) {
-    if (sel.scores) few_select(sel, id / sel.ng, id % sel.ng, lds.sel);
-    else few_list(sel, id, lds.sel);
+    __builtin_amdgcn_s_setprio(3);                   // (what the rest of the workgroups do waits for memory anyway)
+    if (!few) select_one(sel, id, lds.one);
+    else if (sel.scores) few_select(sel, id / sel.ng, id % sel.ng, lds.few);
+    else few_list(sel, id, lds.few);
     return;
   }
-  few_range(K, T, chunks, ws, (id - nsel) % chunks, (id - nsel) / chunks, lds.range);
+  const int w = id - nsel;
+  if (four) {
+    const int sub = threadIdx.x >> 8, c = 4 * w + sub;
+    const bool on = c < total;
+    range_part(K, T, chunks, ws, on ? c % chunks : 0, on ? c / chunks : 0, threadIdx.x & 255, on, lds.range4[sub]);
+  } else {
+    range_chunk(K, T, chunks, ws, w % chunks, w / chunks, lds.range);
+  }
 }
 
 // Channel selection as a launch of its own.  grid nheads, block 1024.
@@ -185,21 +183,28 @@ __global__ __launch_bounds__(1024) void k_metric_select_kernel(const double* __r
 void launch_k_encode(const Geom& g, const EncodeSpan& sp, const void* K, uint8_t* packed,
                      bool use_fft, hipStream_t st);
 
-// The range pass (Range metric) and the protected-token selection of short sequences in one launch.
-void launch_k_range_select(const Geom& g, const void* K, void* ws, const float* scores, const int32_t* idx,
-                           uint8_t* packed_V, hipStream_t st) {
-  const int total = (int)(g.nheads * g.range_chunks);            // T <= ONE_MAX_T: at most 65535 * 64
-  hipLaunchKernelGGL(k_range_select_kernel, dim3(g.B + (total + 3) / 4), dim3(1024), 0, st,
-                     reinterpret_cast<const u32x4*>(K), g.T, g.range_chunks, total, g.B,
-                     reinterpret_cast<_Float16*>(ws), one_sel_args(g, scores, idx, packed_V));
+// Counting the tokens with larger scores, quadratic in the sequence, against one workgroup's four digits: where the
+// selection is what takes time (alone) up to 8192 tokens on each compute unit's share (256 groups of one sequence, whole
+// calls: 20.2 us with the digits, 17.0; of two 22.4 and 22.9); beside a long range pass, which waits for its workgroups, up to
+// 2560 (8 x 4 heads x 1568 tokens 22.7 -> 20.5; 16 x 4 x 1568 28.4 and 29.7, 28 x 4 x 6272 107 and 111).
+bool few_selection(const Geom& g, bool scores, bool alone) {
+  return g.ng <= FEW_MAX_GROUPS && (!scores || (long long)g.B * g.ng * g.T <= (alone ? 8192LL : 2560LL) * device_cu_count());
 }
 
-void launch_k_few_first(const Geom& g, const void* K, void* ws, const float* scores, const int32_t* idx,
-                        uint8_t* packed_V, hipStream_t st) {
-  const int nsel = g.n_s == 0 ? 0 : scores ? g.B * g.ng : g.B;
-  hipLaunchKernelGGL(k_few_first_kernel, dim3(nsel + (unsigned)(g.nheads * g.range_chunks)), dim3(1024), 0, st,
-                     reinterpret_cast<const u32x4*>(K), g.T, g.range_chunks, nsel, reinterpret_cast<_Float16*>(ws),
-                     one_sel_args(g, scores, idx, packed_V));
+// The range pass (Range metric) and the protected-token selection of short sequences (or none) in one launch.
+// few: few_selection(), and the value coding finds RANK and IDX.
+void launch_k_range_select(const Geom& g, const void* K, void* ws, const float* scores, const int32_t* idx,
+                           uint8_t* packed_V, bool few, hipStream_t st) {
+  const int nsel = g.n_s == 0 ? 0 : few && scores ? g.B * g.ng : g.B;
+  const long long total = g.nheads * g.range_chunks, cus = device_cu_count();
+  // Where the selection of a long sequence is the longer part, four chunks a workgroup leave it a compute unit to
+  // itself (4 x 4 heads x 25088 tokens 67 us a call, with a workgroup for each chunk passing through beside it 74; 8 x 32768 53 and 60)
+  const bool four = nsel > 0 && !few && (g.T > 32 * FEW_MAX_GROUPS || nsel >= cus / 4) && total <= 4 * cus;
+  const long long wgs = four ? (total + 3) / 4 : total;
+  // T <= ONE_MAX_T: at most 65535 * 64 chunks
+  hipLaunchKernelGGL(k_range_select_kernel, dim3((unsigned)(nsel + wgs)), dim3(1024), 0, st,
+                     reinterpret_cast<const u32x4*>(K), g.T, g.range_chunks, (int)total, nsel, few ? 1 : 0, four ? 1 : 0,
+                     reinterpret_cast<_Float16*>(ws), one_sel_args(g, scores, idx, packed_V));
 }
 
 // ---------------------------------------------------------------------------
@@ -238,7 +243,7 @@ hipError_t launch_quantize_keys(const Geom& g, const void* K, uint8_t* packed, v
     return hipGetLastError();
   }
   if (stages & 1u)
-    hipLaunchKernelGGL(k_range_kernel, gr1, dim3(256), 0, st, k4, g.T, g.range_chunks, w);
+    hipLaunchKernelGGL(k_range_kernel, gr1, dim3(1024), 0, st, k4, g.T, g.range_chunks, w);
   if (stages & 2u)
     hipLaunchKernelGGL(k_select_kernel, dim3((unsigned)g.nheads), dim3(1024), 0, st, w,
                        g.range_chunks, g.n_a, packed + g.k_perm);

@@ -438,18 +438,16 @@ bool launch_flush_encode(const Geom& g, const EncodeSpan& sp, float gamma, const
 // another: of three launches and 17.3 us for one head x 1568 tokens, 10 % fp16 rows, the token selection by one workgroup
 // took 9; so 10.9 (4.1 + 7.2 on their own).  2-bit rows 18.7 -> 11.2; 4 heads x 3136 tokens 21.1 -> 13.6, 4 x 6272 22.6 -> 19.2, nothing protected
 // 17.3 -> 14.8; 1008 groups 21.3 -> 16.5.  Every workgroup's own selection costs more than it saves from about five groups a
-// compute unit on (1372 groups: 22.5 against 22.7, without rows 19.2 against 21.5; 1568: 24.8 against 28.6), and the
-// counting, quadratic in the sequence, from about 8192 tokens on each compute unit's share (256 groups of one sequence 20.2 -> 17.0, of two
-// 22.4 -> 22.9).  false: too many, nothing done.
-void launch_k_few_first(const Geom& g, const void* K, void* ws, const float* scores, const int32_t* idx,
-                        uint8_t* packed_V, hipStream_t st);
+// compute unit on (1372 groups: 22.5 against 22.7, without rows 19.2 against 21.5; 1568: 24.8 against 28.6).
+// false: too many, or a selection that is not few_selection(); nothing done.
+void launch_k_range_select(const Geom& g, const void* K, void* ws, const float* scores, const int32_t* idx,
+                           uint8_t* packed_V, bool few, hipStream_t st);
+bool few_selection(const Geom& g, bool scores, bool alone);
 
 bool launch_few_groups(const Geom& g, float gamma, const void* K, const void* V, void* ws, const float* scores,
                        const int32_t* idx, uint8_t* packed_K, uint8_t* packed_V, hipStream_t st) {
-  const long long cus = device_cu_count();
-  if (g.ng > FEW_MAX_GROUPS || g.nheads * g.ng > 4 * cus) return false;
-  if (g.n_s > 0 && scores && (long long)g.B * g.ng * g.T > 8192 * cus) return false;
-  launch_k_few_first(g, K, ws, scores, idx, packed_V, st);
+  if (g.nheads * g.ng > 4LL * device_cu_count() || !few_selection(g, scores != nullptr, true)) return false;
+  launch_k_range_select(g, K, ws, scores, idx, packed_V, true, st);
   const EncodeSpan all{g.T, g.ng, 0, g.nheads, 0};
   VEncArgs ve = v_encode_args(g, all, g.n_s, gamma, V, packed_V);
   ve.range_ws = reinterpret_cast<const _Float16*>(ws);

@@ -48,7 +48,7 @@ typedef u32x4 EncTile[32 * VENC_ROW / 16];
 
 // The groups of workgroup bx of head hd (256 threads).  MARK: also MASK = 0 and RANK = mark_rank of the
 // groups when mark_rank >= 0 (a flushed block).  SPLIT: group bx alone, a quarter of its channels each wave.
-// FEW (with SPLIT): only MASK is there yet; the rank of the group is counted, RANK and IDX are written.
+// FEW (one group a wave): only MASK is there yet; the rank of the group is counted, RANK and IDX are written.
 template <bool MARK, bool SPLIT = false, bool FEW = false>
 __device__ __forceinline__ void v_encode_part(const u32x4* __restrict__ V, int T, int ng, int B, int H, int n_s,
                                               float gamma, int gpb, int ngc, int g_out0,
@@ -82,7 +82,7 @@ __device__ __forceinline__ void v_encode_part(const u32x4* __restrict__ V, int T
   if (g < g_end) prefetch(g);
 
   uint32_t few_m = 0, few_r0 = 0;
-  if (FEW && n_s > 0) {                                    // (asked for behind the tile, looked at in front of it)
+  if (FEW && n_s > 0 && g < g_end) {                       // (asked for behind the tile, looked at in front of it)
     const uint32_t* mk = mask + (size_t)b * ngc;
     uint32_t w[FEW_MAX_GROUPS / 64];
     few_m = mk[g];
@@ -180,6 +180,11 @@ __device__ __forceinline__ void v_encode_part(const u32x4* __restrict__ V, int T
       mark_mask[(size_t)b * ngc + g_out0 + g] = 0;
       mark_ranks[(size_t)b * ngc + g_out0 + g] = (uint32_t)mark_rank;
     }
+    if (FEW && n_s > 0 && (!SPLIT || wave == 0) && hd % H == 0 && hd / H < B) {     // layer 0, head 0
+      if (lane == 0) mark_ranks[(size_t)b * ngc + g] = r0;
+      const int at = (int)r0 + __popc(m & ((1u << (lane & 31)) - 1u));
+      if (lane < 32 && ((m >> lane) & 1u) && at < n_s) idx[(size_t)b * n_s + at] = g * G + lane;
+    }
     uint8_t* rec = rec_out + (hd * ngc + g_out0 + g) * (long long)VREC;
     if (SPLIT) {
 #pragma unroll
@@ -189,11 +194,6 @@ __device__ __forceinline__ void v_encode_part(const u32x4* __restrict__ V, int T
           if (kb == 0) reinterpret_cast<uint32_t*>(rec + 1024)[4 * x16 + mp] = sc16[mp];
         }
       if (!FEW) continue;                                  // (a flushed block has no protected rows)
-      if (n_s > 0 && wave == 0 && hd % H == 0 && hd / H < B) {
-        if (lane == 0) mark_ranks[(size_t)b * ngc + g] = r0;
-        const int at = (int)r0 + __popc(m & ((1u << (lane & 31)) - 1u));
-        if (lane < 32 && ((m >> lane) & 1u) && at < n_s) idx[(size_t)b * n_s + at] = g * G + lane;
-      }
       // protected rows among the eight that my wave brought
       uint32_t w = rows_out ? (m >> row0) & 0xFFu : 0u, r = r0 + __popc(m & ((1u << row0) - 1u));
       while (w) {

@@ -78,13 +78,14 @@ __device__ __forceinline__ void range_part(const u32x4* __restrict__ K, int T, i
   }
 }
 
-// The same by 1024 threads, 8 pieces in flight each: a chunk in one go, for calls with few of them.
-struct FewRangeLds {
+// The same by 1024 threads, 8 pieces in flight each: a chunk in one go, two workgroups on a compute unit.  Plain loads: the
+// coding pass finds some of it in the caches (streaming ones: 28 x 4 heads x 6272 tokens 109 us a call, 107 so).
+struct ChunkRangeLds {
   h2 mn[16][16][4], mx[16][16][4];
 };
 
-__device__ __forceinline__ void few_range(const u32x4* __restrict__ K, int T, int chunks, _Float16* __restrict__ ws,
-                                          int chunk, long long hd, FewRangeLds& lds) {
+__device__ __forceinline__ void range_chunk(const u32x4* __restrict__ K, int T, int chunks, _Float16* __restrict__ ws,
+                                          int chunk, long long hd, ChunkRangeLds& lds) {
   const int tid = threadIdx.x, col = tid & 15, row = tid >> 4;
   const int t0 = chunk * RANGE_CHUNK, t1 = min(T, t0 + RANGE_CHUNK);
   const u32x4* base = K + (hd * T) * 16 + col;

@@ -26,9 +26,11 @@ void launch_v_encode(const Geom& g, const EncodeSpan& sp, int n_s, float gamma, 
                      uint8_t* packed, hipStream_t st);
 bool one_workgroup_selection(const Geom& g);
 void launch_k_range_select(const Geom& g, const void* K, void* ws, const float* scores, const int32_t* idx,
-                           uint8_t* packed_V, hipStream_t st);
-bool launch_v_encode_select(const Geom& g, float gamma, const void* V, uint8_t* packed_V, const void* ws,
-                            uint8_t* packed_K, hipStream_t st);
+                           uint8_t* packed_V, bool few, hipStream_t st);
+bool few_selection(const Geom& g, bool scores, bool alone);
+bool v_encode_select_fits(const Geom& g);
+void launch_v_encode_select(const Geom& g, float gamma, const void* V, uint8_t* packed_V, const void* ws,
+                            uint8_t* packed_K, bool few, hipStream_t st);
 bool launch_few_groups(const Geom& g, float gamma, const void* K, const void* V, void* ws, const float* scores,
                        const int32_t* idx, uint8_t* packed_K, uint8_t* packed_V, hipStream_t st);
 bool launch_k_encode_protect2(const Geom& g, const void* K, uint8_t* packed_K, const void* V, uint8_t* packed_V,
@@ -232,15 +234,19 @@ vidkv_status vidkv_quantize_kv(const vidkv_params* p, const void* K, const void*
   if (g.metric == 0 && launch_few_groups(g, p->gamma, K, V, ws_k, sc, ix, pk, pv, st))
     return hipGetLastError() == hipSuccess ? VIDKV_OK : VIDKV_EHIP;
   bool good = true;
-  if (g.metric == 0 && one) {
-    launch_k_range_select(g, K, ws_k, sc, ix, pv, st);
+  const bool fits = v_encode_select_fits(g), together = g.metric == 0 && one;
+  const bool few = together && fits && few_selection(g, sc != nullptr, false);
+  if (together) {
+    launch_k_range_select(g, K, ws_k, sc, ix, pv, few, st);
   } else {
     if (sel) good = launch_quantize_values(g, p->gamma, V, sc, ix, pv, ws_v, 1u, st) == hipSuccess;
     good = launch_quantize_keys(g, K, pk, ws_k, g.metric == 0 ? 1u : 3u, st) == hipSuccess && good;
   }
   if (!good) return VIDKV_EHIP;
   const EncodeSpan all{g.T, g.ng, 0, g.nheads, 0};
-  if (g.metric != 0 || !launch_v_encode_select(g, p->gamma, V, pv, ws_k, pk, st)) {
+  if (g.metric == 0 && fits) {
+    launch_v_encode_select(g, p->gamma, V, pv, ws_k, pk, few, st);
+  } else {
     if (g.metric == 0) good = launch_quantize_keys(g, K, pk, ws_k, 2u, st) == hipSuccess;
     launch_v_encode(g, all, g.n_s, p->gamma, V, pv, st);
   }
