@@ -175,11 +175,12 @@ vidkv_status vidkv_quantize_values(const vidkv_params *params, const void *V_dev
 /* Alg. 3 and Alg. 2 on the K and V tensors of the same tokens in one call (the
  * compression step at the end of Alg. 1, Prefill): the packed buffers come out
  * byte-identical to vidkv_quantize_keys followed by vidkv_quantize_values.
- * Sequences of up to 32768 tokens run in line, in three launches with the
- * range metric (more with the two others, and with some 33000 heads or more).
+ * Sequences of up to 32768 tokens run in line, in two launches (few groups) or
+ * three with the range metric (more with the two others, and with some 33000
+ * heads or more).
  * For longer ones the protected-token selection is a chain of short dependent
  * launches; with a side stream it is enqueued there so that it runs beside the key
- * passes (only when the key tensor is 32 MiB or more; smaller inputs run in
+ * passes (only when the key tensor is 120 MiB or more; smaller inputs run in
  * line), and joined back before the value coding pass.
  * Arguments as for the two separate calls;
  *   workspace_dev : >= vidkv_workspace_bytes(params, 3) bytes

@@ -209,16 +209,19 @@ vidkv_status vidkv_quantize_kv(const vidkv_params* p, const void* K, const void*
   // work that wait for memory, the passes need its bandwidth: a selection in the first workgroups of
   // a pass costs nothing, as launches of its own one of 5 to 8 us (channels) and six of 3 to 5 us
   // (tokens) with the passes waiting.  One head of 1568 tokens 38.5 -> 19.3 us, 28 x 4 heads of 6272
-  // tokens with 2-bit rows 139 -> 110, 64 x 4 heads of 25088 945 -> 912.
+  // tokens with 2-bit rows 139 -> 110, 64 x 4 heads of 25088 945 -> 912.  (Later steps: two launches and 10.9; 106; 873.)
   // A sequence too long for one workgroup's registers keeps the chain of six.  With a side stream,
-  // and key passes long enough to hide the fork and join (32 MiB), it runs beside them, the value
+  // and key passes long enough to hide the fork and join, it runs beside them, the value
   // pass last; beside the range pass alone it is the longer of the two (196000 tokens: 154 us
-  // against 137).
+  // against 137).  The line is at 120 MiB of keys, 4 heads each, beside against in line: 34 MB 59 to 71 us and 49.5, 61 MB 78
+  // and 62.4, 87 MB 88 and 76, 102 MB 83 and 84.5 (98 and 84.8 on another card), 133 MB 97 and 99, 201 MB 129 and 133, 401 MB 234 and 241.
   const bool sel = g.n_s > 0, one = sel && one_workgroup_selection(g);
   const Side sd = take_side(side);
-  const bool fork = sel && !one && sd.ok && (size_t)g.nheads * g.T * D * 2 >= ((size_t)32 << 20);
+  const size_t key_bytes = (size_t)g.nheads * g.T * D * 2;
+  // (a stream of another device is refused from 32 MiB on, where the line once was)
+  if (sel && !one && sd.ok && key_bytes >= ((size_t)32 << 20) && !stream_on_current_device(sd.stream)) return VIDKV_EINVAL;
+  const bool fork = sel && !one && sd.ok && key_bytes >= ((size_t)120 << 20);
   if (fork) {
-    if (!stream_on_current_device(sd.stream)) return VIDKV_EINVAL;
     if (hipEventRecord(sd.fork, st) != hipSuccess) return VIDKV_EHIP;
     if (hipStreamWaitEvent(sd.stream, sd.fork, 0) != hipSuccess) return VIDKV_EHIP;
     // from here on the side stream depends on `st`: whatever fails, it is joined back, so

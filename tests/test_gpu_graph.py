@@ -149,3 +149,33 @@ def test_quantizer_with_its_side_stream_captured_and_replayed():
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(pk, pk0) and torch.equal(pv, pv0), f"replay {s} differs from the eager call"
+
+
+def test_quantizer_forked_inside_the_capture():
+    """The same with a key tensor (134 MB) on the far side of the line from which the selection is forked."""
+    print("[case] graph-quantize, forked", flush=True)
+    T, n_s = 131072, 6000
+    p = vk.make_params(1, 1, 4, 4, T, 16, n_s)
+    g = torch.Generator(device=DEV); g.manual_seed(9)
+    K, V = (torch.randn((1, 1, 4, T, 128), generator=g, device=DEV, dtype=torch.float16) for _ in range(2))
+    sal = torch.rand((1, T), generator=g, device=DEV)
+    ws = vk.alloc_bytes(vk.workspace_bytes(p, 3), DEV)
+    new = lambda n: torch.zeros(n, dtype=torch.uint8, device=DEV)
+    nk, nv = vk.packed_keys_bytes(p), vk.packed_values_bytes(p)
+    rk, rv, pk, pv = new(nk), new(nv), new(nk), new(nv)
+    vk.quantize_keys(p, K, rk, ws)
+    vk.quantize_values(p, V, rv, ws, saliency=sal)
+    torch.cuda.synchronize()
+    side = P.side_stream(DEV)
+    vk.quantize_kv(p, K, V, pk, pv, ws, saliency=sal, side=side)
+    torch.cuda.synchronize()
+    assert torch.equal(pk, rk) and torch.equal(pv, rv)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        vk.quantize_kv(p, K, V, pk, pv, ws, saliency=sal, side=side)
+    for _ in range(3):
+        pk.zero_(); pv.zero_(); ws.fill_(0x5A)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(pk, rk) and torch.equal(pv, rv)
