@@ -136,11 +136,10 @@ int attn_max_splits(const Geom& g) {
 // The costs below are in 0.1 us: of a round of workgroups, two resident per compute unit, that take s
 // pairs of groups one after another in each of 4 waves; 6 us to get going and finish, 2.2 us per pair where a
 // compute unit has one workgroup, 3.5 where it has two.  Fitted at n_a = 64 to a kernel that took that long (the
-// split chosen cost 0.6 % more than the fastest tried on average, 16 % at most) and kept: the present one gets
-// going 1.4 us earlier and spends fewer instructions on a pair.  On it, n_a = 64, 16 with fp16 rows, 96, and 64 with 2-bit rows, 1 to 64
-// sequences x 4 heads of 192 to 12544 tokens with 0 to 512 residual ones, 420 shapes: 1.8 % on average, more than 10 % at
-// 28 of them, 44 % at most (40 sequences x 1568 tokens with 256 residual ones: 39.2 us, 27.3 with all of it in
-// one launch); none of the 420 is slower than on the kernel it was fitted to, 13 % less on average.
+// split chosen cost 0.6 % more than the fastest tried on average, 16 % at most) and kept: later ones get
+// going earlier and spend fewer instructions on a pair, and choose as well (n_a = 64, 16 with fp16 rows, 96, and 64 with
+// 2-bit rows, 1 to 64 sequences x 4 heads of 192 to 12544 tokens, 420 shapes: 1.8 % over the fastest tried; with residual
+// tokens: attn_plan()).
 static long long main_cost(int s, int w, int cus) {
   // a 64-bit product: thousands of rounds of thousands of pairs
   return (long long)((w + 2 * cus - 1) / (2 * cus)) * (60 + (long long)s * (w <= cus ? 22 : 35));

@@ -146,14 +146,15 @@ static __device__ const __align__(256) IdftTab kIdftTab = make_idft_tab();
 //     (fp16 hi + lo parts are 0 below 2^-25 of the running maximum, where the softmax denominator
 //     still counts the token: 196000 tokens at 2^-25.1 of one other lost 0.5 % of the output);
 //   * protected rows' probabilities as hi + 2^-18 lo, two fp16 numbers;
-//   * q enters as it is, or halved where the head has an element of 2^15 or more; what the other
-//     counts take as s/2 and s here is s against q and 2 q, so neither loses bits where it is subnormal;
+//   * q enters as it is and doubled, or half of both where the head has an element of 2^15 or more, where the other
+//     counts take q/2 and q against the two bits' s: neither loses bits where it is subnormal;
 //   * the inverse DFT runs on v_mfma_f32_16x16x4_f32, on the fp32 sums and an fp32 matrix.
 // The other counts have always had fp16 probabilities and -q/16.  What it costs is 48 instead of 32 products
 // of a pair's values (the three parts are used as they are, in all rows: with the operand rows masked by parity, and
 // the second part in the rows that the mask leaves, a third fewer products took more registers than there are) and
 // 256 instead of 96 matrix-pipe cycles of its inverse DFT: n_a = 96, nothing protected, one layer of 196000 tokens
-// 30.7 -> 33.7 us, 4 x 8 x 12544 tokens 86.6 -> 94.4, 2 x 3136 tokens 11.7 -> 11.5 (the 32-bit kernel: 309, 684, 24.2).
+// 30.7 -> 33.7 us, 4 x 8 x 12544 tokens 86.6 -> 94.4, 2 x 3136 tokens 11.7 -> 11.5 (the 32-bit kernel: 309, 684, 24.2; by bit
+// plane, since: 31.8, 79.8 and 8.8 with 100 residual tokens).
 // (The DFT's products between the anomalous items instead of behind them: 34.0, 95.1.)
 // TAIL: workgroups with split >= nsplit of the grid take residual tokens.  A variant of its own,
 // since the branch costs the others 3 % (28 x 8 x 12544 tokens, n_a = 64: 597 us a step against 577).
