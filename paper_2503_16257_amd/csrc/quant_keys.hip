@@ -11,10 +11,11 @@ namespace vidkv {
 
 // Pass 1 as a launch of its own.  grid (range_chunks, nheads).  (256 threads, a quarter of a chunk's pieces at a time: 4 heads
 // x 196000 tokens 131.5 us a whole call, 128.8 so; 28 x 4 x 6272 103.5 and 100.8.)
+template <bool STREAM>
 __global__ __launch_bounds__(1024, 8) void k_range_kernel(const u32x4* __restrict__ K, int T,
                                                           int chunks, _Float16* __restrict__ ws) {
   __shared__ ChunkRangeLds lds;
-  range_chunk(K, T, chunks, ws, blockIdx.x, blockIdx.y, lds);
+  range_chunk<STREAM>(K, T, chunks, ws, blockIdx.x, blockIdx.y, lds);
 }
 
 // Pass 1 with the protected-token selection of the same call in the first nsel workgroups: a chain of
@@ -40,7 +41,7 @@ __global__ __launch_bounds__(1024, 8) void k_range_select_kernel(const u32x4* __
     const bool on = c < total;
     range_part(K, T, chunks, ws, on ? c % chunks : 0, on ? c / chunks : 0, threadIdx.x & 255, on, lds.range4[sub]);
   } else {
-    range_chunk(K, T, chunks, ws, w % chunks, w / chunks, lds.range);
+    range_chunk<false>(K, T, chunks, ws, w % chunks, w / chunks, lds.range);
   }
 }
 
@@ -243,7 +244,10 @@ hipError_t launch_quantize_keys(const Geom& g, const void* K, uint8_t* packed, v
     return hipGetLastError();
   }
   if (stages & 1u)
-    hipLaunchKernelGGL(k_range_kernel, gr1, dim3(1024), 0, st, k4, g.T, g.range_chunks, w);
+    // streaming loads where K is larger than the last-level cache (256 MB) and the coding pass finds nothing of it there
+    // (80 heads x 76192 tokens 869.3 us a call with plain ones, 865.5 so; 4 x 196000, 201 MB: 132.5 and 136 the other way)
+    hipLaunchKernelGGL((size_t)g.nheads * g.T * D * 2 > ((size_t)256 << 20) ? k_range_kernel<true> : k_range_kernel<false>, gr1,
+                       dim3(1024), 0, st, k4, g.T, g.range_chunks, w);
   if (stages & 2u)
     hipLaunchKernelGGL(k_select_kernel, dim3((unsigned)g.nheads), dim3(1024), 0, st, w,
                        g.range_chunks, g.n_a, packed + g.k_perm);

@@ -84,6 +84,7 @@ struct ChunkRangeLds {
   h2 mn[16][16][4], mx[16][16][4];
 };
 
+template <bool STREAM>
 __device__ __forceinline__ void range_chunk(const u32x4* __restrict__ K, int T, int chunks, _Float16* __restrict__ ws,
                                           int chunk, long long hd, ChunkRangeLds& lds) {
   const int tid = threadIdx.x, col = tid & 15, row = tid >> 4;
@@ -92,8 +93,10 @@ __device__ __forceinline__ void range_chunk(const u32x4* __restrict__ K, int T, 
   const _Float16 big = (_Float16)65504.0f;
   U4H x[RANGE_CHUNK / 64];
 #pragma unroll
-  for (int k = 0; k < RANGE_CHUNK / 64; ++k)         // (a row past the end repeats the first one)
-    x[k].u = base[(long long)(t0 + row + 64 * k < t1 ? t0 + row + 64 * k : t0) * 16];
+  for (int k = 0; k < RANGE_CHUNK / 64; ++k) {       // (a row past the end repeats the first one)
+    const u32x4* at = base + (long long)(t0 + row + 64 * k < t1 ? t0 + row + 64 * k : t0) * 16;
+    x[k].u = STREAM ? __builtin_nontemporal_load(at) : *at;
+  }
   h2 mn[4], mx[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) { mn[i] = h2{big, big}; mx[i] = h2{-big, -big}; }
