@@ -10,7 +10,7 @@
 namespace vidkv {
 
 // Pass 1 as a launch of its own.  grid (range_chunks, nheads).  (256 threads, a quarter of a chunk's pieces at a time: 4 heads
-// x 196000 tokens 131.5 us a whole call, 128.8 so; 28 x 4 x 6272 103.5 and 100.8.)
+// x 196000 tokens 131.1 us a whole call, 129.3 so.)
 template <bool STREAM>
 __global__ __launch_bounds__(1024, 8) void k_range_kernel(const u32x4* __restrict__ K, int T,
                                                           int chunks, _Float16* __restrict__ ws) {
@@ -22,7 +22,7 @@ __global__ __launch_bounds__(1024, 8) void k_range_kernel(const u32x4* __restric
 // dependent work that needs no bandwidth, beside a pass that needs nothing else.  few: a workgroup for the tokens of each
 // group (or each sequence's list), which leaves RANK and IDX to the value coding; otherwise one a sequence.  Workgroups of
 // 1024 threads, a chunk each, asked for in one go; four: four chunks each, a quarter of the requests at a time.
-// (Whole calls, four chunks each and one: 28 x 4 heads x 6272 tokens, 20 % 2-bit rows 112.8 -> 107; 28 x 4 x 1568 37.4 -> 36.3.)
+template <bool STREAM>
 __global__ __launch_bounds__(1024, 8) void k_range_select_kernel(const u32x4* __restrict__ K, int T, int chunks, int total,
                                                                  int nsel, int few, int four,
                                                                  _Float16* __restrict__ ws, OneSelArgs sel) {
@@ -39,9 +39,9 @@ __global__ __launch_bounds__(1024, 8) void k_range_select_kernel(const u32x4* __
   if (four) {
     const int sub = threadIdx.x >> 8, c = 4 * w + sub;
     const bool on = c < total;
-    range_part(K, T, chunks, ws, on ? c % chunks : 0, on ? c / chunks : 0, threadIdx.x & 255, on, lds.range4[sub]);
+    range_part<STREAM>(K, T, chunks, ws, on ? c % chunks : 0, on ? c / chunks : 0, threadIdx.x & 255, on, lds.range4[sub]);
   } else {
-    range_chunk<false>(K, T, chunks, ws, w % chunks, w / chunks, lds.range);
+    range_chunk<STREAM>(K, T, chunks, ws, w % chunks, w / chunks, lds.range);
   }
 }
 
@@ -184,6 +184,19 @@ __global__ __launch_bounds__(1024) void k_metric_select_kernel(const double* __r
 void launch_k_encode(const Geom& g, const EncodeSpan& sp, const void* K, uint8_t* packed,
                      bool use_fft, hipStream_t st);
 
+// Streaming loads in the range pass, in each of its forms, where K and as many bytes of V are more than the last-level cache
+// (256 MB): plain ones then push out V, which the value coding is about to read, below it they leave K for the key coding.
+// Whole calls, plain / streaming, us, on the same buffers again and again, on rotating ones, behind a kernel that wrote K,
+// then V, and one that wrote V, then K:
+//   16 x 4 heads x 1568 tokens, 26 MB    27.3 / 27.4   28.5 / 29.0   29.2 / 30.0   29.3 / 29.8
+//   28 x 4 x 2336, 67 MB                 48.7 / 50.0   49.2 / 50.0   48.0 / 50.4   47.6 / 49.1
+//   64 x 4 x 1568, 103 MB                64.8 / 65.7   64.8 / 66.6   66.7 / 68.2   64.2 / 67.6
+//   28 x 4 x 4704, 135 MB                82.9 / 86.2   84.4 / 84.9   93.5 / 86.3   83.4 / 85.7
+//   28 x 4 x 6272, 180 MB               104.9 / 107.7 110.1 / 107.5 124.4 / 108.9 109.1 / 110.9
+//   28 x 4 x 8192, 235 MB               136.2 / 135.9 140.3 / 138.2 160.7 / 139.6 151.6 / 141.9
+//   64 x 4 x 25088, 1644 MB               889 / 886     875 / 877     906 / 889     908 / 887
+static bool stream_keys(const Geom& g) { return (size_t)g.nheads * g.T * D * 2 > ((size_t)128 << 20); }
+
 // Counting the tokens with larger scores, quadratic in the sequence, against one workgroup's four digits: where the
 // selection is what takes time (alone) up to 8192 tokens on each compute unit's share (256 groups of one sequence, whole
 // calls: 20.2 us with the digits, 17.0; of two 22.4 and 22.9); beside a long range pass, which waits for its workgroups, up to
@@ -203,7 +216,7 @@ void launch_k_range_select(const Geom& g, const void* K, void* ws, const float* 
   const bool four = nsel > 0 && !few && (g.T > 32 * FEW_MAX_GROUPS || nsel >= cus / 4) && total <= 4 * cus;
   const long long wgs = four ? (total + 3) / 4 : total;
   // T <= ONE_MAX_T: at most 65535 * 64 chunks
-  hipLaunchKernelGGL(k_range_select_kernel, dim3((unsigned)(nsel + wgs)), dim3(1024), 0, st,
+  hipLaunchKernelGGL(stream_keys(g) ? k_range_select_kernel<true> : k_range_select_kernel<false>, dim3((unsigned)(nsel + wgs)), dim3(1024), 0, st,
                      reinterpret_cast<const u32x4*>(K), g.T, g.range_chunks, (int)total, nsel, few ? 1 : 0, four ? 1 : 0,
                      reinterpret_cast<_Float16*>(ws), one_sel_args(g, scores, idx, packed_V));
 }
@@ -244,10 +257,8 @@ hipError_t launch_quantize_keys(const Geom& g, const void* K, uint8_t* packed, v
     return hipGetLastError();
   }
   if (stages & 1u)
-    // streaming loads where K is larger than the last-level cache (256 MB) and the coding pass finds nothing of it there
-    // (80 heads x 76192 tokens 869.3 us a call with plain ones, 865.5 so; 4 x 196000, 201 MB: 132.5 and 136 the other way)
-    hipLaunchKernelGGL((size_t)g.nheads * g.T * D * 2 > ((size_t)256 << 20) ? k_range_kernel<true> : k_range_kernel<false>, gr1,
-                       dim3(1024), 0, st, k4, g.T, g.range_chunks, w);
+    hipLaunchKernelGGL(stream_keys(g) ? k_range_kernel<true> : k_range_kernel<false>, gr1, dim3(1024), 0, st, k4, g.T,
+                       g.range_chunks, w);
   if (stages & 2u)
     hipLaunchKernelGGL(k_select_kernel, dim3((unsigned)g.nheads), dim3(1024), 0, st, w,
                        g.range_chunks, g.n_a, packed + g.k_perm);

@@ -5,6 +5,10 @@
 
 namespace vidkv {
 
+// STREAM: a load that leaves nothing behind in the caches.
+template <bool STREAM>
+__device__ __forceinline__ u32x4 key_load(const u32x4* p) { return STREAM ? __builtin_nontemporal_load(p) : *p; }
+
 // ---------------------------------------------------------------------------
 // Pass 1: partial per-channel min / max over RANGE_CHUNK tokens of one head.
 // 256 threads: thread (row = tid/16, col = tid%16)
@@ -17,6 +21,7 @@ struct RangeLds {
 };
 
 // on = false: nothing is read or written, only the barrier is kept
+template <bool STREAM>
 __device__ __forceinline__ void range_part(const u32x4* __restrict__ K, int T, int chunks,
                                            _Float16* __restrict__ ws, int chunk, long long hd, int tid,
                                            bool on, RangeLds& lds) {
@@ -34,10 +39,10 @@ __device__ __forceinline__ void range_part(const u32x4* __restrict__ K, int T, i
   // 4 independent 16-byte loads in flight per thread
   for (; t + 48 < t1; t += 64) {
     U4H a, b, c, d;
-    a.u = __builtin_nontemporal_load(base + (long long)t * 16);
-    b.u = __builtin_nontemporal_load(base + (long long)(t + 16) * 16);
-    c.u = __builtin_nontemporal_load(base + (long long)(t + 32) * 16);
-    d.u = __builtin_nontemporal_load(base + (long long)(t + 48) * 16);
+    a.u = key_load<STREAM>(base + (long long)t * 16);
+    b.u = key_load<STREAM>(base + (long long)(t + 16) * 16);
+    c.u = key_load<STREAM>(base + (long long)(t + 32) * 16);
+    d.u = key_load<STREAM>(base + (long long)(t + 48) * 16);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       mn[i] = __builtin_elementwise_min(__builtin_elementwise_min(mn[i], a.h[i]),
@@ -50,7 +55,7 @@ __device__ __forceinline__ void range_part(const u32x4* __restrict__ K, int T, i
   }
   for (; t < t1; t += 16) {
     U4H a;
-    a.u = __builtin_nontemporal_load(base + (long long)t * 16);
+    a.u = key_load<STREAM>(base + (long long)t * 16);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       mn[i] = __builtin_elementwise_min(mn[i], a.h[i]);
@@ -78,8 +83,7 @@ __device__ __forceinline__ void range_part(const u32x4* __restrict__ K, int T, i
   }
 }
 
-// The same by 1024 threads, 8 pieces in flight each: a chunk in one go, two workgroups on a compute unit.  Plain loads: the
-// coding pass finds some of it in the caches (streaming ones: 28 x 4 heads x 6272 tokens 109 us a call, 107 so).
+// The same by 1024 threads, 8 pieces in flight each: a chunk in one go, two workgroups on a compute unit.
 struct ChunkRangeLds {
   h2 mn[16][16][4], mx[16][16][4];
 };
@@ -95,7 +99,7 @@ __device__ __forceinline__ void range_chunk(const u32x4* __restrict__ K, int T, 
 #pragma unroll
   for (int k = 0; k < RANGE_CHUNK / 64; ++k) {       // (a row past the end repeats the first one)
     const u32x4* at = base + (long long)(t0 + row + 64 * k < t1 ? t0 + row + 64 * k : t0) * 16;
-    x[k].u = STREAM ? __builtin_nontemporal_load(at) : *at;
+    x[k].u = key_load<STREAM>(at);
   }
   h2 mn[4], mx[4];
 #pragma unroll
