@@ -3,19 +3,20 @@
 // (Eq. 4) of the selected channels and the sign bits of a 32-point real DFT
 // (Eq. 5) of the others.
 #include <algorithm>
+#include <type_traits>
 
 #include "select_keys.h"
 #include "select_values.h"
 
 namespace vidkv {
 
-// Pass 1 as a launch of its own.  grid (range_chunks, nheads).  (256 threads, a quarter of a chunk's pieces at a time: 4 heads
-// x 196000 tokens 131.1 us a whole call, 129.3 so.)
-template <bool STREAM>
-__global__ __launch_bounds__(1024, 8) void k_range_kernel(const u32x4* __restrict__ K, int T,
-                                                          int chunks, _Float16* __restrict__ ws) {
-  __shared__ ChunkRangeLds lds;
-  range_chunk<STREAM>(K, T, chunks, ws, blockIdx.x, blockIdx.y, lds);
+// Pass 1 as a launch of its own.  grid (range_chunks, nheads); block 1024, WHOLE (a chunk in one go), or 256.
+template <bool WHOLE, bool STREAM>
+__global__ __launch_bounds__(WHOLE ? 1024 : 256) void k_range_kernel(const u32x4* __restrict__ K, int T,
+                                                                     int chunks, _Float16* __restrict__ ws) {
+  __shared__ std::conditional_t<WHOLE, ChunkRangeLds, RangeLds> lds;
+  if constexpr (WHOLE) range_chunk<STREAM>(K, T, chunks, ws, blockIdx.x, blockIdx.y, lds);
+  else range_part<STREAM>(K, T, chunks, ws, blockIdx.x, blockIdx.y, threadIdx.x, true, lds);
 }
 
 // Pass 1 with the protected-token selection of the same call in the first nsel workgroups: a chain of
@@ -184,6 +185,15 @@ __global__ __launch_bounds__(1024) void k_metric_select_kernel(const double* __r
 void launch_k_encode(const Geom& g, const EncodeSpan& sp, const void* K, uint8_t* packed,
                      bool use_fft, hipStream_t st);
 
+// The range pass by 1024 threads a chunk (whole) or 256: a chunk in one go is one wait for memory instead of eight, but a
+// short sequence fills little of it and the workgroup costs what it always does.  From half a chunk on, where the
+// launch does not fill the device from a quarter on.  Nothing protected, 256 / 1024 threads, us: 16 heads x 128 tokens
+// 11.2 / 11.1, 16 x 256 13.6 / 11.4, 16 x 512 18.4 / 12.1, 64 x 1568 24.9 / 22.4, 64 x 6272 66.5 / 65.1; 896 heads x 32 tokens
+// 14.3 / 17.6, x 128 22.2 / 24.7, x 256 39.9 / 40.7, x 512 68.0 / 66.5, x 1024 118.3 / 116.7; 8192 x 32 100 / 142.
+static bool whole_chunks(const Geom& g) {
+  return g.T >= RANGE_CHUNK / (g.nheads * g.range_chunks <= device_cu_count() ? 4 : 2);
+}
+
 // Streaming loads in the range pass, in each of its forms, where K and as many bytes of V are more than the last-level cache
 // (256 MB): plain ones then push out V, which the value coding is about to read, below it they leave K for the key coding.
 // Whole calls, plain / streaming, us, on the same buffers again and again, on rotating ones, behind a kernel that wrote K,
@@ -213,7 +223,7 @@ void launch_k_range_select(const Geom& g, const void* K, void* ws, const float* 
   const long long total = g.nheads * g.range_chunks, cus = device_cu_count();
   // Where the selection of a long sequence is the longer part, four chunks a workgroup leave it a compute unit to
   // itself (4 x 4 heads x 25088 tokens 67 us a call, with a workgroup for each chunk passing through beside it 74; 8 x 32768 53 and 60)
-  const bool four = nsel > 0 && !few && (g.T > 32 * FEW_MAX_GROUPS || nsel >= cus / 4) && total <= 4 * cus;
+  const bool four = !whole_chunks(g) || (nsel > 0 && !few && (g.T > 32 * FEW_MAX_GROUPS || nsel >= cus / 4) && total <= 4 * cus);
   const long long wgs = four ? (total + 3) / 4 : total;
   // T <= ONE_MAX_T: at most 65535 * 64 chunks
   hipLaunchKernelGGL(stream_keys(g) ? k_range_select_kernel<true> : k_range_select_kernel<false>, dim3((unsigned)(nsel + wgs)), dim3(1024), 0, st,
@@ -256,9 +266,12 @@ hipError_t launch_quantize_keys(const Geom& g, const void* K, uint8_t* packed, v
       launch_k_encode(g, EncodeSpan{g.T, g.ng, 0, g.nheads, 0}, K, packed, g.use_fft, st);
     return hipGetLastError();
   }
-  if (stages & 1u)
-    hipLaunchKernelGGL(stream_keys(g) ? k_range_kernel<true> : k_range_kernel<false>, gr1, dim3(1024), 0, st, k4, g.T,
-                       g.range_chunks, w);
+  if (stages & 1u) {
+    const bool whole = whole_chunks(g), stream = stream_keys(g);
+    auto* kernel = whole ? (stream ? k_range_kernel<true, true> : k_range_kernel<true, false>)
+                         : (stream ? k_range_kernel<false, true> : k_range_kernel<false, false>);
+    hipLaunchKernelGGL(kernel, gr1, dim3(whole ? 1024 : 256), 0, st, k4, g.T, g.range_chunks, w);
+  }
   if (stages & 2u)
     hipLaunchKernelGGL(k_select_kernel, dim3((unsigned)g.nheads), dim3(1024), 0, st, w,
                        g.range_chunks, g.n_a, packed + g.k_perm);

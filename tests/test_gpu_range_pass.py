@@ -47,6 +47,13 @@ def _check(L, B, H, T, select):
     assert torch.equal(pk, rk) and torch.equal(pv, rv), "quantize_kv and the separate calls"
 
 
+@pytest.mark.parametrize("select", ["none", "scores", "list"])
+@pytest.mark.parametrize("T", [32, 96, 128, 224, 256, 480, 512, 544, 960, 1056])
+def test_lengths_and_head_counts(T, select):
+    for L, B, H in ((1, 3, 1), (1, 16, 4), (5, 16, 4), (3, 64, 4), (7, 50, 4)):
+        _check(L, B, H, T, select)
+
+
 @pytest.mark.parametrize("L,B,H,T", [(2, 64, 64, 96), (2, 64, 8, 544), (1, 64, 8, 1056), (1, 8, 4, 16416), (1, 2, 4, 65568), (1, 3, 4, 90016)])
 def test_streaming_loads(L, B, H, T):
     """More than 128 MiB of keys (the last: 277 MB), and a little less."""
