@@ -209,10 +209,18 @@ static bool stream_keys(const Geom& g) { return (size_t)g.nheads * g.T * D * 2 >
 
 // Counting the tokens with larger scores, quadratic in the sequence, against one workgroup's four digits: where the
 // selection is what takes time (alone) up to 8192 tokens on each compute unit's share (256 groups of one sequence, whole
-// calls: 20.2 us with the digits, 17.0; of two 22.4 and 22.9); beside a long range pass, which waits for its workgroups, up to
-// 2560 (8 x 4 heads x 1568 tokens 22.7 -> 20.5; 16 x 4 x 1568 28.4 and 29.7, 28 x 4 x 6272 107 and 111).
+// calls: 20.2 us with the digits, 17.0; of two 22.4 and 22.9); beside a range pass, which waits for its workgroups, while
+// they and the chunks are no more than three a compute unit (digits and counting, us: 8 x 4 heads x 1568 tokens, 520, 21.8 and
+// 19.9; 2 x 8 x 4704, 454, 25.4 and 23.2; 56 x 4 x 256, 672, 22.4 and 18.9; 32 x 4 x 512 in 2 layers, 768, 30.2 and 29.3; 8 x 4 x 288 in
+// 16, 656, 33.6 and 34.2; 64 x 4 x 288, 832, 24.0 and 25.8; 8 x 4 x 1568 in 8, 1416, 64.3 and 68.7; 64 x 8 x 544, 2112, 50.2 and 57.9.
+// Where 256 threads take a chunk, the line is at one and a half, four chunks counted as one: 32 x 4 x 64 tokens in 8 layers, 320,
+// 26.8 and 24.7; 64 x 4 x 160, 384, 21.9 and 19.4; 32 x 4 x 160 in 8, 416, 41.8 and 43.7; 64 x 4 x 64 in 8, 640, 41.3 and 42.0.)
+// A list's selection is quick, but ranks and IDX then cost the value coding a little of each group: the same line.
 bool few_selection(const Geom& g, bool scores, bool alone) {
-  return g.ng <= FEW_MAX_GROUPS && (!scores || (long long)g.B * g.ng * g.T <= (alone ? 8192LL : 2560LL) * device_cu_count());
+  if (g.ng > FEW_MAX_GROUPS) return false;
+  const long long cus = device_cu_count(), nsel = scores ? (long long)g.B * g.ng : g.B, chunks = g.nheads * g.range_chunks;
+  if (alone) return !scores || nsel * g.T <= 8192 * cus;
+  return whole_chunks(g) ? nsel + chunks <= 3 * cus : 2 * nsel + (chunks + 1) / 2 <= 3 * cus;
 }
 
 // The range pass (Range metric) and the protected-token selection of short sequences (or none) in one launch.
@@ -221,9 +229,13 @@ void launch_k_range_select(const Geom& g, const void* K, void* ws, const float* 
                            uint8_t* packed_V, bool few, hipStream_t st) {
   const int nsel = g.n_s == 0 ? 0 : few && scores ? g.B * g.ng : g.B;
   const long long total = g.nheads * g.range_chunks, cus = device_cu_count();
-  // Where the selection of a long sequence is the longer part, four chunks a workgroup leave it a compute unit to
-  // itself (4 x 4 heads x 25088 tokens 67 us a call, with a workgroup for each chunk passing through beside it 74; 8 x 32768 53 and 60)
-  const bool four = !whole_chunks(g) || (nsel > 0 && !few && (g.T > 32 * FEW_MAX_GROUPS || nsel >= cus / 4) && total <= 4 * cus);
+  // Beside a workgroup that goes through a sequence's digits, four chunks a workgroup also where the chunks are not nearly
+  // full (64 x 4 heads x 544 tokens in 8 layers 169 us so, 179 with a chunk each; 16 x 4 x 3136, 0.88 full, 43.4 and 40.9), and where
+  // the selection of a long sequence is the longer part and so keeps a compute unit to itself: 8 heads of 25088 tokens 48.1 and 54.4,
+  // 4 of 32768 41.9 and 46.2, 4 x 8 x 12544 68.1 and 69.4; with more workgroups than units 8 heads of two sequences of 32768 97.6 and 91.6.
+  const bool digits = nsel > 0 && !few;
+  const bool four = !whole_chunks(g) || (digits && 8LL * g.T < 7LL * RANGE_CHUNK * g.range_chunks) ||
+                    (digits && g.T > 32 * FEW_MAX_GROUPS && (total + 3) / 4 + nsel <= cus);
   const long long wgs = four ? (total + 3) / 4 : total;
   // T <= ONE_MAX_T: at most 65535 * 64 chunks
   hipLaunchKernelGGL(stream_keys(g) ? k_range_select_kernel<true> : k_range_select_kernel<false>, dim3((unsigned)(nsel + wgs)), dim3(1024), 0, st,

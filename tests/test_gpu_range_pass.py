@@ -54,6 +54,12 @@ def test_lengths_and_head_counts(T, select):
         _check(L, B, H, T, select)
 
 
+@pytest.mark.parametrize("L,B,H,T", [(1, 3, 4, 8224), (1, 20, 8, 3136), (1, 2, 8, 32768), (1, 4, 8, 12544)])
+def test_long_sequences_beside_their_selection(L, B, H, T):
+    for select in ("scores", "list"):
+        _check(L, B, H, T, select)
+
+
 @pytest.mark.parametrize("L,B,H,T", [(2, 64, 64, 96), (2, 64, 8, 544), (1, 64, 8, 1056), (1, 8, 4, 16416), (1, 2, 4, 65568), (1, 3, 4, 90016)])
 def test_streaming_loads(L, B, H, T):
     """More than 128 MiB of keys (the last: 277 MB), and a little less."""
