@@ -180,7 +180,7 @@ vidkv_status vidkv_quantize_values(const vidkv_params *params, const void *V_dev
  * heads or more).
  * For longer ones the protected-token selection is a chain of short dependent
  * launches; with a side stream it is enqueued there so that it runs beside the key
- * passes (only when the key tensor is 120 MiB or more; smaller inputs run in
+ * passes (only when the key tensor is 96 MiB or more; smaller inputs run in
  * line), and joined back before the value coding pass.
  * Arguments as for the two separate calls;
  *   workspace_dev : >= vidkv_workspace_bytes(params, 3) bytes

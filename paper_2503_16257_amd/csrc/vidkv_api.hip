@@ -213,14 +213,16 @@ vidkv_status vidkv_quantize_kv(const vidkv_params* p, const void* K, const void*
   // A sequence too long for one workgroup's registers keeps the chain of six.  With a side stream,
   // and key passes long enough to hide the fork and join, it runs beside them, the value
   // pass last; beside the range pass alone it is the longer of the two (196000 tokens: 154 us
-  // against 137).  The line is at 120 MiB of keys, 4 heads each, beside against in line: 34 MB 59 to 71 us and 49.5, 61 MB 78
-  // and 62.4, 87 MB 88 and 76, 102 MB 83 and 84.5 (98 and 84.8 on another card), 133 MB 97 and 99, 201 MB 129 and 133, 401 MB 234 and 241.
+  // against 137).  The line is at 96 MiB of keys: whole calls in line and beside, us, 5 % protected, K and V just written, on two
+  // cards: 41 MB 56 and 73, 67 MB 68 to 73 and 74, 101 MB 85 to 92 and 82 to 87, 117 MB 95 to 101 and 88 to 90, 134 MB 102 to 108 and 96 to
+  // 100, 164 MB 117 to 124 and 109 to 114, 201 MB 136 to 144 and 128, 268 MB 175 to 180 and 168, 403 MB 244 and 237, 819 MB 463
+  // to 469 and 456; of 32 shapes from there on, 1 to 16 sequences, on the same buffers, rotating or just written ones, none above 1.014.
   const bool sel = g.n_s > 0, one = sel && one_workgroup_selection(g);
   const Side sd = take_side(side);
   const size_t key_bytes = (size_t)g.nheads * g.T * D * 2;
   // (a stream of another device is refused from 32 MiB on, where the line once was)
   if (sel && !one && sd.ok && key_bytes >= ((size_t)32 << 20) && !stream_on_current_device(sd.stream)) return VIDKV_EINVAL;
-  const bool fork = sel && !one && sd.ok && key_bytes >= ((size_t)120 << 20);
+  const bool fork = sel && !one && sd.ok && key_bytes >= ((size_t)96 << 20);
   if (fork) {
     if (hipEventRecord(sd.fork, st) != hipSuccess) return VIDKV_EHIP;
     if (hipStreamWaitEvent(sd.stream, sd.fork, 0) != hipSuccess) return VIDKV_EHIP;
