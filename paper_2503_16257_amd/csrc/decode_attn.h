@@ -103,8 +103,12 @@ struct alignas(256) TailLds {
 // partial (o, m, l) as split index nsplit + ts.  Bound by the memory where there are many of them, by one chain of
 // latencies where there are few.  Both contractions run on the matrix cores, K rows straight from memory as
 // operands, value rows through LDS and its transposing reads; everything a block needs is asked for at once.
-// As exact as in 32-bit arithmetic: q and the keys are fp16 numbers with exact products; a probability p enters as two,
-// hi + 2^-18 lo (22 bits, nothing lost above 2^-43), in the rows of the 8 heads and in the 8 that would be empty.
+// As exact as in 32-bit arithmetic.  q, keys and values are fp16 numbers with exact products.  A probability enters as four
+// fp16 numbers that add up to it, in the rows of the 8 heads and the 8 that would be empty of two products a tile: all
+// its 24 bits down to 2^-41 of the running maximum, 22 to 2^-53, 11 to 2^-65, which times the largest value adds nothing to
+// an fp16 result below 2^24 tokens.  None of the four is subnormal: a product takes a subnormal operand for 2^-14 where it aligns the sum,
+// and where all are a few 2^-24 up to 2^-17 of the sum is lost.  (So for subnormal keys, queries and values, whose scores or results
+// are then too small to show it.)
 __device__ __forceinline__ void attn_tail_part(const AttnArgs& a, int ts, int kvh, int b, TailLds& t) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -127,7 +131,9 @@ __device__ __forceinline__ void attn_tail_part(const AttnArgs& a, int ts, int kv
     // a transposing read hands lane x16 of kb the rows 4 kb .. 4 kb + 3 (of either half) of channel 16 m + x16
     const int rr = 4 * kb + (x16 >> 2);
     const uint32_t at = (uint32_t)reinterpret_cast<uintptr_t>(vrow) + rr * 2 * D + (rr & 7) * 32 + (x16 & 3) * 8;
-    const float lo_row = (kb >> 1) ? 0x1p-18f : 1.0f;         // of my rows' products
+    // parts 0 and 2 of the probabilities are in rows 0..7, 1 and 3 in rows 8..15, part k times 2^(15 + 12 k)
+    const bool odd = x16 >= 8;
+    const float row0 = (kb >> 1) ? 0x1p-27f : 0x1p-15f, row2 = (kb >> 1) ? 0x1p-51f : 0x1p-39f;   // of my rows' products
     for (int it = it0; it < it1; it += 4) {
       const int tok0 = it * 32, nt = min(32, tl - tok0);
       // (a row past the end repeats the last one and counts 0 times)
@@ -164,13 +170,22 @@ __device__ __forceinline__ void attn_tail_part(const AttnArgs& a, int ts, int kv
       const float al = m_run == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m_run - m_new);
       l_run *= al;
       m_run = m_new;
-      Op A;
+      Op A[2];
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const float p = sc[i] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(sc[i] - m_new);
         l_run += p;
-        const _Float16 hi = (_Float16)p;
-        A.v[i] = x16 >= 8 ? (_Float16)((p - (float)hi) * 0x1p18f) : hi;
+        float r = p;                                 // what the parts so far leave
+        _Float16 part[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float up = k == 0 ? 0x1p15f : k == 1 ? 0x1p27f : k == 2 ? 0x1p39f : 0x1p51f;
+          const float x = r * up;
+          part[k] = (_Float16)(fabsf(x) < 0x1p-14f ? 0.0f : x);
+          r = fmaf((float)part[k], -1.0f / up, r);
+        }
+        A[0].v[i] = odd ? part[1] : part[0];
+        A[1].v[i] = odd ? part[3] : part[2];
       }
       if (it != it0) {
         // the sums are laid out by score-tile column as ROW 4 kb + i
@@ -194,9 +209,9 @@ __device__ __forceinline__ void attn_tail_part(const AttnArgs& a, int ts, int kv
         Op B;
         *reinterpret_cast<s16x4*>(&B.u[0]) = lo4[m];
         *reinterpret_cast<s16x4*>(&B.u[2]) = hi4[m];
-        const f4 C = mma(A, B, zero);
+        const f4 C0 = mma(A[0], B, zero), C2 = mma(A[1], B, zero);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o[m][i] = fmaf(lo_row, C[i], o[m][i]);
+        for (int i = 0; i < 4; ++i) o[m][i] = fmaf(row0, C0[i], fmaf(row2, C2[i], o[m][i]));
       }
       asm volatile("" ::: "memory");
     }

@@ -60,11 +60,12 @@ def test_blocks_and_waves(cap, heads, rep):
     _check(q, Kt, Vt, lens, f"cap {cap}")
 
 
-@pytest.mark.parametrize("d", [8.0, 20.0, 25.4, 33.0])
-def test_probabilities_far_below_the_largest(d):
+@pytest.mark.parametrize("n,d", [(300, 8.0), (300, 20.0), (300, 25.4), (300, 33.0), (300, 36.3), (9000, 40.7), (9000, 43.6), (9000, 47.3),
+                                 (9000, 50.2)])
+def test_probabilities_far_below_the_largest(n, d):
     """One token with value 0 takes nearly all the weight, the others have 2^-d of it each and the largest values:
     what they add up to is still there."""
-    n, at = 300, 170
+    at = 170
     Kt = torch.zeros((1, 1, n, 128), dtype=torch.float16, device=DEV)
     Kt[:, :, at, 0] = 8.0
     Vt = torch.full((1, 1, n, 128), 60000.0, dtype=torch.float16, device=DEV)
