@@ -110,7 +110,7 @@ __device__ __forceinline__ uint32_t byte_x8(uint32_t w, uint32_t three) {
   return ((w >> (8 * B)) & 0xFFu) << three;
 }
 
-// Inverse-DFT operands.  split: 16 * (inverse real DFT matrix) as fp16 hi + lo parts, [2 lo + mt][lane][8 halves]: row
+// Inverse-DFT operands.  split: 32 * (inverse real DFT matrix) as fp16 hi + lo parts, [2 lo + mt][lane][8 halves]: row
 // t = 16 mt + x, k-slot (kb, i): i < 4 -> Re X[4kb+i], i >= 4 -> Im X[4kb+i-4] (Re X[16] when that index is 0).
 // full: twice the matrix in fp32, [2 half + mt][lane][4]: k-slots i of the Re half (0) or the Im half (1).
 // (Loaded: computed by every workgroup they took longer, 0.84 us, than q takes to arrive, where only one workgroup
@@ -126,8 +126,8 @@ constexpr IdftTab make_idft_tab() {
       for (int i = 0; i < 8; ++i) {
         const int k = 4 * kb + (i & 3);
         w[i] = i < 4 ? (k == 0 ? 0.5f : cos32(k * t)) : k == 0 ? ((t & 1) ? -0.5f : 0.5f) : -cos32(k * t + 24);
-        const _Float16 hi = (_Float16)w[i];
-        const _Float16 v = (n >> 1) ? (_Float16)(w[i] - (float)hi) : hi;
+        const _Float16 hi = (_Float16)(2.0f * w[i]);
+        const _Float16 v = (n >> 1) ? (_Float16)(2.0f * w[i] - (float)hi) : hi;
         tab.split[n][lane][i >> 1] |= (uint32_t)__builtin_bit_cast(uint16_t, v) << (16 * (i & 1));
       }
       for (int i = 0; i < 4; ++i) tab.full[n][lane][i] = w[4 * (n >> 1) + i] * 0.125f;
@@ -146,8 +146,8 @@ static __device__ const __align__(256) IdftTab kIdftTab = make_idft_tab();
 //     (fp16 hi + lo parts are 0 below 2^-25 of the running maximum, where the softmax denominator
 //     still counts the token: 196000 tokens at 2^-25.1 of one other lost 0.5 % of the output);
 //   * protected rows' probabilities as hi + 2^-18 lo, two fp16 numbers;
-//   * q enters as it is and doubled, or half of both where the head has an element of 2^15 or more, where the other
-//     counts take q/2 and q against the two bits' s: neither loses bits where it is subnormal;
+//   * the normal channels' q enters as it is, where the others' inverse DFT takes q/16 (half of it for a head with an
+//     anomalous channel's element of 2^15 or more);
 //   * the inverse DFT runs on v_mfma_f32_16x16x4_f32, on the fp32 sums and an fp32 matrix.
 // The other counts have always had fp16 probabilities and -q/16.  What it costs is 48 instead of 32 products
 // of a pair's values (the three parts are used as they are, in all rows: with the operand rows masked by parity, and
@@ -433,9 +433,9 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   // The permutation bytes of my channel blocks and quads come in one LDS read each, then
   // every q element in one batch of independent reads (no branch around a read: absent
   // blocks read a valid block and are zeroed afterwards).
-  Op Bn[2][U > 0 ? U : 1];                   // normal channels: -q/16 (FFT) or -q/2 (FULL: -q h) at channels 8 (4u+kb) + e, only in my parity
-  Op Ba[2][UA > 0 ? UA : 1];                 // anomalous: -q h of a quad's 4 channels, then -2 q h (h = 1/2 unless FULL), only in my parity
-  float sc2 = a.scale2;                      // sum -> score in the exp2 domain (FULL: the sums are 2 h times the scores')
+  Op Bn[2][U > 0 ? U : 1];                   // normal channels: -q h (FFT but FULL: -q h / 16; -q/2 with no others) at channels 8 (4u+kb) + e, only in my parity
+  Op Ba[2][UA > 0 ? UA : 1];                 // anomalous: -q h of a quad's 4 channels, then -2 q h, only in my parity
+  float sc2 = a.scale2;                      // sum -> score in the exp2 domain (the sums are 2 h times the scores')
   {
     uint2 pb[U > 0 ? U : 1];
     uint32_t pq[UA > 0 ? UA : 1];
@@ -458,22 +458,23 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     for (int ua = 0; ua < UA; ++ua)
 #pragma unroll
       for (int r = 0; r < 4; ++r) qa[ua][r] = qrow[(pq[ua] >> (8 * r)) & 0xFFu];
-    _Float16 cn = (_Float16)(FFT ? -0.0625f : -0.5f), ca0 = (_Float16)-0.5f, ca1 = (_Float16)-1.0f;
-    if (FULL) {
-      // h = 1, or 1/2 for a head with an element whose double is no fp16 number
+    // The second bit's operand is 2 q h: h = 1, or 1/2 for a head with an anomalous channel's element whose double is no fp16
+    // number.  (Halves for the first bit instead lose the last bit of an element below 2^-13: 128 keys of 60000 against q = 15 2^-24
+    // gave scores 7 % off.)  Without anomalous channels and inverse DFT the sums are the scores themselves.
+    constexpr bool TWICE = UA > 0 || FFT;
+    _Float16 cn = (_Float16)(FFT && !FULL ? -0.0625f : TWICE ? -1.0f : -0.5f), ca0 = (_Float16)-1.0f, ca1 = (_Float16)-2.0f;
+    if (TWICE) sc2 *= 0.5f;
+    if (UA > 0) {
       float mx = 0.0f;
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf((float)qn[u][e]));
 #pragma unroll
       for (int ua = 0; ua < UA; ++ua)
 #pragma unroll
         for (int r = 0; r < 4; ++r) mx = fmaxf(mx, fabsf((float)qa[ua][r]));
       const bool big = swap_max16(swap_max32(mx)) >= 32768.0f;
-      cn = ca0 = (_Float16)(big ? -0.5f : -1.0f);
+      cn = big ? (_Float16)(cn * (_Float16)0.5f) : cn;
+      ca0 = (_Float16)(big ? -0.5f : -1.0f);
       ca1 = (_Float16)(big ? -1.0f : -2.0f);
-      sc2 *= big ? 1.0f : 0.5f;
+      sc2 *= big ? 2.0f : 1.0f;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -621,7 +622,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       accRe = mma(Are, Bn[grp][u], accRe);
       accIm = mma(Aim, Bn[grp][u], accIm);
       if (!FFT) {
-        // constant term, rows all equal: z and s against -q/2 (FULL: -q h), apart: the score takes 2 z + s
+        // constant term, rows all equal: z and s against the same operand, apart: the score takes 2 z + s
         const uint8_t* rec = stage + grp * KREC;
         const int blk = min(4 * u + kb, NB - 1);
         Op zq;
@@ -658,7 +659,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
       A0.u[3] = ((uint32_t)s3 & 0x80008000u) | s4.y; A1.u[3] = ((uint32_t)(s3 >> 32) & 0x80008000u) | s4.y;
       S[0] = mma(A0, Ba[grp][ua], S[0]);
       S[1] = mma(A1, Ba[grp][ua], S[1]);
-      // the constant z + 1.5 s (FULL, twice h times it): rows all equal, s against both planes' operands, z against the second's
+      // the constant z + 1.5 s, 2 h times it: rows all equal, s against both planes' operands, z against the second's
       const h8 q8 = Ba[grp][ua].v;
       const h4 q1 = __builtin_shufflevector(q8, q8, 0, 1, 2, 3), q2 = __builtin_shufflevector(q8, q8, 4, 5, 6, 7);
       const h4 sv4 = __builtin_bit_cast(h4, s4), zv4 = __builtin_bit_cast(h4, z4);
@@ -802,7 +803,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
           S[mt] = mma(Wh[mt], Yl, S[mt]);
         }
       }
-      if (UA > 0) cst = accC[0][0] + accC[1][0] + accC[2][0];                 // = -(sum q (z + 1.5 s)) (FULL: 2 h times it, like S and cst_n)
+      if (UA > 0) cst = accC[0][0] + accC[1][0] + accC[2][0];                 // = -(sum q (z + 1.5 s)), 2 h times it like S and cst_n
       if (!FFT) cst -= cst_n;
     }
   };

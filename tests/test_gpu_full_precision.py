@@ -101,3 +101,32 @@ def test_queries_that_have_no_double(n_a, fft):
     q[:, 2::3, 3::19] = 32752.0
     q[..., 9] = 2.0 ** -24
     _check(w, K, _signed_values(w), q, 1e-3, f"n_a {n_a} fft {fft}", fft=fft)
+
+
+@pytest.mark.parametrize("fft", [1, 0])
+@pytest.mark.parametrize("n_a", [8, 16, 32, 64, 128])
+def test_small_queries_of_anomalous_channels(n_a, fft):
+    """The other counts: the anomalous channels' queries keep all their bits too, where half of them is no fp16 number and the keys
+    are large.  All channels of a token have one of four keys, so that what is lost adds up.  Tolerance: the probabilities are fp16
+    numbers, at most 2^-11 of them off, and the scores spread by about 0.0018 n_a."""
+    w, r = _w(n_a), np.random.default_rng(n_a)
+    K = np.zeros((1, 1, w.Hkv, w.T, 128), np.float16)
+    K[..., :n_a] = (r.integers(0, 4, (1, 1, w.Hkv, w.T, 1)) * 40000.0 - 60000.0).astype(np.float16)
+    q = np.zeros((1, w.Hq, 128), np.float16)
+    q[..., :n_a] = (r.integers(3, 6, (1, w.Hq, 1)) * 4 - 1) * 2.0 ** -24
+    _check(w, K, _signed_values(w), q, 5e-4 + 2.0 ** -11 / (0.0018 * n_a), f"n_a {n_a} fft {fft}", fft=fft)
+
+
+@pytest.mark.parametrize("fft", [1, 0])
+@pytest.mark.parametrize("n_a", [16, 64, 128])
+def test_queries_that_have_no_double_beside_others(n_a, fft):
+    """The same counts with heads that have an element beyond 2^15 and heads that have none, anomalous or not.  Tolerance: fp16
+    probabilities and a spread of the scores of 1 and more; the normal channels' q / 16 is exact here."""
+    w, r = _w(n_a), np.random.default_rng(n_a)
+    K = (2e-5 * r.standard_normal((1, 1, w.Hkv, w.T, 128))).astype(np.float16)
+    K[..., 5::9] *= 4
+    q = r.standard_normal((1, w.Hq, 128)).astype(np.float16)
+    q[:, ::3, 5::9] = 65504.0
+    q[:, 1::3, 7::9] = -32768.0
+    q[:, 2::3, 3::9] = 32752.0
+    _check(w, K, _signed_values(w), q, 2e-3, f"n_a {n_a} fft {fft}", fft=fft)
