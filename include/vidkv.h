@@ -27,7 +27,9 @@
  *    failed check returns a status and launches nothing.  A launch failure
  *    returns VIDKV_EHIP.  Nothing aborts or throws across this boundary.
  *  - Tensors are dense, row-major, fp16 (IEEE binary16) unless stated.
- *    Inputs must be finite; non-finite inputs give unspecified codes.  All
+ *    Inputs must be finite; non-finite inputs give unspecified codes and
+ *    results (an infinite element of a residual or protected value row, for
+ *    one, gives NaN, not infinity, in its channel).  All
  *    stored scales are fp16: a 32-token group of keys whose mean spectral
  *    magnitude (Eq. 5) exceeds 65504 - values of order 10^4 with a common
  *    sign - overflows its scale, with unspecified results for that group.

@@ -79,6 +79,7 @@
 
 namespace vidkv {
 
+typedef unsigned short us2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(4))) uint32_t cu32;   // read with scalar loads
 
 __device__ __forceinline__ float from_xor8(float v) {        // v(lane ^ 8): within a row of 16, 8 lanes on
@@ -462,20 +463,8 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     // number.  (Halves for the first bit instead lose the last bit of an element below 2^-13: 128 keys of 60000 against q = 15 2^-24
     // gave scores 7 % off.)  Without anomalous channels and inverse DFT the sums are the scores themselves.
     constexpr bool TWICE = UA > 0 || FFT;
-    _Float16 cn = (_Float16)(FFT && !FULL ? -0.0625f : TWICE ? -1.0f : -0.5f), ca0 = (_Float16)-1.0f, ca1 = (_Float16)-2.0f;
     if (TWICE) sc2 *= 0.5f;
-    if (UA > 0) {
-      float mx = 0.0f;
-#pragma unroll
-      for (int ua = 0; ua < UA; ++ua)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) mx = fmaxf(mx, fabsf((float)qa[ua][r]));
-      const bool big = swap_max16(swap_max32(mx)) >= 32768.0f;
-      cn = big ? (_Float16)(cn * (_Float16)0.5f) : cn;
-      ca0 = (_Float16)(big ? -0.5f : -1.0f);
-      ca1 = (_Float16)(big ? -1.0f : -2.0f);
-      sc2 *= big ? 2.0f : 1.0f;
-    }
+    const _Float16 cn = (_Float16)(FFT && !FULL ? -0.0625f : TWICE ? -1.0f : -0.5f);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const bool ok = hv && (4 * u + kb) < NB;
@@ -486,18 +475,37 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
         Bn[1][u].v[e] = par ? v : (_Float16)0.0f;
       }
     }
+    us2 most = {0, 0};                       // of the magnitudes of 2 q, as bit patterns
+    auto anomalous_operands = [&](_Float16 h) {
 #pragma unroll
-    for (int ua = 0; ua < UA; ++ua) {
-      const bool ok = hv && (4 * ua + kb) < NQ;
+      for (int ua = 0; ua < UA; ++ua) {
+        const bool ok = hv && (4 * ua + kb) < NQ;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const _Float16 v = ok ? qa[ua][r] : (_Float16)0.0f;
+        for (int plane = 0; plane < 2; ++plane)
 #pragma unroll
-        for (int plane = 0; plane < 2; ++plane) {
-          const _Float16 x = (_Float16)(v * (plane ? ca1 : ca0));
-          Ba[0][ua].v[4 * plane + r] = par ? (_Float16)0.0f : x;
-          Ba[1][ua].v[4 * plane + r] = par ? x : (_Float16)0.0f;
-        }
+          for (int r = 0; r < 4; r += 2) {
+            h2 x = h2{qa[ua][r], qa[ua][r + 1]} * h2{h, h};
+            if (plane) x += x;
+            const uint32_t w = ok ? h2_bits(x) : 0u;
+            if (plane) most = __builtin_elementwise_max(most, __builtin_bit_cast(us2, w & 0x7FFF7FFFu));
+            Ba[0][ua].u[2 * plane + r / 2] = par ? 0u : w;
+            Ba[1][ua].u[2 * plane + r / 2] = par ? w : 0u;
+          }
+      }
+    };
+    anomalous_operands((_Float16)-1.0f);
+    if (UA > 0) {
+      const bool inf = most[0] >= 0x7C00 || most[1] >= 0x7C00;
+      if (__any(inf)) {                      // (as a maximum in front of the operands it was 1 % of a step: 28 layers x 6272 tokens 294.3 us, 289.0 so)
+        const bool big = swap_max16(swap_max32(inf ? 1.0f : 0.0f)) > 0.0f;
+        anomalous_operands((_Float16)(big ? -0.5f : -1.0f));
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int grp = 0; grp < 2; ++grp)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) Bn[grp][u].v[e] *= (_Float16)(big ? 0.5f : 1.0f);
+        if (big) sc2 *= 2.0f;
       }
     }
   }
