@@ -187,7 +187,8 @@ vidkv_status vidkv_quantize_values(const vidkv_params *params, const void *V_dev
  * Arguments as for the two separate calls;
  *   workspace_dev : >= vidkv_workspace_bytes(params, 3) bytes
  *   side          : NULL, or the caller's side stream and events (all three
- *                   handles non-NULL, else VIDKV_EINVAL)                      */
+ *                   handles non-NULL, and where the call uses it, the stream
+ *                   on the current device, else VIDKV_EINVAL)                 */
 vidkv_status vidkv_quantize_kv(const vidkv_params *params, const void *K_dev,
                                const void *V_dev, const float *saliency_dev,
                                const int32_t *salient_idx_dev, void *packed_K_dev,
@@ -218,8 +219,8 @@ vidkv_status vidkv_quantize_kv(const vidkv_params *params, const void *K_dev,
  * with no token at all gets zeros.
  * Everything runs in line on `hip_stream`, with and without a side stream (a
  * large residual block no longer gains from one).
- *   side            : NULL, or the caller's side stream and events: checked,
- *                     not used                                               */
+ *   side            : NULL, or a side stream and events (all three handles
+ *                     non-NULL, else VIDKV_EINVAL): not used                 */
 vidkv_status vidkv_decode_attention(const vidkv_params *params, int32_t layer,
                                     const void *q_dev, const void *packed_K_dev,
                                     const void *packed_V_dev, const void *K_tail_dev,

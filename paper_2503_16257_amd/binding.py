@@ -259,7 +259,7 @@ def decode_attention(p: VidkvParams, layer: int, q, packed_K, packed_V, out, wor
                      K_tail=None, V_tail=None, tail_capacity: int = 0, tail_len=None,
                      stream=None, stages=None, side=None) -> None:
     """vidkv_decode_attention: one decode step of one layer -> out [B,Hq,128] fp16.
-    `side`: a SideStream or None: checked, the call runs in line either way."""
+    `side`: a SideStream or None: not used, the call runs in line either way."""
     L = _lib or lib()
     if stages is None and _native is not None:
         st = _native.decode_attention(p, layer, q, packed_K, packed_V, K_tail, V_tail, tail_capacity, tail_len, out,

@@ -1,7 +1,6 @@
 // C ABI of the VidKV library: argument validation on the host, then kernel
-// launches on the caller's stream (and, for two calls, on a second stream that the
+// launches on the caller's stream (and, for vidkv_quantize_kv, on a second stream that the
 // caller hands in).  Nothing here allocates, synchronizes, or creates streams or events.
-#include <algorithm>
 #include <mutex>
 
 #include "vidkv_common.h"
@@ -17,7 +16,6 @@ hipError_t launch_decode_attention(const Geom& g, int layer, float scale, const 
                                    const uint8_t* pk, const uint8_t* pv, const void* ktail,
                                    const void* vtail, int cap, const int32_t* tail_len, void* out,
                                    void* ws, size_t ws_bytes, unsigned stages, hipStream_t st);
-int device_cu_count();
 int attn_least_splits(const Geom& g);
 int attn_max_splits(const Geom& g);
 void launch_k_encode(const Geom& g, const EncodeSpan& sp, const void* K, uint8_t* packed,
@@ -220,10 +218,9 @@ vidkv_status vidkv_quantize_kv(const vidkv_params* p, const void* K, const void*
   const bool sel = g.n_s > 0, one = sel && one_workgroup_selection(g);
   const Side sd = take_side(side);
   const size_t key_bytes = (size_t)g.nheads * g.T * D * 2;
-  // (a stream of another device is refused from 32 MiB on, where the line once was)
-  if (sel && !one && sd.ok && key_bytes >= ((size_t)32 << 20) && !stream_on_current_device(sd.stream)) return VIDKV_EINVAL;
   const bool fork = sel && !one && sd.ok && key_bytes >= ((size_t)96 << 20);
   if (fork) {
+    if (!stream_on_current_device(sd.stream)) return VIDKV_EINVAL;
     if (hipEventRecord(sd.fork, st) != hipSuccess) return VIDKV_EHIP;
     if (hipStreamWaitEvent(sd.stream, sd.fork, 0) != hipSuccess) return VIDKV_EHIP;
     // from here on the side stream depends on `st`: whatever fails, it is joined back, so
@@ -301,12 +298,6 @@ vidkv_status vidkv_decode_attention_stages(const vidkv_params* p, int32_t layer,
   const uint8_t* pv = static_cast<const uint8_t*>(packed_V);
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (!stream_on_current_device(st)) return VIDKV_EINVAL;
-  const Side sd = take_side(side);
-  // (nothing runs there any more; where a large residual block did, a stream of another device is still refused)
-  const int blocks = std::min((tail_capacity + 31) / 32, ATTN_TAIL_SPLITS);
-  if (sd.ok && K_tail && V_tail && tail_len && (stages & 1u) && g.ng > 0 &&
-      (long long)blocks * g.B * g.H >= 4LL * device_cu_count() && !stream_on_current_device(sd.stream))
-    return VIDKV_EINVAL;
   const hipError_t e = launch_decode_attention(g, layer, p->softmax_scale, q, pk, pv, K_tail, V_tail,
                                                tail_capacity, tail_len, out, ws, ws_bytes, stages, st);
   return e == hipSuccess ? VIDKV_OK : VIDKV_EHIP;
