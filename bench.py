@@ -367,7 +367,7 @@ def main():
 
     vk.lib()                                  # fail loudly if the library is not built
     dev = "cuda:0"
-    side = vk.SideStream(dev)                 # the caller's side stream for the two calls that fork
+    side = vk.SideStream(dev)                 # the caller's side stream, which a large prefill uses
     tm = Timer(torch)
     w = synth.WORKLOADS[args.workload]
     job = Job(vk, synth, torch, np, w, dev, side, use_fft=0 if args.no_fft else 1,

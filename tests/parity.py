@@ -79,7 +79,6 @@ class GpuRun:
         self.pk = vk.alloc_bytes(vk.packed_keys_bytes(self.p), device)
         self.pv = vk.alloc_bytes(vk.packed_values_bytes(self.p), device)
         self.fused = fused
-        self.use_side = True       # hand the library a side stream (it uses it for large calls only)
         self.ws = vk.alloc_bytes(max(vk.workspace_bytes(self.p, i) for i in range(4)), device)
         self.pk.fill_(0xA5)        # stale bytes must not matter
         self.pv.fill_(0x5A)
@@ -125,7 +124,7 @@ class GpuRun:
         out.fill_(float("nan"))
         vk.decode_attention(self.p, layer, q, self.pk, self.pv, out, self.ws, K_tail=K_tail,
                             V_tail=V_tail, tail_capacity=cap, tail_len=tail_len,
-                            side=side_stream(self.dev) if self.use_side else None)
+                            side=side_stream(self.dev))
         torch.cuda.synchronize()
         return out
 

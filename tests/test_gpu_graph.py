@@ -69,11 +69,11 @@ def test_decode_step_of_all_layers_captured_and_replayed():
     P.assert_out_close(got[l, b].cpu().numpy(), ref, "graph replay")
 
 
-def test_large_residual_block_forked_inside_the_capture():
-    """A batch whose residual block is large enough to be forked onto the caller's side
-    stream: the fork and join are captured with the rest and every replay equals the eager run."""
+def test_large_residual_block_captured_and_replayed():
+    """A batch with a large residual block and a side stream, which the call does not use: every replay equals the
+    eager run."""
     w = synth.reduced(synth.WORKLOADS["c5_serving"], 8, B=32)
-    print("[case] graph-decode forked residual block", flush=True)
+    print("[case] graph-decode large residual block", flush=True)
     run = P.GpuRun(w, DEV)
     cap = 256
     g0 = torch.Generator(device=DEV)
@@ -115,13 +115,13 @@ def test_large_residual_block_forked_inside_the_capture():
     n = int(tl[b])
     ref = P.oracle_attention(run, 0, b, q[b].cpu().numpy(), Kt[b, :, :n].cpu().numpy(),
                              Vt[b, :, :n].cpu().numpy())
-    P.assert_out_close(got[b].cpu().numpy(), ref, "graph replay, forked residual block")
+    P.assert_out_close(got[b].cpu().numpy(), ref, "graph replay, large residual block")
 
 
-def test_quantizer_with_its_side_stream_captured_and_replayed():
-    """vidkv_quantize_kv forks the protected-token selection onto the caller's side stream;
-    captured, every replay must write the same bytes as the eager call."""
-    w = synth.reduced(synth.WORKLOADS["c4_long"], 176)       # 35 MB of keys: large enough to fork
+def test_quantizer_with_a_side_stream_captured_and_replayed():
+    """vidkv_quantize_kv below the line from which it uses the side stream that it is given: captured,
+    every replay must write the same bytes as the eager call."""
+    w = synth.reduced(synth.WORKLOADS["c4_long"], 176)       # 35 MB of keys: in line
     print("[case] graph-quantize", flush=True)
     run = P.GpuRun(w, DEV)                                   # eager reference buffers run.pk, run.pv
     sal = torch.from_numpy(synth.saliency(w)).to(DEV)
@@ -151,28 +151,31 @@ def test_quantizer_with_its_side_stream_captured_and_replayed():
         assert torch.equal(pk, pk0) and torch.equal(pv, pv0), f"replay {s} differs from the eager call"
 
 
-def test_quantizer_forked_inside_the_capture():
-    """The same with a key tensor (134 MB) on the far side of the line from which the selection is forked."""
-    print("[case] graph-quantize, forked", flush=True)
+@pytest.mark.parametrize("bits,by_list", [(16, False), (16, True), (2, False), (2, True)])
+def test_quantizer_forked_inside_the_capture(bits, by_list):
+    """The same with a key tensor (134 MB) on the far side of that line: the token selection is forked onto the side stream.
+    Bytes as the two separate calls write them."""
+    print(f"[case] graph-quantize, forked, {bits} bits, {'list' if by_list else 'scores'}", flush=True)
     T, n_s = 131072, 6000
-    p = vk.make_params(1, 1, 4, 4, T, 16, n_s)
+    p = vk.make_params(1, 1, 4, 4, T, 16, n_s, salient_bits=bits)
     g = torch.Generator(device=DEV); g.manual_seed(9)
     K, V = (torch.randn((1, 1, 4, T, 128), generator=g, device=DEV, dtype=torch.float16) for _ in range(2))
     sal = torch.rand((1, T), generator=g, device=DEV)
+    kw = {"salient_idx": sal.topk(n_s).indices.sort(dim=1).values.to(torch.int32).contiguous()} if by_list else {"saliency": sal}
     ws = vk.alloc_bytes(vk.workspace_bytes(p, 3), DEV)
     new = lambda n: torch.zeros(n, dtype=torch.uint8, device=DEV)
     nk, nv = vk.packed_keys_bytes(p), vk.packed_values_bytes(p)
     rk, rv, pk, pv = new(nk), new(nv), new(nk), new(nv)
     vk.quantize_keys(p, K, rk, ws)
-    vk.quantize_values(p, V, rv, ws, saliency=sal)
+    vk.quantize_values(p, V, rv, ws, **kw)
     torch.cuda.synchronize()
     side = P.side_stream(DEV)
-    vk.quantize_kv(p, K, V, pk, pv, ws, saliency=sal, side=side)
+    vk.quantize_kv(p, K, V, pk, pv, ws, side=side, **kw)
     torch.cuda.synchronize()
     assert torch.equal(pk, rk) and torch.equal(pv, rv)
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
-        vk.quantize_kv(p, K, V, pk, pv, ws, saliency=sal, side=side)
+        vk.quantize_kv(p, K, V, pk, pv, ws, side=side, **kw)
     for _ in range(3):
         pk.zero_(); pv.zero_(); ws.fill_(0x5A)
         torch.cuda.synchronize()
