@@ -93,6 +93,8 @@ __device__ __forceinline__ void put_partial(const AttnArgs& a, int split, int kv
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
+__device__ __forceinline__ h2 rtz2(float a, float b) { return __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(a, b)); }
+
 struct alignas(256) TailLds {
   uint8_t v[4][32 * 2 * D];               // per wave: a block's value rows, swizzled; then the wave's sums
   float mw[8][4], lw[8][4];               // [head][wave]
@@ -104,11 +106,10 @@ struct alignas(256) TailLds {
 // latencies where there are few.  Both contractions run on the matrix cores, K rows straight from memory as
 // operands, value rows through LDS and its transposing reads; everything a block needs is asked for at once.
 // As exact as in 32-bit arithmetic.  q, keys and values are fp16 numbers with exact products.  A probability enters as four
-// fp16 numbers that add up to it, in the rows of the 8 heads and the 8 that would be empty of two products a tile: all
-// its 24 bits down to 2^-41 of the running maximum, 22 to 2^-53, 11 to 2^-65, which times the largest value adds nothing to
-// an fp16 result below 2^24 tokens.  None of the four is subnormal: a product takes a subnormal operand for 2^-14 where it aligns the sum,
-// and where all are a few 2^-24 up to 2^-17 of the sum is lost.  (So for subnormal keys, queries and values, whose scores or results
-// are then too small to show it.)
+// fp16 numbers that add up to it, each cut off behind 11 bits, in the rows of the 8 heads and the 8 that would be empty
+// of two products a tile: all its 24 bits down to 2^-48 of the running maximum, what is above 2^-72 below it.  (A product takes a
+// subnormal operand for one of 2^-14 where it aligns its sum, and cuts off 24 bits below: 2^-53 of the running maximum times a
+// value here, less than 2^-25 in a result of up to 4096 tokens; of keys, queries and values that are all a few 2^-24, 2^-17 of a sum.)
 __device__ __forceinline__ void attn_tail_part(const AttnArgs& a, int ts, int kvh, int b, TailLds& t) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -131,9 +132,9 @@ __device__ __forceinline__ void attn_tail_part(const AttnArgs& a, int ts, int kv
     // a transposing read hands lane x16 of kb the rows 4 kb .. 4 kb + 3 (of either half) of channel 16 m + x16
     const int rr = 4 * kb + (x16 >> 2);
     const uint32_t at = (uint32_t)reinterpret_cast<uintptr_t>(vrow) + rr * 2 * D + (rr & 7) * 32 + (x16 & 3) * 8;
-    // parts 0 and 2 of the probabilities are in rows 0..7, 1 and 3 in rows 8..15, part k times 2^(15 + 12 k)
+    // part k is taken times 2^(15 + 11 k), all below 2^15 but p = 1: parts 0 and 2 in rows 0..7, 1 and 3 in rows 8..15
     const bool odd = x16 >= 8;
-    const float row0 = (kb >> 1) ? 0x1p-27f : 0x1p-15f, row2 = (kb >> 1) ? 0x1p-51f : 0x1p-39f;   // of my rows' products
+    const float skip = odd ? -1.0f : 0.0f, up = odd ? 0x1p11f : 1.0f;
     for (int it = it0; it < it1; it += 4) {
       const int tok0 = it * 32, nt = min(32, tl - tok0);
       // (a row past the end repeats the last one and counts 0 times)
@@ -172,20 +173,25 @@ __device__ __forceinline__ void attn_tail_part(const AttnArgs& a, int ts, int kv
       m_run = m_new;
       Op A[2];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float p = sc[i] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(sc[i] - m_new);
-        l_run += p;
-        float r = p;                                 // what the parts so far leave
-        _Float16 part[4];
+      for (int i = 0; i < 8; i += 2) {
+        float p[2];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const float up = k == 0 ? 0x1p15f : k == 1 ? 0x1p27f : k == 2 ? 0x1p39f : 0x1p51f;
-          const float x = r * up;
-          part[k] = (_Float16)(fabsf(x) < 0x1p-14f ? 0.0f : x);
-          r = fmaf((float)part[k], -1.0f / up, r);
+        for (int e = 0; e < 2; ++e) {
+          p[e] = sc[i + e] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(sc[i + e] - m_new);
+          l_run += p[e];
+          p[e] *= 0x1p15f;
         }
-        A[0].v[i] = odd ? part[1] : part[0];
-        A[1].v[i] = odd ? part[3] : part[2];
+        // p: what is left behind a part, at the next one's scale.  Behind the one in front of mine (none for part 0), mine,
+        // the next one, and mine again
+        auto behind = [&](h2 part, float take, float scale) {
+#pragma unroll
+          for (int e = 0; e < 2; ++e) p[e] = fmaf((float)part[e], take, p[e]) * scale;
+        };
+        behind(rtz2(p[0], p[1]), skip, up);
+        A[0].p[i / 2] = rtz2(p[0], p[1]);
+        behind(A[0].p[i / 2], -1.0f, 0x1p11f);
+        behind(rtz2(p[0], p[1]), -1.0f, 0x1p11f);
+        A[1].p[i / 2] = rtz2(p[0], p[1]);
       }
       if (it != it0) {
         // the sums are laid out by score-tile column as ROW 4 kb + i
@@ -209,13 +215,17 @@ __device__ __forceinline__ void attn_tail_part(const AttnArgs& a, int ts, int kv
         Op B;
         *reinterpret_cast<s16x4*>(&B.u[0]) = lo4[m];
         *reinterpret_cast<s16x4*>(&B.u[2]) = hi4[m];
-        const f4 C0 = mma(A[0], B, zero), C2 = mma(A[1], B, zero);
+        const f4 C = mma(A[1], B, zero);
+        o[m] = mma(A[0], B, o[m]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o[m][i] = fmaf(row0, C0[i], fmaf(row2, C2[i], o[m][i]));
+        for (int i = 0; i < 4; ++i) o[m][i] = fmaf(0x1p-22f, C[i], o[m][i]);
       }
       asm volatile("" ::: "memory");
     }
     l_run = swap_sum16(swap_sum32(l_run));
+    const float row = (kb >> 1) ? 0x1p-26f : 0x1p-15f;       // of my rows' part
+#pragma unroll
+    for (int m = 0; m < 8; ++m) o[m] *= row;
   }
   put_wave_sums(o, reinterpret_cast<float*>(&t.v[wave][0]), x16, kb);
   if (kb == 0 && x16 < 8) { t.mw[hcol][wave] = m_run; t.lw[hcol][wave] = l_run; }

@@ -18,7 +18,7 @@ namespace vidkv {
 
 // The residual tokens as a launch of their own (the MFMA kernel takes them along when its grid
 // has room for them).
-__global__ __launch_bounds__(256) void attn_tail_kernel(AttnArgs a) {
+__global__ __launch_bounds__(256, 3) void attn_tail_kernel(AttnArgs a) {
   __shared__ TailLds t;
   attn_tail_part(a, blockIdx.x, blockIdx.y, blockIdx.z, t);
 }
