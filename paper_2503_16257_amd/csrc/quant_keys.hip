@@ -13,7 +13,7 @@ namespace vidkv {
 // Pass 1 as a launch of its own.  grid (range_chunks, nheads); block 1024, WHOLE (a chunk in one go), or 256.
 template <bool WHOLE, bool STREAM>
 __global__ __launch_bounds__(WHOLE ? 1024 : 256) void k_range_kernel(const u32x4* __restrict__ K, int T,
-                                                                     int chunks, _Float16* __restrict__ ws) {
+                                                                     Chunks chunks, _Float16* __restrict__ ws) {
   __shared__ std::conditional_t<WHOLE, ChunkRangeLds, RangeLds> lds;
   if constexpr (WHOLE) range_chunk<STREAM>(K, T, chunks, ws, blockIdx.x, blockIdx.y, lds);
   else range_part<STREAM>(K, T, chunks, ws, blockIdx.x, blockIdx.y, threadIdx.x, true, lds);
@@ -24,7 +24,7 @@ __global__ __launch_bounds__(WHOLE ? 1024 : 256) void k_range_kernel(const u32x4
 // group (or each sequence's list), which leaves RANK and IDX to the value coding; otherwise one a sequence.  Workgroups of
 // 1024 threads, a chunk each, asked for in one go; four: four chunks each, a quarter of the requests at a time.
 template <bool STREAM>
-__global__ __launch_bounds__(1024, 8) void k_range_select_kernel(const u32x4* __restrict__ K, int T, int chunks, int total,
+__global__ __launch_bounds__(1024, 8) void k_range_select_kernel(const u32x4* __restrict__ K, int T, Chunks chunks, int total,
                                                                  int nsel, int few, int four,
                                                                  _Float16* __restrict__ ws, OneSelArgs sel) {
   __shared__ union { ChunkRangeLds range; RangeLds range4[4]; FewSelLds few; OneSelLds one; } lds;
@@ -40,9 +40,9 @@ __global__ __launch_bounds__(1024, 8) void k_range_select_kernel(const u32x4* __
   if (four) {
     const int sub = threadIdx.x >> 8, c = 4 * w + sub;
     const bool on = c < total;
-    range_part<STREAM>(K, T, chunks, ws, on ? c % chunks : 0, on ? c / chunks : 0, threadIdx.x & 255, on, lds.range4[sub]);
+    range_part<STREAM>(K, T, chunks, ws, on ? c % chunks.n : 0, on ? c / chunks.n : 0, threadIdx.x & 255, on, lds.range4[sub]);
   } else {
-    range_chunk<STREAM>(K, T, chunks, ws, w % chunks, w / chunks, lds.range);
+    range_chunk<STREAM>(K, T, chunks, ws, w % chunks.n, w / chunks.n, lds.range);
   }
 }
 
@@ -239,7 +239,7 @@ void launch_k_range_select(const Geom& g, const void* K, void* ws, const float* 
   const long long wgs = four ? (total + 3) / 4 : total;
   // T <= ONE_MAX_T: at most 65535 * 64 chunks
   hipLaunchKernelGGL(stream_keys(g) ? k_range_select_kernel<true> : k_range_select_kernel<false>, dim3((unsigned)(nsel + wgs)), dim3(1024), 0, st,
-                     reinterpret_cast<const u32x4*>(K), g.T, g.range_chunks, (int)total, nsel, few ? 1 : 0, four ? 1 : 0,
+                     reinterpret_cast<const u32x4*>(K), g.T, chunks_of(g), (int)total, nsel, few ? 1 : 0, four ? 1 : 0,
                      reinterpret_cast<_Float16*>(ws), one_sel_args(g, scores, idx, packed_V));
 }
 
@@ -282,7 +282,7 @@ hipError_t launch_quantize_keys(const Geom& g, const void* K, uint8_t* packed, v
     const bool whole = whole_chunks(g), stream = stream_keys(g);
     auto* kernel = whole ? (stream ? k_range_kernel<true, true> : k_range_kernel<true, false>)
                          : (stream ? k_range_kernel<false, true> : k_range_kernel<false, false>);
-    hipLaunchKernelGGL(kernel, gr1, dim3(whole ? 1024 : 256), 0, st, k4, g.T, g.range_chunks, w);
+    hipLaunchKernelGGL(kernel, gr1, dim3(whole ? 1024 : 256), 0, st, k4, g.T, chunks_of(g), w);
   }
   if (stages & 2u)
     hipLaunchKernelGGL(k_select_kernel, dim3((unsigned)g.nheads), dim3(1024), 0, st, w,
