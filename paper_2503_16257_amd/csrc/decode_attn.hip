@@ -178,8 +178,9 @@ struct AttnPlan {
 // tokens': 3.5 us and 2.2 us a turn, 3.2 where a compute unit has two workgroups.  A launch of its own costs 7.0 us
 // and 2.8 us a turn and round of three workgroups a compute unit.  Fitted to 780 shapes (1 to 64 sequences x 1 to 8
 // heads of 192 to 12544 tokens, 32 to 1024 residual ones, four variants), main_cost() as it is: 1.3 % over the fastest split tried on
-// average, 29 % at most.  Large blocks, too (64 x 4 heads x 25088 tokens, 256 residual ones: the launch takes 7.7 us; on a
-// stream of its own beside the packed tokens' the call took 147 us, behind them 140).
+// average, 29 % at most (on residual workgroups 1 to 4 % faster at 1024 tokens, whose probabilities had fewer bits).  Large
+// blocks, too (64 x 4 heads x 25088 tokens, 256 residual ones: the launch takes 6.9 us; on a stream of its own beside
+// the packed tokens' the call took 147 us, behind them 140).
 static AttnPlan attn_plan(const Geom& g, int nmax, int iters) {
   const int bh = (int)std::min((long long)g.B * g.H, 1LL << 20), cus = device_cu_count(), npairs = (g.ng + 1) / 2;
   const int ntail = std::min((iters + 3) / 4, ATTN_TAIL_SPLITS);

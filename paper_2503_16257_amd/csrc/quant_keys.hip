@@ -207,9 +207,9 @@ static bool whole_chunks(const Geom& g) {
 //   64 x 4 x 25088, 1644 MB               889 / 886     875 / 877     906 / 889     908 / 887
 static bool stream_keys(const Geom& g) { return (size_t)g.nheads * g.T * D * 2 > ((size_t)128 << 20); }
 
-// Counting the tokens with larger scores, quadratic in the sequence, against one workgroup's four digits: where the
-// selection is what takes time (alone) up to 8192 tokens on each compute unit's share (256 groups of one sequence, whole
-// calls: 20.2 us with the digits, 17.0; of two 22.4 and 22.9); beside a range pass, which waits for its workgroups, while
+// Counting the tokens with larger scores, quadratic in the sequence, against one workgroup's four digits: up to 8192 tokens on
+// each compute unit's share (the selection by itself, 256 groups of one sequence, whole calls: 20.2 us with the digits, 17.0; of
+// two 22.4 and 22.9; 2 x 8 heads x 8128 tokens, 16129 a unit, 34.3 and 36.0); beside a range pass, which waits for its workgroups, while
 // they and the chunks are no more than three a compute unit (digits and counting, us: 8 x 4 heads x 1568 tokens, 520, 21.8 and
 // 19.9; 2 x 8 x 4704, 454, 25.4 and 23.2; 56 x 4 x 256, 672, 22.4 and 18.9; 32 x 4 x 512 in 2 layers, 768, 30.2 and 29.3; 8 x 4 x 288 in
 // 16, 656, 33.6 and 34.2; 64 x 4 x 288, 832, 24.0 and 25.8; 8 x 4 x 1568 in 8, 1416, 64.3 and 68.7; 64 x 8 x 544, 2112, 50.2 and 57.9.
@@ -219,7 +219,8 @@ static bool stream_keys(const Geom& g) { return (size_t)g.nheads * g.T * D * 2 >
 bool few_selection(const Geom& g, bool scores, bool alone) {
   if (g.ng > FEW_MAX_GROUPS) return false;
   const long long cus = device_cu_count(), nsel = scores ? (long long)g.B * g.ng : g.B, chunks = g.nheads * g.range_chunks;
-  if (alone) return !scores || nsel * g.T <= 8192 * cus;
+  if (scores && nsel * g.T > 8192 * cus) return false;
+  if (alone) return true;
   return whole_chunks(g) ? nsel + chunks <= 3 * cus : 2 * nsel + (chunks + 1) / 2 <= 3 * cus;
 }
 
@@ -231,10 +232,12 @@ void launch_k_range_select(const Geom& g, const void* K, void* ws, const float* 
   const long long total = g.nheads * g.range_chunks, cus = device_cu_count();
   // Beside a workgroup that goes through a sequence's digits, four chunks a workgroup also where the chunks are not nearly
   // full (64 x 4 heads x 544 tokens in 8 layers 169 us so, 179 with a chunk each; 16 x 4 x 3136, 0.88 full, 43.4 and 40.9), and where
-  // the selection of a long sequence is the longer part and so keeps a compute unit to itself: 8 heads of 25088 tokens 48.1 and 54.4,
-  // 4 of 32768 41.9 and 46.2, 4 x 8 x 12544 68.1 and 69.4; with more workgroups than units 8 heads of two sequences of 32768 97.6 and 91.6.
+  // the selection is the longer part and so keeps a compute unit to itself: K and V just written, 4 x 4 heads x 6272 tokens, 208
+  // chunks, 30.2 and 31.5, 4 x 8 x 6272, 416, 38.8 and 40.7, 6 x 8 x 6272, 624, 52.8 and 51.5; 2 x 8 x 8192, 256, 33.4 and 35.8, 8 x 4 x
+  // 8192, 512, 49.6 and 46.4; 4 x 8 x 12544, 800, 72.2 and 73.7, 8 heads of 25088, 392, 51.0 and 54.0, 16 of 32768, 1024, 99.1 and 94.2.
   const bool digits = nsel > 0 && !few;
   const bool four = !whole_chunks(g) || (digits && 8LL * g.T < 7LL * RANGE_CHUNK * g.range_chunks) ||
+                    (digits && g.T > 16 * FEW_MAX_GROUPS && 4 * total <= 7 * cus) ||
                     (digits && g.T > 32 * FEW_MAX_GROUPS && (total + 3) / 4 + nsel <= cus);
   const long long wgs = four ? (total + 3) / 4 : total;
   // T <= ONE_MAX_T: at most 65535 * 64 chunks

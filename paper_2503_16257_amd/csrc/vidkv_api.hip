@@ -207,7 +207,7 @@ vidkv_status vidkv_quantize_kv(const vidkv_params* p, const void* K, const void*
   // work that wait for memory, the passes need its bandwidth: a selection in the first workgroups of
   // a pass costs nothing, as launches of its own one of 5 to 8 us (channels) and six of 3 to 5 us
   // (tokens) with the passes waiting (28 x 4 heads of 6272 tokens with 2-bit rows 139 -> 110 us, 64 x 4 heads of 25088 945 -> 912;
-  // 106 and 873 now).  Few groups: two launches (launch_few_groups(): one head of 1568 tokens 38.5 -> 19.3 as three, 10.9 so).
+  // 105 and 873 now).  Few groups: two launches (launch_few_groups(): one head of 1568 tokens 38.5 -> 19.3 as three, 10.5 so).
   // A sequence too long for one workgroup's registers keeps the chain of six.  With a side stream,
   // and key passes long enough to hide the fork and join, it runs beside them, the value
   // pass last; beside the range pass alone it is the longer of the two (196000 tokens: 154 us
