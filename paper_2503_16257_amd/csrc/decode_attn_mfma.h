@@ -11,8 +11,9 @@
 //   * a 32-point inverse real DFT as a product with a constant matrix (split
 //     into fp16 hi + lo parts, as is Y) giving scores[token][column],
 //   * anomalous key channels (Eq. 4): code*s + z = (z + 1.5 s) + s0 (s/2) + s1 s
-//     with s0, s1 = +-1 taken from the two code bits, rows = tokens; the column
-//     operand is masked by parity so both groups add into the same score tile,
+//     with s0, s1 = +-1 taken from the two code bits, rows = tokens, s as it is stored
+//     against -q and -2 q; the column operand is masked by parity so both groups add
+//     into the same score tile,
 //   * P V: rows = columns of the score tile (probabilities are reused in place
 //     as the A operand), K = tokens, columns = channels with operand +-1 / 0 from
 //     the trits; the per-channel scale of Eq. 6 multiplies the fp32 result.
@@ -146,7 +147,7 @@ static __device__ const __align__(256) IdftTab kIdftTab = make_idft_tab();
 //   * probabilities enter P V as three bf16 parts that add up to the fp32 number, whatever its size
 //     (fp16 hi + lo parts are 0 below 2^-25 of the running maximum, where the softmax denominator
 //     still counts the token: 196000 tokens at 2^-25.1 of one other lost 0.5 % of the output);
-//   * protected rows' probabilities as hi + 2^-18 lo, two fp16 numbers;
+//   * protected rows' probabilities as hi + 2^-18 lo, two fp16 numbers (how many bits: at batch());
 //   * the normal channels' q enters as it is, where the others' inverse DFT takes q/16 (half of it for a head with an
 //     anomalous channel's element of 2^15 or more);
 //   * the inverse DFT runs on v_mfma_f32_16x16x4_f32, on the fp32 sums and an fp32 matrix.
@@ -833,7 +834,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   // one batch: entries lfirst .. min(lcnt, BS) - 1 of the list against the rows in rowbuf (which
   // have landed), then the next batch's rows are requested.  Operand rows 0-7 are the heads'
   // probabilities rounded to fp16, rows 8-15 what the rounding left (FULL: times 2^18, so that the two
-  // carry 22 bits and nothing is lost above 2^-43).
+  // carry 22 bits down to 2^-14 of the running maximum, 22 to 11 down to 2^-25, 11 down to 2^-32 and none below 2^-43).
   auto batch = [&]() __attribute__((always_inline)) {   // (a call would put the running sums into memory)
     const int n = min(lcnt, BS);
     // lane numbers of its own, so that no address of a batch occupies a register between batches

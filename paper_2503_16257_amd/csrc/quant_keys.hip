@@ -203,8 +203,11 @@ static bool whole_chunks(const Geom& g) {
 //   64 x 4 x 1568, 103 MB                64.8 / 65.7   64.8 / 66.6   66.7 / 68.2   64.2 / 67.6
 //   28 x 4 x 4704, 135 MB                82.9 / 86.2   84.4 / 84.9   93.5 / 86.3   83.4 / 85.7
 //   28 x 4 x 6272, 180 MB               104.9 / 107.7 110.1 / 107.5 124.4 / 108.9 109.1 / 110.9
+//   4 x 196000 (token selection beside), 201 MB   124.9 / 127.4   125.3 / 128.3   147.4 / 138.1   136.6 / 136.0
 //   28 x 4 x 8192, 235 MB               136.2 / 135.9 140.3 / 138.2 160.7 / 139.6 151.6 / 141.9
 //   64 x 4 x 25088, 1644 MB               889 / 886     875 / 877     906 / 889     908 / 887
+// So what is read behind a kernel that wrote V last decides; on the same or rotating buffers a call between 128 and 256 MiB loses
+// up to 3 % by it.  Plain loads for the last 32 to 128 MiB alone lie between the two in each column.
 static bool stream_keys(const Geom& g) { return (size_t)g.nheads * g.T * D * 2 > ((size_t)128 << 20); }
 
 // Counting the tokens with larger scores, quadratic in the sequence, against one workgroup's four digits: up to 8192 tokens on
